@@ -22,12 +22,12 @@ namespace wave {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 
-// Two similarities closer than this are re-decided in fp64.  Both are sums that run near 2
-// (units in the last place of 2^-22) with low mantissa bits overwritten by the row code (up
-// to 27 units each: 6.5e-6).  bf16: 8 accumulation steps of at most one unit: together below
-// 2 x (6.5e-6 + 2e-6).  f32: up to 128 additions of half a unit: below 2 x (6.5e-6 + 1.6e-5).
-template <typename T>
-constexpr float kAssignGuard = sizeof(T) == 2 ? 4.0e-5f : 8.0e-5f;
+constexpr float kNegHuge = -3.0e38f;
+// Two similarities closer than this are re-decided in fp64.  It covers the fp32
+// accumulation error of a unit-vector dot product (<= (d + 1) * 2^-24 < 8e-6; in the
+// MFMA path the sums run near 2, so 8 steps of 2^-23) on both values plus the 5 low
+// mantissa bits the MFMA path overwrites with the row code (<= 2^-18 relative each).
+constexpr float kAssignGuard = 4.0e-5f;
 
 struct SegInfo {
   int unit, s, seg_start, L_s, k_s;
@@ -178,19 +178,15 @@ __global__ __launch_bounds__(256) void init_kernel(const T* __restrict__ xhat, T
 }
 
 // ============================================================================
-// Assign: similarities on the matrix cores.  A wave keeps 32 points of one segment as B
-// operands in registers and streams the centroids, 32 at a time, from LDS as A operands,
-// so D[centroid][point] accumulates in a 32 x 32 tile and a lane holds 16 centroid rows of
-// ONE point: the running best / second best never leave the lane.  Four of the five bits
-// of the centroid's row inside the tile are written over low mantissa bits of the
-// similarity (the fifth is the lane's half), so one v_med3 pair carries value and index:
-// 3 VALU instructions per similarity.
-// bf16 rows use v_mfma_f32_32x32x16_bf16; f32 rows use v_mfma_f32_32x32x2_f32 (full fp32
-// products and sums), four per 16-byte chunk: component i of the two halves' chunks is one
-// k pair, and the order of k inside a dot product is free as long as both operands agree.
-// The f32 form replaced one point per thread with an fp32 FMA chain on the vector ALU and
-// centroids broadcast from LDS: 4096 tokens x 128 clusters x 64 channels 58 -> 9 us a
-// step (16 workgroups of four waves before, 32 now).
+// Assign, MFMA path (bf16).  A workgroup of NW waves takes NW * 32 * NF points
+// of one segment.  Each wave keeps its points as B operands (K x N = 16 x 32 per
+// instruction) in registers for the whole kernel and streams the centroids,
+// 32 at a time, through a padded LDS tile as A operands (M x K = 32 x 16), so
+// D[centroid][point] accumulates in v_mfma_f32_32x32x16_bf16 and a lane holds
+// 16 centroid rows of ONE point: the running best / second best never leave the
+// lane.  Four of the five bits of the centroid's row inside the tile are written
+// over low mantissa bits of the similarity (the fifth is the lane's half), so
+// one v_med3 pair carries value and index: 3 VALU instructions per similarity.
 // ============================================================================
 // Similarities of unit vectors lie in [-1, 1]; the accumulators start at
 // kAssignBias so every value is a positive float, whose bit pattern orders like
@@ -204,107 +200,61 @@ __device__ __forceinline__ int med3_i32(int a, int b, int c) {
   return r;
 }
 
-// The running best and second best of one point over the centroid rows a lane has seen:
-// biased similarities as integers (0 is below all of them), and the best one's tile.
-struct Best2 {
-  int best = 0, second = 0, tile = 0;
-};
-
-// Similarity difference of two biased keys (second = 0: no other centroid).
-__device__ __forceinline__ float key_gap(int best, int second) {
-  return __int_as_float(best) - (second > 0 ? __int_as_float(second) : 0.f);
-}
-
-template <bool TAIL>
-__device__ __forceinline__ void assign_epilogue(const floatx16& acc, Best2& b2, int t, int half, int k_s) {
-  const int before = b2.best;
+template <int NF, bool TAIL>
+__device__ __forceinline__ void assign_epilogue(const floatx16 (&acc)[NF], int (&best)[NF],
+                                                int (&second)[NF], int (&btile)[NF], int t, int half,
+                                                int k_s) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    constexpr uint32_t kClear = ~27u;               // bits 0,1,3,4 carry the row code
-    const uint32_t code = 8u * (v / 4) + (v % 4);   // row = code | 4 * half
-    int key = (int)((__float_as_uint(acc[v]) & kClear) | code);
-    if (TAIL && 32 * t + (int)code + 4 * half >= k_s) key = 0;
-    b2.second = med3_i32(b2.best, b2.second, key);
-    b2.best = max(b2.best, key);
-  }
-  b2.tile = (b2.best != before) ? t : b2.tile;
-}
-
-// Lanes l and l ^ 32 hold the same point over disjoint centroid rows: the point's best row
-// (returned), best and second-best keys over both.
-__device__ __forceinline__ int merge_halves(Best2& b2, int half) {
-  int brow = (b2.best & 27) | (4 * half);
-  const int ob = __shfl_xor(b2.best, 32), os = __shfl_xor(b2.second, 32);
-  const int ot = __shfl_xor(b2.tile, 32), orow = __shfl_xor(brow, 32);
-  b2.second = max(min(b2.best, ob), max(b2.second, os));
-  if (ob > b2.best) {
-    b2.best = ob;
-    b2.tile = ot;
-    brow = orow;
-  }
-  return b2.tile * 32 + brow;
-}
-
-template <typename T>
-__device__ __forceinline__ floatx16 mfma_chunk(const uint4& a, const uint4& b, floatx16 acc);
-template <>
-__device__ __forceinline__ floatx16 mfma_chunk<bf16_t>(const uint4& a, const uint4& b, floatx16 acc) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
-                                                 acc, 0, 0, 0);
-}
-template <>
-__device__ __forceinline__ floatx16 mfma_chunk<float>(const uint4& a, const uint4& b, floatx16 acc) {
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
-  return acc;
-}
-
-template <typename T, int D>
-struct ResidentTile {
-  static constexpr int ROWB = D * (int)sizeof(T) + 16;  // LDS row pitch: 16 B pad keeps 16 lanes on 64 distinct banks
-  static constexpr int CPR = D * (int)sizeof(T) / 16;   // 16-byte chunks per centroid row
-  static constexpr int KS = CPR / 2;                    // chunk pairs (one chunk per half of the wave)
-};
-
-// The 32 points of fragment fb (rows past the segment's end repeat its last one) as operands.
-template <typename T, int D>
-__device__ __forceinline__ void load_fragment(const T* X, int fb, int L_s, uint4 (&dst)[ResidentTile<T, D>::KS]) {
-  const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-  const int row = min(32 * fb + col, L_s - 1);
+  for (int f = 0; f < NF; ++f) {
+    const int before = best[f];
 #pragma unroll
-  for (int s = 0; s < ResidentTile<T, D>::KS; ++s)
-    dst[s] = load16(X + (size_t)row * D + (2 * s + half) * Elem<T>::EPC);
+    for (int v = 0; v < 16; ++v) {
+      constexpr uint32_t kClear = ~27u;               // bits 0,1,3,4 carry the row code
+      const uint32_t code = 8u * (v / 4) + (v % 4);   // row = code | 4 * half
+      int key = (int)((__float_as_uint(acc[f][v]) & kClear) | code);
+      if (TAIL && 32 * t + (int)code + 4 * half >= k_s) key = 0;
+      second[f] = med3_i32(best[f], second[f], key);
+      best[f] = max(best[f], key);
+    }
+    btile[f] = (best[f] != before) ? t : btile[f];
+  }
 }
 
-// Centroids staged through LDS tile by tile (segments whose centroids do not fit there):
-// a workgroup of NW waves takes NW fragments.
-template <typename T, int D, int NW>
-__global__ __launch_bounds__(64 * NW) void assign_staged_kernel(
-    const T* __restrict__ xhat, const T* __restrict__ chat, int32_t* __restrict__ assign,
+template <int D, int NF, int NW>
+__global__ __launch_bounds__(64 * NW) void assign_mfma_kernel(
+    const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
     int32_t* __restrict__ flag_list, int32_t* __restrict__ flag_count, int S, int L, int kk, int N_idx,
     int wgs_per_seg) {
-  using RT = ResidentTile<T, D>;
-  constexpr int KS = RT::KS, ROWB = RT::ROWB, CPR = RT::CPR, EPC = Elem<T>::EPC;
-  constexpr int NT = 64 * NW;                  // threads
-  constexpr int CHUNKS = 32 * CPR;             // chunks per tile
+  constexpr int KS = D / 16;            // MFMA k-steps per tile
+  constexpr int PW = 32 * NF;           // points per wave
+  constexpr int PWG = NW * PW;          // points per workgroup
+  constexpr int NT = 64 * NW;           // threads
+  constexpr int ROWB = D * 2 + 16;      // LDS row pitch: 16 B pad keeps 16 lanes on 64 distinct banks
+  constexpr int CPR = D / 8;            // 16-byte chunks per centroid row
+  constexpr int CHUNKS = 32 * CPR;      // chunks per tile
   constexpr int CPT = (CHUNKS + NT - 1) / NT;  // chunks each thread moves per tile
   __shared__ __attribute__((aligned(16))) char lds[2][32 * ROWB];
 
   const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
   const int sg = wg / wgs_per_seg, piece = wg - sg * wgs_per_seg;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
-  const int f0 = piece * NW;
-  if (32 * f0 >= si.L_s) return;
+  const int p0 = piece * PWG;
+  if (p0 >= si.L_s) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
-  const T* X = xhat + ((size_t)si.unit * N_idx + si.seg_start) * D;
-  const T* Cs = chat + (size_t)sg * kk * D;
+  const bf16_t* X = xhat + ((size_t)si.unit * N_idx + si.seg_start) * D;
+  const bf16_t* Cs = chat + (size_t)sg * kk * D;
 
-  uint4 bfrag[KS];
-  load_fragment<T, D>(X, f0 + wave, si.L_s, bfrag);
-  Best2 b2;
+  uint4 bfrag[NF][KS];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    const int row = min(p0 + wave * PW + 32 * f + col, si.L_s - 1);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) bfrag[f][s] = load16(X + (size_t)row * D + (2 * s + half) * 8);
+  }
+  int best[NF], second[NF], btile[NF];  // biased similarities as integers; 0 is below all of them
+#pragma unroll
+  for (int f = 0; f < NF; ++f) best[f] = second[f] = btile[f] = 0;
 
   const int ntiles = (si.k_s + 31) / 32;
   // Centroid tiles travel global -> registers -> LDS.  Two register stages keep
@@ -316,7 +266,7 @@ __global__ __launch_bounds__(64 * NW) void assign_staged_kernel(
       const int id = tid + NT * i, row = id / CPR, ch = id - row * CPR;
       if (CHUNKS % NT == 0 || id < CHUNKS) {
         const int crow = min(32 * t + row, si.k_s - 1);
-        st[i] = load16(Cs + (size_t)crow * D + ch * EPC);
+        st[i] = load16(Cs + (size_t)crow * D + ch * 8);
       }
     }
   };
@@ -330,15 +280,27 @@ __global__ __launch_bounds__(64 * NW) void assign_staged_kernel(
   auto tile_step = [&](int t, uint4 (&st_next)[CPT], uint4 (&st_load)[CPT]) {
     // st_next holds tile t + 1 (requested one step ago); st_load receives tile t + 2
     if (t + 2 < ntiles) gload(t + 2, st_load);
-    constexpr float B0 = kAssignBias;
-    floatx16 acc = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
+    floatx16 acc[NF];
     const char* tile = lds[t & 1];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) acc = mfma_chunk<T>(load16(tile + col * ROWB + (2 * s + half) * 16), bfrag[s], acc);
+    for (int s = 0; s < KS; ++s) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, load16(tile + col * ROWB + (2 * s + half) * 16));
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        const bf16x8 bv = __builtin_bit_cast(bf16x8, bfrag[f][s]);
+        if (s == 0) {
+          constexpr float B0 = kAssignBias;
+          const floatx16 bias = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
+          acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv, bias, 0, 0, 0);
+        } else {
+          acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv, acc[f], 0, 0, 0);
+        }
+      }
+    }
     if (32 * t + 32 > si.k_s)
-      assign_epilogue<true>(acc, b2, t, half, si.k_s);
+      assign_epilogue<NF, true>(acc, best, second, btile, t, half, si.k_s);
     else
-      assign_epilogue<false>(acc, b2, t, half, si.k_s);
+      assign_epilogue<NF, false>(acc, best, second, btile, t, half, si.k_s);
     if (t + 1 < ntiles) sstore((t + 1) & 1, st_next);
     __syncthreads();
   };
@@ -350,56 +312,91 @@ __global__ __launch_bounds__(64 * NW) void assign_staged_kernel(
     tile_step(t, stage[1], stage[0]);
     if (t + 1 < ntiles) tile_step(t + 1, stage[0], stage[1]);
   }
-  const int c = merge_halves(b2, half);
-  const int point = 32 * (f0 + wave) + col;
-  if (half == 0 && point < si.L_s) {
-    const size_t gp = (size_t)si.unit * N_idx + si.seg_start + point;
-    assign[gp] = c;
-    if (key_gap(b2.best, b2.second) < kAssignGuard<T>) flag_list[atomicAdd(flag_count, 1)] = (int32_t)gp;
+
+  // lanes l and l ^ 32 hold the same points over disjoint centroid rows
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    int brow = (best[f] & 27) | (4 * half);
+    const int ob = __shfl_xor(best[f], 32), os = __shfl_xor(second[f], 32);
+    const int ot = __shfl_xor(btile[f], 32), orow = __shfl_xor(brow, 32);
+    const int nsec = max(min(best[f], ob), max(second[f], os));
+    if (ob > best[f]) {
+      best[f] = ob;
+      btile[f] = ot;
+      brow = orow;
+    }
+    const int point = p0 + wave * PW + 32 * f + col;
+    if (half == 0 && point < si.L_s) {
+      const size_t gp = (size_t)si.unit * N_idx + si.seg_start + point;
+      assign[gp] = btile[f] * 32 + brow;
+      const float gap = __int_as_float(best[f]) - (nsec > 0 ? __int_as_float(nsec) : 0.f);
+      if (gap < kAssignGuard) flag_list[atomicAdd(flag_count, 1)] = (int32_t)gp;
+    }
   }
 }
 
-// ----------------------------------------------------------------------------
-// The segment's centroids resident in LDS: a workgroup copies all k_s centroid rows into
-// LDS once (padded rows, at most 144 KiB) and then every wave works through fragments of
-// 32 points on its own: no barrier and no global centroid traffic inside the loop.
-// ----------------------------------------------------------------------------
+// ============================================================================
+// Assign, MFMA path with the segment's centroids resident in LDS: one workgroup
+// of 16 waves copies all k_s centroid rows into LDS once (padded rows, at most
+// ~136 KiB) and then every wave works through fragments of 32 * NF points on
+// its own: no barrier and no global centroid traffic inside the loop.
+// ============================================================================
+template <int D>
+struct ResidentTile {
+  static constexpr int KS = D / 16;        // MFMA k-steps per tile
+  static constexpr int ROWB = D * 2 + 16;  // LDS row pitch: 16 B pad keeps 16 lanes on 64 distinct banks
+  static constexpr int CPR = D / 8;        // 16-byte chunks per centroid row
+};
+
 // The segment's k_s centroid rows into the padded LDS tiles (rows beyond k_s repeat the
-// last one; the epilogue ignores them).  All threads call this; the caller's barrier follows.
-template <typename T, int D>
-__device__ __forceinline__ void resident_load_centroids(const T* Cs, int k_s, char* cent) {
-  using RT = ResidentTile<T, D>;
+// last one; the epilogue ignores them).  All NT threads call this; the caller's barrier follows.
+template <int D, int NT>
+__device__ __forceinline__ void resident_load_centroids(const bf16_t* Cs, int k_s, char* cent) {
+  using RT = ResidentTile<D>;
   const int ntiles = (k_s + 31) / 32;
-  for (int id = threadIdx.x; id < 32 * ntiles * RT::CPR; id += blockDim.x) {
+  for (int id = threadIdx.x; id < 32 * ntiles * RT::CPR; id += NT) {
     const int row = id / RT::CPR, ch = id - row * RT::CPR;
-    store16(cent + row * RT::ROWB + ch * 16, load16(Cs + (size_t)min(row, k_s - 1) * D + ch * Elem<T>::EPC));
+    store16(cent + row * RT::ROWB + ch * 16, load16(Cs + (size_t)min(row, k_s - 1) * D + ch * 8));
   }
 }
 
-// Each wave of the workgroup takes the fragments f_lo + wave, + waves, ... below f_hi of the
-// segment's points X against the first k_s centroid rows in `cent`; emit(point, row, keys) is
+// Wave `wave` of NW takes the fragments f_lo + wave * NF, + NW * NF, ... below f_hi of the
+// segment's points X against the centroids in `cent`; emit(point, cluster, near_tie) is
 // called once per point by the lane that holds it.
-template <typename T, int D, typename Emit>
-__device__ __forceinline__ void resident_assign_fragments(const T* X, const char* cent, int L_s, int k_s,
+template <int D, int NF, int NW, typename Emit>
+__device__ __forceinline__ void resident_assign_fragments(const bf16_t* X, const char* cent, int L_s, int k_s,
                                                           int f_lo, int f_hi, Emit&& emit) {
-  using RT = ResidentTile<T, D>;
+  using RT = ResidentTile<D>;
   constexpr int KS = RT::KS, ROWB = RT::ROWB;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int ntiles = (k_s + 31) / 32;
   const int nfull = k_s / 32;  // tiles without rows beyond k_s
   constexpr float B0 = kAssignBias;
   floatx16 bias = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
-  if constexpr (sizeof(T) == 2)
-    asm volatile("" : "+v"(bias));  // kept in registers: one accumulator-start operand for every tile
-  for (int fb = f_lo + wave; fb < f_hi; fb += nw) {
-    uint4 bfrag[KS];
-    load_fragment<T, D>(X, fb, L_s, bfrag);
-    Best2 b2;
-    auto mfma_tile = [&](int t, floatx16& acc) {
+  asm volatile("" : "+v"(bias));  // kept in registers: one accumulator-start operand for every tile
+  for (int fb = f_lo + wave * NF; fb < f_hi; fb += NW * NF) {
+    uint4 bfrag[NF][KS];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const int row = min(32 * (fb + f) + col, L_s - 1);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) bfrag[f][s] = load16(X + (size_t)row * D + (2 * s + half) * 8);
+    }
+    int best[NF], second[NF], btile[NF];  // biased similarities as integers; 0 is below all of them
+#pragma unroll
+    for (int f = 0; f < NF; ++f) best[f] = second[f] = btile[f] = 0;
+    auto mfma_tile = [&](int t, floatx16 (&acc)[NF]) {
       const char* tile = cent + (size_t)(32 * t + col) * ROWB + half * 16;
 #pragma unroll
-      for (int s = 0; s < KS; ++s) acc = mfma_chunk<T>(load16(tile + s * 32), bfrag[s], s == 0 ? bias : acc);
+      for (int s = 0; s < KS; ++s) {
+        const bf16x8 a = __builtin_bit_cast(bf16x8, load16(tile + s * 32));
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+          const bf16x8 bv = __builtin_bit_cast(bf16x8, bfrag[f][s]);
+          acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv, s == 0 ? bias : acc[f], 0, 0, 0);
+        }
+      }
     };
     // One tile's MFMAs are issued between the integer epilogue instructions of
     // the tile before it (two accumulator sets): the matrix pipe works while the
@@ -407,48 +404,55 @@ __device__ __forceinline__ void resident_assign_fragments(const T* X, const char
     auto interleave = [&]() {
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // the first two LDS reads
 #pragma unroll
-      for (int i = 0; i < KS; ++i) {
+      for (int i = 0; i < KS * NF; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // the LDS read two MFMAs ahead
         __builtin_amdgcn_sched_group_barrier(0x002, 48 / KS, 0);  // a share of the epilogue
       }
     };
-    floatx16 accA, accB;
-    if constexpr (sizeof(T) == 4) {
-      // (an f32 tile keeps the matrix pipe busy eight times as long per epilogue, and its
-      // operands take twice the registers: one accumulator set, the waves overlap each other)
-#pragma unroll 1
-      for (int t = 0; t < nfull; ++t) {
-        mfma_tile(t, accA);
-        assign_epilogue<false>(accA, b2, t, half, k_s);
-      }
-    } else if (nfull > 0) {
+    floatx16 accA[NF], accB[NF];
+    if (nfull > 0) {
       mfma_tile(0, accA);
       int t = 1;
       for (; t + 1 < nfull; t += 2) {
         mfma_tile(t, accB);
-        assign_epilogue<false>(accA, b2, t - 1, half, k_s);
+        assign_epilogue<NF, false>(accA, best, second, btile, t - 1, half, k_s);
         interleave();
         mfma_tile(t + 1, accA);
-        assign_epilogue<false>(accB, b2, t, half, k_s);
+        assign_epilogue<NF, false>(accB, best, second, btile, t, half, k_s);
         interleave();
       }
       if (t < nfull) {
         mfma_tile(t, accB);
-        assign_epilogue<false>(accA, b2, t - 1, half, k_s);
+        assign_epilogue<NF, false>(accA, best, second, btile, t - 1, half, k_s);
         interleave();
-        assign_epilogue<false>(accB, b2, t, half, k_s);
+        assign_epilogue<NF, false>(accB, best, second, btile, t, half, k_s);
       } else {
-        assign_epilogue<false>(accA, b2, t - 1, half, k_s);
+        assign_epilogue<NF, false>(accA, best, second, btile, t - 1, half, k_s);
       }
     }
     if (nfull < ntiles) {  // the last tile has rows beyond k_s
       mfma_tile(nfull, accA);
-      assign_epilogue<true>(accA, b2, nfull, half, k_s);
+      assign_epilogue<NF, true>(accA, best, second, btile, nfull, half, k_s);
     }
-    const int row = merge_halves(b2, half);
-    const int point = 32 * fb + col;
-    if (half == 0 && point < L_s) emit(point, row, b2);
+    // lanes l and l ^ 32 hold the same points over disjoint centroid rows
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      int brow = (best[f] & 27) | (4 * half);
+      const int ob = __shfl_xor(best[f], 32), os = __shfl_xor(second[f], 32);
+      const int ot = __shfl_xor(btile[f], 32), orow = __shfl_xor(brow, 32);
+      const int nsec = max(min(best[f], ob), max(second[f], os));
+      if (ob > best[f]) {
+        best[f] = ob;
+        btile[f] = ot;
+        brow = orow;
+      }
+      const int point = 32 * (fb + f) + col;
+      if (half == 0 && fb + f < f_hi && point < L_s) {
+        const float gap = __int_as_float(best[f]) - (nsec > 0 ? __int_as_float(nsec) : 0.f);
+        emit(point, btile[f] * 32 + brow, gap < kAssignGuard);
+      }
+    }
   }
 }
 
@@ -458,37 +462,58 @@ __device__ __forceinline__ void resident_assign_fragments(const T* X, const char
 template <int D, int NW, typename Emit>
 __device__ __forceinline__ void lean_assign_fragments(const bf16_t* X, const char* cent, int L_s, int k_s,
                                                       int f_hi, Emit&& emit) {
-  using RT = ResidentTile<bf16_t, D>;
+  using RT = ResidentTile<D>;
   constexpr int KS = RT::KS, ROWB = RT::ROWB;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int ntiles = (k_s + 31) / 32, nfull = k_s / 32;
   constexpr float B0 = kAssignBias;
   const floatx16 bias = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
+  auto load_frag = [&](int fb, uint4 (&dst)[KS]) {
+    const int row = min(32 * fb + col, L_s - 1);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) dst[s] = load16(X + (size_t)row * D + (2 * s + half) * 8);
+  };
   uint4 cur[KS], nxt[KS];
-  if (wave < f_hi) load_fragment<bf16_t, D>(X, wave, L_s, cur);
+  if (wave < f_hi) load_frag(wave, cur);
   for (int fb = wave; fb < f_hi; fb += NW) {
-    if (fb + NW < f_hi) load_fragment<bf16_t, D>(X, fb + NW, L_s, nxt);
-    Best2 b2;
+    if (fb + NW < f_hi) load_frag(fb + NW, nxt);
+    int best[1] = {0}, second[1] = {0}, btile[1] = {0};
     for (int t = 0; t < ntiles; ++t) {
       const char* tile = cent + (size_t)(32 * t + col) * ROWB + half * 16;
-      floatx16 acc;
+      floatx16 acc[1];
 #pragma unroll
-      for (int s = 0; s < KS; ++s) acc = mfma_chunk<bf16_t>(load16(tile + s * 32), cur[s], s == 0 ? bias : acc);
-      if (t < nfull) assign_epilogue<false>(acc, b2, t, half, k_s);
-      else assign_epilogue<true>(acc, b2, t, half, k_s);
+      for (int s = 0; s < KS; ++s) {
+        const bf16x8 a = __builtin_bit_cast(bf16x8, load16(tile + s * 32));
+        const bf16x8 bv = __builtin_bit_cast(bf16x8, cur[s]);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bv, s == 0 ? bias : acc[0], 0, 0, 0);
+      }
+      if (t < nfull) assign_epilogue<1, false>(acc, best, second, btile, t, half, k_s);
+      else assign_epilogue<1, true>(acc, best, second, btile, t, half, k_s);
     }
-    const int row = merge_halves(b2, half);
+    // lanes l and l ^ 32 hold the same points over disjoint centroid rows
+    int brow = (best[0] & 27) | (4 * half);
+    const int ob = __shfl_xor(best[0], 32), os = __shfl_xor(second[0], 32);
+    const int ot = __shfl_xor(btile[0], 32), orow = __shfl_xor(brow, 32);
+    const int nsec = max(min(best[0], ob), max(second[0], os));
+    if (ob > best[0]) {
+      best[0] = ob;
+      btile[0] = ot;
+      brow = orow;
+    }
     const int point = 32 * fb + col;
-    if (half == 0 && point < L_s) emit(point, row, b2);
+    if (half == 0 && point < L_s) {
+      const float gap = __int_as_float(best[0]) - (nsec > 0 ? __int_as_float(nsec) : 0.f);
+      emit(point, btile[0] * 32 + brow, gap < kAssignGuard);
+    }
 #pragma unroll
     for (int s = 0; s < KS; ++s) cur[s] = nxt[s];
   }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(1024) void assign_resident_kernel(
-    const T* __restrict__ xhat, const T* __restrict__ chat, int32_t* __restrict__ assign,
+template <int D, int NF, int NW>
+__global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
+    const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
     int32_t* __restrict__ flag_list, int32_t* __restrict__ flag_count, int S, int L, int kk, int N_idx,
     int pieces_per_seg) {
   extern __shared__ __attribute__((aligned(16))) char cent[];  // 32 * ceil(k_s / 32) rows
@@ -497,18 +522,69 @@ __global__ __launch_bounds__(1024) void assign_resident_kernel(
   const int sg = wg / pieces_per_seg, piece = wg - sg * pieces_per_seg;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
   const int nfrag = (si.L_s + 31) / 32;
-  const int per = (nfrag + pieces_per_seg - 1) / pieces_per_seg;
+  const int per = ((nfrag + pieces_per_seg - 1) / pieces_per_seg + NF - 1) / NF * NF;
   const int f_lo = piece * per, f_hi = min(nfrag, f_lo + per);
   if (f_lo >= f_hi) return;
-  const T* X = xhat + ((size_t)si.unit * N_idx + si.seg_start) * D;
-  resident_load_centroids<T, D>(chat + (size_t)sg * kk * D, si.k_s, cent);
+  const bf16_t* X = xhat + ((size_t)si.unit * N_idx + si.seg_start) * D;
+  resident_load_centroids<D, 64 * NW>(chat + (size_t)sg * kk * D, si.k_s, cent);
   __syncthreads();
   const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
-  resident_assign_fragments<T, D>(X, cent, si.L_s, si.k_s, f_lo, f_hi, [&](int point, int cluster, const Best2& b2) {
-    assign[gp0 + point] = cluster;
-    if (key_gap(b2.best, b2.second) < kAssignGuard<T>)
-      flag_list[atomicAdd(flag_count, 1)] = (int32_t)(gp0 + point);
-  });
+  resident_assign_fragments<D, NF, NW>(X, cent, si.L_s, si.k_s, f_lo, f_hi,
+                                       [&](int point, int cluster, bool near_tie) {
+                                         assign[gp0 + point] = cluster;
+                                         if (near_tie) flag_list[atomicAdd(flag_count, 1)] = (int32_t)(gp0 + point);
+                                       });
+}
+
+// ============================================================================
+// Assign, plain path (any storage type): one point per thread, fp32 FMA chain,
+// centroids broadcast from LDS.
+// ============================================================================
+template <typename T, int D>
+__global__ __launch_bounds__(256) void assign_plain_kernel(
+    const T* __restrict__ xhat, const T* __restrict__ chat, int32_t* __restrict__ assign,
+    int32_t* __restrict__ flag_list, int32_t* __restrict__ flag_count, int S, int L, int kk, int N_idx,
+    int wgs_per_seg) {
+  constexpr int CT = 16;  // centroids per LDS tile
+  __shared__ __attribute__((aligned(16))) float cs[CT][D];
+  const int sg = blockIdx.x / wgs_per_seg, piece = blockIdx.x - sg * wgs_per_seg;
+  const SegInfo si = seg_info(sg, S, L, kk, N_idx);
+  const int p0 = piece * 256;
+  if (p0 >= si.L_s) return;
+  const int point = p0 + threadIdx.x;
+  const T* xr = xhat + ((size_t)si.unit * N_idx + si.seg_start + min(point, si.L_s - 1)) * D;
+  const T* Cs = chat + (size_t)sg * kk * D;
+  float x[D];
+#pragma unroll
+  for (int e = 0; e < D; ++e) x[e] = to_f32(xr[e]);
+  float best = kNegHuge, second = kNegHuge;
+  int bidx = 0;
+  for (int c0 = 0; c0 < si.k_s; c0 += CT) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < CT * D; i += 256) {
+      const int r = i / D, e = i - r * D;
+      cs[r][e] = to_f32(Cs[(size_t)min(c0 + r, si.k_s - 1) * D + e]);
+    }
+    __syncthreads();
+    const int nc = min(CT, si.k_s - c0);
+    for (int r = 0; r < nc; ++r) {
+      float a = 0.f;
+#pragma unroll
+      for (int e = 0; e < D; ++e) a = fmaf(x[e], cs[r][e], a);
+      if (a > best) {
+        second = best;
+        best = a;
+        bidx = c0 + r;
+      } else {
+        second = fmaxf(second, a);
+      }
+    }
+  }
+  if (point < si.L_s) {
+    const size_t gp = (size_t)si.unit * N_idx + si.seg_start + point;
+    assign[gp] = bidx;
+    if (best - second < kAssignGuard) flag_list[atomicAdd(flag_count, 1)] = (int32_t)gp;
+  }
 }
 
 // ============================================================================
@@ -980,7 +1056,7 @@ constexpr int SMALL_NW = 16;
 
 template <int D>
 inline size_t small_kmeans_lds(int kk) {
-  return (size_t)32 * ((kk + 31) / 32) * ResidentTile<bf16_t, D>::ROWB +
+  return (size_t)32 * ((kk + 31) / 32) * ResidentTile<D>::ROWB +
          sizeof(int) * ((size_t)SMALL_NW * kk + kk + 2 * SMALL_L_MAX + 2 * (size_t)kk);
 }
 
@@ -989,7 +1065,7 @@ __global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ order,
     int32_t* __restrict__ count, int32_t* __restrict__ start, int S, int L, int kk, int N_idx, int iters,
     int key_bits) {
-  using RT = ResidentTile<bf16_t, D>;
+  using RT = ResidentTile<D>;
   constexpr int NT = 64 * SMALL_NW, LPR = D / 8, GROUPS = NT / LPR;
   extern __shared__ __attribute__((aligned(16))) char small_lds[];
   char* cent = small_lds;
@@ -1006,7 +1082,7 @@ __global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
   const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
   const bf16_t* X = xhat + p0 * D;
   const int nfrag = (si.L_s + 31) / 32;
-  resident_load_centroids<bf16_t, D>(chat + (size_t)sg * kk * D, si.k_s, cent);
+  resident_load_centroids<D, NT>(chat + (size_t)sg * kk * D, si.k_s, cent);
 #ifdef WAVE_TRACE  // phase times of workgroup 0 (100 MHz clock), printed at the end
   unsigned long long tp[5] = {0, 0, 0, 0, 0}, tl = wall_clock64();
   int nf_total = 0;
@@ -1019,10 +1095,9 @@ __global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
     __syncthreads();
     WAVE_PHASE(0);
     lean_assign_fragments<D, SMALL_NW>(X, cent, si.L_s, si.k_s, nfrag,
-                                       [&](int point, int cluster, const Best2& b2) {
+                                       [&](int point, int cluster, bool near_tie) {
                                          a_s[point] = cluster;
-                                         if (key_gap(b2.best, b2.second) < kAssignGuard<bf16_t>)
-                                           flags[atomicAdd(&nflag, 1)] = point;
+                                         if (near_tie) flags[atomicAdd(&nflag, 1)] = point;
                                        });
     __syncthreads();
     WAVE_PHASE(1);
@@ -1229,58 +1304,29 @@ static int key_bits_for(int kk) {
   return b;
 }
 
-// How the resident assign step is cut: waves per workgroup and workgroups per segment.
-struct AssignSplit {
-  int waves, pieces;
-};
-// Every workgroup copies the segment's centroids into LDS before its waves start, and the CU's
-// waves share its matrix pipes.  Measured at 512 x 128 bf16 on full CUs of 16 waves: about
-// 15 us per fragment of each wave and 5 us for the copy; fewer waves per CU shorten a fragment
-// down to about 4 us.  Both scale with the number of centroids, so their ratio does not depend
-// on it.  The split that the model finds cheapest is taken: two workgroups of 16 waves per
-// segment for a large batch (as before), eight for the 32 segments of a 32K-token sequence
-// (89 -> 37 us a step: 64 workgroups left three quarters of the CUs idle), workgroups of four
-// waves for a few short segments.
-static AssignSplit assign_split(int segs, int Lmax, size_t lds) {
-  const int nfrag = (Lmax + 31) / 32;
-  AssignSplit best{16, 1};
-  double best_cost = 1e300;
-  for (int nw = 16; nw >= 4; nw >>= 1) {
-    const int by_lds = (int)(160 * 1024 / (lds + 1024)), by_waves = 32 / nw;
-    const int per_cu = by_lds < 1 ? 1 : (by_lds < by_waves ? by_lds : by_waves);
-    for (int p = 1; p <= 64 && (p == 1 || (p - 1) * nw < nfrag); ++p) {
-      const long long wgs = (long long)segs * p;
-      const long long on_cu = (wgs + 255) / 256;                      // workgroups per CU over the launch
-      const int resident = (int)(on_cu < per_cu ? on_cu : per_cu);
-      const double frag = 15.0 / 16.0 * resident * nw, f = frag < 4.0 ? 4.0 : frag;
-      const int per = (nfrag + p - 1) / p, steps = (per + nw - 1) / nw;
-      const double cost = (double)((on_cu + resident - 1) / resident) * (5.0 * resident + steps * f);
-      if (cost < best_cost * 0.999) {
-        best_cost = cost;
-        best = {nw, p};
-      }
-    }
-  }
-  return best;
-}
-
 template <typename T, int D>
 static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t* flag, int32_t* nflag,
                           int S, int L, int kk, int N_idx, int segs, hipStream_t st) {
-  using RT = ResidentTile<T, D>;
   const int Lmax = L < N_idx ? L : N_idx;
-  // Centroids resident in LDS when a segment's padded rows fit (k = 512 at d = 128 in bf16 is
-  // 136 KiB of the 160 KiB).  Otherwise the centroids are staged through LDS tile by tile.
-  const int kmax = kk < Lmax ? kk : Lmax;
-  const size_t resident_lds = (size_t)32 * ((kmax + 31) / 32) * RT::ROWB;
-  if (resident_lds <= 144 * 1024) {
-    const AssignSplit sp = assign_split(segs, Lmax, resident_lds);
-    WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<T, D>), segs * sp.pieces, 64 * sp.waves, resident_lds, st,
-                xhat, chat, assign, flag, nflag, S, L, kk, N_idx, sp.pieces);
+  if constexpr (sizeof(T) == 2) {
+    // Centroids resident in LDS when a segment's padded rows fit (k = 512 at d = 128 is
+    // 136 KiB of the 160 KiB); two workgroups per segment keep the last round of
+    // workgroups short.  Otherwise the centroids are staged through LDS tile by tile.
+    const int kmax = kk < Lmax ? kk : Lmax;
+    const size_t resident_lds = (size_t)32 * ((kmax + 31) / 32) * (D * 2 + 16);
+    if (resident_lds <= 144 * 1024) {
+      const int pieces = Lmax > 2048 ? 2 : 1;
+      WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16>), segs * pieces, 1024, resident_lds, st,
+                  xhat, chat, assign, flag, nflag, S, L, kk, N_idx, pieces);
+    } else {
+      constexpr int PWG = 8 * 32;
+      const int wps = (Lmax + PWG - 1) / PWG;
+      WAVE_LAUNCH("assign_mfma", (assign_mfma_kernel<D, 1, 8>), segs * wps, 64 * 8, 0, st, xhat, chat,
+                  assign, flag, nflag, S, L, kk, N_idx, wps);
+    }
   } else {
-    constexpr int NW = 8;
-    const int wps = (Lmax + NW * 32 - 1) / (NW * 32);
-    WAVE_LAUNCH("assign_mfma", (assign_staged_kernel<T, D, NW>), segs * wps, 64 * NW, 0, st, xhat, chat,
+    const int wps = (Lmax + 255) / 256;
+    WAVE_LAUNCH("assign_plain", (assign_plain_kernel<T, D>), segs * wps, 256, 0, st, xhat, chat,
                 assign, flag, nflag, S, L, kk, N_idx, wps);
   }
 }
