@@ -1,0 +1,41 @@
+"""GPU parity of the k-means rounds at the sizes where their launch shapes and tiles change: the
+index arrays of whole builds against the oracle's, bit for bit."""
+import pytest
+import torch
+
+from paper_2505_02922_amd import binding as wb
+from paper_2505_02922_amd import synth
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+
+def _keys(kind, B, N, d, seed):
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn(B, 1, N, d, generator=g)
+    if kind == "mixture":    # well separated: few points change cluster after the first rounds
+        centre = torch.randn(64, d, generator=g)
+        x = centre[torch.randint(0, 64, (B, 1, N), generator=g)] + 0.3 * x
+    elif kind == "ties":     # few distinct keys: equal similarities and clusters that stay empty
+        few = torch.randn(23, d, generator=g)
+        x = few[torch.randint(0, 23, (B, 1, N), generator=g)]
+    return x                 # "plain": no clusters, most points near a boundary
+
+
+# (N - 5 tokens are indexed.  4097 points: the last of two or three workgroups' shares has one
+# fragment with one point; k = 33: a tile with one row; k = 1000 at d = 64: 32 tiles, as many as
+# stay resident; plain keys: hundreds of points per workgroup need the full comparison)
+@pytest.mark.parametrize("kind,d,N,L,k,iters", [
+    ("mixture", 128, 4102, 4097, 33, 7), ("plain", 128, 9000, 8192, 512, 8), ("mixture", 64, 4000, 2100, 1000, 5),
+    ("ties", 128, 3000, 2100, 65, 5), ("plain", 64, 8197, 8192, 40, 6), ("plain", 128, 2205, 2200, 1, 4)])
+def test_rounds_match_oracle(kind, d, N, L, k, iters):
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="rounds", B=1, Hq=1, Hkv=1, N=N, d=d, n_sink=2, n_local=3,
+                      segment_len=L, clusters_per_segment=k, iters=iters)
+    K = _keys(kind, 1, N, d, N + k).to(torch.bfloat16)
+    V = torch.randn(1, 1, N, d, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16)
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), wl.n_sink, wl.n_local, L, k, iters, 0)
+    torch.cuda.synchronize()
+    for name in wb.BUFFER_NAMES:
+        got = ix.t[name].cpu()
+        assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
