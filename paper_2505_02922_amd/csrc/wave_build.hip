@@ -497,22 +497,148 @@ struct __attribute__((aligned(8))) PointBounds {
   int own, others;
 };
 
-// A point's cluster from a comparison with every centroid.  A near-tie is left to the fp64 step,
-// which may pick another of the centroids near `best`: the bound on the others is then `best`.
-__device__ __forceinline__ void settle_point(int32_t* assign, PointBounds* bounds, int32_t* flag_list,
-                                             int32_t* flag_count, size_t gp, int cluster, int best, int second) {
+// A point's cluster from a comparison with every centroid.
+__device__ __forceinline__ void settle_point(int32_t* assign, PointBounds* bounds, size_t gp, int cluster, int own,
+                                             int others) {
   assign[gp] = cluster;
-  const bool near_tie = key_gap(best, second) < kAssignGuard;
-  if (near_tie) flag_list[atomicAdd(flag_count, 1)] = (int32_t)gp;
-  if (bounds) bounds[gp] = PointBounds{best, near_tie ? best : second};
+  if (bounds) bounds[gp] = PointBounds{own, others};
+}
+
+constexpr int ASSIGN_POINTS = 4096;  // most points of a workgroup of the resident kernels
+constexpr int LIST_FRAGS = 4;        // fragments of listed points per round of compare_listed
+
+// The listed points (first + left[0, n)) of the segment's points X against every centroid, by the
+// whole workgroup: the waves share out (fragment of the list, centroid tile), the centroids come
+// from the cache, and the tiles' best two are merged per point.  A point whose two best are
+// closer than the guard gets fp64 similarities (exact for the stored operands up to fp64
+// rounding, ties to the lowest centroid) of the centroids in every tile whose best is that
+// close, one lane per centroid; the bound on its other similarities is then `best` too.
+// scratch: 3584 bytes per centroid tile.  settle(point, cluster, own, others) is called once
+// per listed point.  (16 sequences x 120K tokens: about 8 near-ties per segment in the first
+// round.  A launch of their own, one workgroup per point over every centroid in fp64, took
+// 575 us for it and 260 us a round on keys with heavy-tailed channels.)
+template <int D, int NW, typename Settle>
+__device__ __forceinline__ void compare_listed(const bf16_t* X, const bf16_t* Cs, int first, const uint16_t* left,
+                                               int n, int k_s, char* scratch, int* nitem, Settle&& settle) {
+  constexpr int KS = ResidentTile<D>::KS, PTS = 32 * LIST_FRAGS;
+  static_assert(PTS <= 64 * NW, "one thread per point");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, col = lane & 31;
+  const int ntiles = (k_s + 31) / 32;
+  int* part = reinterpret_cast<int*>(scratch);     // per (fragment, tile): 32 x (best, second, row)
+  int* item = part + LIST_FRAGS * ntiles * 96;     // (point, tile) pairs for the fp64 step
+  double* item_v = reinterpret_cast<double*>(item + PTS * ntiles);
+  int* item_c = reinterpret_cast<int*>(item_v + PTS * ntiles);
+  for (int b0 = 0; b0 < n; b0 += PTS) {
+    const int nf = min(LIST_FRAGS, (n - b0 + 31) / 32);
+    if (tid == 0) *nitem = 0;
+    for (int it = wave; it < nf * ntiles; it += NW) {
+      const int f = it / ntiles, t = it - f * ntiles;
+      const bf16_t* xr = X + (size_t)(first + left[min(b0 + 32 * f + col, n - 1)]) * D + half * 8;
+      const bf16_t* cr = Cs + (size_t)min(32 * t + col, k_s - 1) * D + half * 8;
+      uint4 a[KS], b[KS];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a[s] = load16(cr + 16 * s);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) b[s] = load16(xr + 16 * s);
+      constexpr float B0 = kAssignBias;
+      floatx16 acc[1] = {{B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0}};
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[s]),
+                                                         __builtin_bit_cast(bf16x8, b[s]), acc[0], 0, 0, 0);
+      int best[1] = {0}, second[1] = {0}, btile[1] = {0};
+      assign_epilogue<1, true>(acc, best, second, btile, t, half, k_s);
+      const int row = merge_halves(best[0], second[0], btile[0], half);
+      if (half == 0) {
+        int* o = part + (it * 32 + col) * 3;
+        o[0] = best[0];
+        o[1] = second[0];
+        o[2] = row;
+      }
+    }
+    __syncthreads();
+    int best = 0, row = 0, first_item = 0, items = 0;
+    if (tid < PTS && b0 + tid < n) {
+      const int* mine = part + ((tid >> 5) * ntiles * 32 + (tid & 31)) * 3;
+      int second = mine[1];
+      best = mine[0], row = mine[2];
+      for (int t = 1; t < ntiles; ++t) {
+        const int* o = mine + t * 96;
+        second = max(max(second, o[1]), min(best, o[0]));
+        row = o[0] > best ? o[2] : row;
+        best = max(best, o[0]);
+      }
+      if (key_gap(best, second) < kAssignGuard) {
+        for (int t = 0; t < ntiles; ++t) items += key_gap(best, mine[t * 96]) < kAssignGuard ? 1 : 0;
+        first_item = atomicAdd(nitem, items);
+        int j = first_item;
+        for (int t = 0; t < ntiles; ++t)
+          if (key_gap(best, mine[t * 96]) < kAssignGuard) item[j++] = tid << 16 | t;
+      } else {
+        settle(first + left[b0 + tid], row, best, second);
+      }
+    }
+    __syncthreads();
+    const int ni = *nitem;
+    for (int it = 2 * wave + half; it < ni; it += 2 * NW) {  // half a wave per item
+      const int c = 32 * (item[it] & 0xffff) + col;
+      const bf16_t* xr = X + (size_t)(first + left[b0 + (item[it] >> 16)]) * D;
+      const bf16_t* cr = Cs + (size_t)min(c, k_s - 1) * D;
+      double acc = 0.0;
+#pragma unroll 4
+      for (int e0 = 0; e0 < D; e0 += 8) {
+        float xf[8], cf[8];
+        unpack<bf16_t>(load16(xr + e0), xf);
+        unpack<bf16_t>(load16(cr + e0), cf);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc = fma((double)xf[e], (double)cf[e], acc);
+      }
+      double bv = -1.0e300;
+      int bc = 0x7fffffff;
+      if (c < k_s && acc > bv) {
+        bv = acc;
+        bc = c;
+      }
+      for (int off = 16; off >= 1; off >>= 1) {
+        const double ov = __shfl_xor(bv, off);
+        const int oc = __shfl_xor(bc, off);
+        if (ov > bv || (ov == bv && oc < bc)) {
+          bv = ov;
+          bc = oc;
+        }
+      }
+      if (col == 0) {
+        item_v[it] = bv;
+        item_c[it] = bc;
+      }
+    }
+    __syncthreads();
+    if (items > 0) {
+      double bv = -1.0e300;  // (nothing comparable: the fp32 decision stands)
+      for (int j = first_item; j < first_item + items; ++j)  // tiles ascend: strict > keeps the lowest centroid
+        if (item_v[j] > bv) {
+          bv = item_v[j];
+          row = item_c[j];
+        }
+      settle(first + left[b0 + tid], row, best, best);
+    }
+    __syncthreads();
+  }
+}
+
+template <int D>
+inline size_t resident_lds(int kmax) {
+  return (size_t)32 * ((kmax + 31) / 32) * ResidentTile<D>::ROWB + sizeof(uint16_t) * ASSIGN_POINTS;
 }
 
 template <int D, int NF, int NW>
 __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    PointBounds* __restrict__ bounds, int32_t* __restrict__ flag_list, int32_t* __restrict__ flag_count, int S,
-    int L, int kk, int N_idx, int pieces_per_seg) {
-  extern __shared__ __attribute__((aligned(16))) char cent[];  // 32 * ceil(k_s / 32) rows
+    PointBounds* __restrict__ bounds, int S, int L, int kk, int N_idx, int pieces_per_seg) {
+  // 32 * ceil(k_s / 32) padded rows, then the near-ties
+  extern __shared__ __attribute__((aligned(16))) char cent[];
+  __shared__ int nleft, nitem;
 
   const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
   const int sg = wg / pieces_per_seg, piece = wg - sg * pieces_per_seg;
@@ -521,15 +647,25 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
   const int per = ((nfrag + pieces_per_seg - 1) / pieces_per_seg + NF - 1) / NF * NF;
   const int f_lo = piece * per, f_hi = min(nfrag, f_lo + per);
   if (f_lo >= f_hi) return;
-  const bf16_t* X = xhat + ((size_t)si.unit * N_idx + si.seg_start) * D;
-  resident_load_centroids<D, 64 * NW>(chat + (size_t)sg * kk * D, si.k_s, cent);
-  __syncthreads();
   const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
+  const bf16_t* X = xhat + gp0 * D;
+  const bf16_t* Cs = chat + (size_t)sg * kk * D;
+  uint16_t* left = reinterpret_cast<uint16_t*>(cent + (size_t)32 * ((si.k_s + 31) / 32) * ResidentTile<D>::ROWB);
+  if (threadIdx.x == 0) nleft = 0;
+  resident_load_centroids<D, 64 * NW>(Cs, si.k_s, cent);
+  __syncthreads();
+  auto settle = [&](int point, int cluster, int own, int others) {
+    settle_point(assign, bounds, gp0 + point, cluster, own, others);
+  };
   resident_assign_fragments<D, NF, NW>(X, cent, si.L_s, si.k_s, f_lo, f_hi,
                                        [&](int point, int cluster, int best, int second) {
-                                         settle_point(assign, bounds, flag_list, flag_count, gp0 + point, cluster,
-                                                      best, second);
+                                         if (key_gap(best, second) < kAssignGuard)
+                                           left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
+                                         else
+                                           settle(point, cluster, best, second);
                                        });
+  __syncthreads();
+  compare_listed<D, NW>(X, Cs, 32 * f_lo, left, nleft, si.k_s, cent, &nitem, settle);
 }
 
 // ============================================================================
@@ -539,50 +675,43 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
 //   own centroid unchanged   c1 below own: the point stays; c1 above own: it moves to c1's
 //   own centroid changed     c1 above `others`: no unchanged centroid can beat it, c1's cluster;
 //                            otherwise the point is compared with every centroid
-// each by more than the guard of the fp32 similarities; what is closer goes to the fp64
-// step, which compares with every centroid.  (A near-tie that the fp64 step has decided stays
-// decided while no changed centroid comes near.)  So the partition is, in every round, the one
+// each by more than the guard of the fp32 similarities; what is closer is compared with every
+// centroid as well.  (A near-tie that was decided in fp64 stays decided while no changed centroid
+// comes near.)  So the partition is, in every round, the one
 // that the full comparison gives.
 // The share of changed centroids falls from 82 % in the third round to 3 % in the tenth on
 // 8192-token segments of 512 clusters, and 1 % of the points need every centroid: a round costs
 // between a full pass and reading xhat once (16 sequences x 120K tokens: 1.85 ms full, 0.8 ms
 // at the streaming rate).
 //
-// A workgroup takes at most DELTA_POINTS points of a segment.  It lists the changed centroids,
+// A workgroup takes at most ASSIGN_POINTS points of a segment.  It lists the changed centroids,
 // copies their rows into LDS and streams its points past them as in the kernel above, two
 // accumulator sets while many tiles make the matrix pipe the bound, else the next fragment's
-// rows requested ahead.  Points that need every centroid are listed; at the end the waves share
-// them out by (fragment of the list, centroid tile) with the centroids read from the cache,
-// and the tiles' best two are merged per point.
+// rows requested ahead.  Points that need every centroid are listed and compared at the end.
 // ============================================================================
-constexpr int DELTA_POINTS = 4096;
-constexpr int DELTA_FRAGS = 4;  // fragments of the list per round of the full comparison
-
 template <int D>
 inline size_t delta_lds(int kmax) {
   const int ntiles = (kmax + 31) / 32;
-  return (size_t)32 * ntiles * ResidentTile<D>::ROWB + sizeof(uint32_t) * ntiles +
-         sizeof(uint16_t) * (32 * (size_t)ntiles + DELTA_POINTS);
+  return resident_lds<D>(kmax) + sizeof(uint32_t) * ntiles + sizeof(uint16_t) * 32 * (size_t)ntiles;
 }
 
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW) void assign_delta_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    PointBounds* __restrict__ bounds, const int32_t* __restrict__ changed, int32_t* __restrict__ flag_list,
-    int32_t* __restrict__ flag_count, int S, int L, int kk, int N_idx, int pieces_per_seg) {
+    PointBounds* __restrict__ bounds, const int32_t* __restrict__ changed, int S, int L, int kk, int N_idx,
+    int pieces_per_seg) {
   using RT = ResidentTile<D>;
-  constexpr int KS = RT::KS, ROWB = RT::ROWB, CPR = RT::CPR, NT = 64 * NW;
+  constexpr int ROWB = RT::ROWB, CPR = RT::CPR, NT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) char cent[];
-  __shared__ int wave_n[NW], nleft;
+  __shared__ int wave_n[NW], nleft, nitem;
   const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
   const int sg = wg / pieces_per_seg, piece = wg - sg * pieces_per_seg;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
   const int nfrag = (si.L_s + 31) / 32;
-  const int per = (nfrag + pieces_per_seg - 1) / pieces_per_seg;  // (32 * per <= DELTA_POINTS: the launch's rule)
+  const int per = (nfrag + pieces_per_seg - 1) / pieces_per_seg;
   const int f_lo = piece * per, f_hi = min(nfrag, f_lo + per);
   if (f_lo >= f_hi) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, col = lane & 31;
   const int ntiles_all = (si.k_s + 31) / 32;
   uint32_t* marks = reinterpret_cast<uint32_t*>(cent + (size_t)32 * ntiles_all * ROWB);  // one bit per centroid
   uint16_t* list = reinterpret_cast<uint16_t*>(marks + ntiles_all);                      // changed centroids
@@ -619,29 +748,23 @@ __global__ __launch_bounds__(64 * NW) void assign_delta_kernel(
   }
   __syncthreads();
 
+  auto settle = [&](int point, int cluster, int own, int others) {
+    settle_point(assign, bounds, gp0 + point, cluster, own, others);
+  };
   auto decide = [&](int point, int row, int c1, int c2) {
     const size_t gp = gp0 + point;
     const int own_c = assign[gp];
     const PointBounds pb = bounds[gp];
-    if (!((marks[own_c / 32] >> (own_c & 31)) & 1u)) {
-      if (key_gap(pb.own, c1) > kAssignGuard) {
-        if (c1 > pb.others) bounds[gp].others = c1;
-        return;
-      }
-      const int rest = max(max(pb.own, pb.others), c2);
-      if (key_gap(c1, rest) > kAssignGuard) {
-        assign[gp] = list[row];
-        bounds[gp] = PointBounds{c1, rest};
-      } else {  // near-tie
-        const int top = max(pb.own, c1);
-        flag_list[atomicAdd(flag_count, 1)] = (int32_t)gp;
-        bounds[gp] = PointBounds{top, top};
-      }
-    } else if (key_gap(c1, pb.others) > kAssignGuard) {
-      settle_point(assign, bounds, flag_list, flag_count, gp, list[row], c1, max(c2, pb.others));
-    } else {
-      left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
+    const bool own_changed = (marks[own_c / 32] >> (own_c & 31)) & 1u;
+    if (!own_changed && key_gap(pb.own, c1) > kAssignGuard) {
+      if (c1 > pb.others) bounds[gp].others = c1;
+      return;
     }
+    const int rest = max(own_changed ? pb.others : max(pb.own, pb.others), c2);
+    if (key_gap(c1, rest) > kAssignGuard)
+      settle(point, list[row], c1, rest);
+    else
+      left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
   };
   if (nch > 64)
     resident_assign_fragments<D, 1, NW>(X, cent, si.L_s, nch, f_lo, f_hi, decide);
@@ -649,52 +772,7 @@ __global__ __launch_bounds__(64 * NW) void assign_delta_kernel(
     lean_assign_fragments<D, NW>(X, cent, si.L_s, nch, f_lo, f_hi, decide);
   __syncthreads();
 
-  // the listed points against every centroid
-  const int n = nleft;
-  int* part = reinterpret_cast<int*>(cent);  // per (fragment, tile): 32 x (best, second, row)
-  for (int b0 = 0; b0 < n; b0 += 32 * DELTA_FRAGS) {
-    const int nf = min(DELTA_FRAGS, (n - b0 + 31) / 32);
-    for (int it = wave; it < nf * ntiles_all; it += NW) {
-      const int f = it / ntiles_all, t = it - f * ntiles_all;
-      const int point = 32 * f_lo + left[min(b0 + 32 * f + col, n - 1)];
-      const bf16_t* xr = X + (size_t)point * D + half * 8;
-      const bf16_t* cr = Cs + (size_t)min(32 * t + col, si.k_s - 1) * D + half * 8;
-      uint4 a[KS], b[KS];
-#pragma unroll
-      for (int s = 0; s < KS; ++s) a[s] = load16(cr + 16 * s);
-#pragma unroll
-      for (int s = 0; s < KS; ++s) b[s] = load16(xr + 16 * s);
-      constexpr float B0 = kAssignBias;
-      floatx16 acc[1] = {{B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0}};
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[s]),
-                                                         __builtin_bit_cast(bf16x8, b[s]), acc[0], 0, 0, 0);
-      int best[1] = {0}, second[1] = {0}, btile[1] = {0};
-      assign_epilogue<1, true>(acc, best, second, btile, t, half, si.k_s);
-      const int row = merge_halves(best[0], second[0], btile[0], half);
-      if (half == 0) {
-        int* o = part + (it * 32 + col) * 3;
-        o[0] = best[0];
-        o[1] = second[0];
-        o[2] = row;
-      }
-    }
-    __syncthreads();
-    const int i = b0 + tid;
-    if (tid < 32 * DELTA_FRAGS && i < n) {
-      const int* o = part + ((tid >> 5) * ntiles_all * 32 + (tid & 31)) * 3;
-      int best = o[0], second = o[1], row = o[2];
-      for (int t = 1; t < ntiles_all; ++t) {
-        o += 32 * 3;
-        second = max(max(second, o[1]), min(best, o[0]));
-        row = o[0] > best ? o[2] : row;
-        best = max(best, o[0]);
-      }
-      settle_point(assign, bounds, flag_list, flag_count, gp0 + 32 * f_lo + left[i], row, best, second);
-    }
-    __syncthreads();
-  }
+  compare_listed<D, NW>(X, Cs, 32 * f_lo, left, nleft, si.k_s, cent, &nitem, settle);
 }
 
 // ============================================================================
@@ -1486,38 +1564,39 @@ static int key_bits_for(int kk) {
   return b;
 }
 
-// bounds, changed: null in a round that compares every point with every centroid; with `bounds`
-// alone such a round leaves what the next one needs to compare with the changed centroids only.
+// One assign step.  bounds, changed: null in a round that compares every point with every
+// centroid; with `bounds` alone such a round leaves what the next one needs to compare with the
+// changed centroids only.
 template <typename T, int D>
 static void launch_assign(const T* xhat, const T* chat, int32_t* assign, PointBounds* bounds,
                           const int32_t* changed, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
-                          int segs, hipStream_t st) {
-  const int Lmax = L < N_idx ? L : N_idx;
+                          int segs, int refine_wgs, hipStream_t st) {
+  const int Lmax = L < N_idx ? L : N_idx, kmax = kk < Lmax ? kk : Lmax;
   if constexpr (sizeof(T) == 2) {
-    const int kmax = kk < Lmax ? kk : Lmax;
-    const size_t resident_lds = (size_t)32 * ((kmax + 31) / 32) * ResidentTile<D>::ROWB;
     if (centroids_resident(WAVE_BF16, D, kmax)) {
-      // two workgroups per segment keep the last round of workgroups short
-      int pieces = Lmax > 2048 ? 2 : 1;
-      if (changed) {
-        if (pieces < (Lmax + DELTA_POINTS - 1) / DELTA_POINTS) pieces = (Lmax + DELTA_POINTS - 1) / DELTA_POINTS;
+      // at least two workgroups per long segment keep the last round of workgroups short
+      int pieces = (Lmax + ASSIGN_POINTS - 1) / ASSIGN_POINTS;
+      if (pieces < 2 && Lmax > 2048) pieces = 2;
+      if (changed)
         WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16>), segs * pieces, 1024, delta_lds<D>(kmax), st, xhat,
-                    chat, assign, bounds, changed, flag, nflag, S, L, kk, N_idx, pieces);
-      } else {
-        WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16>), segs * pieces, 1024, resident_lds, st,
-                    xhat, chat, assign, bounds, flag, nflag, S, L, kk, N_idx, pieces);
-      }
-    } else {  // the centroids are staged through LDS tile by tile
-      constexpr int PWG = 8 * 32;
-      const int wps = (Lmax + PWG - 1) / PWG;
-      WAVE_LAUNCH("assign_mfma", (assign_mfma_kernel<D, 1, 8>), segs * wps, 64 * 8, 0, st, xhat, chat,
-                  assign, flag, nflag, S, L, kk, N_idx, wps);
+                    chat, assign, bounds, changed, S, L, kk, N_idx, pieces);
+      else
+        WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16>), segs * pieces, 1024, resident_lds<D>(kmax),
+                    st, xhat, chat, assign, bounds, S, L, kk, N_idx, pieces);
+      return;
     }
+    // the centroids are staged through LDS tile by tile
+    constexpr int PWG = 8 * 32;
+    const int wps = (Lmax + PWG - 1) / PWG;
+    WAVE_LAUNCH("assign_mfma", (assign_mfma_kernel<D, 1, 8>), segs * wps, 64 * 8, 0, st, xhat, chat,
+                assign, flag, nflag, S, L, kk, N_idx, wps);
   } else {
     const int wps = (Lmax + 255) / 256;
     WAVE_LAUNCH("assign_plain", (assign_plain_kernel<T, D>), segs * wps, 256, 0, st, xhat, chat,
                 assign, flag, nflag, S, L, kk, N_idx, wps);
   }
+  WAVE_LAUNCH("refine", (refine_kernel<T, D>), refine_wgs, 256, 0, st, xhat, chat, assign, flag, nflag, S,
+              L, kk, N_idx);
 }
 
 template <typename T, int D>
@@ -1593,9 +1672,7 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   for (int t = 0; t < iters && !small; ++t) {
     // Rounds 0 and 1 meet all new centroids; from round 2 on only the changed ones are compared.
     launch_assign<T, D>(xhat, chat, assign, t >= 1 ? bounds : nullptr, delta && t >= 2 ? changed[(t - 1) & 1] : nullptr, flag,
-                        nflag, S, L, kk, N_idx, g.segs, st);
-    WAVE_LAUNCH("refine", (refine_kernel<T, D>), 1024, 256, 0, st, xhat, chat, assign, flag, nflag, S,
-                L, kk, N_idx);
+                        nflag, S, L, kk, N_idx, g.segs, 1024, st);
     // (first round: nothing to compare with, every cluster is updated and every mark cleared)
     WAVE_LAUNCH("sort", sort_kernel, g.segs, 64 * W, sort_lds, st, assign, order, count, start, nflag,
                 prev, changed[t & 1], t == 0 ? 1 : 0, S, L, kk, N_idx, kb);
@@ -1641,9 +1718,7 @@ static wave_status assign_step_td(const void* xhat, const void* chat, int L_s, i
   hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, nflag);
   // one unit, one segment: S = 1, L = N_idx = L_s, kk = k_s
   launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, nullptr, nullptr, flag,
-                      nflag, 1, L_s, k_s, L_s, 1, st);
-  WAVE_LAUNCH("refine", (refine_kernel<T, D>), 256, 256, 0, st, static_cast<const T*>(xhat),
-              static_cast<const T*>(chat), assign, flag, nflag, 1, L_s, k_s, L_s);
+                      nflag, 1, L_s, k_s, L_s, 1, 256, st);
   return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;
 }
 
