@@ -56,13 +56,15 @@ __device__ __forceinline__ double div_shared(double a, double b, double r) {
 // ============================================================================
 template <typename T, int D>
 __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, double* __restrict__ mean,
-                                                       int32_t* __restrict__ flag_count, int S, int L,
+                                                       int32_t* __restrict__ flag_count,
+                                                       int32_t* __restrict__ range, int S, int L,
                                                        int kk, int N, int N_idx, int n_sink) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
   const int sg = blockIdx.x;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   if (sg == 0 && threadIdx.x == 0) *flag_count = 0;
+  if (range && threadIdx.x < 2) range[2 * sg + threadIdx.x] = threadIdx.x ? 0 : 255;  // for normalise_kernel
   const T* Ku = K + ((size_t)si.unit * N + n_sink + si.seg_start) * D + sub * EPC;
   double acc[EPC];
 #pragma unroll
@@ -97,6 +99,48 @@ __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, 
   }
 }
 
+// Exponent fields of the nonzero elements of a 16-byte chunk: their smallest and largest
+// (a subnormal counts as exponent field 1, which has the same unit in the last place).
+template <typename T>
+__device__ __forceinline__ void exponent_range(const uint4& raw, int& emin, int& emax);
+template <>
+__device__ __forceinline__ void exponent_range<bf16_t>(const uint4& raw, int& emin, int& emax) {
+  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t v = h ? w[i] >> 16 : w[i] & 0xffffu;
+      if (v & 0x7fffu) {
+        const int e = max(1, (int)((v >> 7) & 0xffu));
+        emin = min(emin, e);
+        emax = max(emax, e);
+      }
+    }
+  }
+}
+template <>
+__device__ __forceinline__ void exponent_range<float>(const uint4& raw, int& emin, int& emax) {
+  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (w[i] & 0x7fffffffu) {
+      const int e = max(1, (int)((w[i] >> 23) & 0xffu));
+      emin = min(emin, e);
+      emax = max(emax, e);
+    }
+}
+template <typename T>
+struct MantissaBits;
+template <>
+struct MantissaBits<bf16_t> {
+  static constexpr int value = 7;
+};
+template <>
+struct MantissaBits<float> {
+  static constexpr int value = 23;
+};
+
 // ============================================================================
 // Centre, normalise, round to the storage type.  A workgroup takes NORM_ROWS rows of one
 // segment and keeps the mean in registers.  (HBM-bound.  With rows of any segment in a
@@ -108,7 +152,7 @@ constexpr int NORM_ROWS = 128;
 template <typename T, int D>
 __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
                                                         const double* __restrict__ mean,
-                                                        T* __restrict__ xhat, int S, int L, int kk, int N,
+                                                        T* __restrict__ xhat, int32_t* __restrict__ range, int S, int L, int kk, int N,
                                                         int N_idx, int n_sink, int chunks) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR, U = 4;
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
@@ -116,6 +160,14 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
   const int lo = chunk * NORM_ROWS, hi = min(si.L_s, lo + NORM_ROWS);
   if (lo >= hi) return;
+  // (range: the smallest and the largest exponent field of the segment's nonzero elements)
+  __shared__ int seg_emin, seg_emax;
+  if (threadIdx.x == 0) {
+    seg_emin = 255;
+    seg_emax = 0;
+  }
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  u16x2 least = {0xffff, 0xffff}, most = {0, 0};  // magnitude bits - 1 (zero: the largest), magnitude bits
   double mu[EPC];
 #pragma unroll
   for (int e = 0; e < EPC; ++e) mu[e] = mean[(size_t)sg * D + sub * EPC + e];
@@ -143,6 +195,33 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
 #pragma unroll
       for (int e = 0; e < EPC; ++e) o[e] = quant_store<T>(div_shared(x[e], dv, rdv));
       if (r0 + u * GROUPS < hi) store16(Xu + (size_t)(r0 + u * GROUPS) * D, *reinterpret_cast<uint4*>(o));
+      if (range) {
+        const u16x2* w = reinterpret_cast<const u16x2*>(o);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const u16x2 mag = w[i] & (unsigned short)0x7fff;
+          most = __builtin_elementwise_max(most, mag);
+          least = __builtin_elementwise_min(least, mag - (unsigned short)1);
+        }
+      }
+    }
+  }
+  if (range) {
+    int emax = max(most.x, most.y) >> 7, emin = min(least.x, least.y);
+    emin = emin == 0xffff ? 255 : max(1, (emin + 1) >> 7);
+    for (int off = 32; off >= 1; off >>= 1) {
+      emin = min(emin, __shfl_xor(emin, off));
+      emax = max(emax, __shfl_xor(emax, off));
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+      atomicMin(&seg_emin, emin);
+      atomicMax(&seg_emax, emax);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      atomicMin(&range[2 * sg], seg_emin);
+      atomicMax(&range[2 * sg + 1], seg_emax);
     }
   }
 }
@@ -514,11 +593,21 @@ struct __attribute__((aligned(8))) PointBounds {
   int own, others;
 };
 
-// A point's cluster from a comparison with every centroid.
-__device__ __forceinline__ void settle_point(int32_t* assign, PointBounds* bounds, size_t gp, int cluster, int own,
-                                             int others) {
+// A point that changed its cluster in round t carries (t, the cluster it left) in prev[].
+constexpr int PREV_CLUSTER_BITS = 11;  // (at most 1024 centroids are resident)
+
+// The round's outcome for a point.  bounds: null when no later round needs it (nor prev).
+__device__ __forceinline__ void settle_point(int32_t* assign, int32_t* prev, PointBounds* bounds, int round,
+                                             size_t gp, int cluster, int own, int others) {
+  if (bounds) {
+    const int before = assign[gp];
+    if (before != cluster)
+      prev[gp] = round << PREV_CLUSTER_BITS | before;
+    else if (round == 1)
+      prev[gp] = 0;  // (the first round to leave marks: every point's are set)
+    bounds[gp] = PointBounds{own, others};
+  }
   assign[gp] = cluster;
-  if (bounds) bounds[gp] = PointBounds{own, others};
 }
 
 constexpr int ASSIGN_POINTS = 4096;  // most points of a workgroup of the resident kernels
@@ -652,7 +741,8 @@ inline size_t resident_lds(int kmax) {
 template <int D, int NF, int NW>
 __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    PointBounds* __restrict__ bounds, int S, int L, int kk, int N_idx, int pieces_per_seg) {
+    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, int round, int S, int L, int kk, int N_idx,
+    int pieces_per_seg) {
   // 32 * ceil(k_s / 32) padded rows, then the near-ties
   extern __shared__ __attribute__((aligned(16))) char cent[];
   __shared__ int nleft, nitem;
@@ -672,7 +762,7 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
   resident_load_centroids<D, 64 * NW>(Cs, si.k_s, cent);
   __syncthreads();
   auto settle = [&](int point, int cluster, int own, int others) {
-    settle_point(assign, bounds, gp0 + point, cluster, own, others);
+    settle_point(assign, prev, bounds, round, gp0 + point, cluster, own, others);
   };
   resident_assign_fragments<D, NF, NW>(X, cent, si.L_s, si.k_s, f_lo, f_hi,
                                        [&](int point, int cluster, int best, int second) {
@@ -715,8 +805,8 @@ inline size_t delta_lds(int kmax) {
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW) void assign_delta_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    PointBounds* __restrict__ bounds, const int32_t* __restrict__ changed, int S, int L, int kk, int N_idx,
-    int pieces_per_seg) {
+    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, const int32_t* __restrict__ changed, int round,
+    int S, int L, int kk, int N_idx, int pieces_per_seg) {
   using RT = ResidentTile<D>;
   constexpr int ROWB = RT::ROWB, CPR = RT::CPR, NT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) char cent[];
@@ -766,7 +856,7 @@ __global__ __launch_bounds__(64 * NW) void assign_delta_kernel(
   __syncthreads();
 
   auto settle = [&](int point, int cluster, int own, int others) {
-    settle_point(assign, bounds, gp0 + point, cluster, own, others);
+    settle_point(assign, prev, bounds, round, gp0 + point, cluster, own, others);
   };
   auto decide = [&](int point, int row, int c1, int c2) {
     const size_t gp = gp0 + point;
@@ -927,8 +1017,7 @@ constexpr int SORT_HIST_INTS = 11264;  // LDS budget for the per-wave counters
 // a point's cluster differs from it (and `compare` is set: not in the first round), both clusters
 // are marked in changed[] (plain stores of 1: who wins does not matter).  The update step
 // recomputes only marked clusters: a cluster nobody entered or left keeps its member sum and with
-// it, bit for bit, its centroid.  The next round's assign step reads the marks too, so
-// consecutive rounds use two arrays in turn; the update step clears the one that comes next.
+// it, bit for bit, its centroid.
 __device__ __forceinline__ void sort_segment(const int32_t* a, int32_t* ord, int32_t* cnt, int32_t* first,
                                              int L_s, int kk, int key_bits, int* hist, int32_t* prev = nullptr,
                                              int32_t* changed = nullptr, bool compare = false) {
@@ -1027,54 +1116,12 @@ __global__ __launch_bounds__(1024) void sort_kernel(const int32_t* __restrict__ 
   }
   sort_segment(assign + (size_t)si.unit * N_idx + si.seg_start, order + (size_t)si.unit * N_idx + si.seg_start,
                count + (size_t)sg * kk, start + (size_t)sg * kk, si.L_s, kk, key_bits, hist,
-               prev + (size_t)si.unit * N_idx + si.seg_start, changed + (size_t)sg * kk, !first_round);
+               prev ? prev + (size_t)si.unit * N_idx + si.seg_start : nullptr, changed + (size_t)sg * kk, !first_round);
 }
 
 // ============================================================================
 // Update: one group of LPR lanes per cluster sums its members' xhat in fp64.
 // ============================================================================
-// Exponent fields of the nonzero elements of a 16-byte chunk: their smallest and largest
-// (a subnormal counts as exponent field 1, which has the same unit in the last place).
-template <typename T>
-__device__ __forceinline__ void exponent_range(const uint4& raw, int& emin, int& emax);
-template <>
-__device__ __forceinline__ void exponent_range<bf16_t>(const uint4& raw, int& emin, int& emax) {
-  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t v = h ? w[i] >> 16 : w[i] & 0xffffu;
-      if (v & 0x7fffu) {
-        const int e = max(1, (int)((v >> 7) & 0xffu));
-        emin = min(emin, e);
-        emax = max(emax, e);
-      }
-    }
-  }
-}
-template <>
-__device__ __forceinline__ void exponent_range<float>(const uint4& raw, int& emin, int& emax) {
-  const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (w[i] & 0x7fffffffu) {
-      const int e = max(1, (int)((w[i] >> 23) & 0xffu));
-      emin = min(emin, e);
-      emax = max(emax, e);
-    }
-}
-template <typename T>
-struct MantissaBits;
-template <>
-struct MantissaBits<bf16_t> {
-  static constexpr int value = 7;
-};
-template <>
-struct MantissaBits<float> {
-  static constexpr int value = 23;
-};
-
 // The member rows ord[0, n) of the segment's points X (already offset to the lane's chunk)
 // added to acc in fp64 in that order, U loads in flight.  STATS: also the exponent range of
 // what was added.  (STREAM: the rows are read once per launch and should not displace other
@@ -1112,6 +1159,12 @@ __device__ __forceinline__ void sum_members(const T* X, const int32_t* ord, int 
 
 // The member sum of a cluster, normalised and rounded, to dst (the lane's 16-byte chunk of the
 // centroid row); members that cancel keep the centroid.
+template <int EPC>
+__device__ __forceinline__ void store_sums(double* sums, const double (&acc)[EPC]) {
+#pragma unroll
+  for (int e = 0; e < EPC; ++e) sums[e] = acc[e];
+}
+
 template <typename T, int D>
 __device__ __forceinline__ void finish_centroid(const double (&acc)[Elem<T>::EPC], T* dst) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC;
@@ -1130,17 +1183,19 @@ __device__ __forceinline__ void finish_centroid(const double (&acc)[Elem<T>::EPC
 
 // One cluster's update by the calling group of LPR lanes (lane `sub` of it): the n member
 // rows ord[0, n) of the segment's points X are summed in fp64 in that order, U loads in
-// flight, and the normalised sum goes to dst.
+// flight, and the normalised sum goes to dst (the sum itself to `sums`, unless null).
 template <typename T, int D, int U, bool STREAM>
-__device__ __forceinline__ void update_cluster(const T* X, const int32_t* ord, int n, T* dst, int sub) {
+__device__ __forceinline__ void update_cluster(const T* X, const int32_t* ord, int n, T* dst, int sub,
+                                               double* sums = nullptr) {
   constexpr int EPC = Elem<T>::EPC;
-  if (n == 0) return;  // an empty cluster keeps its centroid
+  if (n == 0 && !sums) return;  // an empty cluster keeps its centroid
   double acc[EPC];
 #pragma unroll
   for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
   int emin = 0, emax = 0;
   sum_members<T, D, U, STREAM, false>(X + sub * EPC, ord, n, acc, emin, emax);
-  finish_centroid<T, D>(acc, dst);
+  if (sums) store_sums<EPC>(sums, acc);
+  finish_centroid<T, D>(acc, dst);  // (a sum of nothing is zero)
 }
 
 // Clusters of more than UPD_BIG members (heavy-tailed data: a thousand tokens in one cluster)
@@ -1161,7 +1216,8 @@ __global__ __launch_bounds__(256) void update_big_kernel(const T* __restrict__ x
                                                          const int32_t* __restrict__ count,
                                                          const int32_t* __restrict__ start,
                                                          const int32_t* __restrict__ big_list,
-                                                         const int32_t* __restrict__ big_count, int S, int L,
+                                                         const int32_t* __restrict__ big_count,
+                                                         double* __restrict__ sums, int S, int L,
                                                          int kk, int N_idx) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
   __shared__ double part[GROUPS * D];
@@ -1210,6 +1266,7 @@ __global__ __launch_bounds__(256) void update_big_kernel(const T* __restrict__ x
       }
       const int lg = 32 - __clz(n - 1);  // ceil(log2 n), n > UPD_BIG
       T* dst = chat + (size_t)gc * D + sub * EPC;
+      if (sums) store_sums<EPC>(sums + (size_t)gc * D + sub * EPC, tot);  // (used where the test below holds)
       if (hi < lo || hi - lo + lg <= 52 - MantissaBits<T>::value)  // (hi < lo: every addend is zero)
         finish_centroid<T, D>(tot, dst);
       else
@@ -1219,16 +1276,16 @@ __global__ __launch_bounds__(256) void update_big_kernel(const T* __restrict__ x
   }
 }
 
-// First round: every cluster is summed.
+// First round: every cluster is summed (changed: cleared; sums: see update_moves_kernel, or null).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void update_kernel(const T* __restrict__ xhat, T* __restrict__ chat,
                                                      const int32_t* __restrict__ order,
                                                      const int32_t* __restrict__ count,
                                                      const int32_t* __restrict__ start,
-                                                     int32_t* __restrict__ next_changed,
+                                                     int32_t* __restrict__ changed,
                                                      int32_t* __restrict__ big_list,
-                                                     int32_t* __restrict__ big_count, int S, int L, int kk,
-                                                     int N_idx, int nclusters) {
+                                                     int32_t* __restrict__ big_count, double* __restrict__ sums,
+                                                     int S, int L, int kk, int N_idx, int nclusters) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   const int gc = blockIdx.x * GROUPS + grp;  // sg * kk + c
@@ -1236,14 +1293,15 @@ __global__ __launch_bounds__(256) void update_kernel(const T* __restrict__ xhat,
   const int sg = gc / kk, c = gc - sg * kk;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
   if (c >= si.k_s) return;
-  if (sub == 0) next_changed[gc] = 0;  // the marks that the next round's sort sets
+  if (sub == 0) changed[gc] = 0;
   const int n = count[gc];
   if (n > UPD_BIG) {  // left to update_big_kernel
     if (sub == 0) big_list[atomicAdd(big_count, 1)] = gc;
     return;
   }
   const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
-  update_cluster<T, D, 4, true>(xhat + p0 * D, order + p0 + start[gc], n, chat + (size_t)gc * D + sub * EPC, sub);
+  update_cluster<T, D, 4, true>(xhat + p0 * D, order + p0 + start[gc], n, chat + (size_t)gc * D + sub * EPC, sub,
+                                sums ? sums + (size_t)gc * D + sub * EPC : nullptr);
 }
 
 // The update of the later rounds: only clusters that a point entered or left in this round
@@ -1256,7 +1314,7 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
                                                              const int32_t* __restrict__ order,
                                                              const int32_t* __restrict__ count,
                                                              const int32_t* __restrict__ start,
-                                                             const int32_t* changed, int32_t* next_changed,
+                                                             int32_t* __restrict__ changed,
                                                              int32_t* __restrict__ big_list,
                                                              int32_t* __restrict__ big_count, int S, int L,
                                                              int kk, int N_idx, int nclusters) {
@@ -1266,8 +1324,7 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int gc_mine = blockIdx.x * 256 + tid;
   const bool on = gc_mine < nclusters && changed[gc_mine] != 0;
-  if (on && next_changed == changed) next_changed[gc_mine] = 0;  // (one array: only this step reads the marks)
-  if (gc_mine < nclusters && next_changed != changed) next_changed[gc_mine] = 0;
+  if (on) changed[gc_mine] = 0;
   const uint64_t mk = __ballot(on);
   if (lane == 0) wave_n[wave] = __popcll(mk);
   __syncthreads();
@@ -1292,6 +1349,154 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
     const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
     update_cluster<T, D, 4, true>(xhat + p0 * D, order + p0 + start[gc], members,
                                   chat + (size_t)gc * D + sub * EPC, sub);
+  }
+}
+
+// ============================================================================
+// Update from the points that moved (later rounds of the resident bf16 path): the fp64 member
+// sums are kept from round to round and only the rows of the points that changed cluster in
+// this round are subtracted from one sum and added to another.  The result is the sum of the
+// members bit for bit, whatever the order, when no addition rounds; that is certain when
+// every sum of a subset of the segment's points is representable, the condition above with
+// the exponent range of the whole segment (gathered by normalise_kernel) and n = L_s.  A segment
+// that fails it (a component below 2^-31 of the largest; keys spread over 2^20 .. 2^26 in
+// practice) is sorted and its changed clusters are summed again by the first workgroup.
+// No sort and no pass over the members: a round costs the scan of the marks in prev[], 2 KiB per
+// changed cluster and 512 B per moved point.
+// Also leaves in changed[] which centroids the next round's assign step compares.
+//
+// A workgroup owns the clusters [c_lo, c_hi) of a segment: it counts the arrivals and departures
+// of each (MOVE_CAP at once; more are taken in ranges of the points), lists them by cluster in
+// LDS, and one group of lanes per changed cluster works through its list.
+// ============================================================================
+constexpr int MOVE_NT = 512, MOVE_CAP = 4096;
+
+inline size_t update_moves_lds(int kk) {
+  const size_t list = MOVE_CAP, hist = (size_t)(MOVE_NT / 64 + 1) * kk;
+  return sizeof(int) * (3 * (size_t)kk + (list > hist ? list : hist));
+}
+
+template <int D>
+__global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
+    const bf16_t* __restrict__ xhat, bf16_t* __restrict__ chat, double* __restrict__ sums,
+    const int32_t* __restrict__ assign, const int32_t* __restrict__ prev, int32_t* __restrict__ changed,
+    const int32_t* __restrict__ range, int32_t* order, int32_t* count, int32_t* start, int round, int S, int L,
+    int kk, int N_idx, int pieces, int key_bits) {
+  constexpr int EPC = 8, LPR = D / EPC, GROUPS = MOVE_NT / LPR, U = 4;
+  extern __shared__ int moves_lds[];
+  int* cnt = moves_lds;         // entries per cluster
+  int* end = cnt + kk;          // behind its last entry
+  int* touched = end + kk;      // the clusters with entries
+  int* entry = touched + kk;    // point * 2 + (1: leaves); the sort's counters
+  __shared__ int totals[2];     // entries, touched clusters
+  const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
+  const int sg = wg / pieces, piece = wg - sg * pieces;
+  const SegInfo si = seg_info(sg, S, L, kk, N_idx);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = tid % LPR;
+  const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
+  const int32_t* as = assign + p0;
+  const int32_t* pv = prev + p0;
+  const bf16_t* X = xhat + p0 * D;
+  const int emin = range[2 * sg], emax = range[2 * sg + 1];
+  const int lg = si.L_s > 1 ? 32 - __clz(si.L_s - 1) : 0;  // ceil(log2 L_s)
+  const bool exact = emax < emin || emax - emin + lg <= 52 - MantissaBits<bf16_t>::value;
+  const int per = exact ? (si.k_s + pieces - 1) / pieces : si.k_s;
+  const int c_lo = min(si.k_s, piece * per), c_hi = min(si.k_s, c_lo + per);
+  if (c_lo >= c_hi) return;
+
+  auto visit = [&](int lo, int hi, auto&& f) {  // f(cluster, entry) for the round's entries of points [lo, hi)
+    for (int i0 = lo + tid; i0 < hi; i0 += U * MOVE_NT) {
+      int tag[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) tag[u] = pv[min(i0 + u * MOVE_NT, hi - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * MOVE_NT;
+        if (i >= hi || tag[u] >> PREV_CLUSTER_BITS != round) continue;
+        const int from = tag[u] & ((1 << PREV_CLUSTER_BITS) - 1), to = as[i];
+        if (from >= c_lo && from < c_hi) f(from, 2 * i + 1);
+        if (to >= c_lo && to < c_hi) f(to, 2 * i);
+      }
+    }
+  };
+  auto count_entries = [&](int lo, int hi) {
+    for (int c = c_lo + tid; c < c_hi; c += MOVE_NT) cnt[c] = 0;
+    __syncthreads();
+    visit(lo, hi, [&](int c, int) { atomicAdd(&cnt[c], 1); });
+    __syncthreads();
+    if (wave == 0) {  // first places and the list of touched clusters
+      int at = 0, n = 0;
+      for (int c0 = c_lo; c0 < c_hi; c0 += 64) {
+        const int c = c0 + lane;
+        const int v = c < c_hi ? cnt[c] : 0;
+        int inc = v;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const int t = __shfl_up(inc, off);
+          if (lane >= off) inc += t;
+        }
+        const uint64_t mk = __ballot(v > 0);
+        if (c < c_hi) end[c] = at + inc - v;
+        if (v > 0) touched[n + __popcll(mk & ((1ull << lane) - 1ull))] = c;
+        at += __shfl(inc, 63);
+        n += __popcll(mk);
+      }
+      if (lane == 0) {
+        totals[0] = at;
+        totals[1] = n;
+      }
+    }
+    __syncthreads();
+  };
+  count_entries(0, si.L_s);
+  for (int c = c_lo + tid; c < c_hi; c += MOVE_NT) changed[(size_t)sg * kk + c] = cnt[c] > 0 ? 1 : 0;
+  if (!exact) {
+    const int n = totals[1];
+    sort_segment(as, order + p0, count + (size_t)sg * kk, start + (size_t)sg * kk, si.L_s, kk, key_bits, entry);
+    __syncthreads();
+    for (int j = tid / LPR; j < n; j += GROUPS) {
+      const size_t gc = (size_t)sg * kk + touched[j];
+      update_cluster<bf16_t, D, 4, false>(X, order + p0 + start[gc], count[gc], chat + gc * D + sub * EPC, sub);
+    }
+    return;
+  }
+  const int span = totals[0] <= MOVE_CAP ? si.L_s : MOVE_CAP / 2;
+  for (int lo = 0; lo < si.L_s; lo += span) {
+    const int hi = min(si.L_s, lo + span);
+    if (span < si.L_s) {
+      __syncthreads();
+      count_entries(lo, hi);
+    }
+    visit(lo, hi, [&](int c, int e) { entry[atomicAdd(&end[c], 1)] = e; });
+    __syncthreads();
+    const int n = totals[1];
+    for (int j = tid / LPR; j < n; j += GROUPS) {
+      const int c = touched[j];
+      const int ne = cnt[c], e0 = end[c] - ne;
+      const size_t gc = (size_t)sg * kk + c;
+      double* own = sums + gc * D + sub * EPC;
+      double acc[EPC];
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) acc[e] = own[e];
+      for (int i = 0; i < ne; i += U) {
+        int en[U];
+        uint4 raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) en[u] = entry[e0 + min(i + u, ne - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[u] = load16(X + (size_t)(en[u] >> 1) * D + sub * EPC);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          float f[EPC];
+          unpack<bf16_t>(raw[u], f);
+          const double sign = i + u >= ne ? 0.0 : (en[u] & 1) ? -1.0 : 1.0;
+#pragma unroll
+          for (int e = 0; e < EPC; ++e) acc[e] = fma(sign, (double)f[e], acc[e]);
+        }
+      }
+      store_sums<EPC>(own, acc);
+      finish_centroid<bf16_t, D>(acc, chat + gc * D + sub * EPC);
+    }
   }
 }
 
@@ -1561,8 +1766,9 @@ BuildGeom build_geometry(const wave_index& ix) {
   g.off_nflag = o;  o = align_up(o + 256);
   g.off_init = o;   o = align_up(o + (size_t)g.segs * ix.d * sizeof(double));  // segment means
   if (delta_rounds(ix)) {
-    g.off_changed = o; o = align_up(o + ncl * sizeof(int32_t));     // the changed marks of odd rounds
-    g.off_bounds = o;  o = align_up(o + pts * sizeof(PointBounds));
+    g.off_bounds = o; o = align_up(o + pts * sizeof(PointBounds));
+    g.off_sums = o;   o = align_up(o + ncl * ix.d * sizeof(double));        // the clusters' member sums
+    g.off_range = o;  o = align_up(o + 2 * (size_t)g.segs * sizeof(int32_t));
   }
   g.total = o;
   return g;
@@ -1583,10 +1789,10 @@ static int key_bits_for(int kk) {
 
 // One assign step.  bounds, changed: null in a round that compares every point with every
 // centroid; with `bounds` alone such a round leaves what the next one needs to compare with the
-// changed centroids only.
+// changed centroids only, and in prev which points moved.
 template <typename T, int D>
-static void launch_assign(const T* xhat, const T* chat, int32_t* assign, PointBounds* bounds,
-                          const int32_t* changed, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
+static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t* prev, PointBounds* bounds,
+                          const int32_t* changed, int round, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
                           int segs, int refine_wgs, hipStream_t st) {
   const int Lmax = L < N_idx ? L : N_idx, kmax = kk < Lmax ? kk : Lmax;
   if constexpr (sizeof(T) == 2) {
@@ -1596,10 +1802,10 @@ static void launch_assign(const T* xhat, const T* chat, int32_t* assign, PointBo
       if (pieces < 2 && Lmax > 2048) pieces = 2;
       if (changed)
         WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16>), segs * pieces, 1024, delta_lds<D>(kmax), st, xhat,
-                    chat, assign, bounds, changed, S, L, kk, N_idx, pieces);
+                    chat, assign, prev, bounds, changed, round, S, L, kk, N_idx, pieces);
       else
         WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16>), segs * pieces, 1024, resident_lds<D>(kmax),
-                    st, xhat, chat, assign, bounds, S, L, kk, N_idx, pieces);
+                    st, xhat, chat, assign, prev, bounds, round, S, L, kk, N_idx, pieces);
       return;
     }
     // the centroids are staged through LDS tile by tile
@@ -1651,21 +1857,22 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   int32_t* count = reinterpret_cast<int32_t*>(w + g.off_count);
   int32_t* start = count + ncl;
   const bool delta = delta_rounds(ix);
-  // per cluster: a point entered or left it in an even / odd round
-  int32_t* changed[2] = {start + ncl, delta ? reinterpret_cast<int32_t*>(w + g.off_changed) : start + ncl};
-  PointBounds* bounds = delta ? reinterpret_cast<PointBounds*>(w + g.off_bounds) : nullptr;
+  int32_t* changed = start + ncl;  // per cluster: a point entered or left it in the current round
   int32_t* prev = reinterpret_cast<int32_t*>(w + g.off_prev);  // every point's cluster of the round before
+  PointBounds* bounds = delta ? reinterpret_cast<PointBounds*>(w + g.off_bounds) : nullptr;
+  double* sums = delta ? reinterpret_cast<double*>(w + g.off_sums) : nullptr;
+  int32_t* range = delta ? reinterpret_cast<int32_t*>(w + g.off_range) : nullptr;
   int32_t* flag = reinterpret_cast<int32_t*>(w + g.off_flag);
   int32_t* nflag = reinterpret_cast<int32_t*>(w + g.off_nflag);
   double* mean = reinterpret_cast<double*>(w + g.off_init);
   const int S = ix.S, L = ix.segment_len, N_idx = ix.N_idx;
   constexpr int GROUPS = 256 / (D / Elem<T>::EPC);
 
-  WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs, 256, 0, st, K, mean, nflag, S, L, kk, ix.N,
+  WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs, 256, 0, st, K, mean, nflag, range, S, L, kk, ix.N,
               N_idx, ns);
   {
     const int chunks = ((L < N_idx ? L : N_idx) + NORM_ROWS - 1) / NORM_ROWS;
-    WAVE_LAUNCH("normalise", (normalise_kernel<T, D>), g.segs * chunks, 256, 0, st, K, mean, xhat, S, L, kk, ix.N,
+    WAVE_LAUNCH("normalise", (normalise_kernel<T, D>), g.segs * chunks, 256, 0, st, K, mean, xhat, range, S, L, kk, ix.N,
                 N_idx, ns, chunks);
   }
   WAVE_LAUNCH("init", (init_kernel<T, D>), g.segs, 256, 2 * sizeof(int) * (size_t)kk, st, xhat, chat, S, L,
@@ -1684,27 +1891,42 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
       WAVE_LAUNCH("kmeans_small", (kmeans_small_kernel<D>), g.segs, 64 * SMALL_NW, small_kmeans_lds<D>(kk), st,
                   xhat, chat, order, count, start, S, L, kk, N_idx, iters, kb);
   }
+  auto sort = [&](int32_t* prev_or_null, int t) {
+    WAVE_LAUNCH("sort", sort_kernel, g.segs, 64 * W, sort_lds, st, assign, order, count, start, nflag,
+                prev_or_null, changed, t == 0 ? 1 : 0, S, L, kk, N_idx, kb);
+  };
+  auto update = [&](int t) {
+    // (first round: nothing to compare with, every cluster is updated and every mark cleared.
+    // Large clusters go onto a list, which the second kernel takes: nflag[1] counts them and
+    // the flagged-point list, consumed by refine, is free to hold them)
+    if (t == 0)
+      WAVE_LAUNCH("update", (update_kernel<T, D>), cl_grid, 256, 0, st, xhat, chat, order, count,
+                  start, changed, flag, nflag + 1, sums, S, L, kk, N_idx, ncl);
+    else
+      WAVE_LAUNCH("update", (update_touched_kernel<T, D>), (ncl + 255) / 256, 256, 0, st, xhat, chat,
+                  order, count, start, changed, flag, nflag + 1, S, L, kk, N_idx, ncl);
+    const int big_grid = ncl / UPD_BIG + 1 < 2048 ? ncl / UPD_BIG + 1 : 2048;
+    WAVE_LAUNCH("update", (update_big_kernel<T, D>), big_grid, 256, 0, st, xhat, chat, order, count,
+                start, flag, nflag + 1, sums, S, L, kk, N_idx);
+  };
   for (int t = 0; t < iters && !small; ++t) {
     // Rounds 0 and 1 meet all new centroids; from round 2 on only the changed ones are compared.
-    launch_assign<T, D>(xhat, chat, assign, t >= 1 ? bounds : nullptr, delta && t >= 2 ? changed[(t - 1) & 1] : nullptr, flag,
-                        nflag, S, L, kk, N_idx, g.segs, 1024, st);
-    // (first round: nothing to compare with, every cluster is updated and every mark cleared)
-    WAVE_LAUNCH("sort", sort_kernel, g.segs, 64 * W, sort_lds, st, assign, order, count, start, nflag,
-                prev, changed[t & 1], t == 0 ? 1 : 0, S, L, kk, N_idx, kb);
-    if (t + 1 < iters) {
-      // (large clusters go onto a list, which the third kernel takes: nflag[1] counts them and
-      // the flagged-point list, consumed by refine, is free to hold them)
-      if (t == 0) {
-        WAVE_LAUNCH("update", (update_kernel<T, D>), cl_grid, 256, 0, st, xhat, chat, order, count,
-                    start, changed[1], flag, nflag + 1, S, L, kk, N_idx, ncl);
-      } else {
-        WAVE_LAUNCH("update", (update_touched_kernel<T, D>), (ncl + 255) / 256, 256, 0, st, xhat, chat,
-                    order, count, start, changed[t & 1], changed[(t + 1) & 1], flag, nflag + 1, S, L, kk, N_idx, ncl);
+    launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, delta && t >= 2 ? changed : nullptr, t,
+                        flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
+    const bool last = t + 1 == iters;
+    if (!delta || t == 0 || last) sort(delta ? nullptr : prev, t);
+    if (last) break;
+    if constexpr (sizeof(T) == 2) {
+      if (delta && t >= 1) {
+        // a few segments are shared by several workgroups each, of at least 64 clusters
+        int pieces = 1;
+        while (g.segs * pieces < 512 && kk / pieces >= 128) pieces *= 2;
+        WAVE_LAUNCH("update", (update_moves_kernel<D>), g.segs * pieces, MOVE_NT, update_moves_lds(kk), st, xhat,
+                    chat, sums, assign, prev, changed, range, order, count, start, t, S, L, kk, N_idx, pieces, kb);
+        continue;
       }
-      const int big_grid = ncl / UPD_BIG + 1 < 2048 ? ncl / UPD_BIG + 1 : 2048;
-      WAVE_LAUNCH("update", (update_big_kernel<T, D>), big_grid, 256, 0, st, xhat, chat, order, count,
-                  start, flag, nflag + 1, S, L, kk, N_idx);
     }
+    update(t);
   }
   WAVE_LAUNCH("finalize", (finalize_kernel<T, D>), cl_grid, 256, 0, st, K, V, order, count, start,
               static_cast<T*>(ix.centroids), static_cast<T*>(ix.vsum), ix.sizes, ix.offsets, ix.perm,
@@ -1732,7 +1954,7 @@ static wave_status assign_step_td(const void* xhat, const void* chat, int L_s, i
   int32_t* flag = nflag + 64;
   hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, nflag);
   // one unit, one segment: S = 1, L = N_idx = L_s, kk = k_s
-  launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, nullptr, nullptr, flag,
+  launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, nullptr, nullptr, nullptr, 0, flag,
                       nflag, 1, L_s, k_s, L_s, 1, 256, st);
   return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;
 }

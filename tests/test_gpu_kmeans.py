@@ -19,15 +19,21 @@ def _keys(kind, B, N, d, seed):
     elif kind == "ties":     # few distinct keys: equal similarities and clusters that stay empty
         few = torch.randn(23, d, generator=g)
         x = few[torch.randint(0, 23, (B, 1, N), generator=g)]
+    elif kind == "wide":     # a zero-mean channel with values so far apart that their fp64 sums round
+        i = torch.arange(N) - 2                      # (two sink tokens; +1, -1, tiny, tiny, ...)
+        tiny = torch.randn(N, generator=g) * 2.0 ** -42
+        x[..., 0] = torch.where(i % 4 < 2, 1.0 - 2.0 * (i % 2), tiny)
     return x                 # "plain": no clusters, most points near a boundary
 
 
 # (N - 5 tokens are indexed.  4097 points: the last of two or three workgroups' shares has one
 # fragment with one point; k = 33: a tile with one row; k = 1000 at d = 64: 32 tiles, as many as
-# stay resident; plain keys: hundreds of points per workgroup need the full comparison)
+# stay resident; plain keys: hundreds of points per workgroup need the full comparison, and of 20000
+# points in 33 clusters more move in a round than the update lists at once)
 @pytest.mark.parametrize("kind,d,N,L,k,iters", [
     ("mixture", 128, 4102, 4097, 33, 7), ("plain", 128, 9000, 8192, 512, 8), ("mixture", 64, 4000, 2100, 1000, 5),
-    ("ties", 128, 3000, 2100, 65, 5), ("plain", 64, 8197, 8192, 40, 6), ("plain", 128, 2205, 2200, 1, 4)])
+    ("ties", 128, 3000, 2100, 65, 5), ("plain", 64, 8197, 8192, 40, 6), ("plain", 128, 2205, 2200, 1, 4),
+    ("plain", 128, 20005, 20000, 33, 4), ("wide", 128, 4605, 2300, 200, 5), ("wide", 64, 2205, 2200, 1000, 4)])
 def test_rounds_match_oracle(kind, d, N, L, k, iters):
     wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="rounds", B=1, Hq=1, Hkv=1, N=N, d=d, n_sink=2, n_local=3,
                       segment_len=L, clusters_per_segment=k, iters=iters)
