@@ -57,7 +57,9 @@ __device__ __forceinline__ double div_shared(double a, double b, double r) {
 template <typename T, int D>
 __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, double* __restrict__ mean,
                                                        int32_t* __restrict__ flag_count,
-                                                       int32_t* __restrict__ range, int S, int L,
+                                                       int32_t* __restrict__ range,
+                                                       int32_t* __restrict__ nchanged,
+                                                       int32_t* __restrict__ nlisted, int S, int L,
                                                        int kk, int N, int N_idx, int n_sink) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
   const int sg = blockIdx.x;
@@ -65,6 +67,7 @@ __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, 
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   if (sg == 0 && threadIdx.x == 0) *flag_count = 0;
   if (range && threadIdx.x < 2) range[2 * sg + threadIdx.x] = threadIdx.x ? 0 : 255;  // for normalise_kernel
+  if (range && threadIdx.x == 0) nchanged[sg] = nlisted[sg] = 0;  // for update_moves_kernel, assign_listed_kernel
   const T* Ku = K + ((size_t)si.unit * N + n_sink + si.seg_start) * D + sub * EPC;
   double acc[EPC];
 #pragma unroll
@@ -461,11 +464,13 @@ __device__ __forceinline__ void resident_load_centroids(const bf16_t* Cs, int k_
 }
 
 // Wave `wave` of NW takes the fragments f_lo + wave * NF, + NW * NF, ... below f_hi of the
-// segment's points X against the centroids in `cent`; emit(point, row, best, second) is called
-// once per point by the lane that holds it (the keys of its two best rows and the best one's number).
-template <int D, int NF, int NW, typename Emit>
+// segment's points X against the centroids in `cent`; emit(point, row, best, second, state) is
+// called once per point by the lane that holds it (the keys of its two best rows and the best one's
+// number; state: what fetch(point) returned when the point's row was requested).
+struct NoState {};
+template <int D, int NF, int NW, typename Fetch, typename Emit>
 __device__ __forceinline__ void resident_assign_fragments(const bf16_t* X, const char* cent, int L_s, int k_s,
-                                                          int f_lo, int f_hi, Emit&& emit) {
+                                                          int f_lo, int f_hi, Fetch&& fetch, Emit&& emit) {
   using RT = ResidentTile<D>;
   constexpr int KS = RT::KS, ROWB = RT::ROWB;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -477,9 +482,11 @@ __device__ __forceinline__ void resident_assign_fragments(const bf16_t* X, const
   asm volatile("" : "+v"(bias));  // kept in registers: one accumulator-start operand for every tile
   for (int fb = f_lo + wave * NF; fb < f_hi; fb += NW * NF) {
     uint4 bfrag[NF][KS];
+    decltype(fetch(0)) state[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
       const int row = min(32 * (fb + f) + col, L_s - 1);
+      state[f] = fetch(row);
 #pragma unroll
       for (int s = 0; s < KS; ++s) bfrag[f][s] = load16(X + (size_t)row * D + (2 * s + half) * 8);
     }
@@ -539,17 +546,18 @@ __device__ __forceinline__ void resident_assign_fragments(const bf16_t* X, const
     for (int f = 0; f < NF; ++f) {
       const int row = merge_halves(best[f], second[f], btile[f], half);
       const int point = 32 * (fb + f) + col;
-      if (half == 0 && fb + f < f_hi && point < L_s) emit(point, row, best[f], second[f]);
+      if (half == 0 && fb + f < f_hi && point < L_s) emit(point, row, best[f], second[f], state[f]);
     }
   }
 }
 
 // The same step for few centroid tiles (short segments): one accumulator set and no
 // instruction interleaving, the next fragment's rows requested before the current one is
-// worked on.  Same similarities, same epilogue, same emit.
-template <int D, int NW, typename Emit>
+// worked on.  Same similarities, same epilogue, same fetch and emit.  (fetch belongs to the
+// requests made ahead: a load issued behind them and used at once would wait for all of them.)
+template <int D, int NW, typename Fetch, typename Emit>
 __device__ __forceinline__ void lean_assign_fragments(const bf16_t* X, const char* cent, int L_s, int k_s,
-                                                      int f_lo, int f_hi, Emit&& emit) {
+                                                      int f_lo, int f_hi, Fetch&& fetch, Emit&& emit) {
   using RT = ResidentTile<D>;
   constexpr int KS = RT::KS, ROWB = RT::ROWB;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -557,15 +565,17 @@ __device__ __forceinline__ void lean_assign_fragments(const bf16_t* X, const cha
   const int ntiles = (k_s + 31) / 32, nfull = k_s / 32;
   constexpr float B0 = kAssignBias;
   const floatx16 bias = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
-  auto load_frag = [&](int fb, uint4 (&dst)[KS]) {
+  decltype(fetch(0)) state, next_state;
+  auto load_frag = [&](int fb, uint4 (&dst)[KS], decltype(fetch(0))& st) {
     const int row = min(32 * fb + col, L_s - 1);
+    st = fetch(row);
 #pragma unroll
     for (int s = 0; s < KS; ++s) dst[s] = load16(X + (size_t)row * D + (2 * s + half) * 8);
   };
   uint4 cur[KS], nxt[KS];
-  if (f_lo + wave < f_hi) load_frag(f_lo + wave, cur);
+  if (f_lo + wave < f_hi) load_frag(f_lo + wave, cur, state);
   for (int fb = f_lo + wave; fb < f_hi; fb += NW) {
-    if (fb + NW < f_hi) load_frag(fb + NW, nxt);
+    if (fb + NW < f_hi) load_frag(fb + NW, nxt, next_state);
     int best[1] = {0}, second[1] = {0}, btile[1] = {0};
     for (int t = 0; t < ntiles; ++t) {
       const char* tile = cent + (size_t)(32 * t + col) * ROWB + half * 16;
@@ -581,9 +591,10 @@ __device__ __forceinline__ void lean_assign_fragments(const bf16_t* X, const cha
     }
     const int row = merge_halves(best[0], second[0], btile[0], half);
     const int point = 32 * fb + col;
-    if (half == 0 && point < L_s) emit(point, row, best[0], second[0]);
+    if (half == 0 && point < L_s) emit(point, row, best[0], second[0], state);
 #pragma unroll
     for (int s = 0; s < KS; ++s) cur[s] = nxt[s];
+    state = next_state;
   }
 }
 
@@ -593,144 +604,37 @@ struct __attribute__((aligned(8))) PointBounds {
   int own, others;
 };
 
+struct PointState {
+  int cluster;
+  PointBounds bounds;
+};
+
 // A point that changed its cluster in round t carries (t, the cluster it left) in prev[].
 constexpr int PREV_CLUSTER_BITS = 11;  // (at most 1024 centroids are resident)
 
-// The round's outcome for a point.  bounds: null when no later round needs it (nor prev).
+// The round's outcome for a point that was in cluster `before`.  bounds: null when no later round
+// needs it (nor prev, nor `before`).
 __device__ __forceinline__ void settle_point(int32_t* assign, int32_t* prev, PointBounds* bounds, int round,
-                                             size_t gp, int cluster, int own, int others) {
+                                             size_t gp, int before, int cluster, int own, int others) {
   if (bounds) {
-    const int before = assign[gp];
+    bounds[gp] = PointBounds{own, others};
     if (before != cluster)
       prev[gp] = round << PREV_CLUSTER_BITS | before;
     else if (round == 1)
       prev[gp] = 0;  // (the first round to leave marks: every point's are set)
-    bounds[gp] = PointBounds{own, others};
+    if (before == cluster) return;
   }
   assign[gp] = cluster;
 }
 
 constexpr int ASSIGN_POINTS = 4096;  // most points of a workgroup of the resident kernels
-constexpr int LIST_FRAGS = 4;        // fragments of listed points per round of compare_listed
-
-// The listed points (first + left[0, n)) of the segment's points X against every centroid, by the
-// whole workgroup: the waves share out (fragment of the list, centroid tile), the centroids come
-// from the cache, and the tiles' best two are merged per point.  A point whose two best are
-// closer than the guard gets fp64 similarities (exact for the stored operands up to fp64
-// rounding, ties to the lowest centroid) of the centroids in every tile whose best is that
-// close, one lane per centroid; the bound on its other similarities is then `best` too.
-// scratch: 3584 bytes per centroid tile.  settle(point, cluster, own, others) is called once
-// per listed point.  (16 sequences x 120K tokens: about 8 near-ties per segment in the first
-// round.  A launch of their own, one workgroup per point over every centroid in fp64, took
-// 575 us for it and 260 us a round on keys with heavy-tailed channels.)
-template <int D, int NW, typename Settle>
-__device__ __forceinline__ void compare_listed(const bf16_t* X, const bf16_t* Cs, int first, const uint16_t* left,
-                                               int n, int k_s, char* scratch, int* nitem, Settle&& settle) {
-  constexpr int KS = ResidentTile<D>::KS, PTS = 32 * LIST_FRAGS;
-  static_assert(PTS <= 64 * NW, "one thread per point");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, col = lane & 31;
-  const int ntiles = (k_s + 31) / 32;
-  int* part = reinterpret_cast<int*>(scratch);     // per (fragment, tile): 32 x (best, second, row)
-  int* item = part + LIST_FRAGS * ntiles * 96;     // (point, tile) pairs for the fp64 step
-  double* item_v = reinterpret_cast<double*>(item + PTS * ntiles);
-  int* item_c = reinterpret_cast<int*>(item_v + PTS * ntiles);
-  for (int b0 = 0; b0 < n; b0 += PTS) {
-    const int nf = min(LIST_FRAGS, (n - b0 + 31) / 32);
-    if (tid == 0) *nitem = 0;
-    for (int it = wave; it < nf * ntiles; it += NW) {
-      const int f = it / ntiles, t = it - f * ntiles;
-      const bf16_t* xr = X + (size_t)(first + left[min(b0 + 32 * f + col, n - 1)]) * D + half * 8;
-      const bf16_t* cr = Cs + (size_t)min(32 * t + col, k_s - 1) * D + half * 8;
-      uint4 a[KS], b[KS];
-#pragma unroll
-      for (int s = 0; s < KS; ++s) a[s] = load16(cr + 16 * s);
-#pragma unroll
-      for (int s = 0; s < KS; ++s) b[s] = load16(xr + 16 * s);
-      constexpr float B0 = kAssignBias;
-      floatx16 acc[1] = {{B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0}};
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[s]),
-                                                         __builtin_bit_cast(bf16x8, b[s]), acc[0], 0, 0, 0);
-      int best[1] = {0}, second[1] = {0}, btile[1] = {0};
-      assign_epilogue<1, true>(acc, best, second, btile, t, half, k_s);
-      const int row = merge_halves(best[0], second[0], btile[0], half);
-      if (half == 0) {
-        int* o = part + (it * 32 + col) * 3;
-        o[0] = best[0];
-        o[1] = second[0];
-        o[2] = row;
-      }
-    }
-    __syncthreads();
-    int best = 0, row = 0, first_item = 0, items = 0;
-    if (tid < PTS && b0 + tid < n) {
-      const int* mine = part + ((tid >> 5) * ntiles * 32 + (tid & 31)) * 3;
-      int second = mine[1];
-      best = mine[0], row = mine[2];
-      for (int t = 1; t < ntiles; ++t) {
-        const int* o = mine + t * 96;
-        second = max(max(second, o[1]), min(best, o[0]));
-        row = o[0] > best ? o[2] : row;
-        best = max(best, o[0]);
-      }
-      if (key_gap(best, second) < kAssignGuard) {
-        for (int t = 0; t < ntiles; ++t) items += key_gap(best, mine[t * 96]) < kAssignGuard ? 1 : 0;
-        first_item = atomicAdd(nitem, items);
-        int j = first_item;
-        for (int t = 0; t < ntiles; ++t)
-          if (key_gap(best, mine[t * 96]) < kAssignGuard) item[j++] = tid << 16 | t;
-      } else {
-        settle(first + left[b0 + tid], row, best, second);
-      }
-    }
-    __syncthreads();
-    const int ni = *nitem;
-    for (int it = 2 * wave + half; it < ni; it += 2 * NW) {  // half a wave per item
-      const int c = 32 * (item[it] & 0xffff) + col;
-      const bf16_t* xr = X + (size_t)(first + left[b0 + (item[it] >> 16)]) * D;
-      const bf16_t* cr = Cs + (size_t)min(c, k_s - 1) * D;
-      double acc = 0.0;
-#pragma unroll 4
-      for (int e0 = 0; e0 < D; e0 += 8) {
-        float xf[8], cf[8];
-        unpack<bf16_t>(load16(xr + e0), xf);
-        unpack<bf16_t>(load16(cr + e0), cf);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc = fma((double)xf[e], (double)cf[e], acc);
-      }
-      double bv = -1.0e300;
-      int bc = 0x7fffffff;
-      if (c < k_s && acc > bv) {
-        bv = acc;
-        bc = c;
-      }
-      for (int off = 16; off >= 1; off >>= 1) {
-        const double ov = __shfl_xor(bv, off);
-        const int oc = __shfl_xor(bc, off);
-        if (ov > bv || (ov == bv && oc < bc)) {
-          bv = ov;
-          bc = oc;
-        }
-      }
-      if (col == 0) {
-        item_v[it] = bv;
-        item_c[it] = bc;
-      }
-    }
-    __syncthreads();
-    if (items > 0) {
-      double bv = -1.0e300;  // (nothing comparable: the fp32 decision stands)
-      for (int j = first_item; j < first_item + items; ++j)  // tiles ascend: strict > keeps the lowest centroid
-        if (item_v[j] > bv) {
-          bv = item_v[j];
-          row = item_c[j];
-        }
-      settle(first + left[b0 + tid], row, best, best);
-    }
-    __syncthreads();
-  }
+// A workgroup's list of points for assign_listed_kernel goes behind what is there of its segment's.
+__device__ __forceinline__ void publish_list(const uint16_t* left, int n, int first, int32_t* list, int32_t* count) {
+  __shared__ int at;
+  if (n == 0) return;  // (the same for the whole workgroup)
+  if (threadIdx.x == 0) at = atomicAdd(count, n);
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += blockDim.x) list[at + i] = first + left[i];
 }
 
 template <int D>
@@ -741,11 +645,11 @@ inline size_t resident_lds(int kmax) {
 template <int D, int NF, int NW>
 __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, int round, int S, int L, int kk, int N_idx,
-    int pieces_per_seg) {
+    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, int32_t* __restrict__ listed,
+    int32_t* __restrict__ nlisted, int round, int S, int L, int kk, int N_idx, int pieces_per_seg) {
   // 32 * ceil(k_s / 32) padded rows, then the near-ties
   extern __shared__ __attribute__((aligned(16))) char cent[];
-  __shared__ int nleft, nitem;
+  __shared__ int nleft;
 
   const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
   const int sg = wg / pieces_per_seg, piece = wg - sg * pieces_per_seg;
@@ -762,17 +666,17 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
   resident_load_centroids<D, 64 * NW>(Cs, si.k_s, cent);
   __syncthreads();
   auto settle = [&](int point, int cluster, int own, int others) {
-    settle_point(assign, prev, bounds, round, gp0 + point, cluster, own, others);
+    settle_point(assign, prev, bounds, round, gp0 + point, bounds ? assign[gp0 + point] : 0, cluster, own, others);
   };
-  resident_assign_fragments<D, NF, NW>(X, cent, si.L_s, si.k_s, f_lo, f_hi,
-                                       [&](int point, int cluster, int best, int second) {
+  resident_assign_fragments<D, NF, NW>(X, cent, si.L_s, si.k_s, f_lo, f_hi, [](int) { return NoState{}; },
+                                       [&](int point, int cluster, int best, int second, NoState) {
                                          if (key_gap(best, second) < kAssignGuard)
                                            left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
                                          else
                                            settle(point, cluster, best, second);
                                        });
   __syncthreads();
-  compare_listed<D, NW>(X, Cs, 32 * f_lo, left, nleft, si.k_s, cent, &nitem, settle);
+  publish_list(left, nleft, 32 * f_lo, listed + gp0, &nlisted[sg]);
 }
 
 // ============================================================================
@@ -783,7 +687,7 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
 //   own centroid changed     c1 above `others`: no unchanged centroid can beat it, c1's cluster;
 //                            otherwise the point is compared with every centroid
 // each by more than the guard of the fp32 similarities; what is closer is compared with every
-// centroid as well.  (A near-tie that was decided in fp64 stays decided while no changed centroid
+// centroid as well (assign_listed_kernel).  (A near-tie that was decided in fp64 stays decided while no changed centroid
 // comes near.)  So the partition is, in every round, the one
 // that the full comparison gives.
 // The share of changed centroids falls from 82 % in the third round to 3 % in the tenth on
@@ -791,95 +695,258 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
 // between a full pass and reading xhat once (16 sequences x 120K tokens: 1.85 ms full, 0.8 ms
 // at the streaming rate).
 //
-// A workgroup takes at most ASSIGN_POINTS points of a segment.  It lists the changed centroids,
-// copies their rows into LDS and streams its points past them as in the kernel above, two
-// accumulator sets while many tiles make the matrix pipe the bound, else the next fragment's
-// rows requested ahead.  Points that need every centroid are listed and compared at the end.
+// A workgroup lists the changed centroids of a segment, copies their rows into LDS and streams
+// a share of the segment's points past them as in the kernel above, two accumulator sets while
+// many tiles make the matrix pipe the bound, else the next fragment's rows requested ahead.
+// Points that need every centroid are listed for assign_listed_kernel.
+// Two launches share the segments by their number of changed centroids: up to
+// delta_light_rows a workgroup of 8 waves needs half of a CU's LDS, so that one workgroup's start
+// and end (chains of short dependent steps, 10 .. 25 us) run under another's streaming;
+// segments with more take a whole CU with 16 waves.
 // ============================================================================
+constexpr int LIGHT_POINTS = 2048;
+
 template <int D>
-inline size_t delta_lds(int kmax) {
-  const int ntiles = (kmax + 31) / 32;
-  return resident_lds<D>(kmax) + sizeof(uint32_t) * ntiles + sizeof(uint16_t) * 32 * (size_t)ntiles;
+constexpr int delta_light_rows() {
+  return D == 128 ? 256 : 512;  // 68 / 72 KiB of rows
 }
 
+template <int D>
+inline size_t delta_lds(int kmax, int rows, int points) {
+  const size_t padded = 32 * (size_t)((kmax + 31) / 32);
+  const size_t held = padded < (size_t)rows ? padded : rows;
+  return held * ResidentTile<D>::ROWB + padded / 8 + sizeof(uint16_t) * (held + points);
+}
+
+// The segments with lo < (changed centroids) <= hi; `hi` rows (or all, if fewer) fit in LDS.
 template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) void assign_delta_kernel(
+__global__ __launch_bounds__(64 * NW, 4) void assign_delta_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, const int32_t* __restrict__ changed, int round,
-    int S, int L, int kk, int N_idx, int pieces_per_seg) {
+    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, const int32_t* __restrict__ changed,
+    const int32_t* __restrict__ nchanged, int32_t* __restrict__ listed, int32_t* __restrict__ nlisted, int lo,
+    int hi, int round, int S, int L, int kk, int N_idx,
+    int pieces_per_seg, int total) {
   using RT = ResidentTile<D>;
   constexpr int ROWB = RT::ROWB, CPR = RT::CPR, NT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) char cent[];
-  __shared__ int wave_n[NW], nleft, nitem;
-  const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
-  const int sg = wg / pieces_per_seg, piece = wg - sg * pieces_per_seg;
-  const SegInfo si = seg_info(sg, S, L, kk, N_idx);
-  const int nfrag = (si.L_s + 31) / 32;
-  const int per = (nfrag + pieces_per_seg - 1) / pieces_per_seg;
-  const int f_lo = piece * per, f_hi = min(nfrag, f_lo + per);
-  if (f_lo >= f_hi) return;
+  __shared__ int wave_n[NW], nleft;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ntiles_all = (si.k_s + 31) / 32;
-  uint32_t* marks = reinterpret_cast<uint32_t*>(cent + (size_t)32 * ntiles_all * ROWB);  // one bit per centroid
-  uint16_t* list = reinterpret_cast<uint16_t*>(marks + ntiles_all);                      // changed centroids
-  uint16_t* left = list + 32 * ntiles_all;                                               // points for the full comparison
+  for (int wg = xcd_logical_block(blockIdx.x, gridDim.x); wg < total; wg += gridDim.x) {
+    const int sg = wg / pieces_per_seg, piece = wg - sg * pieces_per_seg;
+    const int nch = nchanged[sg];
+    if (nch <= lo || nch > hi) continue;  // (the same for the whole workgroup)
+    const SegInfo si = seg_info(sg, S, L, kk, N_idx);
+    const int nfrag = (si.L_s + 31) / 32;
+    const int per = (nfrag + pieces_per_seg - 1) / pieces_per_seg;
+    const int f_lo = piece * per, f_hi = min(nfrag, f_lo + per);
+    if (f_lo >= f_hi) continue;
+    const int ntiles_all = (si.k_s + 31) / 32, held = min(32 * ntiles_all, hi);
+    uint32_t* marks = reinterpret_cast<uint32_t*>(cent + (size_t)held * ROWB);  // one bit per centroid
+    uint16_t* list = reinterpret_cast<uint16_t*>(marks + ntiles_all);           // changed centroids
+    uint16_t* left = list + held;                                               // points for the full comparison
+    const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
+    const bf16_t* X = xhat + gp0 * D;
+    const bf16_t* Cs = chat + (size_t)sg * kk * D;
+
+    // the changed centroids, in ascending order
+    if (tid == 0) nleft = 0;
+    int n = 0;
+    for (int c0 = 0; c0 < si.k_s; c0 += NT) {
+      const int c = c0 + tid;
+      const bool on = c < si.k_s && changed[(size_t)sg * kk + c] != 0;
+      const uint64_t mk = __ballot(on);
+      if (lane == 0) {
+        wave_n[wave] = __popcll(mk);
+        if (c < 32 * ntiles_all) marks[c / 32] = (uint32_t)mk;
+        if (c + 32 < 32 * ntiles_all) marks[c / 32 + 1] = (uint32_t)(mk >> 32);
+      }
+      __syncthreads();
+      int base = n;
+      for (int w = 0; w < NW; ++w) {
+        base += w < wave ? wave_n[w] : 0;
+        n += wave_n[w];
+      }
+      if (on) list[base + __popcll(mk & ((1ull << lane) - 1ull))] = (uint16_t)c;
+      __syncthreads();
+    }
+    for (int id = tid; id < (nch + 31) / 32 * 32 * CPR; id += NT) {
+      const int row = id / CPR, ch = id - row * CPR;
+      store16(cent + row * ROWB + ch * 16, load16(Cs + (size_t)list[min(row, nch - 1)] * D + ch * 8));
+    }
+    __syncthreads();
+
+    auto fetch = [&](int point) { return PointState{assign[gp0 + point], bounds[gp0 + point]}; };
+    auto decide = [&](int point, int row, int c1, int c2, const PointState& ps) {
+      const size_t gp = gp0 + point;
+      const int own_c = ps.cluster;
+      const PointBounds pb = ps.bounds;
+      const bool own_changed = (marks[own_c / 32] >> (own_c & 31)) & 1u;
+      if (!own_changed && key_gap(pb.own, c1) > kAssignGuard) {
+        if (c1 > pb.others) bounds[gp].others = c1;
+        return;
+      }
+      const int rest = max(own_changed ? pb.others : max(pb.own, pb.others), c2);
+      if (key_gap(c1, rest) > kAssignGuard)
+        settle_point(assign, prev, bounds, round, gp, own_c, list[row], c1, rest);
+      else
+        left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
+    };
+    if (nch > 64)
+      resident_assign_fragments<D, 1, NW>(X, cent, si.L_s, nch, f_lo, f_hi, fetch, decide);
+    else
+      lean_assign_fragments<D, NW>(X, cent, si.L_s, nch, f_lo, f_hi, fetch, decide);
+    __syncthreads();
+    publish_list(left, nleft, 32 * f_lo, listed + gp0, &nlisted[sg]);
+    __syncthreads();
+  }
+}
+
+// ============================================================================
+// Assign, the points that the kernels above list: each against every centroid of its segment.
+// A workgroup of four waves takes LIST_POINTS at a time; a segment's list is shared by LIST_SPLIT
+// workgroups (the lists are uneven: a large cluster whose centroid moved can put a thousand points on
+// one), the first shares of all segments before the second ones, most of which are empty.
+// The points' rows are staged in LDS, the waves share out the centroid tiles, read from the
+// cache, and the tiles' best two are merged per point.  A point whose two best are closer than the
+// guard gets fp64 similarities (exact for the stored operands up to fp64 rounding, ties to
+// the lowest centroid) of the centroids in every tile whose best is that close, one lane per
+// centroid; the bound on its other similarities is then `best` too.
+// (A chain of short dependent steps.  At the end of each listing workgroup, in the LDS that it
+// holds, the same steps added 270 .. 400 us to a round that streams its points in 700 us.)
+// ============================================================================
+constexpr int LIST_POINTS = 64, LIST_SPLIT = 16;
+
+template <int D>
+inline size_t listed_lds(int kmax) {
+  return (size_t)LIST_POINTS * ResidentTile<D>::ROWB + sizeof(int) * 3 * LIST_POINTS * (size_t)((kmax + 31) / 32);
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 4) void assign_listed_kernel(
+    const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
+    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, const int32_t* __restrict__ listed,
+    const int32_t* __restrict__ nlisted, int32_t* __restrict__ nlisted_next, int round, int segs, int S, int L,
+    int kk, int N_idx) {
+  using RT = ResidentTile<D>;
+  constexpr int KS = RT::KS, ROWB = RT::ROWB, CPR = RT::CPR, NW = 4, FRAGS = LIST_POINTS / 32;
+  extern __shared__ __attribute__((aligned(16))) char rows[];
+  int* part = reinterpret_cast<int*>(rows + LIST_POINTS * ROWB);  // per (tile, point): best, second, row
+  __shared__ int near_p[LIST_POINTS], near_best[LIST_POINTS], near_row[LIST_POINTS], nnear;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, col = lane & 31;
+  const int share = blockIdx.x / segs, sg = blockIdx.x - share * segs;
+  if (share == 0 && tid == 0) nlisted_next[sg] = 0;
+  const int n = nlisted[sg];
+  if (share * LIST_POINTS >= n) return;
+  const SegInfo si = seg_info(sg, S, L, kk, N_idx);
+  const int ntiles = (si.k_s + 31) / 32;
   const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
   const bf16_t* X = xhat + gp0 * D;
   const bf16_t* Cs = chat + (size_t)sg * kk * D;
-
-  // the changed centroids, in ascending order
-  if (tid == 0) nleft = 0;
-  int nch = 0;
-  for (int c0 = 0; c0 < si.k_s; c0 += NT) {
-    const int c = c0 + tid;
-    const bool on = c < si.k_s && changed[(size_t)sg * kk + c] != 0;
-    const uint64_t mk = __ballot(on);
-    if (lane == 0) {
-      wave_n[wave] = __popcll(mk);
-      if (c < 32 * ntiles_all) marks[c / 32] = (uint32_t)mk;
-      if (c + 32 < 32 * ntiles_all) marks[c / 32 + 1] = (uint32_t)(mk >> 32);
-    }
-    __syncthreads();
-    int base = nch;
-    for (int w = 0; w < NW; ++w) {
-      base += w < wave ? wave_n[w] : 0;
-      nch += wave_n[w];
-    }
-    if (on) list[base + __popcll(mk & ((1ull << lane) - 1ull))] = (uint16_t)c;
-    __syncthreads();
-  }
-  if (nch == 0) return;  // (the same for the whole workgroup)
-  for (int id = tid; id < (nch + 31) / 32 * 32 * CPR; id += NT) {
-    const int row = id / CPR, ch = id - row * CPR;
-    store16(cent + row * ROWB + ch * 16, load16(Cs + (size_t)list[min(row, nch - 1)] * D + ch * 8));
-  }
-  __syncthreads();
-
+  const int32_t* left = listed + gp0;
   auto settle = [&](int point, int cluster, int own, int others) {
-    settle_point(assign, prev, bounds, round, gp0 + point, cluster, own, others);
+    settle_point(assign, prev, bounds, round, gp0 + point, bounds ? assign[gp0 + point] : 0, cluster, own, others);
   };
-  auto decide = [&](int point, int row, int c1, int c2) {
-    const size_t gp = gp0 + point;
-    const int own_c = assign[gp];
-    const PointBounds pb = bounds[gp];
-    const bool own_changed = (marks[own_c / 32] >> (own_c & 31)) & 1u;
-    if (!own_changed && key_gap(pb.own, c1) > kAssignGuard) {
-      if (c1 > pb.others) bounds[gp].others = c1;
-      return;
+  for (int b0 = share * LIST_POINTS; b0 < n; b0 += LIST_SPLIT * LIST_POINTS) {
+    if (tid == 0) nnear = 0;
+    uint4 a[KS];
+    auto load_tile = [&](int t) {
+      const bf16_t* cr = Cs + (size_t)min(32 * t + col, si.k_s - 1) * D + half * 8;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a[s] = load16(cr + 16 * s);
+    };
+    if (wave < ntiles) load_tile(wave);
+    for (int id = tid; id < LIST_POINTS * CPR; id += 64 * NW) {
+      const int p = id / CPR, ch = id - p * CPR;
+      store16(rows + p * ROWB + ch * 16, load16(X + (size_t)left[min(b0 + p, n - 1)] * D + ch * 8));
     }
-    const int rest = max(own_changed ? pb.others : max(pb.own, pb.others), c2);
-    if (key_gap(c1, rest) > kAssignGuard)
-      settle(point, list[row], c1, rest);
-    else
-      left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
-  };
-  if (nch > 64)
-    resident_assign_fragments<D, 1, NW>(X, cent, si.L_s, nch, f_lo, f_hi, decide);
-  else
-    lean_assign_fragments<D, NW>(X, cent, si.L_s, nch, f_lo, f_hi, decide);
-  __syncthreads();
-
-  compare_listed<D, NW>(X, Cs, 32 * f_lo, left, nleft, si.k_s, cent, &nitem, settle);
+    __syncthreads();
+    for (int t = wave; t < ntiles; t += NW) {
+      constexpr float B0 = kAssignBias;
+      floatx16 acc[FRAGS];
+#pragma unroll
+      for (int f = 0; f < FRAGS; ++f) acc[f] = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int f = 0; f < FRAGS; ++f)
+          acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              __builtin_bit_cast(bf16x8, a[s]),
+              __builtin_bit_cast(bf16x8, load16(rows + (32 * f + col) * ROWB + (2 * s + half) * 16)), acc[f], 0, 0, 0);
+      if (t + NW < ntiles) load_tile(t + NW);
+      int best[FRAGS] = {}, second[FRAGS] = {}, btile[FRAGS] = {};
+      assign_epilogue<FRAGS, true>(acc, best, second, btile, t, half, si.k_s);
+#pragma unroll
+      for (int f = 0; f < FRAGS; ++f) {
+        const int row = merge_halves(best[f], second[f], btile[f], half);
+        if (half == 0) {
+          int* o = part + (t * LIST_POINTS + 32 * f + col) * 3;
+          o[0] = best[f];
+          o[1] = second[f];
+          o[2] = row;
+        }
+      }
+    }
+    __syncthreads();
+    if (tid < LIST_POINTS && b0 + tid < n) {
+      const int* mine = part + tid * 3;
+      int best = mine[0], second = mine[1], row = mine[2];
+      for (int t = 1; t < ntiles; ++t) {
+        const int* o = mine + t * LIST_POINTS * 3;
+        second = max(max(second, o[1]), min(best, o[0]));
+        row = o[0] > best ? o[2] : row;
+        best = max(best, o[0]);
+      }
+      if (key_gap(best, second) < kAssignGuard) {
+        const int q = atomicAdd(&nnear, 1);
+        near_p[q] = tid;
+        near_best[q] = best;
+        near_row[q] = row;
+      } else {
+        settle(left[b0 + tid], row, best, second);
+      }
+    }
+    __syncthreads();
+    for (int q = wave; q < nnear; q += NW) {
+      const int p = near_p[q], best = near_best[q];
+      uint64_t close = __ballot(lane < ntiles &&
+                                key_gap(best, part[(min(lane, ntiles - 1) * LIST_POINTS + p) * 3]) < kAssignGuard);
+      double bv = -1.0e300;
+      int bc = 0x7fffffff;
+      while (close) {  // two tiles at a time, one per half of the wave
+        const int t0 = __ffsll((unsigned long long)close) - 1;
+        close &= close - 1;
+        const int t1 = close ? __ffsll((unsigned long long)close) - 1 : t0;
+        close &= close - 1;
+        const int c = 32 * (half ? t1 : t0) + col;
+        const bf16_t* cr = Cs + (size_t)min(c, si.k_s - 1) * D;
+        double acc = 0.0;
+#pragma unroll 4
+        for (int e0 = 0; e0 < D; e0 += 8) {
+          float xf[8], cf[8];
+          unpack<bf16_t>(load16(rows + p * ROWB + e0 * 2), xf);
+          unpack<bf16_t>(load16(cr + e0), cf);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc = fma((double)xf[e], (double)cf[e], acc);
+        }
+        if (c < si.k_s && acc > bv) {  // (c ascends within a lane: strict > keeps the lowest)
+          bv = acc;
+          bc = c;
+        }
+      }
+      for (int off = 32; off >= 1; off >>= 1) {
+        const double ov = __shfl_xor(bv, off);
+        const int oc = __shfl_xor(bc, off);
+        if (ov > bv || (ov == bv && oc < bc)) {
+          bv = ov;
+          bc = oc;
+        }
+      }
+      // (nothing comparable: the fp32 decision stands)
+      if (lane == 0) settle(left[b0 + p], bc < si.k_s ? bc : near_row[q], best, best);
+    }
+    __syncthreads();
+  }
 }
 
 // ============================================================================
@@ -1363,7 +1430,7 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
 // practice) is sorted and its changed clusters are summed again by the first workgroup.
 // No sort and no pass over the members: a round costs the scan of the marks in prev[], 2 KiB per
 // changed cluster and 512 B per moved point.
-// Also leaves in changed[] which centroids the next round's assign step compares.
+// Also leaves in changed[] and nchanged[] which centroids the next round's assign step compares.
 //
 // A workgroup owns the clusters [c_lo, c_hi) of a segment: it counts the arrivals and departures
 // of each (MOVE_CAP at once; more are taken in ranges of the points), lists them by cluster in
@@ -1380,7 +1447,7 @@ template <int D>
 __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
     const bf16_t* __restrict__ xhat, bf16_t* __restrict__ chat, double* __restrict__ sums,
     const int32_t* __restrict__ assign, const int32_t* __restrict__ prev, int32_t* __restrict__ changed,
-    const int32_t* __restrict__ range, int32_t* order, int32_t* count, int32_t* start, int round, int S, int L,
+    int32_t* __restrict__ nchanged, int32_t* __restrict__ nchanged_next, const int32_t* __restrict__ range, int32_t* order, int32_t* count, int32_t* start, int round, int S, int L,
     int kk, int N_idx, int pieces, int key_bits) {
   constexpr int EPC = 8, LPR = D / EPC, GROUPS = MOVE_NT / LPR, U = 4;
   extern __shared__ int moves_lds[];
@@ -1402,6 +1469,7 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
   const bool exact = emax < emin || emax - emin + lg <= 52 - MantissaBits<bf16_t>::value;
   const int per = exact ? (si.k_s + pieces - 1) / pieces : si.k_s;
   const int c_lo = min(si.k_s, piece * per), c_hi = min(si.k_s, c_lo + per);
+  if (piece == 0 && tid == 0) nchanged_next[sg] = 0;
   if (c_lo >= c_hi) return;
 
   auto visit = [&](int lo, int hi, auto&& f) {  // f(cluster, entry) for the round's entries of points [lo, hi)
@@ -1450,6 +1518,7 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
   };
   count_entries(0, si.L_s);
   for (int c = c_lo + tid; c < c_hi; c += MOVE_NT) changed[(size_t)sg * kk + c] = cnt[c] > 0 ? 1 : 0;
+  if (tid == 0 && totals[1] > 0) atomicAdd(&nchanged[sg], totals[1]);
   if (!exact) {
     const int n = totals[1];
     sort_segment(as, order + p0, count + (size_t)sg * kk, start + (size_t)sg * kk, si.L_s, kk, key_bits, entry);
@@ -1555,8 +1624,8 @@ __global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
     if (tid == 0) nflag = 0;
     __syncthreads();
     WAVE_PHASE(0);
-    lean_assign_fragments<D, SMALL_NW>(X, cent, si.L_s, si.k_s, 0, nfrag,
-                                       [&](int point, int cluster, int best, int second) {
+    lean_assign_fragments<D, SMALL_NW>(X, cent, si.L_s, si.k_s, 0, nfrag, [](int) { return NoState{}; },
+                                       [&](int point, int cluster, int best, int second, NoState) {
                                          a_s[point] = cluster;
                                          if (key_gap(best, second) < kAssignGuard) flags[atomicAdd(&nflag, 1)] = point;
                                        });
@@ -1768,7 +1837,7 @@ BuildGeom build_geometry(const wave_index& ix) {
   if (delta_rounds(ix)) {
     g.off_bounds = o; o = align_up(o + pts * sizeof(PointBounds));
     g.off_sums = o;   o = align_up(o + ncl * ix.d * sizeof(double));        // the clusters' member sums
-    g.off_range = o;  o = align_up(o + 2 * (size_t)g.segs * sizeof(int32_t));
+    g.off_range = o;  o = align_up(o + 6 * (size_t)g.segs * sizeof(int32_t));  // exponents, changed centroids, listed points
   }
   g.total = o;
   return g;
@@ -1789,23 +1858,35 @@ static int key_bits_for(int kk) {
 
 // One assign step.  bounds, changed: null in a round that compares every point with every
 // centroid; with `bounds` alone such a round leaves what the next one needs to compare with the
-// changed centroids only, and in prev which points moved.
+// changed centroids only, and in prev which points moved.  nlisted: points listed per segment (all
+// zero), or null: the centroids of a segment do not stay in LDS; nlisted_next is cleared.
 template <typename T, int D>
 static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t* prev, PointBounds* bounds,
-                          const int32_t* changed, int round, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
+                          const int32_t* changed, const int32_t* nchanged, int32_t* nlisted, int32_t* nlisted_next, int round, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
                           int segs, int refine_wgs, hipStream_t st) {
   const int Lmax = L < N_idx ? L : N_idx, kmax = kk < Lmax ? kk : Lmax;
   if constexpr (sizeof(T) == 2) {
-    if (centroids_resident(WAVE_BF16, D, kmax)) {
+    if (nlisted) {
       // at least two workgroups per long segment keep the last round of workgroups short
       int pieces = (Lmax + ASSIGN_POINTS - 1) / ASSIGN_POINTS;
       if (pieces < 2 && Lmax > 2048) pieces = 2;
-      if (changed)
-        WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16>), segs * pieces, 1024, delta_lds<D>(kmax), st, xhat,
-                    chat, assign, prev, bounds, changed, round, S, L, kk, N_idx, pieces);
-      else
+      if (changed) {
+        constexpr int light = delta_light_rows<D>();
+        const int light_pieces = (Lmax + LIGHT_POINTS - 1) / LIGHT_POINTS;
+        if (kmax > light) {  // (usually none after a few rounds: no more workgroups than a CU each)
+          const int total = segs * pieces;
+          WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16>), total < 256 ? total : 256, 1024,
+                      delta_lds<D>(kmax, 1 << 20, ASSIGN_POINTS), st, xhat, chat, assign, prev, bounds, changed,
+                      nchanged, flag, nlisted, light, 1 << 20, round, S, L, kk, N_idx, pieces, total);
+        }
+        WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 8>), segs * light_pieces, 512,
+                    delta_lds<D>(kmax, light, LIGHT_POINTS), st, xhat, chat, assign, prev, bounds, changed,
+                    nchanged, flag, nlisted, 0, light, round, S, L, kk, N_idx, light_pieces, segs * light_pieces);
+      } else
         WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16>), segs * pieces, 1024, resident_lds<D>(kmax),
-                    st, xhat, chat, assign, prev, bounds, round, S, L, kk, N_idx, pieces);
+                    st, xhat, chat, assign, prev, bounds, flag, nlisted, round, S, L, kk, N_idx, pieces);
+      WAVE_LAUNCH("assign_listed", (assign_listed_kernel<D>), segs * LIST_SPLIT, 256, listed_lds<D>(kmax), st, xhat,
+                  chat, assign, prev, bounds, flag, nlisted, nlisted_next, round, segs, S, L, kk, N_idx);
       return;
     }
     // the centroids are staged through LDS tile by tile
@@ -1862,13 +1943,17 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   PointBounds* bounds = delta ? reinterpret_cast<PointBounds*>(w + g.off_bounds) : nullptr;
   double* sums = delta ? reinterpret_cast<double*>(w + g.off_sums) : nullptr;
   int32_t* range = delta ? reinterpret_cast<int32_t*>(w + g.off_range) : nullptr;
+  // changed centroids per segment (of even and of odd rounds: each round clears the other one)
+  int32_t* nchanged[2] = {range + 2 * (size_t)g.segs, range + 3 * (size_t)g.segs};
+  // points listed by the assign step, per segment (likewise)
+  int32_t* nlisted[2] = {delta ? range + 4 * (size_t)g.segs : nullptr, delta ? range + 5 * (size_t)g.segs : nullptr};
   int32_t* flag = reinterpret_cast<int32_t*>(w + g.off_flag);
   int32_t* nflag = reinterpret_cast<int32_t*>(w + g.off_nflag);
   double* mean = reinterpret_cast<double*>(w + g.off_init);
   const int S = ix.S, L = ix.segment_len, N_idx = ix.N_idx;
   constexpr int GROUPS = 256 / (D / Elem<T>::EPC);
 
-  WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs, 256, 0, st, K, mean, nflag, range, S, L, kk, ix.N,
+  WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs, 256, 0, st, K, mean, nflag, range, nchanged[1], nlisted[0], S, L, kk, ix.N,
               N_idx, ns);
   {
     const int chunks = ((L < N_idx ? L : N_idx) + NORM_ROWS - 1) / NORM_ROWS;
@@ -1911,8 +1996,8 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   };
   for (int t = 0; t < iters && !small; ++t) {
     // Rounds 0 and 1 meet all new centroids; from round 2 on only the changed ones are compared.
-    launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, delta && t >= 2 ? changed : nullptr, t,
-                        flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
+    launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, delta && t >= 2 ? changed : nullptr,
+                        nchanged[(t + 1) & 1], nlisted[t & 1], nlisted[(t + 1) & 1], t, flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
     const bool last = t + 1 == iters;
     if (!delta || t == 0 || last) sort(delta ? nullptr : prev, t);
     if (last) break;
@@ -1922,7 +2007,7 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
         int pieces = 1;
         while (g.segs * pieces < 512 && kk / pieces >= 128) pieces *= 2;
         WAVE_LAUNCH("update", (update_moves_kernel<D>), g.segs * pieces, MOVE_NT, update_moves_lds(kk), st, xhat,
-                    chat, sums, assign, prev, changed, range, order, count, start, t, S, L, kk, N_idx, pieces, kb);
+                    chat, sums, assign, prev, changed, nchanged[t & 1], nchanged[(t + 1) & 1], range, order, count, start, t, S, L, kk, N_idx, pieces, kb);
         continue;
       }
     }
@@ -1954,8 +2039,8 @@ static wave_status assign_step_td(const void* xhat, const void* chat, int L_s, i
   int32_t* flag = nflag + 64;
   hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, nflag);
   // one unit, one segment: S = 1, L = N_idx = L_s, kk = k_s
-  launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, nullptr, nullptr, nullptr, 0, flag,
-                      nflag, 1, L_s, k_s, L_s, 1, 256, st);
+  launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, nullptr, nullptr, nullptr, nullptr,
+                      centroids_resident(sizeof(T) == 2 ? WAVE_BF16 : WAVE_F32, D, k_s) ? nflag : nullptr, nflag + 1, 0, flag, nflag, 1, L_s, k_s, L_s, 1, 256, st);
   return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;
 }
 
