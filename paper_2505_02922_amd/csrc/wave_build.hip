@@ -1867,12 +1867,19 @@ static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t
   const int Lmax = L < N_idx ? L : N_idx, kmax = kk < Lmax ? kk : Lmax;
   if constexpr (sizeof(T) == 2) {
     if (nlisted) {
-      // at least two workgroups per long segment keep the last round of workgroups short
-      int pieces = (Lmax + ASSIGN_POINTS - 1) / ASSIGN_POINTS;
+      // At least two workgroups per long segment keep the last round of workgroups short; a few
+      // segments are cut finer, down to a fragment per wave, until every CU has its share (32 segments
+      // of 8192 points x 512 centroids: 104 us a full pass with 2 each).
+      auto cut = [&](int points, int wgs_wanted, int least_points) {
+        int pieces = (Lmax + points - 1) / points;
+        const int want = wgs_wanted / segs, most = (Lmax + least_points - 1) / least_points;
+        return want > pieces ? (want < most ? want : (most > pieces ? most : pieces)) : pieces;
+      };
+      int pieces = cut(ASSIGN_POINTS, 256, 512);
       if (pieces < 2 && Lmax > 2048) pieces = 2;
       if (changed) {
         constexpr int light = delta_light_rows<D>();
-        const int light_pieces = (Lmax + LIGHT_POINTS - 1) / LIGHT_POINTS;
+        const int light_pieces = cut(LIGHT_POINTS, 512, 256);
         if (kmax > light) {  // (usually none after a few rounds: no more workgroups than a CU each)
           const int total = segs * pieces;
           WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16>), total < 256 ? total : 256, 1024,
