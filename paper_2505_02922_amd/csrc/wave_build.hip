@@ -950,53 +950,67 @@ __global__ __launch_bounds__(256, 4) void assign_listed_kernel(
 }
 
 // ============================================================================
-// Assign, plain path (any storage type): one point per thread, fp32 FMA chain,
-// centroids broadcast from LDS.
+// Assign, f32: one wave per workgroup and 32 points of a segment, on v_mfma_f32_32x32x2_f32 (fp32
+// products and sums).  The points stay in registers as B operands; the centroids are A operands
+// read from the cache: a tile of 32 rows is 128 .. 256 bytes per lane for 2048 .. 4096 cycles of the
+// matrix pipe, which is the bound.  Component i of the 16-byte chunks of the wave's two halves is one
+// k pair; the order of k inside a dot product is free as long as both operands agree.  A lane holds
+// 16 centroids of one point; the ranking is in plain floats (inputs of any length are ranked).
+// (One point per thread with a chain of fp32 FMAs and centroids broadcast from LDS took 60 us a step
+// at 4096 tokens x 128 clusters x 64 channels, on 16 workgroups.)
 // ============================================================================
-template <typename T, int D>
-__global__ __launch_bounds__(256) void assign_plain_kernel(
-    const T* __restrict__ xhat, const T* __restrict__ chat, int32_t* __restrict__ assign,
+template <int D>
+__global__ __launch_bounds__(64) void assign_f32_kernel(
+    const float* __restrict__ xhat, const float* __restrict__ chat, int32_t* __restrict__ assign,
     int32_t* __restrict__ flag_list, int32_t* __restrict__ flag_count, int S, int L, int kk, int N_idx,
-    int wgs_per_seg) {
-  constexpr int CT = 16;  // centroids per LDS tile
-  __shared__ __attribute__((aligned(16))) float cs[CT][D];
-  const int sg = blockIdx.x / wgs_per_seg, piece = blockIdx.x - sg * wgs_per_seg;
+    int frags_per_seg) {
+  constexpr int KS = D / 8;  // pairs of 16-byte chunks, one per half of the wave
+  const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
+  const int sg = wg / frags_per_seg, frag = wg - sg * frags_per_seg;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
-  const int p0 = piece * 256;
-  if (p0 >= si.L_s) return;
-  const int point = p0 + threadIdx.x;
-  const T* xr = xhat + ((size_t)si.unit * N_idx + si.seg_start + min(point, si.L_s - 1)) * D;
-  const T* Cs = chat + (size_t)sg * kk * D;
-  float x[D];
+  if (32 * frag >= si.L_s) return;
+  const int lane = threadIdx.x, half = lane >> 5, col = lane & 31;
+  const int point = 32 * frag + col;
+  const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
+  const float* xr = xhat + (gp0 + min(point, si.L_s - 1)) * D + half * 4;
+  const float* Cs = chat + (size_t)sg * kk * D + half * 4;
+  uint4 b[KS];
 #pragma unroll
-  for (int e = 0; e < D; ++e) x[e] = to_f32(xr[e]);
+  for (int s = 0; s < KS; ++s) b[s] = load16(xr + 8 * s);
   float best = kNegHuge, second = kNegHuge;
   int bidx = 0;
-  for (int c0 = 0; c0 < si.k_s; c0 += CT) {
-    __syncthreads();
-    for (int i = threadIdx.x; i < CT * D; i += 256) {
-      const int r = i / D, e = i - r * D;
-      cs[r][e] = to_f32(Cs[(size_t)min(c0 + r, si.k_s - 1) * D + e]);
-    }
-    __syncthreads();
-    const int nc = min(CT, si.k_s - c0);
-    for (int r = 0; r < nc; ++r) {
-      float a = 0.f;
+#pragma unroll 1
+  for (int t = 0; 32 * t < si.k_s; ++t) {
+    const float* cr = Cs + (size_t)min(32 * t + col, si.k_s - 1) * D;
+    floatx16 acc = {};
 #pragma unroll
-      for (int e = 0; e < D; ++e) a = fmaf(x[e], cs[r][e], a);
-      if (a > best) {
-        second = best;
-        best = a;
-        bidx = c0 + r;
-      } else {
-        second = fmaxf(second, a);
-      }
+    for (int s = 0; s < KS; ++s) {
+      const uint4 a = load16(cr + 8 * s);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b[s].x), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b[s].y), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b[s].z), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b[s].w), acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = 32 * t + 8 * (v / 4) + (v % 4) + 4 * half;
+      const float sim = row < si.k_s ? acc[v] : kNegHuge;
+      const bool up = sim > best;
+      second = up ? best : fmaxf(second, sim);
+      best = up ? sim : best;
+      bidx = up ? row : bidx;
     }
   }
-  if (point < si.L_s) {
-    const size_t gp = (size_t)si.unit * N_idx + si.seg_start + point;
-    assign[gp] = bidx;
-    if (best - second < kAssignGuard) flag_list[atomicAdd(flag_count, 1)] = (int32_t)gp;
+  // lanes l and l ^ 32 hold the same point over disjoint centroid rows
+  const float ob = __shfl_xor(best, 32), os = __shfl_xor(second, 32);
+  const int oi = __shfl_xor(bidx, 32);
+  second = fmaxf(fminf(best, ob), fmaxf(second, os));
+  const bool other = ob > best || (ob == best && oi < bidx);
+  bidx = other ? oi : bidx;
+  best = fmaxf(best, ob);
+  if (half == 0 && point < si.L_s) {
+    assign[gp0 + point] = bidx;
+    if (best - second < kAssignGuard) flag_list[atomicAdd(flag_count, 1)] = (int32_t)(gp0 + point);
   }
 }
 
@@ -1902,9 +1916,9 @@ static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t
     WAVE_LAUNCH("assign_mfma", (assign_mfma_kernel<D, 1, 8>), segs * wps, 64 * 8, 0, st, xhat, chat,
                 assign, flag, nflag, S, L, kk, N_idx, wps);
   } else {
-    const int wps = (Lmax + 255) / 256;
-    WAVE_LAUNCH("assign_plain", (assign_plain_kernel<T, D>), segs * wps, 256, 0, st, xhat, chat,
-                assign, flag, nflag, S, L, kk, N_idx, wps);
+    const int frags = (Lmax + 31) / 32;
+    WAVE_LAUNCH("assign_f32", (assign_f32_kernel<D>), segs * frags, 64, 0, st, xhat, chat, assign, flag, nflag, S, L,
+                kk, N_idx, frags);
   }
   WAVE_LAUNCH("refine", (refine_kernel<T, D>), refine_wgs, 256, 0, st, xhat, chat, assign, flag, nflag, S,
               L, kk, N_idx);

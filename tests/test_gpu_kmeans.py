@@ -1,8 +1,10 @@
 """GPU parity of the k-means rounds at the sizes where their launch shapes and tiles change: the
 index arrays of whole builds against the oracle's, bit for bit."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import wave_oracle as wo
 from paper_2505_02922_amd import binding as wb
 from paper_2505_02922_amd import synth
 from tests import parity_util as pu
@@ -45,3 +47,16 @@ def test_rounds_match_oracle(kind, d, N, L, k, iters):
     for name in wb.BUFFER_NAMES:
         got = ix.t[name].cpu()
         assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
+
+
+# (33 points: a fragment with one; k = 33, 129, 289: a tile with one centroid; equal centroids: the lowest wins)
+@pytest.mark.parametrize("d,L,k", [(128, 33, 33), (64, 4097, 129), (128, 1000, 289), (64, 1, 1), (64, 70, 31)])
+def test_assign_step_f32_tile_edges(d, L, k):
+    g = np.random.default_rng(1000 * L + k)
+    xhat, chat = (x / np.linalg.norm(x, axis=1, keepdims=True)
+                  for x in (g.standard_normal((L, d)), g.standard_normal((k, d))))
+    xhat, chat = wo.quant(xhat, "f32"), wo.quant(chat, "f32")
+    chat[k // 2:] = np.where(np.arange(k // 2, k)[:, None] % 5 == 0, chat[0], chat[k // 2:])
+    a = wb.wave_kmeans_assign_step(torch.from_numpy(xhat).float().cuda(), torch.from_numpy(chat).float().cuda())
+    torch.cuda.synchronize()
+    assert pu.check_assign(a.cpu().numpy(), xhat, chat, f"d={d} L={L} k={k}") == 0
