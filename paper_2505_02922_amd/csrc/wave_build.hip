@@ -262,6 +262,7 @@ __global__ __launch_bounds__(256) void init_kernel(const T* __restrict__ xhat, T
     int cur = target[i], bound = i;
     while (true) {
       int t = -1;
+#pragma unroll 8
       for (int u = 0; u < bound; ++u) t = target[u] == cur ? u : t;  // latest earlier step onto cur
       if (t < 0) break;
       cur = t;
@@ -1387,7 +1388,7 @@ __global__ __launch_bounds__(256) void update_kernel(const T* __restrict__ xhat,
 
 // The update of the later rounds: only clusters that a point entered or left in this round
 // (marked by the sort step) are summed again.  Most are untouched: a workgroup reads the marks
-// of 256 consecutive clusters at once, lists the marked ones in LDS and its 16-lane groups take
+// of `span` (256 at most) consecutive clusters at once, lists the marked ones in LDS and its 16-lane groups take
 // them from the list (one mark per group and workgroup, as in update_kernel, is a round trip and
 // a workgroup launch per 16 clusters even when none of them changed).
 template <typename T, int D>
@@ -1398,13 +1399,13 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
                                                              int32_t* __restrict__ changed,
                                                              int32_t* __restrict__ big_list,
                                                              int32_t* __restrict__ big_count, int S, int L,
-                                                             int kk, int N_idx, int nclusters) {
+                                                             int kk, int N_idx, int nclusters, int span) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
   __shared__ int list[256];
   __shared__ int wave_n[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int gc_mine = blockIdx.x * 256 + tid;
-  const bool on = gc_mine < nclusters && changed[gc_mine] != 0;
+  const int gc_mine = blockIdx.x * span + tid;
+  const bool on = tid < span && gc_mine < nclusters && changed[gc_mine] != 0;
   if (on) changed[gc_mine] = 0;
   const uint64_t mk = __ballot(on);
   if (lane == 0) wave_n[wave] = __popcll(mk);
@@ -2001,6 +2002,11 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
     WAVE_LAUNCH("sort", sort_kernel, g.segs, 64 * W, sort_lds, st, assign, order, count, start, nflag,
                 prev_or_null, changed, t == 0 ? 1 : 0, S, L, kk, N_idx, kb);
   };
+  // clusters whose marks a workgroup of the later updates reads: 256 in a large batch; few enough to
+  // give 1024 workgroups, down to one per group of lanes (2 segments of 128 clusters in one workgroup:
+  // 125 us a round)
+  int span = (ncl + 1023) / 1024;
+  span = span < GROUPS ? GROUPS : (span > 256 ? 256 : span);
   auto update = [&](int t) {
     // (first round: nothing to compare with, every cluster is updated and every mark cleared.
     // Large clusters go onto a list, which the second kernel takes: nflag[1] counts them and
@@ -2009,8 +2015,8 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
       WAVE_LAUNCH("update", (update_kernel<T, D>), cl_grid, 256, 0, st, xhat, chat, order, count,
                   start, changed, flag, nflag + 1, sums, S, L, kk, N_idx, ncl);
     else
-      WAVE_LAUNCH("update", (update_touched_kernel<T, D>), (ncl + 255) / 256, 256, 0, st, xhat, chat,
-                  order, count, start, changed, flag, nflag + 1, S, L, kk, N_idx, ncl);
+      WAVE_LAUNCH("update", (update_touched_kernel<T, D>), (ncl + span - 1) / span, 256, 0, st, xhat, chat,
+                  order, count, start, changed, flag, nflag + 1, S, L, kk, N_idx, ncl, span);
     const int big_grid = ncl / UPD_BIG + 1 < 2048 ? ncl / UPD_BIG + 1 : 2048;
     WAVE_LAUNCH("update", (update_big_kernel<T, D>), big_grid, 256, 0, st, xhat, chat, order, count,
                 start, flag, nflag + 1, sums, S, L, kk, N_idx);
