@@ -601,6 +601,7 @@ __device__ __forceinline__ void lean_assign_fragments(const bf16_t* X, const cha
 
 // What the assign step of one round leaves for the next about a point: the key of its cluster's
 // similarity and a key that no other centroid's similarity exceeds (both up to the fp32 error).
+// (A unit's bounds start `bounds_skip` entries further on than the units' points are counted.)
 struct __attribute__((aligned(8))) PointBounds {
   int own, others;
 };
@@ -646,7 +647,7 @@ inline size_t resident_lds(int kmax) {
 template <int D, int NF, int NW>
 __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, int32_t* __restrict__ listed,
+    int32_t* __restrict__ prev, PointBounds* bounds, long long bounds_skip, int32_t* __restrict__ listed,
     int32_t* __restrict__ nlisted, int round, int S, int L, int kk, int N_idx, int pieces_per_seg) {
   // 32 * ceil(k_s / 32) padded rows, then the near-ties
   extern __shared__ __attribute__((aligned(16))) char cent[];
@@ -660,6 +661,7 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
   const int f_lo = piece * per, f_hi = min(nfrag, f_lo + per);
   if (f_lo >= f_hi) return;
   const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
+  if (bounds) bounds += si.unit * bounds_skip;
   const bf16_t* X = xhat + gp0 * D;
   const bf16_t* Cs = chat + (size_t)sg * kk * D;
   uint16_t* left = reinterpret_cast<uint16_t*>(cent + (size_t)32 * ((si.k_s + 31) / 32) * ResidentTile<D>::ROWB);
@@ -723,7 +725,7 @@ inline size_t delta_lds(int kmax, int rows, int points) {
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, 4) void assign_delta_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, const int32_t* __restrict__ changed,
+    int32_t* __restrict__ prev, PointBounds* all_bounds, long long bounds_skip, const int32_t* __restrict__ changed,
     const int32_t* __restrict__ nchanged, int32_t* __restrict__ listed, int32_t* __restrict__ nlisted, int lo,
     int hi, int round, int S, int L, int kk, int N_idx,
     int pieces_per_seg, int total) {
@@ -746,6 +748,7 @@ __global__ __launch_bounds__(64 * NW, 4) void assign_delta_kernel(
     uint16_t* list = reinterpret_cast<uint16_t*>(marks + ntiles_all);           // changed centroids
     uint16_t* left = list + held;                                               // points for the full comparison
     const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
+    PointBounds* bounds = all_bounds + si.unit * bounds_skip;
     const bf16_t* X = xhat + gp0 * D;
     const bf16_t* Cs = chat + (size_t)sg * kk * D;
 
@@ -825,7 +828,7 @@ inline size_t listed_lds(int kmax) {
 template <int D>
 __global__ __launch_bounds__(256, 4) void assign_listed_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
-    int32_t* __restrict__ prev, PointBounds* __restrict__ bounds, const int32_t* __restrict__ listed,
+    int32_t* __restrict__ prev, PointBounds* bounds, long long bounds_skip, const int32_t* __restrict__ listed,
     const int32_t* __restrict__ nlisted, int32_t* __restrict__ nlisted_next, int round, int segs, int S, int L,
     int kk, int N_idx) {
   using RT = ResidentTile<D>;
@@ -845,6 +848,7 @@ __global__ __launch_bounds__(256, 4) void assign_listed_kernel(
   const bf16_t* X = xhat + gp0 * D;
   const bf16_t* Cs = chat + (size_t)sg * kk * D;
   const int32_t* left = listed + gp0;
+  if (bounds) bounds += si.unit * bounds_skip;
   auto settle = [&](int point, int cluster, int own, int others) {
     settle_point(assign, prev, bounds, round, gp0 + point, bounds ? assign[gp0 + point] : 0, cluster, own, others);
   };
@@ -1299,7 +1303,7 @@ __global__ __launch_bounds__(256) void update_big_kernel(const T* __restrict__ x
                                                          const int32_t* __restrict__ start,
                                                          const int32_t* __restrict__ big_list,
                                                          const int32_t* __restrict__ big_count,
-                                                         double* __restrict__ sums, int S, int L,
+                                                         double* sums, long long sums_skip, int S, int L,
                                                          int kk, int N_idx) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
   __shared__ double part[GROUPS * D];
@@ -1348,7 +1352,7 @@ __global__ __launch_bounds__(256) void update_big_kernel(const T* __restrict__ x
       }
       const int lg = 32 - __clz(n - 1);  // ceil(log2 n), n > UPD_BIG
       T* dst = chat + (size_t)gc * D + sub * EPC;
-      if (sums) store_sums<EPC>(sums + (size_t)gc * D + sub * EPC, tot);  // (used where the test below holds)
+      if (sums) store_sums<EPC>(sums + si.unit * sums_skip + (size_t)gc * D + sub * EPC, tot);  // (used where the test below holds)
       if (hi < lo || hi - lo + lg <= 52 - MantissaBits<T>::value)  // (hi < lo: every addend is zero)
         finish_centroid<T, D>(tot, dst);
       else
@@ -1366,8 +1370,8 @@ __global__ __launch_bounds__(256) void update_kernel(const T* __restrict__ xhat,
                                                      const int32_t* __restrict__ start,
                                                      int32_t* __restrict__ changed,
                                                      int32_t* __restrict__ big_list,
-                                                     int32_t* __restrict__ big_count, double* __restrict__ sums,
-                                                     int S, int L, int kk, int N_idx, int nclusters) {
+                                                     int32_t* __restrict__ big_count, double* sums,
+                                                     long long sums_skip, int S, int L, int kk, int N_idx, int nclusters) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   const int gc = blockIdx.x * GROUPS + grp;  // sg * kk + c
@@ -1383,7 +1387,7 @@ __global__ __launch_bounds__(256) void update_kernel(const T* __restrict__ xhat,
   }
   const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
   update_cluster<T, D, 4, true>(xhat + p0 * D, order + p0 + start[gc], n, chat + (size_t)gc * D + sub * EPC, sub,
-                                sums ? sums + (size_t)gc * D + sub * EPC : nullptr);
+                                sums ? sums + si.unit * sums_skip + (size_t)gc * D + sub * EPC : nullptr);
 }
 
 // The update of the later rounds: only clusters that a point entered or left in this round
@@ -1460,7 +1464,7 @@ inline size_t update_moves_lds(int kk) {
 
 template <int D>
 __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
-    const bf16_t* __restrict__ xhat, bf16_t* __restrict__ chat, double* __restrict__ sums,
+    const bf16_t* __restrict__ xhat, bf16_t* __restrict__ chat, double* sums, long long sums_skip,
     const int32_t* __restrict__ assign, const int32_t* __restrict__ prev, int32_t* __restrict__ changed,
     int32_t* __restrict__ nchanged, int32_t* __restrict__ nchanged_next, const int32_t* __restrict__ range, int32_t* order, int32_t* count, int32_t* start, int round, int S, int L,
     int kk, int N_idx, int pieces, int key_bits) {
@@ -1558,7 +1562,7 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
       const int c = touched[j];
       const int ne = cnt[c], e0 = end[c] - ne;
       const size_t gc = (size_t)sg * kk + c;
-      double* own = sums + gc * D + sub * EPC;
+      double* own = sums + si.unit * sums_skip + gc * D + sub * EPC;
       double acc[EPC];
 #pragma unroll
       for (int e = 0; e < EPC; ++e) acc[e] = own[e];
@@ -1823,9 +1827,15 @@ static bool small_segments(const wave_index& ix) {
          min_kL(ix) <= SMALL_K_MAX;
 }
 
-// Builds whose later rounds compare the points with the changed centroids only.
+// Builds whose later rounds compare the points with the changed centroids only.  What these rounds
+// keep (bounds per point, member sums per cluster, a few counters per segment) lies in the index's
+// own k_perm and v_perm rows (of an update: the new ones), which only the last step writes: 8 bytes
+// per point in k_perm, then 6 counters per segment in the first unit's; 8 d bytes per cluster in
+// v_perm.  That fits with four points per cluster or more.
 static bool delta_rounds(const wave_index& ix) {
-  return centroids_resident(ix.dtype, ix.d, min_kL(ix)) && !small_segments(ix);
+  if (!centroids_resident(ix.dtype, ix.d, min_kL(ix)) || small_segments(ix)) return false;
+  const long long segs = (long long)ix.B * ix.Hkv * ix.S, points = ix.N_idx;
+  return 4ll * ix.S * min_kL(ix) <= points && 8 * points + 24 * segs + 16 <= 2ll * ix.d * points;
 }
 
 BuildGeom build_geometry(const wave_index& ix) {
@@ -1849,11 +1859,6 @@ BuildGeom build_geometry(const wave_index& ix) {
   g.off_flag = o;   o = align_up(o + pts * sizeof(int32_t));
   g.off_nflag = o;  o = align_up(o + 256);
   g.off_init = o;   o = align_up(o + (size_t)g.segs * ix.d * sizeof(double));  // segment means
-  if (delta_rounds(ix)) {
-    g.off_bounds = o; o = align_up(o + pts * sizeof(PointBounds));
-    g.off_sums = o;   o = align_up(o + ncl * ix.d * sizeof(double));        // the clusters' member sums
-    g.off_range = o;  o = align_up(o + 6 * (size_t)g.segs * sizeof(int32_t));  // exponents, changed centroids, listed points
-  }
   g.total = o;
   return g;
 }
@@ -1877,7 +1882,7 @@ static int key_bits_for(int kk) {
 // zero), or null: the centroids of a segment do not stay in LDS; nlisted_next is cleared.
 template <typename T, int D>
 static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t* prev, PointBounds* bounds,
-                          const int32_t* changed, const int32_t* nchanged, int32_t* nlisted, int32_t* nlisted_next, int round, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
+                          long long bounds_skip, const int32_t* changed, const int32_t* nchanged, int32_t* nlisted, int32_t* nlisted_next, int round, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
                           int segs, int refine_wgs, hipStream_t st) {
   const int Lmax = L < N_idx ? L : N_idx, kmax = kk < Lmax ? kk : Lmax;
   if constexpr (sizeof(T) == 2) {
@@ -1898,17 +1903,17 @@ static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t
         if (kmax > light) {  // (usually none after a few rounds: no more workgroups than a CU each)
           const int total = segs * pieces;
           WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16>), total < 256 ? total : 256, 1024,
-                      delta_lds<D>(kmax, 1 << 20, ASSIGN_POINTS), st, xhat, chat, assign, prev, bounds, changed,
+                      delta_lds<D>(kmax, 1 << 20, ASSIGN_POINTS), st, xhat, chat, assign, prev, bounds, bounds_skip, changed,
                       nchanged, flag, nlisted, light, 1 << 20, round, S, L, kk, N_idx, pieces, total);
         }
         WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 8>), segs * light_pieces, 512,
-                    delta_lds<D>(kmax, light, LIGHT_POINTS), st, xhat, chat, assign, prev, bounds, changed,
+                    delta_lds<D>(kmax, light, LIGHT_POINTS), st, xhat, chat, assign, prev, bounds, bounds_skip, changed,
                     nchanged, flag, nlisted, 0, light, round, S, L, kk, N_idx, light_pieces, segs * light_pieces);
       } else
         WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16>), segs * pieces, 1024, resident_lds<D>(kmax),
-                    st, xhat, chat, assign, prev, bounds, flag, nlisted, round, S, L, kk, N_idx, pieces);
+                    st, xhat, chat, assign, prev, bounds, bounds_skip, flag, nlisted, round, S, L, kk, N_idx, pieces);
       WAVE_LAUNCH("assign_listed", (assign_listed_kernel<D>), segs * LIST_SPLIT, 256, listed_lds<D>(kmax), st, xhat,
-                  chat, assign, prev, bounds, flag, nlisted, nlisted_next, round, segs, S, L, kk, N_idx);
+                  chat, assign, prev, bounds, bounds_skip, flag, nlisted, nlisted_next, round, segs, S, L, kk, N_idx);
       return;
     }
     // the centroids are staged through LDS tile by tile
@@ -1959,20 +1964,27 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   const int ncl = g.segs * kk;
   int32_t* count = reinterpret_cast<int32_t*>(w + g.off_count);
   int32_t* start = count + ncl;
+  const int S = ix.S, L = ix.segment_len, N_idx = ix.N_idx;
   const bool delta = delta_rounds(ix);
   int32_t* changed = start + ncl;  // per cluster: a point entered or left it in the current round
   int32_t* prev = reinterpret_cast<int32_t*>(w + g.off_prev);  // every point's cluster of the round before
-  PointBounds* bounds = delta ? reinterpret_cast<PointBounds*>(w + g.off_bounds) : nullptr;
-  double* sums = delta ? reinterpret_cast<double*>(w + g.off_sums) : nullptr;
-  int32_t* range = delta ? reinterpret_cast<int32_t*>(w + g.off_range) : nullptr;
-  // changed centroids per segment (of even and of odd rounds: each round clears the other one)
-  int32_t* nchanged[2] = {range + 2 * (size_t)g.segs, range + 3 * (size_t)g.segs};
-  // points listed by the assign step, per segment (likewise)
-  int32_t* nlisted[2] = {delta ? range + 4 * (size_t)g.segs : nullptr, delta ? range + 5 * (size_t)g.segs : nullptr};
+  // (see delta_rounds)
+  PointBounds* bounds = delta ? reinterpret_cast<PointBounds*>(ix.k_perm) : nullptr;
+  double* sums = delta ? reinterpret_cast<double*>(ix.v_perm) : nullptr;
+  const long long unit8 = (long long)row_stride(ix) * D * (long long)sizeof(T) / 8;  // 8-byte words per unit there
+  const long long bounds_skip = unit8 - N_idx, sums_skip = unit8 - (long long)S * kk * D;
+  int32_t* per_seg = delta ? reinterpret_cast<int32_t*>(bounds + N_idx) : nullptr;
+  int32_t* range = per_seg;  // smallest and largest exponent of a segment's normalised keys
+  // changed centroids, and points listed by the assign step (of even and of odd rounds: each round
+  // clears the other one)
+  int32_t *nchanged[2] = {}, *nlisted[2] = {};
+  for (int i = 0; i < 2 && delta; ++i) {
+    nchanged[i] = per_seg + (2 + i) * (size_t)g.segs;
+    nlisted[i] = per_seg + (4 + i) * (size_t)g.segs;
+  }
   int32_t* flag = reinterpret_cast<int32_t*>(w + g.off_flag);
   int32_t* nflag = reinterpret_cast<int32_t*>(w + g.off_nflag);
   double* mean = reinterpret_cast<double*>(w + g.off_init);
-  const int S = ix.S, L = ix.segment_len, N_idx = ix.N_idx;
   constexpr int GROUPS = 256 / (D / Elem<T>::EPC);
 
   WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs, 256, 0, st, K, mean, nflag, range, nchanged[1], nlisted[0], S, L, kk, ix.N,
@@ -2013,17 +2025,17 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
     // the flagged-point list, consumed by refine, is free to hold them)
     if (t == 0)
       WAVE_LAUNCH("update", (update_kernel<T, D>), cl_grid, 256, 0, st, xhat, chat, order, count,
-                  start, changed, flag, nflag + 1, sums, S, L, kk, N_idx, ncl);
+                  start, changed, flag, nflag + 1, sums, sums_skip, S, L, kk, N_idx, ncl);
     else
       WAVE_LAUNCH("update", (update_touched_kernel<T, D>), (ncl + span - 1) / span, 256, 0, st, xhat, chat,
                   order, count, start, changed, flag, nflag + 1, S, L, kk, N_idx, ncl, span);
     const int big_grid = ncl / UPD_BIG + 1 < 2048 ? ncl / UPD_BIG + 1 : 2048;
     WAVE_LAUNCH("update", (update_big_kernel<T, D>), big_grid, 256, 0, st, xhat, chat, order, count,
-                start, flag, nflag + 1, sums, S, L, kk, N_idx);
+                start, flag, nflag + 1, sums, sums_skip, S, L, kk, N_idx);
   };
   for (int t = 0; t < iters && !small; ++t) {
     // Rounds 0 and 1 meet all new centroids; from round 2 on only the changed ones are compared.
-    launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, delta && t >= 2 ? changed : nullptr,
+    launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, bounds_skip, delta && t >= 2 ? changed : nullptr,
                         nchanged[(t + 1) & 1], nlisted[t & 1], nlisted[(t + 1) & 1], t, flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
     const bool last = t + 1 == iters;
     if (!delta || t == 0 || last) sort(delta ? nullptr : prev, t);
@@ -2034,7 +2046,7 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
         int pieces = 1;
         while (g.segs * pieces < 512 && kk / pieces >= 128) pieces *= 2;
         WAVE_LAUNCH("update", (update_moves_kernel<D>), g.segs * pieces, MOVE_NT, update_moves_lds(kk), st, xhat,
-                    chat, sums, assign, prev, changed, nchanged[t & 1], nchanged[(t + 1) & 1], range, order, count, start, t, S, L, kk, N_idx, pieces, kb);
+                    chat, sums, sums_skip, assign, prev, changed, nchanged[t & 1], nchanged[(t + 1) & 1], range, order, count, start, t, S, L, kk, N_idx, pieces, kb);
         continue;
       }
     }
@@ -2066,7 +2078,7 @@ static wave_status assign_step_td(const void* xhat, const void* chat, int L_s, i
   int32_t* flag = nflag + 64;
   hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, nflag);
   // one unit, one segment: S = 1, L = N_idx = L_s, kk = k_s
-  launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, nullptr, nullptr, nullptr, nullptr,
+  launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, nullptr, nullptr, 0, nullptr, nullptr,
                       centroids_resident(sizeof(T) == 2 ? WAVE_BF16 : WAVE_F32, D, k_s) ? nflag : nullptr, nflag + 1, 0, flag, nflag, 1, L_s, k_s, L_s, 1, 256, st);
   return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;
 }

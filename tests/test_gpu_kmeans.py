@@ -33,19 +33,20 @@ def _keys(kind, B, N, d, seed):
 # stay resident; plain keys: hundreds of points per workgroup need the full comparison, and of 20000
 # points in 33 clusters more move in a round than the update lists at once)
 @pytest.mark.parametrize("kind,d,N,L,k,iters", [
-    ("mixture", 128, 4102, 4097, 33, 7), ("plain", 128, 9000, 8192, 512, 8), ("mixture", 64, 4000, 2100, 1000, 5),
+    ("mixture", 128, 4102, 4097, 33, 7), ("plain", 128, 9000, 8192, 512, 8), ("mixture", 64, 4205, 4200, 1000, 5),
     ("ties", 128, 3000, 2100, 65, 5), ("plain", 64, 8197, 8192, 40, 6), ("plain", 128, 2205, 2200, 1, 4),
-    ("plain", 128, 20005, 20000, 33, 4), ("wide", 128, 4605, 2300, 200, 5), ("wide", 64, 2205, 2200, 1000, 4)])
+    ("plain", 128, 20005, 20000, 33, 4), ("wide", 128, 4605, 2300, 200, 5), ("wide", 64, 4405, 4400, 1000, 4)])
 def test_rounds_match_oracle(kind, d, N, L, k, iters):
-    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="rounds", B=1, Hq=1, Hkv=1, N=N, d=d, n_sink=2, n_local=3,
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="rounds", B=2, Hq=1, Hkv=1, N=N, d=d, n_sink=2, n_local=3,
                       segment_len=L, clusters_per_segment=k, iters=iters)
-    K = _keys(kind, 1, N, d, N + k).to(torch.bfloat16)
-    V = torch.randn(1, 1, N, d, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16)
+    K = _keys(kind, 2, N, d, N + k).to(torch.bfloat16)
+    V = torch.randn(2, 1, N, d, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16)
     ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
-    ix = wb.wave_index_build(K.cuda(), V.cuda(), wl.n_sink, wl.n_local, L, k, iters, 0)
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), wl.n_sink, wl.n_local, L, k, iters, 0, row_capacity=N + 9)
     torch.cuda.synchronize()
     for name in wb.BUFFER_NAMES:
         got = ix.t[name].cpu()
+        got = got[:, :, :N - 5] if name in ("perm", "k_perm", "v_perm") else got
         assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
 
 
