@@ -1452,8 +1452,8 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
 // Also leaves in changed[] and nchanged[] which centroids the next round's assign step compares.
 //
 // A workgroup owns the clusters [c_lo, c_hi) of a segment: it counts the arrivals and departures
-// of each (MOVE_CAP at once; more are taken in ranges of the points), lists them by cluster in
-// LDS, and one group of lanes per changed cluster works through its list.
+// of each (MOVE_CAP at once; more are taken in ranges of the points, the centroids after the last
+// one), lists them by cluster in LDS, and one group of lanes per changed cluster works through its list.
 // ============================================================================
 constexpr int MOVE_NT = 512, MOVE_CAP = 4096;
 
@@ -1583,8 +1583,21 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
         }
       }
       store_sums<EPC>(own, acc);
-      finish_centroid<bf16_t, D>(acc, chat + gc * D + sub * EPC);
+      if (span == si.L_s) finish_centroid<bf16_t, D>(acc, chat + gc * D + sub * EPC);
     }
+  }
+  if (span == si.L_s) return;
+  // Taken in ranges: a centroid comes from the round's last sum alone.  (A sum of some of the moves may
+  // not be one of any round, and where the last one is zero the centroid of the round before stays.)
+  __syncthreads();
+  for (int c = c_lo + tid / LPR; c < c_hi; c += GROUPS) {
+    const size_t gc = (size_t)sg * kk + c;
+    if (!changed[gc]) continue;
+    const double* own = sums + si.unit * sums_skip + gc * D + sub * EPC;
+    double acc[EPC];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) acc[e] = own[e];
+    finish_centroid<bf16_t, D>(acc, chat + gc * D + sub * EPC);
   }
 }
 

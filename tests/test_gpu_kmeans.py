@@ -50,6 +50,33 @@ def test_rounds_match_oracle(kind, d, N, L, k, iters):
         assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
 
 
+# A cluster that loses its last members in a round keeps the centroid it had, also when so many points
+# move that the update takes them in ranges of 2048 and the members leave in different ones.
+@pytest.mark.parametrize("d,scale,seed", [(64, 400.0, 3), (128, 2000.0, 2)])
+def test_cluster_emptied_across_ranges_keeps_its_centroid(d, scale, seed):
+    L, k, iters = 8192, 100, 6
+    x = torch.randn(L, d, generator=torch.Generator().manual_seed(seed))
+    x[:, 5] *= scale
+    x = x.to(torch.bfloat16)
+    trace = []
+    wo.kmeans_segment(x.double().numpy(), wo.init_indices(0, 0, 0, 0, L, k), iters, "bf16", trace)
+    split = 0
+    for (_, _, before), (_, _, after) in zip(trace[:-2], trace[1:-1]):   # (the last round has no update)
+        if (before != after).sum() > 2048:
+            for c in np.setdiff1d(before, after):
+                split += len(set(np.nonzero(before == c)[0] // 2048)) > 1
+    assert split > 0
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="emptied", B=1, Hq=1, Hkv=1, N=L, d=d, n_sink=0, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=iters)
+    K, V = x.view(1, 1, L, d), torch.randn(1, 1, L, d, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16)
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), 0, 0, L, k, iters, 0)
+    torch.cuda.synchronize()
+    for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
+        got = ix.t[name].cpu()
+        assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
+
+
 # (33 points: a fragment with one; k = 33, 129, 289: a tile with one centroid; equal centroids: the lowest wins)
 @pytest.mark.parametrize("d,L,k", [(128, 33, 33), (64, 4097, 129), (128, 1000, 289), (64, 1, 1), (64, 70, 31)])
 def test_assign_step_f32_tile_edges(d, L, k):
