@@ -1844,11 +1844,16 @@ static bool small_segments(const wave_index& ix) {
 // keep (bounds per point, member sums per cluster, a few counters per segment) lies in the index's
 // own k_perm and v_perm rows (of an update: the new ones), which only the last step writes: 8 bytes
 // per point in k_perm, then 6 counters per segment in the first unit's; 8 d bytes per cluster in
-// v_perm.  That fits with four points per cluster or more.
+// v_perm.  That fits with four points per cluster or more.  (With fewer every round is a full pass,
+// and centroids staged tile by tile are then the faster form, whether they fit in LDS or not: to copy
+// a segment's rows first costs more than it saves on its few points.  128 segments of 1024 points x 512
+// centroids: a build in 2.50 ms against 2.70; only many segments of 2000 points x 512 turn, 4224 of them
+// 17.5 against 16.7 ms.)
 static bool delta_rounds(const wave_index& ix) {
-  if (!centroids_resident(ix.dtype, ix.d, min_kL(ix)) || small_segments(ix)) return false;
+  if (!centroids_resident(ix.dtype, ix.d, min_kL(ix))) return false;
   const long long segs = (long long)ix.B * ix.Hkv * ix.S, points = ix.N_idx;
-  return 4ll * ix.S * min_kL(ix) <= points && 8 * points + 24 * segs + 16 <= 2ll * ix.d * points;
+  return 4ll * ix.S * min_kL(ix) <= points && 8 * points + 24 * segs + 16 <= 2ll * ix.d * points &&
+         segs * LIST_SPLIT * 256 < (1ll << 32);  // (a launch has fewer than 2^32 threads)
 }
 
 BuildGeom build_geometry(const wave_index& ix) {
@@ -1978,7 +1983,8 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   int32_t* count = reinterpret_cast<int32_t*>(w + g.off_count);
   int32_t* start = count + ncl;
   const int S = ix.S, L = ix.segment_len, N_idx = ix.N_idx;
-  const bool delta = delta_rounds(ix);
+  const bool small = small_segments(ix) && !no_small_kmeans();
+  const bool delta = !small && delta_rounds(ix);
   int32_t* changed = start + ncl;  // per cluster: a point entered or left it in the current round
   int32_t* prev = reinterpret_cast<int32_t*>(w + g.off_prev);  // every point's cluster of the round before
   // (see delta_rounds)
@@ -2016,9 +2022,7 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   const size_t sort_lds = ((size_t)W * kk + kk) * sizeof(int);
   const int kb = key_bits_for(kk);
   const int cl_grid = (ncl + GROUPS - 1) / GROUPS;
-  bool small = false;
   if constexpr (sizeof(T) == 2) {
-    small = small_segments(ix) && !no_small_kmeans();
     if (small)
       WAVE_LAUNCH("kmeans_small", (kmeans_small_kernel<D>), g.segs, 64 * SMALL_NW, small_kmeans_lds<D>(kk), st,
                   xhat, chat, order, count, start, S, L, kk, N_idx, iters, kb);

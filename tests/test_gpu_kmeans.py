@@ -88,3 +88,26 @@ def test_assign_step_f32_tile_edges(d, L, k):
     a = wb.wave_kmeans_assign_step(torch.from_numpy(xhat).float().cuda(), torch.from_numpy(chat).float().cuda())
     torch.cuda.synchronize()
     assert pu.check_assign(a.cpu().numpy(), xhat, chat, f"d={d} L={L} k={k}") == 0
+
+
+# Which rounds run.  Short segments whose one-workgroup kernel is switched off go the way of the long ones:
+# incremental rounds, or (fewer than four points per cluster, a ragged last segment counted as a whole one)
+# a full pass every round.
+@pytest.mark.parametrize("N,d,L,k,no_small,assign", [
+    (2125, 128, 1024, 64, "1", "assign_delta"), (700, 64, 300, 128, "1", "refine"), (2048, 128, 1024, 256, "", "assign_delta"),
+    (2125, 128, 1024, 256, "", "refine"), (2125, 128, 1024, 64, "", "kmeans_small")])
+def test_short_segments_and_few_points_per_cluster(N, d, L, k, no_small, assign, monkeypatch):
+    iters = 4
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="short", B=1, Hq=2, Hkv=2, N=N, d=d, n_sink=0, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=iters, n_components=64)
+    K, V = synth.make_kv(wl)
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    monkeypatch.setenv("WAVE_NO_SMALL_KMEANS", no_small)
+    wb.wave_profile_enable(True)
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), 0, 0, L, k, iters, 0)
+    launches = {name: n for name, (_, n) in wb.wave_profile_read().items()}
+    wb.wave_profile_enable(False)
+    for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
+        got = ix.t[name].cpu()
+        assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
+    assert {"assign_delta", "refine", "kmeans_small"} & set(launches) == {assign}, launches
