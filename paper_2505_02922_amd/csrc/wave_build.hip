@@ -1698,7 +1698,7 @@ __global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
           bi = oi;
         }
       }
-      if (lane == 0) a_s[point] = bi;
+      if (lane == 0 && bi < si.k_s) a_s[point] = bi;  // (nothing comparable: the fp32 decision stands)
     }
     __syncthreads();
     WAVE_PHASE(2);

@@ -111,3 +111,23 @@ def test_short_segments_and_few_points_per_cluster(N, d, L, k, no_small, assign,
         got = ix.t[name].cpu()
         assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
     assert {"assign_delta", "refine", "kmeans_small"} & set(launches) == {assign}, launches
+
+
+# Keys that are no numbers: every similarity of their segment is NaN, and no comparison decides.  The
+# partition is still one of all tokens, and the units beside them are what they are without.
+@pytest.mark.parametrize("dtype,L,k", [("bf16", 256, 16), ("bf16", 2100, 64), ("bf16", 300, 250), ("f32", 300, 40)])
+@pytest.mark.parametrize("bad", [float("nan"), -float("nan"), float("inf")])
+def test_keys_that_are_no_numbers(dtype, L, k, bad):
+    N = 4300
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="nan", dtype=dtype, B=1, Hq=2, Hkv=2, N=N, n_sink=0, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=4, n_components=64)
+    K, V = synth.make_kv(wl)
+    K[0, 0, 10, 3] = K[0, 0, N - 1] = bad
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), 0, 0, L, k, wl.iters, 0)
+    torch.cuda.synchronize()
+    sizes, offsets, perm = (ix.t[name][0].cpu() for name in ("sizes", "offsets", "perm"))
+    assert (perm.sort(-1).values == torch.arange(N)).all() and (sizes >= 0).all()
+    assert (offsets[:, 0] == 0).all() and torch.equal(offsets.diff(dim=-1), sizes) and (offsets[:, -1] == N).all()
+    ref = pu.oracle_build(wl, K, V, units=[(0, 1)])[(0, 1)]
+    for name in ("centroids", "vsum", "sizes", "perm"):
+        assert np.array_equal(ix.t[name][0, 1].double().cpu().numpy(), getattr(ref, name)), name
