@@ -172,6 +172,27 @@ def segment_study() -> int:
 # ---------------------------------------------------------------------------------------------
 # Phases of the benchmark of one workload
 # ---------------------------------------------------------------------------------------------
+def assign_figures(wl, n_idx, prof):
+    """What the assign launches of one profiled build did.  `prof`: {kernel: (ms, launches)}.  The
+    flops and rates are those of the full passes, which compare every point with every centroid of
+    its segment; most rounds of a bf16 build compare the changed centroids only (assign_delta) and
+    have no flop count that does not depend on the data.  The share is all the assign steps'."""
+    full, tail = divmod(n_idx, wl.segment_len)
+    kk = min(wl.clusters_per_segment, wl.segment_len)
+    pass_flops = 2.0 * wl.d * wl.B * wl.Hkv * (full * wl.segment_len * kk + tail * min(kk, tail))
+    ms, passes = prof.get("assign_mfma" if wl.dtype == "bf16" else "assign_f32", (0.0, 0))
+    info = {"assign_full_passes": passes, "assign_flops": pass_flops * passes, "assign_ms_per_launch": None,
+            "assign_tflops": None, "assign_frac_of_bf16_peak": None, "assign_share_of_build": None}
+    if passes > 0 and ms > 0:
+        rate = pass_flops * passes / ms / 1e9
+        info["assign_ms_per_launch"] = round(ms / passes, 4)
+        info["assign_tflops"] = round(rate, 2)
+        info["assign_frac_of_bf16_peak"] = round(rate / MFMA_BF16_PEAK_TFLOPS, 4)
+        steps = sum(v[0] for k, v in prof.items() if k.startswith("assign_") or k == "refine")
+        info["assign_share_of_build"] = round(steps / sum(v[0] for v in prof.values()), 3)
+    return info
+
+
 def build_phase(wb, wl, K, V, dev, timed: bool):
     """Builds the index (once untimed; then 3 timed repeats and one profiled call when `timed`)."""
     import torch
@@ -194,22 +215,8 @@ def build_phase(wb, wl, K, V, dev, timed: bool):
     build()
     prof = wb.wave_profile_read()
     wb.wave_profile_enable(False)
-    plan_full = ix.N_idx // wl.segment_len
-    tail = ix.N_idx - plan_full * wl.segment_len
-    kk = min(wl.clusters_per_segment, wl.segment_len)
-    assign_flops = 2.0 * wl.d * wl.iters * wl.B * wl.Hkv * (
-        plan_full * wl.segment_len * kk + tail * min(kk, tail))
-    assign_name = "assign_mfma" if wl.dtype == "bf16" else "assign_plain"
-    assign_ms, assign_n = prof.get(assign_name, (0.0, 0))
-    info = {"ms": round(_median(build_ms), 3), "assign_flops": assign_flops,
-            "assign_ms_per_launch": None, "assign_tflops": None, "assign_frac_of_bf16_peak": None,
-            "assign_share_of_build": None,
+    info = {"ms": round(_median(build_ms), 3), **assign_figures(wl, ix.N_idx, prof),
             "kernels_ms": {k: round(v[0], 3) for k, v in sorted(prof.items())}}
-    if assign_n > 0 and assign_ms > 0:
-        info["assign_ms_per_launch"] = round(assign_ms / assign_n, 4)
-        info["assign_tflops"] = round(assign_flops / assign_ms / 1e9, 2)
-        info["assign_frac_of_bf16_peak"] = round(assign_flops / assign_ms / 1e9 / MFMA_BF16_PEAK_TFLOPS, 4)
-        info["assign_share_of_build"] = round(assign_ms / sum(v[0] for v in prof.values()), 3)
     del bws
     torch.cuda.empty_cache()
     return ix, info

@@ -297,6 +297,26 @@ def test_workload_retrieve_count_matches_the_oracle():
             assert wl.retrieve_count(m) == want
 
 
+def test_bench_rates_the_assign_passes_that_ran():
+    """The benchmark's assign rate counts the launches that compare every point with every centroid
+    (two of an incremental build's rounds), whatever the number of rounds, in bf16 and in fp32."""
+    import bench
+    from paper_2505_02922_amd import synth
+    wl = synth.scaled(synth.WORKLOADS["qwen7b_64k_b64"], B=2, Hkv=3, Hq=3, N=20000)
+    n_idx = 2 * 8192 + 100
+    flops = 2.0 * 128 * 6 * (2 * 8192 * 512 + 100 * 100)
+    prof = {"assign_mfma": (2 * flops / 1e12, 2), "assign_delta": (3.0, 36), "assign_listed": (1.0, 20), "finalize": (4.0, 1)}
+    got = bench.assign_figures(wl, n_idx, prof)
+    assert got["assign_full_passes"] == 2 and got["assign_flops"] == 2 * flops
+    assert got["assign_tflops"] == 1000.0 and got["assign_frac_of_bf16_peak"] == 0.4
+    assign = 2 * flops / 1e12 + 4.0
+    assert got["assign_share_of_build"] == round(assign / (assign + 4.0), 3)
+    f32 = bench.assign_figures(synth.scaled(wl, dtype="f32"), n_idx, {"assign_f32": (10 * flops / 1e11, 10), "refine": (1.0, 10)})
+    assert f32["assign_full_passes"] == 10 and f32["assign_tflops"] == 100.0
+    short = bench.assign_figures(wl, n_idx, {"kmeans_small": (1.0, 1)})   # no such launch: no figure
+    assert short["assign_full_passes"] == 0 and short["assign_tflops"] is None
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
