@@ -613,6 +613,7 @@ struct PointState {
 
 // A point that changed its cluster in round t carries (t, the cluster it left) in prev[].
 constexpr int PREV_CLUSTER_BITS = 11;  // (at most 1024 centroids are resident)
+constexpr int PREV_ROUNDS = 1 << (31 - PREV_CLUSTER_BITS);  // rounds that fit beside them in an int
 
 // The round's outcome for a point that was in cluster `before`.  bounds: null when no later round
 // needs it (nor prev, nor `before`).
@@ -1984,7 +1985,7 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   int32_t* start = count + ncl;
   const int S = ix.S, L = ix.segment_len, N_idx = ix.N_idx;
   const bool small = small_segments(ix) && !no_small_kmeans();
-  const bool delta = !small && delta_rounds(ix);
+  const bool delta = !small && iters <= PREV_ROUNDS && delta_rounds(ix);
   int32_t* changed = start + ncl;  // per cluster: a point entered or left it in the current round
   int32_t* prev = reinterpret_cast<int32_t*>(w + g.off_prev);  // every point's cluster of the round before
   // (see delta_rounds)
