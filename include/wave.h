@@ -146,7 +146,9 @@ wave_status wave_index_plan(wave_index *ix, size_t bytes[WAVE_INDEX_BUFFERS],
  * and offsets may be old_ix's when both indexes have the same cluster_capacity
  * >= the new m: the new clusters are then written behind the old ones in place
  * (an update of 1K tokens then writes its 64 clusters and 1K rows per unit and
- * copies nothing that was indexed before); likewise k_steady and
+ * copies nothing that was indexed before; the new k_perm and v_perm rows are
+ * working memory until the stream work completes, as in wave_index_build, the
+ * old ones stay readable throughout); likewise k_steady and
  * v_steady may be old_ix's when no segment is flushed and both indexes have
  * the same steady_capacity >= the new p: only the new tokens' rows are then
  * written, behind the old window); workspace DEVICE, 256-byte aligned.  The
@@ -176,10 +178,17 @@ wave_status wave_index_append(const wave_index *old_ix, const void *K_new, const
  * accumulate in fp64 and are rounded once (to nearest even) to dtype.
  *   K, V       DEVICE [B,Hkv,N,d] dtype, read only, may be released after the
  *              stream work completes
- *   ix         dimensions + planned fields + the nine DEVICE buffers (written)
+ *   ix         dimensions + planned fields + the nine DEVICE buffers (written).
+ *              The k_perm and v_perm rows are working memory of the k-means
+ *              until the stream work completes: from the start of the call
+ *              they hold nothing that another stream could read, and they must
+ *              not overlap K or V
  *   workspace  DEVICE, 256-byte aligned, >= build_workspace_bytes
- * From the second round on, only clusters that a point entered or left are
- * summed again (the others keep their centroid bit for bit).  bf16 segments of
+ * From the second round on, only clusters that a point entered or left get a
+ * new centroid (the others keep theirs bit for bit); where the sums stay exact
+ * in fp64 in any order, which is tested per segment, the points that moved are
+ * taken out of one member sum and added to another, elsewhere the members are
+ * summed again.  bf16 segments of
  * at most 2048 tokens and 128 clusters are clustered by one workgroup each that
  * runs all rounds; WAVE_NO_SMALL_KMEANS=1 in the environment keeps them on the
  * kernels of the long segments (same result, one launch per step). */

@@ -7,11 +7,17 @@
 //   mean        fp64 mean of the segment's keys
 //   normalise   xhat = quant((K - mean) / |K - mean|)             (fp64, one rounding)
 //   init        k seeded distinct points of the segment become the first centroids
-//   T times:    assign  (bf16 MFMA similarities, fp32 accumulate; running best and
-//                        second best per point; near-ties flagged)
-//               refine  (flagged points re-decided with fp64 similarities)
-//               sort    (stable counting sort of the segment's points by cluster)
+//   T times:    assign  (MFMA similarities, fp32 accumulate; running best and
+//                        second best per point; near-ties re-decided with fp64
+//                        similarities)
 //               update  (centroid = quant(member sum / |member sum|), fp64)
+//   sort        stable counting sort of the segment's points by cluster, after the
+//               last round and wherever an update reads members by cluster
+// Three forms of the T rounds, same results: bf16 segments of a few clusters in one
+// workgroup each (kmeans_small_kernel); bf16 with a segment's centroids in LDS and four
+// points per cluster or more: later rounds compare changed centroids and sum moved
+// points (assign_delta_kernel, update_moves_kernel); else assign, refine, sort and update
+// of the touched clusters, a launch each.
 //   finalize    sizes, offsets, mean of raw keys, value sums, permuted K/V rows
 #include <stdlib.h>
 
@@ -1446,8 +1452,9 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
 // members bit for bit, whatever the order, when no addition rounds; that is certain when
 // every sum of a subset of the segment's points is representable, the condition above with
 // the exponent range of the whole segment (gathered by normalise_kernel) and n = L_s.  A segment
-// that fails it (a component below 2^-31 of the largest; keys spread over 2^20 .. 2^26 in
-// practice) is sorted and its changed clusters are summed again by the first workgroup.
+// that fails it (nonzero components further apart than 2^(45 - ceil(log2 L_s)), 2^32 at 8192 points;
+// the benchmark's keys spread over 2^19 .. 2^28) is sorted and its changed clusters are summed again
+// by the first workgroup.
 // No sort and no pass over the members: a round costs the scan of the marks in prev[], 2 KiB per
 // changed cluster and 512 B per moved point.
 // Also leaves in changed[] and nchanged[] which centroids the next round's assign step compares.
