@@ -21,6 +21,8 @@
 //   finalize    sizes, offsets, mean of raw keys, value sums, permuted K/V rows
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "wave_common.h"
 
 namespace wave {
@@ -154,7 +156,9 @@ struct MantissaBits<float> {
 // Centre, normalise, round to the storage type.  A workgroup takes NORM_ROWS rows of one
 // segment and keeps the mean in registers.  (HBM-bound.  With rows of any segment in a
 // workgroup every lane read its 64 bytes of the fp64 mean again for each 16 bytes of key:
-// 2.06 ms for 16 sequences x 120K tokens, 1.78 ms so, 4.5 TB/s.)
+// 2.06 ms for 16 sequences x 120K tokens, 1.78 ms so, 4.5 TB/s.)  Four rows of a group in flight where
+// that many are left, else one by one: four with repeats of the last one took 485 us for 65536
+// segments of 16 rows, 172 us so.
 // ============================================================================
 constexpr int NORM_ROWS = 128;
 
@@ -182,12 +186,13 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
   for (int e = 0; e < EPC; ++e) mu[e] = mean[(size_t)sg * D + sub * EPC + e];
   const T* Ku = K + ((size_t)si.unit * N + n_sink + si.seg_start) * D + sub * EPC;
   T* Xu = xhat + ((size_t)si.unit * N_idx + si.seg_start) * D + sub * EPC;
-  for (int r0 = lo + grp; r0 < hi; r0 += U * GROUPS) {
-    uint4 raw[U];
+  auto rows = [&](auto batch, int r0) {  // rows r0, r0 + GROUPS, ... below hi, in flight together
+    constexpr int N = decltype(batch)::value;
+    uint4 raw[N];
 #pragma unroll
-    for (int u = 0; u < U; ++u) raw[u] = load16(Ku + (size_t)min(r0 + u * GROUPS, hi - 1) * D);
+    for (int u = 0; u < N; ++u) raw[u] = load16(Ku + (size_t)(r0 + u * GROUPS) * D);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < N; ++u) {
       float f[EPC];
       unpack<T>(raw[u], f);
       double x[EPC], n2 = 0.0;
@@ -203,7 +208,7 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
       T o[EPC];
 #pragma unroll
       for (int e = 0; e < EPC; ++e) o[e] = quant_store<T>(div_shared(x[e], dv, rdv));
-      if (r0 + u * GROUPS < hi) store16(Xu + (size_t)(r0 + u * GROUPS) * D, *reinterpret_cast<uint4*>(o));
+      store16(Xu + (size_t)(r0 + u * GROUPS) * D, *reinterpret_cast<uint4*>(o));
       if (range) {
         const u16x2* w = reinterpret_cast<const u16x2*>(o);
 #pragma unroll
@@ -214,7 +219,10 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
         }
       }
     }
-  }
+  };
+  int r0 = lo;
+  for (; r0 + U * GROUPS <= hi; r0 += U * GROUPS) rows(std::integral_constant<int, U>{}, r0 + grp);
+  for (r0 += grp; r0 < hi; r0 += GROUPS) rows(std::integral_constant<int, 1>{}, r0);
   if (range) {
     int emax = max(most.x, most.y) >> 7, emin = min(least.x, least.y);
     emin = emin == 0xffff ? 255 : max(1, (emin + 1) >> 7);

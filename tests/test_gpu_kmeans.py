@@ -131,3 +131,20 @@ def test_keys_that_are_no_numbers(dtype, L, k, bad):
     ref = pu.oracle_build(wl, K, V, units=[(0, 1)])[(0, 1)]
     for name in ("centroids", "vsum", "sizes", "perm"):
         assert np.array_equal(ix.t[name][0, 1].double().cpu().numpy(), getattr(ref, name)), name
+
+
+# Segments around the rows that the normalise step takes at once (64 of bf16 at d = 128, 32 of f32) and that a
+# workgroup takes (128): whole batches, rows one by one behind them, none of either.
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("L", [1, 15, 16, 33, 64, 127, 129, 191, 257])
+def test_segments_around_the_normalise_batches(dtype, d, L):
+    N, k = 5 * L + 3, 4
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="rows", dtype=dtype, B=1, Hq=2, Hkv=2, N=N, d=d, n_sink=1, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=3, n_components=8)
+    K, V = synth.make_kv(wl)
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), 1, 0, L, k, wl.iters, 0)
+    torch.cuda.synchronize()
+    for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
+        got = ix.t[name].cpu()
+        assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
