@@ -172,7 +172,7 @@ wave_status wave_index_append(const wave_index *old_ix, const void *K_new, const
  * centroid; the partition is the one of the last assign); then per cluster its
  * size, the mean of its raw keys, the sum of its values, and the key/value rows
  * permuted so that clusters are contiguous.  Similarities are bf16 MFMA
- * products accumulated in fp32 (fp32 FMA for f32 data); any point whose two
+ * products accumulated in fp32 (fp32 MFMA for f32 data); any point whose two
  * best similarities are closer than the accumulation error bound is re-decided
  * in fp64; centring, normalisation, centroid updates, means and value sums
  * accumulate in fp64 and are rounded once (to nearest even) to dtype.
