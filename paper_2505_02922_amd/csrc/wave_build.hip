@@ -663,8 +663,11 @@ template <int D, int NF, int NW>
 __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
     int32_t* __restrict__ prev, PointBounds* bounds, long long bounds_skip, int32_t* __restrict__ listed,
-    int32_t* __restrict__ nlisted, int round, int S, int L, int kk, int N_idx, int pieces_per_seg) {
-  // 32 * ceil(k_s / 32) padded rows, then the near-ties
+    int32_t* __restrict__ nlisted, int32_t* __restrict__ nflag, int round, int S, int L, int kk, int N_idx,
+    int pieces_per_seg) {
+  // Near-ties go to a list per segment in `listed`, for assign_listed_kernel, or (nlisted null) to one for
+  // all segments, counted by nflag, for refine_kernel (which may leave the fp32 decision).
+  // LDS: 32 * ceil(k_s / 32) padded rows, then the workgroup's near-ties
   extern __shared__ __attribute__((aligned(16))) char cent[];
   __shared__ int nleft;
 
@@ -688,13 +691,15 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
   };
   resident_assign_fragments<D, NF, NW>(X, cent, si.L_s, si.k_s, f_lo, f_hi, [](int) { return NoState{}; },
                                        [&](int point, int cluster, int best, int second, NoState) {
-                                         if (key_gap(best, second) < kAssignGuard)
-                                           left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
-                                         else
-                                           settle(point, cluster, best, second);
+                                         const bool near = key_gap(best, second) < kAssignGuard;
+                                         if (near) left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
+                                         if (!near || !nlisted) settle(point, cluster, best, second);
                                        });
   __syncthreads();
-  publish_list(left, nleft, 32 * f_lo, listed + gp0, &nlisted[sg]);
+  if (nlisted)
+    publish_list(left, nleft, 32 * f_lo, listed + gp0, &nlisted[sg]);
+  else
+    publish_list(left, nleft, (int)gp0 + 32 * f_lo, listed, nflag);
 }
 
 // ============================================================================
@@ -1850,6 +1855,17 @@ static bool centroids_resident(int dtype, int d, int kmax) {
   return dtype == WAVE_BF16 && (size_t)32 * ((kmax + 31) / 32) * (d * 2 + 16) <= 144 * 1024;
 }
 
+// Builds whose rounds are all full passes (fewer than four points per cluster) keep the centroids in LDS
+// only for many segments of many points at d = 128; elsewhere the centroids staged tile by tile are
+// the faster form, whether they fit or not: to copy a segment's rows first costs more than it saves
+// on its few points, and one workgroup per CU leaves a last round of them.  Builds in ms, staged
+// and resident: 528 segments of 2000 points x 512 centroids 2.46 and 2.70, 2112 of them 8.86 and 8.60,
+// 4224 of them 17.3 and 16.5; 4096 of 1024 x 512 18.6 and 18.7, of 512 x 256 14.0 and 15.8; at d = 64
+// 4224 of 2000 x 512 10.7 and 11.2.
+static bool resident_full_passes(int dtype, int d, int kmax, int Lmax, int segs) {
+  return centroids_resident(dtype, d, kmax) && d == 128 && Lmax >= 1536 && segs >= 2048;
+}
+
 // Segments that one workgroup clusters by itself (kmeans_small_kernel).
 static bool small_segments(const wave_index& ix) {
   return ix.dtype == WAVE_BF16 && (ix.segment_len < ix.N_idx ? ix.segment_len : ix.N_idx) <= SMALL_L_MAX &&
@@ -1860,11 +1876,7 @@ static bool small_segments(const wave_index& ix) {
 // keep (bounds per point, member sums per cluster, a few counters per segment) lies in the index's
 // own k_perm and v_perm rows (of an update: the new ones), which only the last step writes: 8 bytes
 // per point in k_perm, then 6 counters per segment in the first unit's; 8 d bytes per cluster in
-// v_perm.  That fits with four points per cluster or more.  (With fewer every round is a full pass,
-// and centroids staged tile by tile are then the faster form, whether they fit in LDS or not: to copy
-// a segment's rows first costs more than it saves on its few points.  128 segments of 1024 points x 512
-// centroids: a build in 2.50 ms against 2.70; only many segments of 2000 points x 512 turn, 4224 of them
-// 17.5 against 16.7 ms.)
+// v_perm.  That fits with four points per cluster or more.
 static bool delta_rounds(const wave_index& ix) {
   if (!centroids_resident(ix.dtype, ix.d, min_kL(ix))) return false;
   const long long segs = (long long)ix.B * ix.Hkv * ix.S, points = ix.N_idx;
@@ -1913,14 +1925,14 @@ static int key_bits_for(int kk) {
 // One assign step.  bounds, changed: null in a round that compares every point with every
 // centroid; with `bounds` alone such a round leaves what the next one needs to compare with the
 // changed centroids only, and in prev which points moved.  nlisted: points listed per segment (all
-// zero), or null: the centroids of a segment do not stay in LDS; nlisted_next is cleared.
+// zero; nlisted_next is cleared), or null: near-ties of all segments go to one list, for refine_kernel.
 template <typename T, int D>
 static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t* prev, PointBounds* bounds,
                           long long bounds_skip, const int32_t* changed, const int32_t* nchanged, int32_t* nlisted, int32_t* nlisted_next, int round, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
                           int segs, int refine_wgs, hipStream_t st) {
   const int Lmax = L < N_idx ? L : N_idx, kmax = kk < Lmax ? kk : Lmax;
   if constexpr (sizeof(T) == 2) {
-    if (nlisted) {
+    if (nlisted || resident_full_passes(WAVE_BF16, D, kmax, Lmax, segs)) {
       // At least two workgroups per long segment keep the last round of workgroups short; a few
       // segments are cut finer, down to a fragment per wave, until every CU has its share (32 segments
       // of 8192 points x 512 centroids: 104 us a full pass with 2 each, 37 us so).
@@ -1945,16 +1957,18 @@ static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t
                     nchanged, flag, nlisted, 0, light, round, S, L, kk, N_idx, light_pieces, segs * light_pieces);
       } else
         WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16>), segs * pieces, 1024, resident_lds<D>(kmax),
-                    st, xhat, chat, assign, prev, bounds, bounds_skip, flag, nlisted, round, S, L, kk, N_idx, pieces);
-      WAVE_LAUNCH("assign_listed", (assign_listed_kernel<D>), segs * LIST_SPLIT, 256, listed_lds<D>(kmax), st, xhat,
-                  chat, assign, prev, bounds, bounds_skip, flag, nlisted, nlisted_next, round, segs, S, L, kk, N_idx);
-      return;
+                    st, xhat, chat, assign, prev, bounds, bounds_skip, flag, nlisted, nflag, round, S, L, kk, N_idx, pieces);
+      if (nlisted) {
+        WAVE_LAUNCH("assign_listed", (assign_listed_kernel<D>), segs * LIST_SPLIT, 256, listed_lds<D>(kmax), st, xhat,
+                    chat, assign, prev, bounds, bounds_skip, flag, nlisted, nlisted_next, round, segs, S, L, kk, N_idx);
+        return;
+      }
+    } else {  // the centroids are staged through LDS tile by tile
+      constexpr int PWG = 8 * 32;
+      const int wps = (Lmax + PWG - 1) / PWG;
+      WAVE_LAUNCH("assign_mfma", (assign_mfma_kernel<D, 1, 8>), segs * wps, 64 * 8, 0, st, xhat, chat,
+                  assign, flag, nflag, S, L, kk, N_idx, wps);
     }
-    // the centroids are staged through LDS tile by tile
-    constexpr int PWG = 8 * 32;
-    const int wps = (Lmax + PWG - 1) / PWG;
-    WAVE_LAUNCH("assign_mfma", (assign_mfma_kernel<D, 1, 8>), segs * wps, 64 * 8, 0, st, xhat, chat,
-                assign, flag, nflag, S, L, kk, N_idx, wps);
   } else {
     const int frags = (Lmax + 31) / 32;
     WAVE_LAUNCH("assign_f32", (assign_f32_kernel<D>), segs * frags, 64, 0, st, xhat, chat, assign, flag, nflag, S, L,

@@ -148,3 +148,23 @@ def test_segments_around_the_normalise_batches(dtype, d, L):
     for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
         got = ix.t[name].cpu()
         assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
+
+
+# Full passes with the centroids in LDS and one list of near-ties for all segments: 2048 segments of 1537 points
+# (a fragment with one point) with 31 * 13 clusters; three units against the oracle.  (refine, not
+# assign_listed, takes the near-ties.)
+def test_full_passes_of_many_segments_keep_their_centroids_in_lds():
+    B, Hkv, L, k, iters, N = 64, 8, 1537, 403, 3, 4 * 1537
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="many", B=B, Hq=Hkv, Hkv=Hkv, N=N, n_sink=0, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=iters)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K, V = (torch.randn(B, Hkv, N, 128, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    wb.wave_profile_enable(True)
+    ix = wb.wave_index_build(K, V, 0, 0, L, k, iters, 0)
+    launches = {name: n for name, (_, n) in wb.wave_profile_read().items()}
+    wb.wave_profile_enable(False)
+    assert launches["refine"] == launches["assign_mfma"] == iters and "assign_listed" not in launches
+    units = [(0, 0), (31, 5), (B - 1, Hkv - 1)]
+    for (b, h), ref in pu.oracle_build(wl, K, V, units=units).items():
+        for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
+            assert np.array_equal(ix.t[name][b, h].double().cpu().numpy(), getattr(ref, name)), (b, h, name)
