@@ -156,7 +156,7 @@ struct MantissaBits<float> {
 // Centre, normalise, round to the storage type.  A workgroup takes NORM_ROWS rows of one
 // segment and keeps the mean in registers.  (HBM-bound.  With rows of any segment in a
 // workgroup every lane read its 64 bytes of the fp64 mean again for each 16 bytes of key:
-// 2.06 ms for 16 sequences x 120K tokens, 1.78 ms so, 4.5 TB/s.)  Four rows of a group in flight where
+// 2.16 ms for 16 sequences x 120K tokens, 1.95 ms so, 4.1 TB/s.)  Four rows of a group in flight where
 // that many are left, else one by one: four with repeats of the last one took 485 us for 65536
 // segments of 16 rows, 172 us so.
 // ============================================================================
@@ -715,7 +715,7 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
 // that the full comparison gives.
 // The share of changed centroids falls from 82 % in the third round to 3 % in the tenth on
 // 8192-token segments of 512 clusters, and 1 % of the points need every centroid: a round costs
-// between a full pass and reading xhat once (16 sequences x 120K tokens: 1.85 ms full, 0.8 ms
+// between a full pass and reading xhat once (16 sequences x 120K tokens: 1.9 ms full, 0.8 ms
 // at the streaming rate).
 //
 // A workgroup lists the changed centroids of a segment, copies their rows into LDS and streams
