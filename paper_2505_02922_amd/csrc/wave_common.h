@@ -132,14 +132,50 @@ __device__ __forceinline__ double group_sum_f64(double x) {
   return x;
 }
 
+// Over the 64 lanes with DPP: the steps inside a row of 16 lanes, then the last lane of a row into the
+// next row and lane 31 into the upper half.  (A __shfl is an LDS access whose result takes about 100
+// cycles; a chain of six of them is longer than the work between two barriers of the selection.)
+constexpr int DPP_ROW_SHR = 0x110;       // + n: lanes take the value n lanes below, inside a row
+constexpr int DPP_ROW_BCAST15 = 0x142;   // lane 15 of a row into the next row
+constexpr int DPP_ROW_BCAST31 = 0x143;   // lane 31 into the upper two rows
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp_or(int otherwise, int x) {  // lanes without a source: `otherwise`
+  return __builtin_amdgcn_update_dpp(otherwise, x, CTRL, ROWS, 0xF, false);
+}
+// f(accumulated so far, value from below) for every lane; lane 63 has seen all of them
+template <typename F>
+__device__ __forceinline__ int wave_scan(int x, int neutral, F&& f) {
+  x = f(x, dpp_or<DPP_ROW_SHR + 1>(neutral, x));
+  x = f(x, dpp_or<DPP_ROW_SHR + 2>(neutral, x));
+  x = f(x, dpp_or<DPP_ROW_SHR + 4>(neutral, x));
+  x = f(x, dpp_or<DPP_ROW_SHR + 8>(neutral, x));
+  x = f(x, dpp_or<DPP_ROW_BCAST15, 0xA>(neutral, x));
+  x = f(x, dpp_or<DPP_ROW_BCAST31, 0xC>(neutral, x));
+  return x;
+}
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  return wave_scan(x, 0, [](int a, int b) { return a + b; });
+}
 __device__ __forceinline__ float wave_max(float x) {
-  for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-  return x;
+  const int neg_inf = (int)0xff800000u;
+  return __int_as_float(__builtin_amdgcn_readlane(
+      wave_scan(__float_as_int(x), neg_inf,
+                [](int a, int b) { return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b))); }), 63));
 }
-__device__ __forceinline__ int wave_sum_i(int x) {
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-  return x;
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readlane(
+      wave_scan((int)x, 0, [](int a, int b) { return (int)max((uint32_t)a, (uint32_t)b); }), 63);
 }
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readlane(
+      wave_scan((int)x, -1, [](int a, int b) { return (int)min((uint32_t)a, (uint32_t)b); }), 63);
+}
+__device__ __forceinline__ float wave_add_f(float x) {  // (another order than wave_sum_f)
+  return __int_as_float(__builtin_amdgcn_readlane(
+      wave_scan(__float_as_int(x), 0,
+                [](int a, int b) { return __float_as_int(__int_as_float(a) + __int_as_float(b)); }), 63));
+}
+__device__ __forceinline__ int wave_sum_i(int x) { return __builtin_amdgcn_readlane(wave_incl_scan(x), 63); }
 __device__ __forceinline__ float wave_sum_f(float x) {
   for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
   return x;
@@ -192,6 +228,7 @@ struct DecodeGeom {
   int mwords;                      // 32-bit words of the selection bitmap per query head
   int rcap;                        // entries of the selected-id list per query head
   int fused;                       // selection and retrieval fused into one workgroup per head
+  int solo;                        // few heads: selection, retrieval and merge in one workgroup per head
   int neg_in_gather, neg_slots;    // selected clusters' estimation terms: taken out by the retrieval kernel / a partial of their own
   int sliced, nslices, slice_len;  // selection cut into slices ranked by workgroups of their own
   int est_with_slices_pct;         // sliced path: share of the estimation work in the slices' launch

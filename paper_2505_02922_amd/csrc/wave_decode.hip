@@ -451,12 +451,7 @@ __device__ __forceinline__ float key_to_float(uint32_t k) {
 template <int NT>
 __device__ __forceinline__ int block_excl_scan(int v, int* scratch, int& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int t = __shfl_up(inc, off);
-    if (lane >= off) inc += t;
-  }
+  const int inc = wave_incl_scan(v);
   __syncthreads();  // scratch may still be read from a previous call
   if (lane == 63) scratch[wave] = inc;
   __syncthreads();
@@ -476,16 +471,11 @@ __device__ __forceinline__ int block_excl_scan(int v, int* scratch, int& total) 
 // the lanes.  Returns the lane's first position.  All 64 lanes call this.
 __device__ __forceinline__ int wave_excl_scan_alloc(int n, int* counter) {
   const int lane = threadIdx.x & 63;
-  int inc = n;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int t = __shfl_up(inc, off);
-    if (lane >= off) inc += t;
-  }
-  const int total = __shfl(inc, 63);
+  const int inc = wave_incl_scan(n);
+  const int total = __builtin_amdgcn_readlane(inc, 63);
   int base = 0;
   if (lane == 0 && total > 0) base = atomicAdd(counter, total);
-  base = __shfl(base, 0);
+  base = __builtin_amdgcn_readfirstlane(base);
   return base + inc - n;
 }
 
@@ -1037,10 +1027,8 @@ __device__ __forceinline__ int select_core(
     kmax = max(kmax, ky);
     kmin = min(kmin, ky > kKeyNegInf ? ky : 0xffffffffu);
   });
-  for (int o = 32; o >= 1; o >>= 1) {
-    kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
-    kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
-  }
+  kmax = wave_max_u(kmax);
+  kmin = wave_min_u(kmin);
   if (lane == 0) {
     scan_scratch[wave] = nv;
     tbl_cnt[wave] = (int)kmax;       // tbl_cnt doubles as scratch for the two extrema
@@ -1653,6 +1641,18 @@ __device__ __forceinline__ void merge_groups_and_store(AttnState<T, D, NG>& st, 
 // ============================================================================
 // 4. Merge: one normalisation over the partial results of the three zones.
 // ============================================================================
+// One component of a head's output and (where lse is given) its log-sum-exp.
+// Z > 0 for every index whose stored centroids are the means of their stored rows (the
+// estimation bound: a selected cluster's term never exceeds its rows' exact terms).  An
+// index that breaks this can cancel the normaliser away: that is reported as NaN, not
+// as a silent zero.
+__device__ __forceinline__ void store_normalised(float A, float M, float Z, float* __restrict__ out,
+                                                 float* __restrict__ lse) {
+  const float bad = __uint_as_float(0x7fc00000u);
+  *out = Z > 0.f ? A / Z : bad;
+  if (lse) *lse = Z > 0.f ? (M + log2f(Z)) * kLn2 : bad;
+}
+
 // All NT threads of the workgroup must call this (it contains barriers).  Thread
 // t owns output dimension t % D and every (NT / D)-th partial result, which it
 // folds into a running (max, sum, acc) of its own, UB partials per trip to memory
@@ -1713,13 +1713,7 @@ __device__ __forceinline__ void merge_head(const float* __restrict__ p, int n1,
       Zt = fmaf(s_z[g], w, Zt);
       At = fmaf(s_a[g * D + e], w, At);
     }
-    // Zt > 0 for every index whose stored centroids are the means of their stored rows (the
-    // estimation bound: a selected cluster's term never exceeds its rows' exact terms).  An
-    // index that breaks this can cancel the normaliser away: that is reported as NaN, not
-    // as a silent zero.
-    const float bad = __uint_as_float(0x7fc00000u);
-    out_head[e] = Zt > 0.f ? At / Zt : bad;
-    if (e == 0) *lse_head = Zt > 0.f ? (Mx + log2f(Zt)) * kLn2 : bad;
+    store_normalised(At, Mx, Zt, out_head + e, e == 0 ? lse_head : nullptr);
   }
 }
 
@@ -2093,6 +2087,438 @@ __global__ __launch_bounds__(NT) void select_gather_kernel(
   WAVE_STAMP(bitmap + (size_t)bh * mwords, 21);
 }
 
+// ----------------------------------------------------------------------------
+// The selection as a chain of few steps, for a workgroup whose threads hold the keys of their
+// positions (thread tid: k * NT + tid) in registers.
+//   1. extrema and number of the valid keys;
+//   2. P pivots at once halve the value interval log2(P + 1) times per barrier, until at most
+//      LEAN_SURV keys are left between the bounds;
+//   3. one wave ranks these, and finds the scores inside the guard band; where more of them than
+//      needed lie in it, their fp64 scores decide (as in select_core);
+//   4. ids and scores in ascending id order to s_ids / s_z.
+// Returns the number of selected clusters, or -1 where the general form has to rank the head (nothing
+// is written then): infinite or no numbers among the scores, more than a wave's worth of equal ones.  The selected set is select_core's.  All NT threads call this; a barrier ends it.
+// ----------------------------------------------------------------------------
+constexpr int LEAN_SURV = 32;
+
+template <int NT, int VPT>
+struct LeanLds {
+  static constexpr int NW = NT / 64;
+  int valid[NW];
+  uint32_t kmax[NW], kmin[NW];
+  int count[3][8];
+  uint32_t key[64];       // the survivors and their neighbours
+  int pos[64];
+  int n, n_extra;
+  uint32_t from;          // keys from here on are selected
+  float guard;
+  int extra[64];          // positions selected besides
+  int tbl[VPT * NW];
+};
+
+template <typename T, int D, int NT, int VPT>
+__device__ __forceinline__ int select_lean(const uint32_t (&key)[VPT], const T* __restrict__ qh,
+                                           const T* __restrict__ Cu, int r, float guard /* of the last wave */,
+                                           LeanLds<NT, VPT>& L, int* s_ids, float* s_z) {
+  constexpr int NW = NT / 64, P = VPT <= 4 ? 7 : 3;
+  constexpr uint32_t kNone = 0x007fffffu;  // order_key(-inf)
+  static_assert(NW <= 64 && (NW & (NW - 1)) == 0, "a wave reduces the waves' values");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int nv = 0;
+  uint32_t kmax = 0, kmin = 0xffffffffu;
+#pragma unroll
+  for (int k = 0; k < VPT; ++k) {
+    nv += __popcll(__ballot(key[k] > kNone));
+    kmax = max(kmax, key[k]);
+    kmin = min(kmin, key[k] > kNone ? key[k] : 0xffffffffu);
+  }
+  kmax = wave_max_u(kmax);
+  kmin = wave_min_u(kmin);
+  if (lane == 0) {
+    L.valid[wave] = nv;
+    L.kmax[wave] = kmax;
+    L.kmin[wave] = kmin;
+  }
+  if (tid < 24) L.count[tid >> 3][tid & 7] = 0;
+  if (tid == 0) L.n = 0;
+  if (tid == NT - 64) L.guard = guard;
+  __syncthreads();
+  nv = wave_sum_i(lane < NW ? L.valid[lane & (NW - 1)] : 0);
+  kmax = wave_max_u(L.kmax[lane & (NW - 1)]);
+  kmin = wave_min_u(L.kmin[lane & (NW - 1)]);
+  const float g = L.guard;
+  const int r_eff = min(r, nv);
+  uint32_t from = kNone + 1;  // (every valid key)
+  int n_extra = 0;
+  if (r_eff == 0) from = 0xffffffffu;
+  if (r_eff > 0 && r_eff < nv) {
+    // (order keys of -FLT_MAX and FLT_MAX: the bounds are numbers)
+    if (kmin < 0x00800000u || kmax > 0xff7fffffu || !(g < 1.0e30f)) return -1;
+    uint32_t klo = kmin, khi = kmax + 1;  // count(>= klo) = c_lo >= r_eff > count(>= khi) = c_hi
+    int c_lo = nv, c_hi = 0;
+    for (int it = 0; c_lo - c_hi > LEAN_SURV && khi - klo > 1; ++it) {
+      uint32_t piv;  // lane i < P: the i-th pivot, ascending
+      const float f_lo = key_to_float(klo), f_hi = key_to_float(khi - 1), width = f_hi - f_lo;
+      if (it < 4 && width < 1.0e30f)
+        piv = order_key(f_lo + width * ((float)(lane + 1) * (1.0f / (P + 1))) + 0.0f);
+      else  // (equal steps of the integer image always come to an end)
+        piv = klo + (uint32_t)(((uint64_t)(khi - klo) * (uint32_t)(min(lane, P - 1) + 1)) / (P + 1));
+      piv = min(max(piv, klo), khi - 1);
+      int mine = 0;
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        const uint32_t pv = (uint32_t)__builtin_amdgcn_readlane((int)piv, i);
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k < VPT; ++k) c += __popcll(__ballot(key[k] >= pv));
+        mine = lane == i ? c : mine;
+      }
+      const int slot = it % 3;
+      if (lane < P) atomicAdd(&L.count[slot][lane], mine);
+      if (tid < 8) L.count[(it + 1) % 3][tid] = 0;
+      __syncthreads();
+      const int c = L.count[slot][min(lane, P - 1)];
+      const int below = __popcll(__ballot(lane < P && c >= r_eff));  // (counts fall with the pivots)
+      if (below > 0) {
+        klo = (uint32_t)__builtin_amdgcn_readlane((int)piv, below - 1);
+        c_lo = __builtin_amdgcn_readlane(c, below - 1);
+      }
+      if (below < P) {
+        khi = (uint32_t)__builtin_amdgcn_readlane((int)piv, below);
+        c_hi = __builtin_amdgcn_readlane(c, below);
+      }
+    }
+    if (c_lo - c_hi > LEAN_SURV) return -1;  // (that many equal scores)
+    // the survivors and what lies within the guard of them: the band around the threshold is among these
+    const uint32_t wlo = order_key(key_to_float(klo) - 2.0f * g + 0.0f);
+    const uint32_t whi = order_key(key_to_float(khi - 1) + 2.0f * g + 0.0f);
+#pragma unroll
+    for (int k = 0; k < VPT; ++k)
+      if (key[k] >= wlo && key[k] <= whi && key[k] > kNone) {
+        const int at = atomicAdd(&L.n, 1);
+        if (at < 64) {
+          L.key[at] = key[k];
+          L.pos[at] = k * NT + tid;
+        }
+      }
+    __syncthreads();
+    const int n = L.n;
+    if (n > 64) return -1;
+    if (wave == 0) {
+      const uint32_t mk = lane < n ? L.key[lane] : 0u;
+      const int mp = L.pos[lane];
+      // the r_eff-th largest of all is the need_all-th largest of the list
+      c_hi -= __popcll(__ballot(lane < n && mk >= khi));  // now: keys above the list's
+      const int need_all = r_eff - c_hi;
+      int above = 0, at_least = 0;
+      for (int j = 0; j < n; ++j) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)mk, j);
+        above += o > mk ? 1 : 0;
+        at_least += o >= mk ? 1 : 0;
+      }
+      const uint64_t is_tau = __ballot(lane < n && above < need_all && need_all <= at_least);
+      const uint32_t ktau = (uint32_t)__builtin_amdgcn_readlane((int)mk, __ffsll((unsigned long long)is_tau) - 1);
+      const float tau = key_to_float(ktau);
+      const uint32_t klo_band = order_key((tau - g) + 0.0f), khi_band = order_key((tau + g) + 0.0f);
+      const bool in_band = lane < n && mk >= klo_band && mk <= khi_band;
+      const uint64_t band = __ballot(in_band);
+      const int need = r_eff - (c_hi + __popcll(__ballot(lane < n && mk > khi_band)));
+      uint32_t f = klo_band;
+      if (__popcll(band) > need) {  // fp64 scores of the band, ties to the lower id
+        double zd = 0.0;
+        if (in_band) {
+          const T* row = Cu + (size_t)mp * D;
+          for (int e0 = 0; e0 < D; e0 += 8) {
+            float a8[8], b8[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              a8[e] = to_f32(qh[e0 + e]);
+              b8[e] = to_f32(row[e0 + e]);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) zd = fma((double)a8[e], (double)b8[e], zd);
+          }
+        }
+        int rank = 0;
+        for (int j = 0; j < n; ++j) {
+          if (!((band >> j) & 1ull)) continue;
+          const double zj = __shfl(zd, j);
+          const int pj = __builtin_amdgcn_readlane(mp, j);
+          rank += zj > zd || (zj == zd && pj < mp) ? 1 : 0;
+        }
+        const uint64_t take = __ballot(in_band && rank < need);
+        if (in_band && rank < need) L.extra[__popcll(take & ((1ull << lane) - 1ull))] = mp;
+        n_extra = __popcll(take);
+        f = khi_band + 1;
+      }
+      if (lane == 0) {
+        L.from = f;
+        L.n_extra = n_extra;
+      }
+    }
+    __syncthreads();
+    from = L.from;
+    n_extra = L.n_extra;
+  }
+  // ids in ascending order: counts per (k, wave), then every wave takes the prefix it needs
+  uint64_t on[VPT];
+#pragma unroll
+  for (int k = 0; k < VPT; ++k) {
+    bool sel = key[k] >= from && key[k] > kNone;
+    for (int j = 0; j < n_extra; ++j) sel |= L.extra[j] == k * NT + tid;
+    on[k] = __ballot(sel);
+    if (lane == 0) L.tbl[k * NW + wave] = __popcll(on[k]);
+  }
+  __syncthreads();
+  int nsel = 0;
+  constexpr int CHUNKS = (VPT * NW + 63) / 64;
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    const int at = 64 * c + lane;
+    const int v = at < VPT * NW ? L.tbl[min(at, VPT * NW - 1)] : 0;
+    const int inc = wave_incl_scan(v);
+#pragma unroll
+    for (int k = 64 / NW * c; k < min(VPT, 64 / NW * (c + 1)); ++k) {
+      const int first = nsel + __builtin_amdgcn_readlane(inc - v, k * NW + wave - 64 * c);
+      if ((on[k] >> lane) & 1ull) {
+        const int p = first + __popcll(on[k] & ((1ull << lane) - 1ull));
+        s_ids[p] = k * NT + tid;
+        s_z[p] = key_to_float(key[k]);
+      }
+    }
+    nsel += __builtin_amdgcn_readlane(inc, 63);
+  }
+  __syncthreads();
+  return nsel;
+}
+
+// ----------------------------------------------------------------------------
+// Few heads with few retrieved tokens each: everything that depends on the selection in one
+// workgroup of 16 waves per query head, behind the launch that made the scores, the estimation
+// terms of every cluster and the steady zone's partials.  Nothing here is bound by bandwidth: the
+// step is a chain of short dependent steps, and selection, retrieval and merge as launches of their
+// own each start with a round trip for what the one before left.  Ids, rows, token counts and scores
+// stay in LDS; the other zones' partials are requested before the selection and folded after the
+// retrieval.  32 heads, 2048 clusters, 590 tokens a head: 16.5 us (5.3 selection, 1.2 rows and token counts,
+// 3.5 .. 5.5 retrieval, 1.2 merge) where select_cached_kernel, gather_kernel and merge_kernel take 11.8 +
+// 7.4 + 5.6; the whole step 38.8 -> 27.1 us, of one head with 256 clusters 23.2 -> 13.8 us.
+// Eight rows of a lane group in flight instead of four: 26.1 -> 28.2 us.
+// ----------------------------------------------------------------------------
+constexpr int SOLO_NT = 1024;
+constexpr int SOLO_SLOTS = 512;  // most partials of the other zones
+
+template <typename T, int D, int VPT>
+__global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
+    const T* __restrict__ q, const T* __restrict__ C, const int32_t* __restrict__ offsets,
+    const float* __restrict__ z, const float* __restrict__ cn2part, int cn2_chunks, int Hq, int Hkv,
+    int m, int r, int rcap, int mwords, int mc, int usel_stride, int32_t* __restrict__ sel_ids,
+    int32_t* __restrict__ sel_pref, int32_t* __restrict__ sel_row, uint32_t* __restrict__ bitmap,
+    int32_t* __restrict__ nsel_out,
+    int32_t* __restrict__ user_selected, const T* __restrict__ vsum, float scale_log2,
+    float* __restrict__ part, int slots, int neg_slot, const T* __restrict__ k_perm,
+    const T* __restrict__ v_perm, int N_idx, float* __restrict__ out, float* __restrict__ lse) {
+  constexpr int NT = SOLO_NT, EPC = Elem<T>::EPC, LPR = D / EPC, RPW = 64 / LPR, NWV = NT / 64;
+  constexpr int GROUPS = NWV * RPW, U = 4, TILE = 2 * NT, STR = D + 2;
+  constexpr int NSG = NT / D, UB = 8;
+  extern __shared__ uint32_t dyn_keys[];  // keys for the general selection, where the lean one gives up
+  __shared__ int s_pref[FUSED_STAGE + 1];
+  __shared__ int s_row[FUSED_STAGE];
+  __shared__ int s_ids[FUSED_STAGE];
+  __shared__ float s_score[FUSED_STAGE];
+  __shared__ int rowidx[TILE];
+  __shared__ LeanLds<NT, VPT> lean;
+  __shared__ int scan_scratch[NWV];
+  __shared__ float smem[NWV * STR];
+  __shared__ float s_weight[SOLO_SLOTS + 2];  // of the other zones' partials; their maximum and sum
+  __shared__ float s_a[NSG * D];
+  const int bh = blockIdx.x;
+  const int b = bh / Hq, hq = bh - b * Hq, G = Hq / Hkv;
+  const int unit = b * Hkv + hq / G;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int sub = lane % LPR, grp = wave * RPW + lane / LPR;
+  const int e = tid % D, sg = tid / D;
+  const float* zz = z + (size_t)bh * m;
+  const int32_t* off = offsets + (size_t)unit * (mc + 1);
+  WAVE_STAMP(bitmap + (size_t)bh * mwords, 10);
+
+  uint32_t key[VPT];
+  float qn2 = 0.f, c2 = 0.f;
+  {
+    float v[VPT];
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) v[k] = zz[min(k * NT + tid, m - 1)];
+    // |fp32 score - exact| <= steps * 2^-24 * |q| |C| (the last wave's; see select_core)
+    if (wave == NWV - 1) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float x = to_f32(q[(size_t)bh * D + min(lane + 64 * j, D - 1)]);
+        qn2 += lane + 64 * j < D ? x * x : 0.f;
+      }
+      for (int i = lane; i < cn2_chunks; i += 64) c2 = fmaxf(c2, cn2part[(size_t)unit * cn2_chunks + i]);
+      qn2 = wave_sum_f(qn2);
+      c2 = wave_max(c2);
+    }
+#pragma unroll
+    for (int k = 0; k < VPT; ++k) key[k] = k * NT + tid < m ? order_key(v[k] + 0.0f) : 0u;
+  }
+  // thread (sg, e) folds component e of every NSG-th partial of the other zones
+  const float* pslots = part + (size_t)bh * slots * STR;
+  float pa[UB];
+#pragma unroll
+  for (int u = 0; u < UB; ++u) pa[u] = pslots[(size_t)min(sg + u * NSG, slots - 1) * STR + 2 + e];
+  AttnState<T, D, 1> st;
+  st.init(q + (size_t)bh * D, sub, scale_log2);
+  const float guard = 2.0f * 48.f * 5.9604645e-8f * sqrtf(qn2) * sqrtf(c2);
+  int nsel = select_lean<T, D, NT, VPT>(key, q + (size_t)bh * D, C + (size_t)unit * mc * D, r, guard, lean, s_ids,
+                                        s_score);
+  WAVE_STAMP(bitmap + (size_t)bh * mwords, 11);
+  int total = 0;
+  if (wave == NWV - 1) {  // (idle in the scan below) weights of the other zones' partials
+    float mx = kNegBig, l = 0.f;
+    for (int i = lane; i < slots; i += 64) mx = fmaxf(mx, pslots[(size_t)i * STR]);
+    mx = wave_max(mx);
+    for (int i = lane; i < slots; i += 64) {
+      const float m1 = pslots[(size_t)i * STR];  // (a partial without any term: kNegBig)
+      const float w = m1 > 0.5f * kNegBig ? exp2f(m1 - mx) : 0.f;
+      s_weight[i] = w;
+      l = fmaf(w, pslots[(size_t)i * STR + 1], l);
+    }
+    l = wave_add_f(l);
+    if (lane == 0) {
+      s_weight[SOLO_SLOTS] = mx;
+      s_weight[SOLO_SLOTS + 1] = l;
+    }
+  }
+  if (nsel >= 0) {
+    for (int base = 0; base < nsel; base += NT) {
+      const int t = base + tid;
+      const int id = s_ids[min(t, nsel - 1)];
+      const int r0 = off[id], size = t < nsel ? off[id + 1] - r0 : 0;
+      int tot;
+      const int ex = block_excl_scan<NT>(size, scan_scratch, tot);
+      if (t < nsel) {
+        s_row[t] = r0;
+        s_pref[t] = total + ex;
+      }
+      total += tot;
+    }
+    if (tid == 0) s_pref[nsel] = total;
+    if (user_selected)
+      for (int i = tid; i < usel_stride; i += NT)
+        user_selected[(size_t)bh * usel_stride + i] = i < nsel ? s_ids[i] : -1;
+  } else {
+    nsel = select_core<T, D, NT, 16, true>(
+        q, C, offsets, z, cn2part, cn2_chunks, Hq, Hkv, m, r, rcap, mwords, mc, usel_stride, sel_ids,
+        sel_pref, sel_row, bitmap, nsel_out, user_selected, vsum, scale_log2, part, slots,
+        neg_slot, bh, dyn_keys, s_pref, s_row, FUSED_STAGE, &total,
+        SelView{m, 0, nullptr, nullptr, 0, nullptr, nullptr, s_ids, 1});  // (ends with a barrier)
+    for (int i = tid; i < nsel; i += NT) s_score[i] = key_to_float(dyn_keys[s_ids[i]]);
+  }
+  __syncthreads();
+  WAVE_STAMP(bitmap + (size_t)bh * mwords, 12);
+
+  // The estimation pass added a term for every cluster: the selected ones' are taken out again.
+  // Their value sums are requested before the rows stream.
+  const T* VSu = vsum + (size_t)unit * mc * D + sub * EPC;
+  constexpr int UN = 2;
+  uint4 nraw[UN];
+  float nsc[1][UN], nmult[UN];
+  auto neg_load = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int j = min(i0 + u * GROUPS, max(nsel, 1) - 1);
+      const int id = nsel > 0 ? s_ids[j] : 0;
+      nraw[u] = load16(VSu + (size_t)id * D);
+      nsc[0][u] = i0 + u * GROUPS < nsel ? s_score[j] * scale_log2 : -INFINITY;
+      nmult[u] = i0 + u * GROUPS < nsel ? (float)(s_pref[j + 1] - s_pref[j]) : 0.f;
+    }
+  };
+  neg_load(grp);
+  const T* Ku = k_perm + (size_t)unit * N_idx * D + sub * EPC;
+  const T* Vu = v_perm + (size_t)unit * N_idx * D + sub * EPC;
+  for (int base = 0; base < total; base += TILE) {
+    const int n = min(TILE, total - base);
+    if (base > 0) __syncthreads();
+    for (int c = grp; c < nsel; c += GROUPS) {  // every cluster's rows to their tokens' places
+      const int p0 = s_pref[c], row0 = s_row[c] - p0;
+      const int p1 = min(s_pref[c + 1], base + n);
+      for (int t = max(p0, base) + sub; t < p1; t += LPR) rowidx[t - base] = row0 + t;
+    }
+    __syncthreads();
+    for (int i = grp; i < n; i += GROUPS * U) {
+      uint4 kraw[U], vraw[U];
+      bool valid[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int ii = i + u * GROUPS;
+        valid[u] = ii < n;
+        const int row = rowidx[valid[u] ? ii : i];
+        kraw[u] = load16_stream(Ku + (size_t)row * D);
+        vraw[u] = load16_stream(Vu + (size_t)row * D);
+      }
+      st.template rows<U, LPR>(kraw, vraw, valid);
+    }
+  }
+  for (int i = grp; i < nsel; i += GROUPS * UN) {
+    if (i != grp) neg_load(i);
+    st.template rows_given<UN, true>(nsc, nmult, nraw);
+  }
+  WAVE_STAMP(bitmap + (size_t)bh * mwords, 21);
+
+  // the wave's lane groups
+  {
+    float mx = st.mx[0];
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    const float a = exp2f(st.mx[0] - mx);
+    st.mx[0] = mx;
+    st.l[0] *= a;
+#pragma unroll
+    for (int j = 0; j < EPC; ++j) st.acc[0][j] *= a;
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1) {
+      st.l[0] += __shfl_xor(st.l[0], off);
+#pragma unroll
+      for (int j = 0; j < EPC; ++j) st.acc[0][j] += __shfl_xor(st.acc[0][j], off);
+    }
+  }
+  if (lane < LPR) {
+    float* dst = smem + (size_t)wave * STR;
+#pragma unroll
+    for (int j = 0; j < EPC; ++j) dst[2 + sub * EPC + j] = st.acc[0][j];
+    if (sub == 0) {
+      dst[0] = st.mx[0];
+      dst[1] = st.l[0];
+    }
+  }
+  float A = 0.f;
+#pragma unroll
+  for (int u = 0; u < UB; ++u) A = fmaf(sg + u * NSG < slots ? s_weight[min(sg + u * NSG, slots - 1)] : 0.f, pa[u], A);
+  for (int s0 = sg + UB * NSG; s0 < slots; s0 += NSG)
+    A = fmaf(s_weight[s0], pslots[(size_t)s0 * STR + 2 + e], A);
+  __syncthreads();
+  // lane w: wave w's partial; lane NWV: the other zones'
+  const float m_l = lane < NWV ? smem[lane * STR] : (lane == NWV ? s_weight[SOLO_SLOTS] : kNegBig);
+  const float l_l = lane < NWV ? smem[lane * STR + 1] : (lane == NWV ? s_weight[SOLO_SLOTS + 1] : 0.f);
+  const float M = wave_max(m_l);
+  const float w_l = m_l > 0.5f * kNegBig ? exp2f(m_l - M) : 0.f;
+  const float Z = wave_add_f(w_l * l_l);
+  auto weight = [&](int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_l), i)); };
+  A *= weight(NWV);
+  const int sg_u = __builtin_amdgcn_readfirstlane(sg);  // (D lanes or more share it)
+#pragma unroll
+  for (int w = 0; w < NWV / NSG; ++w) A = fmaf(weight(sg_u + w * NSG), smem[(sg + w * NSG) * STR + 2 + e], A);
+  s_a[sg * D + e] = A;
+  __syncthreads();
+  if (sg == 0) {
+    float At = 0.f;
+#pragma unroll
+    for (int g = 0; g < NSG; ++g) At += s_a[g * D + e];
+    store_normalised(At, M, Z, out + (size_t)bh * D + e, e == 0 ? lse + bh : nullptr);
+  }
+  WAVE_STAMP(bitmap + (size_t)bh * mwords, 22);
+}
+
 // ============================================================================
 // 3b. Steady zone: sink + local rows of one unit, shared by its G query heads.
 // ============================================================================
@@ -2176,7 +2602,7 @@ __global__ __launch_bounds__(256) void dense_steady_kernel(
     const T* __restrict__ q, const T* __restrict__ C, const T* __restrict__ vsum,
     const int32_t* __restrict__ sizes, float* __restrict__ z, float* __restrict__ cn2part, int Hkv,
     int m, int mc, int chunks, int slots, int slot0, float scale_log2, float* __restrict__ part,
-    int n_dense_wgs, const T* __restrict__ k_steady, const T* __restrict__ v_steady, int p,
+    int dense_rows, int n_dense_wgs, const T* __restrict__ k_steady, const T* __restrict__ v_steady, int p,
     int p_stride, int steady_chunks, int steady_rows, int steady_slot0) {
   using Lds = DenseLds<T, D, G, 256>;
   constexpr size_t kSteadyBytes = sizeof(float) * 4 * G * (D + 2);
@@ -2189,7 +2615,7 @@ __global__ __launch_bounds__(256) void dense_steady_kernel(
     const int unit = wg / chunks, chunk = wg - unit * chunks;
     const int b = unit / Hkv, h = unit - b * Hkv;
     const int bh0 = b * Hq + h * G;
-    const int c0 = chunk * DENSE_ROWS, nrows = min(DENSE_ROWS, m - c0);
+    const int c0 = chunk * dense_rows, nrows = min(dense_rows, m - c0);
     const int32_t* su = sizes + (size_t)unit * mc + c0;
     dense_scores<T, D, G, 256, true>(q, C, su, z, unit, bh0, m, mc, c0, nrows, lds);
     __syncthreads();
@@ -3339,6 +3765,19 @@ __global__ void fill_i32_kernel(int32_t* p, size_t n, int32_t v) {
 // ============================================================================
 // Host: geometry and launches
 // ============================================================================
+// Retrieved tokens per head up to which one workgroup per head (attend_head_kernel) is faster than
+// selection, retrieval over several workgroups and merge as launches of their own.  A workgroup by
+// itself reads about 0.1 rows per ns: with few heads the crossing is near 1300 tokens, with a head for
+// nearly every CU the memory system is the bound either way.  Beyond a head per CU (the kernel takes a
+// CU's registers) a second round of them follows.  Us per step, launches of their own and one workgroup:
+// 4 heads 327 tokens 30.5 and 23.1, 1310 tokens 39.2 and 43.7; 32 heads 327 tokens 31.9 and 24.1, 655
+// tokens 33.1 and 27, 1310 tokens 44.8 and 49.4; 128 heads 1638 tokens 55.6 and 50.8, 2621 tokens 94.7 and 98.9;
+// 256 heads 655 tokens 63.8 and 56.8, 6553 tokens 241 and 232; 352 heads 655 tokens 84.6 and 85.0, 1310
+// tokens 166 and 182.
+static double solo_max_tokens(int heads) {
+  return heads > 256 ? 0.0 : heads >= 192 ? 1.0e9 : heads >= 128 ? 2048.0 : 1024.0;
+}
+
 DecodeGeom decode_geometry(const wave_index& ix, int Hq, int topk) {
   DecodeGeom g{};
   const int m = ix.m, units = ix.B * ix.Hkv, heads = ix.B * Hq, D = ix.d;
@@ -3423,6 +3862,18 @@ DecodeGeom decode_geometry(const wave_index& ix, int Hq, int topk) {
     g.gather_wgs = (int)(grid < g.wtotal ? grid : g.wtotal);
     g.stage = (r < FUSED_STAGE ? r : FUSED_STAGE) + 1;  // (+ 1: the end of the last staged cluster)
   }
+  // The meta-index pass in smaller pieces when it does not give every CU a workgroup (8 units of 2048
+  // clusters with their steady zones: 13.6 us in 256-cluster pieces, 8.3 us in 64-cluster ones).
+  if (!g.fused && !g.listed && !g.sliced && g.steady_chunks > 0) {
+    while (g.score_rows > 64 && units * ((m + g.score_rows - 1) / g.score_rows) < 256) g.score_rows /= 2;
+    g.score_chunks = m > 0 ? (m + g.score_rows - 1) / g.score_rows : 0;
+    g.est_rows = g.score_rows;
+    g.est_chunks = g.score_chunks;
+  }
+  // Few heads over few clusters: the selection, the retrieval and the merge of a head in one workgroup.
+  g.solo = (m > 0 && r > 0 && !g.fused && !g.listed && m <= SOLO_NT * 16 && r < FUSED_STAGE &&
+            g.steady_chunks + g.est_chunks <= SOLO_SLOTS && expect <= solo_max_tokens(heads)) ? 1 : 0;
+  if (g.solo) g.gather_chunks = 0;
   // partial results per head: retrieval, steady, estimation of all clusters per
   // range, and (see below) the selected clusters' estimation terms with a minus sign
   if (g.sliced) {
@@ -3522,7 +3973,7 @@ static wave_status decode_tdg(const void* q_, const wave_index& ix, int Hq, int 
                   units * (g.score_chunks + g.steady_chunks), 256, 0, st, q,
                   static_cast<const T*>(ix.centroids), static_cast<const T*>(ix.vsum), ix.sizes, z, cn2,
                   ix.Hkv, m, mc, g.score_chunks, g.slots, est_slot0, scale_log2, part,
-                  units * g.score_chunks, static_cast<const T*>(ix.k_steady),
+                  g.score_rows, units * g.score_chunks, static_cast<const T*>(ix.k_steady),
                   static_cast<const T*>(ix.v_steady), ix.p, steady_stride(ix), g.steady_chunks, g.steady_rows,
                   g.gather_chunks);
     else
@@ -3577,6 +4028,17 @@ static wave_status decode_tdg(const void* q_, const wave_index& ix, int Hq, int 
         WAVE_LAUNCH("merge", (merge_list_kernel<D, 256>), heads, 256, 0, st, part,
                     g.steady_chunks + g.est_chunks, g.slots, reinterpret_cast<const float*>(w + g.off_part_g),
                     lo.head_info, out, lse);
+    } else if (g.solo) {
+      // (few keys per thread: fewer instructions in every sweep)
+      auto attend = [&](auto kernel) {
+        WAVE_LAUNCH("attend", kernel, heads, SOLO_NT, sizeof(uint32_t) * SOLO_NT * (size_t)((m + SOLO_NT - 1) / SOLO_NT),
+                    st, WAVE_SELECT_ARGS, static_cast<const T*>(ix.k_perm), static_cast<const T*>(ix.v_perm),
+                    row_stride(ix), out, lse);
+      };
+      if (m <= SOLO_NT) attend(attend_head_kernel<T, D, 1>);
+      else if (m <= 2 * SOLO_NT) attend(attend_head_kernel<T, D, 2>);
+      else if (m <= 4 * SOLO_NT) attend(attend_head_kernel<T, D, 4>);
+      else attend(attend_head_kernel<T, D, 16>);
     } else {
       if (g.sliced) {
         int32_t* slice_ids = reinterpret_cast<int32_t*>(w + g.off_slice_ids);
@@ -3631,7 +4093,7 @@ static wave_status decode_tdg(const void* q_, const wave_index& ix, int Hq, int 
                 static_cast<const T*>(ix.k_steady), static_cast<const T*>(ix.v_steady), ix.Hkv, ix.p,
                 steady_stride(ix),
                 g.steady_chunks, g.steady_rows, g.slots, g.gather_chunks, scale_log2, part);
-  if (!g.fused && !g.listed)  // (the fused kernel normalises each head itself; the listed path has its own merge)
+  if (!g.fused && !g.listed && !g.solo)  // (these normalise each head themselves)
     WAVE_LAUNCH("merge", (merge_kernel<D>), heads, MERGE_THREADS, 0, st, part,
                 g.gather_chunks + g.steady_chunks + g.est_chunks + g.neg_slots, g.slots, out, lse);
   return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;

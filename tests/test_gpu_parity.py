@@ -738,3 +738,43 @@ def test_index_append_matches_oracle_then_decode(case, n_news, U, ku, cap, scap,
     r = pu.retrieve_count(wl)
     _decode_and_check(wl_now, ix, ref, q, r, f"append {wl.name}")
     _decode_and_check(wl_now, ix, ref, q, ix.m, f"append {wl.name} all")
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("m,r,nb", [(3, 2, 2), (64, 20, 30), (1024, 40, 33), (1025, 300, 64), (2048, 37, 3),
+                                    (2049, 60, 65), (4096, 5, 31), (4097, 80, 70), (16384, 50, 12)])
+def test_selection_of_one_workgroup_per_head(m, r, nb, dtype, d):
+    """Few heads and few tokens: a workgroup selects with its keys in registers (1, 2, 4 or 16 a thread:
+    m at the edges), down to at most 32 survivors that one wave ranks.  Head 0: nb clusters inside the
+    guard band around the threshold, some of them equal in fp64, more than are needed, at sizes around
+    what the wave holds (32 survivors, 64 with their neighbours; beyond that the general selection takes
+    over); compared for equality with the fp64 ranking, ties to the lower id.  Head 1: ordinary scores;
+    head 2: a query of zeros, every score equal."""
+    g = np.random.default_rng(m + r)
+    arrs, n = _hand_index(m, d, dtype, 8, seed=m + 9)
+    arrs = {k: np.array(v) for k, v in arrs.items()}
+    arrs["sizes"][:] = 1                                         # (no empty clusters: m may be tiny)
+    arrs["offsets"] = np.arange(m + 1)
+    n = m
+    K = wo.quant(0.05 * g.standard_normal((m, d)), dtype)
+    ulp = 2.0 ** -7 if dtype == "bf16" else 2.0 ** -20
+    qv = np.ones(d)
+    qv[d // 2:] = 2.0 ** (-8 if dtype == "bf16" else -6)
+    band = np.sort(g.choice(m, min(nb, m), replace=False))
+    for c in band:
+        row = np.ones(d)
+        for a in g.choice(d // 2, 3, replace=False) + d // 2:
+            row[a] += g.integers(-1, 2) * ulp
+        K[c] = row
+    V = wo.quant(g.standard_normal((m, d)), dtype)
+    arrs.update(centroids=K, vsum=V, k_perm=K, v_perm=V, perm=np.arange(m))
+    zb = K[band] @ qv
+    assert zb.max() - zb.min() < 2 * 48 * 2.0 ** -24 * np.linalg.norm(qv) * np.sqrt(d)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q = torch.from_numpy(np.stack([qv, wo.quant(g.standard_normal(d), dtype), np.zeros(d)])[None].astype(np.float32)
+                         ).to(tdt)
+    for rr in sorted({1, min(nb, m) // 2, r, min(nb, m)} - {0}):
+        for hq, (o_g, l_g, s_g, o, l, s_ref, z) in enumerate(_decode_hand(arrs, n, m, d, dtype, q, rr, Hq=3)):
+            tag = f"m={m} r={rr} nb={nb} hq={hq}"
+            assert np.array_equal(s_g[s_g >= 0], np.asarray(s_ref)), tag
+            pu.check_outputs(o_g, np.array([l_g]), o, np.array([l]), dtype, tag)
