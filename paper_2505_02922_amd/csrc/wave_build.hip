@@ -613,6 +613,63 @@ __device__ __forceinline__ void lean_assign_fragments(const bf16_t* X, const cha
   }
 }
 
+// The same for segments whose points a workgroup holds in registers from round to round: KEEP fragments
+// per wave, fragment f of wave w is the segment's f * NW + w.
+template <int D, int KEEP, int NW>
+__device__ __forceinline__ void load_kept_fragments(const bf16_t* X, int L_s, uint4 (&kept)[KEEP][D / 16]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int f = 0; f < KEEP; ++f) {
+    const int row = min(32 * (f * NW + wave) + (lane & 31), L_s - 1);
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) kept[f][s] = load16(X + (size_t)row * D + (2 * s + (lane >> 5)) * 8);
+  }
+}
+
+// Fragments f0 and f0 + NW of the segment against all centroids: a pair shares the reads of a tile (with
+// one fragment at a time the reads take as long as the matrix instructions).
+template <int D, int NW, typename Emit>
+__device__ __forceinline__ void assign_pair(const uint4 (&x0)[D / 16], const uint4 (&x1)[D / 16], int f0,
+                                            const char* cent, int L_s, int k_s, Emit&& emit) {
+  using RT = ResidentTile<D>;
+  constexpr int KS = RT::KS, ROWB = RT::ROWB;
+  const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int ntiles = (k_s + 31) / 32, nfull = k_s / 32;
+  constexpr float B0 = kAssignBias;
+  const floatx16 bias = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
+  int best[2] = {}, second[2] = {}, btile[2] = {};
+  for (int t = 0; t < ntiles; ++t) {
+    const char* tile = cent + (size_t)(32 * t + col) * ROWB + half * 16;
+    floatx16 acc[2];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, load16(tile + s * 32));
+      acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, x0[s]), s == 0 ? bias : acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, x1[s]), s == 0 ? bias : acc[1], 0, 0, 0);
+    }
+    if (t < nfull) assign_epilogue<2, false>(acc, best, second, btile, t, half, k_s);
+    else assign_epilogue<2, true>(acc, best, second, btile, t, half, k_s);
+  }
+#pragma unroll
+  for (int f = 0; f < 2; ++f) {
+    const int row = merge_halves(best[f], second[f], btile[f], half);
+    const int point = 32 * (f0 + f * NW) + col;
+    if (half == 0 && point < L_s) emit(point, row, best[f], second[f], NoState{});
+  }
+}
+
+template <int D, int KEEP, int NW, typename Emit>
+__device__ __forceinline__ void assign_kept_fragments(const uint4 (&kept)[KEEP][D / 16], const char* cent, int L_s,
+                                                      int k_s, Emit&& emit) {
+  const int wave = threadIdx.x >> 6;
+  static_assert(KEEP % 2 == 0, "whole pairs");
+#pragma unroll
+  for (int f = 0; f < KEEP; f += 2) {
+    if (32 * (f * NW + wave) >= L_s) break;
+    assign_pair<D, NW>(kept[f], kept[f + 1], f * NW + wave, cent, L_s, k_s, emit);
+  }
+}
+
 // What the assign step of one round leaves for the next about a point: the key of its cluster's
 // similarity and a key that no other centroid's similarity exceeds (both up to the fp32 error).
 // (A unit's bounds start `bounds_skip` entries further on than the units' points are counted.)
@@ -1624,47 +1681,66 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
 
 // ============================================================================
 // Short segments (an index update's 1K tokens into 64 clusters; small builds): all T
-// iterations of one segment in ONE workgroup of 16 waves, with the centroids, the
+// iterations of one segment in ONE workgroup, with the centroids, the
 // assignments, the sorted order and the cluster counts in LDS from the first
 // iteration to the last.  Per iteration: assign (the resident MFMA form), near-ties
-// re-decided with fp64 similarities by one wave each, the counting sort, the update
-// straight into the LDS centroid rows; the steps are those of the kernels above,
-// separated by workgroup barriers instead of launches.  Only the normalised keys are
-// read from global memory; the last iteration's order, counts and first positions
-// are written there for the finalize step.  Launches per build: 5 instead of 4 T + 3.
+// re-decided with fp64 similarities by one wave each, and the update of the clusters that a
+// point entered or left, straight into the LDS centroid rows; a round in which no point
+// moves ends the rounds.  Launches per build: 5 instead of 4 T + 3.
+//
+// KEEP > 0 (up to 1024 points at d = 128, 2048 at d = 64): every wave holds KEEP fragments of points in
+// registers from the first round to the last; else they are read again in every round (256 KiB
+// per workgroup and round at 1024 points).
+// SUMS (the member sums fit in 64 KiB of LDS): later rounds add the points that moved to one sum and
+// take them out of another, wherever that is exact; they need no sort and no pass over members.
+// Else a round sorts the points and sums the members of the changed clusters.
+// 128 segments of 1024 points x 64 clusters, ten rounds: 200 us with every member summed again and the
+// points read again in each round, 165 with the changed clusters summed, 105 us so (about 3.5 us assign, where the
+// matrix instructions take 1.7, and 4 us update a round).  120K tokens x 16 in such segments: build
+// 17.4 -> 11.6 ms; in segments of 2048 points x 128 clusters (neither KEEP nor SUMS) 17.9 -> 15.1 ms.
 // ============================================================================
 constexpr int SMALL_L_MAX = 2048;   // points per segment
 constexpr int SMALL_K_MAX = 128;    // clusters per segment
-constexpr int SMALL_NW = 16;
+constexpr int SMALL_NW = 16;        // most waves
+// With the points in registers half as many waves of twice the registers.  (The others keep 16: the
+// gathers of the update are chains of round trips; 8 waves took 494 instead of 442 us for 16 segments of
+// 2048 points x 128 clusters x 8 KV heads.)
+template <int KEEP>
+constexpr int small_waves() { return KEEP > 0 ? SMALL_NW / 2 : SMALL_NW; }
 
 template <int D>
-inline size_t small_kmeans_lds(int kk) {
+inline size_t small_kmeans_lds(int kk, bool keep_sums) {
   return (size_t)32 * ((kk + 31) / 32) * ResidentTile<D>::ROWB +
-         sizeof(int) * ((size_t)SMALL_NW * kk + kk + 2 * SMALL_L_MAX + 2 * (size_t)kk);
+         sizeof(int) * ((size_t)SMALL_NW * kk + kk + 3 * SMALL_L_MAX + 4 * (size_t)kk) +
+         (keep_sums ? sizeof(double) * D * (size_t)kk : 0);
 }
 
-template <int D>
-__global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
+template <int D, int KEEP, bool SUMS>
+__global__ __launch_bounds__(64 * small_waves<KEEP>()) void kmeans_small_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ order,
     int32_t* __restrict__ count, int32_t* __restrict__ start, int S, int L, int kk, int N_idx, int iters,
     int key_bits) {
   using RT = ResidentTile<D>;
-  constexpr int NT = 64 * SMALL_NW, LPR = D / 8, GROUPS = NT / LPR;
+  constexpr int NW = small_waves<KEEP>(), NT = 64 * NW, LPR = D / 8, GROUPS = NT / LPR;
   extern __shared__ __attribute__((aligned(16))) char small_lds[];
   char* cent = small_lds;
   int* hist = reinterpret_cast<int*>(small_lds + (size_t)32 * ((kk + 31) / 32) * RT::ROWB);  // sort_segment's
-  int* a_s = hist + SMALL_NW * kk + kk;   // cluster of every point
+  int* a_s = hist + NW * kk + kk;   // cluster of every point
   int* ord_s = a_s + SMALL_L_MAX;         // points by cluster; before the sort: the near-tie list
   int* cnt_s = ord_s + SMALL_L_MAX;
   int* first_s = cnt_s + kk;
+  int* changed_s = first_s + kk;
+  int* prev_s = changed_s + kk;           // every point's cluster of the round before
+  double* sums = reinterpret_cast<double*>(prev_s + SMALL_L_MAX);  // (SUMS) member sums
   int* flags = ord_s;
-  __shared__ int nflag;
+  __shared__ int nflag, nmoved;
+  __shared__ int seg_emin, seg_emax;
   const int sg = blockIdx.x;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
   const bf16_t* X = xhat + p0 * D;
-  const int nfrag = (si.L_s + 31) / 32;
+  [[maybe_unused]] const int nfrag = (si.L_s + 31) / 32;
   resident_load_centroids<D, NT>(chat + (size_t)sg * kk * D, si.k_s, cent);
 #ifdef WAVE_TRACE  // phase times of workgroup 0 (100 MHz clock), printed at the end
   unsigned long long tp[5] = {0, 0, 0, 0, 0}, tl = wall_clock64();
@@ -1673,24 +1749,48 @@ __global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
 #else
 #define WAVE_PHASE(k) do { } while (0)
 #endif
+  // SUMS: where no fp64 addition of the segment's points rounds (see update_moves_kernel), the member
+  // sums stay from round to round and the points that moved are taken out of one and added to another
+  bool moves = false;
+  if constexpr (SUMS) {
+    if (tid == 0) {
+      seg_emin = 255;
+      seg_emax = 0;
+    }
+    __syncthreads();
+    int emin = 255, emax = 0;
+#pragma unroll 2
+    for (int i = tid; i < si.L_s * RT::CPR; i += NT) exponent_range<bf16_t>(load16(X + (size_t)i * 8), emin, emax);
+    atomicMin(&seg_emin, emin);
+    atomicMax(&seg_emax, emax);
+    __syncthreads();
+    const int lg = si.L_s > 1 ? 32 - __clz(si.L_s - 1) : 0;  // ceil(log2 L_s)
+    moves = seg_emax < seg_emin || seg_emax - seg_emin + lg <= 52 - MantissaBits<bf16_t>::value;
+  }
+  uint4 kept[KEEP > 0 ? KEEP : 1][RT::KS];
+  if constexpr (KEEP > 0) load_kept_fragments<D, KEEP, NW>(X, si.L_s, kept);
   for (int t = 0; t < iters; ++t) {
-    if (tid == 0) nflag = 0;
+    if (tid == 0) nflag = nmoved = 0;
     __syncthreads();
     WAVE_PHASE(0);
-    lean_assign_fragments<D, SMALL_NW>(X, cent, si.L_s, si.k_s, 0, nfrag, [](int) { return NoState{}; },
-                                       [&](int point, int cluster, int best, int second, NoState) {
-                                         a_s[point] = cluster;
-                                         if (key_gap(best, second) < kAssignGuard) flags[atomicAdd(&nflag, 1)] = point;
-                                       });
+    auto emit = [&](int point, int cluster, int best, int second, NoState) {
+      a_s[point] = cluster;
+      if (key_gap(best, second) < kAssignGuard) flags[atomicAdd(&nflag, 1)] = point;
+    };
+    if constexpr (KEEP > 0)
+      assign_kept_fragments<D, KEEP, NW>(kept, cent, si.L_s, si.k_s, emit);
+    else
+      lean_assign_fragments<D, NW>(X, cent, si.L_s, si.k_s, 0, nfrag, [](int) { return NoState{}; }, emit);
     __syncthreads();
     WAVE_PHASE(1);
+    for (int c = tid; c < kk; c += NT) changed_s[c] = 0;  // (every wave is done with the last round's)
     // near-ties: fp64 similarities in index order against the LDS copy of the centroids,
     // ties to the lowest centroid (the arithmetic of refine_kernel)
     const int nf = nflag;
 #ifdef WAVE_TRACE
     nf_total += nf;
 #endif
-    for (int it = wave; it < nf; it += SMALL_NW) {
+    for (int it = wave; it < nf; it += NW) {
       const int point = flags[it];
       const bf16_t* xr = X + (size_t)point * D;
       double bv = -1.0e300;
@@ -1723,14 +1823,65 @@ __global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
     }
     __syncthreads();
     WAVE_PHASE(2);
-    sort_segment(a_s, ord_s, cnt_s, first_s, si.L_s, kk, key_bits, hist);
+    if (SUMS && moves && t > 0) {
+      for (int i = tid; i < si.L_s; i += NT) {
+        const int to = a_s[i], from = prev_s[i];
+        if (to != from) {
+          changed_s[to] = changed_s[from] = 1;
+          ord_s[atomicAdd(&nmoved, 1)] = i;
+        }
+      }
+      __syncthreads();
+      const int n = nmoved;
+      if (n == 0 || t + 1 == iters) break;  // (nothing moved: all later rounds would repeat this one)
+      constexpr int PER = D / 64, U = 4;
+      for (int e = wave; e < n; e += U * NW) {
+        int point[U];
+        float x[U][PER];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          point[u] = ord_s[min(e + u * NW, n - 1)];
+#pragma unroll
+          for (int j = 0; j < PER; ++j) x[u][j] = to_f32(X[(size_t)point[u] * D + 64 * j + lane]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (e + u * NW < n) {
+            const int to = a_s[point[u]], from = prev_s[point[u]];
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+              atomicAdd(&sums[to * D + 64 * j + lane], (double)x[u][j]);
+              atomicAdd(&sums[from * D + 64 * j + lane], -(double)x[u][j]);
+            }
+            prev_s[point[u]] = to;  // (every lane the same; no other wave has this point)
+          }
+      }
+      __syncthreads();
+      WAVE_PHASE(3);
+      for (int c = tid / LPR; c < si.k_s; c += GROUPS)
+        if (changed_s[c]) {
+          double acc[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[e] = sums[c * D + (tid % LPR) * 8 + e];
+          finish_centroid<bf16_t, D>(acc, reinterpret_cast<bf16_t*>(cent + (size_t)c * RT::ROWB) + (tid % LPR) * 8);
+        }
+      WAVE_PHASE(4);
+      continue;
+    }
+    sort_segment(a_s, ord_s, cnt_s, first_s, si.L_s, kk, key_bits, hist, prev_s, changed_s, t > 0);
     __syncthreads();
     WAVE_PHASE(3);
+    if (t > 0) {
+      bool any = false;
+      for (int c = lane; c < si.k_s; c += 64) any |= changed_s[c] != 0;
+      if (!__ballot(any)) break;  // (the same for every wave)
+    }
     if (t + 1 < iters)
       for (int c = tid / LPR; c < si.k_s; c += GROUPS)
-        update_cluster<bf16_t, D, 8, false>(X, ord_s + first_s[c], cnt_s[c],
-                                     reinterpret_cast<bf16_t*>(cent + (size_t)c * RT::ROWB) + (tid % LPR) * 8,
-                                     tid % LPR);
+        if (t == 0 || changed_s[c])  // (a cluster that no point entered or left keeps its sum)
+          update_cluster<bf16_t, D, 8, false>(
+              X, ord_s + first_s[c], cnt_s[c], reinterpret_cast<bf16_t*>(cent + (size_t)c * RT::ROWB) + (tid % LPR) * 8,
+              tid % LPR, SUMS ? sums + c * D + (tid % LPR) * 8 : nullptr);
     WAVE_PHASE(4);
   }
 #ifdef WAVE_TRACE
@@ -1739,6 +1890,11 @@ __global__ __launch_bounds__(64 * SMALL_NW) void kmeans_small_kernel(
            tp[0], tp[1], tp[2], tp[3], tp[4], nf_total);
 #endif
 #undef WAVE_PHASE
+  if (SUMS && moves && iters > 1) {  // (the last rounds did not sort)
+    __syncthreads();
+    sort_segment(a_s, ord_s, cnt_s, first_s, si.L_s, kk, key_bits, hist);
+    __syncthreads();
+  }
   for (int i = tid; i < si.L_s; i += NT) order[p0 + i] = ord_s[i];
   for (int c = tid; c < kk; c += NT) {
     count[(size_t)sg * kk + c] = cnt_s[c];
@@ -2053,9 +2209,19 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   const int kb = key_bits_for(kk);
   const int cl_grid = (ncl + GROUPS - 1) / GROUPS;
   if constexpr (sizeof(T) == 2) {
-    if (small)
-      WAVE_LAUNCH("kmeans_small", (kmeans_small_kernel<D>), g.segs, 64 * SMALL_NW, small_kmeans_lds<D>(kk), st,
-                  xhat, chat, order, count, start, S, L, kk, N_idx, iters, kb);
+    if (small) {
+      auto run = [&](auto kernel, int waves, bool keep_sums) {
+        WAVE_LAUNCH("kmeans_small", kernel, g.segs, 64 * waves, small_kmeans_lds<D>(kk, keep_sums), st, xhat, chat,
+                    order, count, start, S, L, kk, N_idx, iters, kb);
+      };
+      constexpr int KEEP = 512 / D, KW = small_waves<KEEP>();  // (128 registers a lane)
+      const bool keep = (L < N_idx ? L : N_idx) <= 32 * KEEP * KW;
+      const bool keep_sums = (size_t)kk * D <= 8192;  // 64 KiB
+      if (keep && keep_sums) run(kmeans_small_kernel<D, KEEP, true>, KW, true);
+      else if (keep) run(kmeans_small_kernel<D, KEEP, false>, KW, false);
+      else if (keep_sums) run(kmeans_small_kernel<D, 0, true>, SMALL_NW, true);
+      else run(kmeans_small_kernel<D, 0, false>, SMALL_NW, false);
+    }
   }
   auto sort = [&](int32_t* prev_or_null, int t) {
     WAVE_LAUNCH("sort", sort_kernel, g.segs, 64 * W, sort_lds, st, assign, order, count, start, nflag,

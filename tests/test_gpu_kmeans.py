@@ -168,3 +168,24 @@ def test_full_passes_of_many_segments_keep_their_centroids_in_lds():
     for (b, h), ref in pu.oracle_build(wl, K, V, units=units).items():
         for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
             assert np.array_equal(ix.t[name][b, h].double().cpu().numpy(), getattr(ref, name)), (b, h, name)
+
+
+# Segments that one workgroup clusters: points in registers up to 1024 (d = 128) or 2048 (d = 64), member
+# sums in LDS up to 64 or 128 clusters, their edges and remainders; segments whose sums round (wide), clusters
+# that run empty (ties), and rounds enough that the points stop moving before the last.
+@pytest.mark.parametrize("kind,d,L,k,iters", [
+    ("mixture", 128, 1024, 64, 9), ("plain", 128, 1024, 65, 6), ("plain", 128, 1025, 64, 6), ("mixture", 128, 2048, 128, 8),
+    ("mixture", 64, 2048, 128, 9), ("plain", 64, 2047, 127, 5), ("ties", 128, 1000, 64, 7), ("ties", 64, 33, 32, 6),
+    ("wide", 128, 700, 40, 5), ("wide", 64, 2040, 128, 4), ("wide", 128, 2048, 33, 4), ("plain", 128, 31, 1, 30),
+    ("mixture", 128, 513, 33, 1), ("mixture", 64, 257, 64, 2)])
+def test_segments_of_one_workgroup_match_oracle(kind, d, L, k, iters):
+    N = 5 + 2 * L + L // 3 + 1
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="short", B=2, Hq=1, Hkv=1, N=N, d=d, n_sink=2, n_local=3,
+                      segment_len=L, clusters_per_segment=k, iters=iters)
+    K = _keys(kind, 2, N, d, N + k).to(torch.bfloat16)
+    V = torch.randn(2, 1, N, d, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16)
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), wl.n_sink, wl.n_local, L, k, iters, 0)
+    torch.cuda.synchronize()
+    for name in wb.BUFFER_NAMES:
+        assert torch.equal(ix.t[name].cpu().double(), ref[name].reshape(ix.t[name].shape).double()), name
