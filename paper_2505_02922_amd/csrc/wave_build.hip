@@ -1032,38 +1032,124 @@ __global__ __launch_bounds__(256, 4) void assign_listed_kernel(
 }
 
 // ============================================================================
-// Assign, f32: one wave per workgroup and 32 points of a segment, on v_mfma_f32_32x32x2_f32 (fp32
-// products and sums).  The points stay in registers as B operands; the centroids are A operands
+// Refine: every flagged point gets its argmax from fp64 similarities (exact for
+// the stored operands up to fp64 rounding), ties to the lowest centroid.
+// ============================================================================
+// The argmax of the k_s fp64 similarities of one point (row x) by the 256 threads of a workgroup, ties to
+// the lowest centroid; thread 0 has it, 0x7fffffff where no similarity is comparable.
+template <typename T, int D>
+__device__ __forceinline__ int refine_point(const T* __restrict__ x, const T* __restrict__ Cs, int k_s) {
+  __shared__ double xs[D];
+  __shared__ double bval[4];
+  __shared__ int bidx[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __syncthreads();
+  if (threadIdx.x < D) xs[threadIdx.x] = to_f64(x[threadIdx.x]);
+  __syncthreads();
+  double bv = -1.0e300;
+  int bi = 0x7fffffff;
+  for (int c = threadIdx.x; c < k_s; c += 256) {
+    const T* row = Cs + (size_t)c * D;
+    double a = 0.0;
+    constexpr int EPC = Elem<T>::EPC;
+#pragma unroll 2
+    for (int e0 = 0; e0 < D; e0 += 4 * EPC) {  // 16-byte chunks, summed in index order
+      uint4 raw[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) raw[u] = load16(row + e0 + u * EPC);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float f[EPC];
+        unpack<T>(raw[u], f);
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) a = fma(xs[e0 + u * EPC + e], (double)f[e], a);
+      }
+    }
+    if (a > bv) {  // c ascends within a thread, so strict > keeps the lowest index
+      bv = a;
+      bi = c;
+    }
+  }
+  for (int off = 32; off >= 1; off >>= 1) {
+    const double ov = __shfl_xor(bv, off);
+    const int oi = __shfl_xor(bi, off);
+    if (ov > bv || (ov == bv && oi < bi)) {
+      bv = ov;
+      bi = oi;
+    }
+  }
+  if (lane == 0) {
+    bval[wave] = bv;
+    bidx[wave] = bi;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < 4; ++w)
+      if (bval[w] > bv || (bval[w] == bv && bidx[w] < bi)) {
+        bv = bval[w];
+        bi = bidx[w];
+      }
+  return bi;
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void refine_kernel(const T* __restrict__ xhat, const T* __restrict__ chat,
+                                                     int32_t* __restrict__ assign,
+                                                     const int32_t* __restrict__ flag_list,
+                                                     const int32_t* __restrict__ flag_count, int S,
+                                                     int L, int kk, int N_idx) {
+  const int n = *flag_count;
+  for (int it = blockIdx.x; it < n; it += gridDim.x) {
+    const int gp = flag_list[it];
+    const int unit = gp / N_idx, pos = gp - unit * N_idx;
+    const int s = pos / L;
+    const int L_s = min(L, N_idx - s * L), k_s = min(kk, L_s);
+    const int bi = refine_point<T, D>(xhat + (size_t)gp * D, chat + ((size_t)unit * S + s) * kk * D, k_s);
+    if (threadIdx.x == 0 && bi < k_s) assign[gp] = bi;  // (no similarity is comparable: the point stays where it is)
+  }
+}
+
+// ============================================================================
+// Assign, f32: workgroups of four waves on v_mfma_f32_32x32x2_f32 (fp32 products and sums).  A wave keeps 32
+// points in registers as B operands; the centroids are A operands
 // read from the cache: a tile of 32 rows is 128 .. 256 bytes per lane for 2048 .. 4096 cycles of the
 // matrix pipe, which is the bound.  Component i of the 16-byte chunks of the wave's two halves is one
 // k pair; the order of k inside a dot product is free as long as both operands agree.  A lane holds
 // 16 centroids of one point; the ranking is in plain floats (inputs of any length are ranked).
-// (One point per thread with a chain of fp32 FMAs and centroids broadcast from LDS took 60 us a step
-// at 4096 tokens x 128 clusters x 64 channels, on 16 workgroups; 11 us so.)
+// SPLIT: the four waves have the same points and share out the tiles (fewer than 1024 fragments of points,
+// one per SIMD, else leave SIMDs idle); else each wave has its own points and all tiles.
+// Points whose two best are closer than the guard are decided here, from fp64 similarities.
+// (4096 tokens x 128 clusters x 64 channels, a round: one point per thread with a chain of fp32 FMAs 60 us; one
+// wave per 32 points with all tiles and the near-ties in a launch of their own 11.4 + 3; 4.9 us so.  Split
+// with 8192 fragments, 64 clusters x 128 channels: 92 us, not split 67.)
 // ============================================================================
-template <int D>
-__global__ __launch_bounds__(64) void assign_f32_kernel(
-    const float* __restrict__ xhat, const float* __restrict__ chat, int32_t* __restrict__ assign,
-    int32_t* __restrict__ flag_list, int32_t* __restrict__ flag_count, int S, int L, int kk, int N_idx,
-    int frags_per_seg) {
-  constexpr int KS = D / 8;  // pairs of 16-byte chunks, one per half of the wave
+template <int D, bool SPLIT>
+__global__ __launch_bounds__(256) void assign_f32_kernel(
+    const float* __restrict__ xhat, const float* __restrict__ chat, int32_t* __restrict__ assign, int S, int L, int kk,
+    int N_idx, int wgs_per_seg) {
+  constexpr int KS = D / 8, NW = 4;  // pairs of 16-byte chunks, one per half of the wave
+  constexpr int FRAGS = SPLIT ? 1 : NW;
+  __shared__ float part_best[SPLIT ? NW : 1][32], part_second[SPLIT ? NW : 1][32];
+  __shared__ int part_row[SPLIT ? NW : 1][32];
+  __shared__ int near_p[32 * FRAGS], near_n;
   const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
-  const int sg = wg / frags_per_seg, frag = wg - sg * frags_per_seg;
+  const int sg = wg / wgs_per_seg, wg_frag = (wg - sg * wgs_per_seg) * FRAGS;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
-  if (32 * frag >= si.L_s) return;
-  const int lane = threadIdx.x, half = lane >> 5, col = lane & 31;
-  const int point = 32 * frag + col;
+  if (32 * wg_frag >= si.L_s) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5, col = lane & 31;
+  const int frag = wg_frag + (SPLIT ? 0 : wave);
   const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
-  const float* xr = xhat + (gp0 + min(point, si.L_s - 1)) * D + half * 4;
-  const float* Cs = chat + (size_t)sg * kk * D + half * 4;
+  const float* xr = xhat + (gp0 + min(32 * frag + col, si.L_s - 1)) * D + half * 4;
+  const float* Cs = chat + (size_t)sg * kk * D;
+  if (threadIdx.x == 0) near_n = 0;
   uint4 b[KS];
 #pragma unroll
   for (int s = 0; s < KS; ++s) b[s] = load16(xr + 8 * s);
   float best = kNegHuge, second = kNegHuge;
   int bidx = 0;
 #pragma unroll 1
-  for (int t = 0; 32 * t < si.k_s; ++t) {
-    const float* cr = Cs + (size_t)min(32 * t + col, si.k_s - 1) * D;
+  for (int t = SPLIT ? wave : 0; 32 * t < si.k_s; t += SPLIT ? NW : 1) {
+    const float* cr = Cs + (size_t)min(32 * t + col, si.k_s - 1) * D + half * 4;
     floatx16 acc = {};
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -1083,87 +1169,34 @@ __global__ __launch_bounds__(64) void assign_f32_kernel(
       bidx = up ? row : bidx;
     }
   }
-  // lanes l and l ^ 32 hold the same point over disjoint centroid rows
-  const float ob = __shfl_xor(best, 32), os = __shfl_xor(second, 32);
-  const int oi = __shfl_xor(bidx, 32);
-  second = fmaxf(fminf(best, ob), fmaxf(second, os));
-  const bool other = ob > best || (ob == best && oi < bidx);
-  bidx = other ? oi : bidx;
-  best = fmaxf(best, ob);
-  if (half == 0 && point < si.L_s) {
-    assign[gp0 + point] = bidx;
-    if (best - second < kAssignGuard) flag_list[atomicAdd(flag_count, 1)] = (int32_t)(gp0 + point);
+  auto merge = [&](float ob, float os, int oi) {
+    second = fmaxf(fminf(best, ob), fmaxf(second, os));
+    const bool other = ob > best || (ob == best && oi < bidx);
+    bidx = other ? oi : bidx;
+    best = fmaxf(best, ob);
+  };
+  // lanes l and l ^ 32 hold the same point over disjoint centroid rows, and so do the waves of SPLIT
+  merge(__shfl_xor(best, 32), __shfl_xor(second, 32), __shfl_xor(bidx, 32));
+  if constexpr (SPLIT) {
+    if (half == 0) {
+      part_best[wave][col] = best;
+      part_second[wave][col] = second;
+      part_row[wave][col] = bidx;
+    }
   }
-}
-
-// ============================================================================
-// Refine: every flagged point gets its argmax from fp64 similarities (exact for
-// the stored operands up to fp64 rounding), ties to the lowest centroid.
-// ============================================================================
-template <typename T, int D>
-__global__ __launch_bounds__(256) void refine_kernel(const T* __restrict__ xhat, const T* __restrict__ chat,
-                                                     int32_t* __restrict__ assign,
-                                                     const int32_t* __restrict__ flag_list,
-                                                     const int32_t* __restrict__ flag_count, int S,
-                                                     int L, int kk, int N_idx) {
-  __shared__ double xs[D];
-  __shared__ double bval[4];
-  __shared__ int bidx[4];
-  const int n = *flag_count;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int it = blockIdx.x; it < n; it += gridDim.x) {
-    const int gp = flag_list[it];
-    const int unit = gp / N_idx, pos = gp - unit * N_idx;
-    const int s = pos / L;
-    const int L_s = min(L, N_idx - s * L), k_s = min(kk, L_s);
-    const T* Cs = chat + ((size_t)unit * S + s) * kk * D;
-    __syncthreads();
-    if (threadIdx.x < D) xs[threadIdx.x] = to_f64(xhat[(size_t)gp * D + threadIdx.x]);
-    __syncthreads();
-    double bv = -1.0e300;
-    int bi = 0x7fffffff;
-    for (int c = threadIdx.x; c < k_s; c += 256) {
-      const T* row = Cs + (size_t)c * D;
-      double a = 0.0;
-      constexpr int EPC = Elem<T>::EPC;
-      for (int e0 = 0; e0 < D; e0 += 4 * EPC) {  // four 16-byte chunks in flight, summed in index order
-        uint4 raw[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) raw[u] = load16(row + e0 + u * EPC);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          float f[EPC];
-          unpack<T>(raw[u], f);
-#pragma unroll
-          for (int e = 0; e < EPC; ++e) a = fma(xs[e0 + u * EPC + e], (double)f[e], a);
-        }
-      }
-      if (a > bv) {  // c ascends within a thread, so strict > keeps the lowest index
-        bv = a;
-        bi = c;
-      }
-    }
-    for (int off = 32; off >= 1; off >>= 1) {
-      const double ov = __shfl_xor(bv, off);
-      const int oi = __shfl_xor(bi, off);
-      if (ov > bv || (ov == bv && oi < bi)) {
-        bv = ov;
-        bi = oi;
-      }
-    }
-    if (lane == 0) {
-      bval[wave] = bv;
-      bidx[wave] = bi;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int w = 1; w < 4; ++w)
-        if (bval[w] > bv || (bval[w] == bv && bidx[w] < bi)) {
-          bv = bval[w];
-          bi = bidx[w];
-        }
-      if (bi < k_s) assign[gp] = bi;  // (no similarity is comparable: the point stays where it is)
-    }
+  __syncthreads();
+  const int point = 32 * frag + col;
+  if (half == 0 && (!SPLIT || wave == 0) && point < si.L_s) {
+    if constexpr (SPLIT)
+      for (int w = 1; w < NW; ++w) merge(part_best[w][col], part_second[w][col], part_row[w][col]);
+    assign[gp0 + point] = bidx;  // (stands where nothing is comparable)
+    if (best - second < kAssignGuard) near_p[atomicAdd(&near_n, 1)] = point;
+  }
+  __syncthreads();
+  for (int i = 0; i < near_n; ++i) {
+    const int p = near_p[i];
+    const int bi = refine_point<float, D>(xhat + (gp0 + p) * D, Cs, si.k_s);
+    if (threadIdx.x == 0 && bi < si.k_s) assign[gp0 + p] = bi;
   }
 }
 
@@ -1373,6 +1406,55 @@ __device__ __forceinline__ void update_cluster(const T* X, const int32_t* ord, i
 // component spread over more than 2^34 at bf16) is summed again one by one by one group.
 constexpr int UPD_BIG = 128;
 
+// One such cluster by the NT threads of a workgroup: the n member rows ord[0, n) of the segment's points X
+// to the centroid row dst (sums: also the sum itself, or null; used where the test holds).
+template <typename T, int D, int NT>
+__device__ __forceinline__ void update_cluster_by_workgroup(const T* X, const int32_t* ord, int n, T* dst, double* sums) {
+  constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = NT / LPR;
+  __shared__ double part[GROUPS * D];
+  __shared__ int erange[2 * GROUPS];
+  const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
+  const int per = (n + GROUPS - 1) / GROUPS;
+  const int i0 = min(n, grp * per), i1 = min(n, i0 + per);
+  double acc[EPC];
+#pragma unroll
+  for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
+  int emin = 255, emax = 0;
+  sum_members<T, D, 4, true, true>(X + sub * EPC, ord + i0, i1 - i0, acc, emin, emax);
+#pragma unroll
+  for (int off = 1; off < LPR; off <<= 1) {
+    emin = min(emin, __shfl_xor(emin, off));
+    emax = max(emax, __shfl_xor(emax, off));
+  }
+#pragma unroll
+  for (int e = 0; e < EPC; ++e) part[grp * D + sub * EPC + e] = acc[e];
+  if (sub == 0) {
+    erange[2 * grp] = emin;
+    erange[2 * grp + 1] = emax;
+  }
+  __syncthreads();
+  if (grp == 0) {
+    double tot[EPC];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) tot[e] = part[sub * EPC + e];
+    int lo = erange[0], hi = erange[1];
+#pragma unroll 1
+    for (int g = 1; g < GROUPS; ++g) {
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) tot[e] += part[g * D + sub * EPC + e];
+      lo = min(lo, erange[2 * g]);
+      hi = max(hi, erange[2 * g + 1]);
+    }
+    const int lg = 32 - __clz(n - 1);  // ceil(log2 n), n > UPD_BIG
+    if (sums) store_sums<EPC>(sums + sub * EPC, tot);
+    if (hi < lo || hi - lo + lg <= 52 - MantissaBits<T>::value)  // (hi < lo: every addend is zero)
+      finish_centroid<T, D>(tot, dst + sub * EPC);
+    else
+      update_cluster<T, D, 4, true>(X, ord, n, dst + sub * EPC, sub);
+  }
+  __syncthreads();
+}
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void update_big_kernel(const T* __restrict__ xhat, T* __restrict__ chat,
                                                          const int32_t* __restrict__ order,
@@ -1382,60 +1464,14 @@ __global__ __launch_bounds__(256) void update_big_kernel(const T* __restrict__ x
                                                          const int32_t* __restrict__ big_count,
                                                          double* sums, long long sums_skip, int S, int L,
                                                          int kk, int N_idx) {
-  constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
-  __shared__ double part[GROUPS * D];
-  __shared__ int erange[2 * GROUPS];
-  const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   const int nbig = *big_count;
 #pragma unroll 1
   for (int b = blockIdx.x; b < nbig; b += gridDim.x) {  // (the same for every thread of the workgroup)
     const int gc = big_list[b];
-    const int sg = gc / kk;
-    const SegInfo si = seg_info(sg, S, L, kk, N_idx);
+    const SegInfo si = seg_info(gc / kk, S, L, kk, N_idx);
     const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
-    const int n = count[gc];
-    const int32_t* ord = order + p0 + start[gc];
-    const T* X = xhat + p0 * D + sub * EPC;
-    const int per = (n + GROUPS - 1) / GROUPS;
-    const int i0 = min(n, grp * per), i1 = min(n, i0 + per);
-    double acc[EPC];
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
-    int emin = 255, emax = 0;
-    sum_members<T, D, 4, true, true>(X, ord + i0, i1 - i0, acc, emin, emax);
-#pragma unroll
-    for (int off = 1; off < LPR; off <<= 1) {
-      emin = min(emin, __shfl_xor(emin, off));
-      emax = max(emax, __shfl_xor(emax, off));
-    }
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) part[grp * D + sub * EPC + e] = acc[e];
-    if (sub == 0) {
-      erange[2 * grp] = emin;
-      erange[2 * grp + 1] = emax;
-    }
-    __syncthreads();
-    if (grp == 0) {
-      double tot[EPC];
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) tot[e] = part[sub * EPC + e];
-      int lo = erange[0], hi = erange[1];
-#pragma unroll 1
-      for (int g = 1; g < GROUPS; ++g) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) tot[e] += part[g * D + sub * EPC + e];
-        lo = min(lo, erange[2 * g]);
-        hi = max(hi, erange[2 * g + 1]);
-      }
-      const int lg = 32 - __clz(n - 1);  // ceil(log2 n), n > UPD_BIG
-      T* dst = chat + (size_t)gc * D + sub * EPC;
-      if (sums) store_sums<EPC>(sums + si.unit * sums_skip + (size_t)gc * D + sub * EPC, tot);  // (used where the test below holds)
-      if (hi < lo || hi - lo + lg <= 52 - MantissaBits<T>::value)  // (hi < lo: every addend is zero)
-        finish_centroid<T, D>(tot, dst);
-      else
-        update_cluster<T, D, 4, true>(xhat + p0 * D, ord, n, dst, sub);
-    }
-    __syncthreads();
+    update_cluster_by_workgroup<T, D, 256>(xhat + p0 * D, order + p0 + start[gc], count[gc], chat + (size_t)gc * D,
+                                           sums ? sums + si.unit * sums_skip + (size_t)gc * D : nullptr);
   }
 }
 
@@ -1514,6 +1550,125 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
                                   chat + (size_t)gc * D + sub * EPC, sub);
   }
 }
+
+// ============================================================================
+// The f32 builds' update, with the sort in it: a workgroup owns the clusters [c_lo, c_hi) of a segment, reads
+// this round's and the last round's cluster of every point of the segment, and sorts the points of its
+// changed clusters (in the first round and where `all` is set: of all its clusters) into their place of order[],
+// positions ascending; their counts and first places go to count[] and start[].  Then a group of lanes
+// per changed cluster sums its members in that order (fp32 sums may round in fp64, so the order is kept),
+// the whole workgroup one of more than UPD_BIG.  `all`: the last round; nothing is summed.
+// (One workgroup per segment sorting all points, update_touched_kernel and update_big_kernel: three launches
+// and 6.2 + 2 .. 12 + 1.3 us a round for 2 segments of 2048 points x 128 clusters, 4.2 .. 15 us so; a whole
+// build of them 285 -> 163 us, of 100 segments of 4096 points x 256 clusters 2.03 -> 1.99 ms.)
+// ============================================================================
+constexpr int SCAN_NT = 512, SCAN_CLUSTERS = 64;  // threads; most clusters of a workgroup
+
+template <typename T, int D>
+__global__ __launch_bounds__(SCAN_NT) void update_scan_kernel(
+    const T* __restrict__ xhat, T* __restrict__ chat, const int32_t* __restrict__ assign,
+    const int32_t* __restrict__ before, int32_t* order, int32_t* __restrict__ count, int32_t* __restrict__ start,
+    int first_round, int all, int S, int L, int kk, int N_idx, int span, int pieces) {
+  constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = SCAN_NT / LPR, NW = SCAN_NT / 64, U = 4;
+  __shared__ int hist[NW * SCAN_CLUSTERS];   // members per (wave's stripe of points, cluster); then places
+  __shared__ int lower[NW];                  // points in clusters before c_lo, per stripe
+  __shared__ int changed[SCAN_CLUSTERS], cnt[SCAN_CLUSTERS], first[SCAN_CLUSTERS];
+  const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
+  const int sg = wg / pieces, piece = wg - sg * pieces;
+  const SegInfo si = seg_info(sg, S, L, kk, N_idx);
+  const int c_lo = piece * span, c_n = min(si.k_s - c_lo, span);
+  if (c_n <= 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = tid % LPR;
+  const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
+  const int32_t* as = assign + p0;
+  const int32_t* pv = before + p0;
+  const bool every = first_round || all;
+  for (int i = tid; i < NW * SCAN_CLUSTERS; i += SCAN_NT) hist[i] = 0;
+  if (tid < SCAN_CLUSTERS) changed[tid] = every ? 1 : 0;
+  __syncthreads();
+  const int stripe = (si.L_s + NW - 1) / NW;
+  const int s0 = min(si.L_s, wave * stripe), s1 = min(si.L_s, s0 + stripe);
+  int below = 0;
+  for (int i0 = s0; i0 < s1; i0 += 64 * U) {
+    int a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + 64 * u + lane, s1 - 1);
+      a[u] = as[i] - c_lo;
+      b[u] = every ? a[u] : pv[i] - c_lo;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool on = i0 + 64 * u + lane < s1;
+      below += __popcll(__ballot(on && a[u] < 0));
+      const bool in = on && a[u] >= 0 && a[u] < c_n;
+      if (in) atomicAdd(&hist[wave * SCAN_CLUSTERS + a[u]], 1);
+      if (on && a[u] != b[u]) {
+        if (in) changed[a[u]] = 1;
+        if (b[u] >= 0 && b[u] < c_n) changed[b[u]] = 1;
+      }
+    }
+  }
+  if (lane == 0) lower[wave] = below;
+  __syncthreads();
+  if (!__ballot(lane < c_n && changed[min(lane, c_n - 1)])) return;  // (the same for every wave)
+  if (wave == 0) {  // places: clusters in order, each cluster's stripes in order
+    int n = 0, base = 0;
+    for (int w = 0; w < NW; ++w) {
+      const int t = lane < c_n ? hist[w * SCAN_CLUSTERS + lane] : 0;
+      hist[w * SCAN_CLUSTERS + lane] = n;
+      n += t;
+      base += lower[w];
+    }
+    const int at = base + wave_incl_scan(n) - n;
+    for (int w = 0; w < NW; ++w) hist[w * SCAN_CLUSTERS + lane] += at;
+    cnt[lane] = n;
+    first[lane] = at;
+    if (lane < c_n && changed[lane]) {
+      count[(size_t)sg * kk + c_lo + lane] = n;
+      start[(size_t)sg * kk + c_lo + lane] = at;
+    }
+  }
+  __syncthreads();
+  for (int i1 = s0; i1 < s1; i1 += 64 * U) {
+    int a[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = as[min(i1 + 64 * u + lane, s1 - 1)] - c_lo;
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+      const int i = i1 + 64 * u + lane;
+      const int key = u == 0 ? a[0] : u == 1 ? a[1] : u == 2 ? a[2] : a[3];
+      const bool on = i < s1 && key >= 0 && key < c_n && changed[min(max(key, 0), c_n - 1)];
+      uint64_t peers = __ballot(on);
+      if (!peers) continue;
+#pragma unroll
+      for (int bit = 0; bit < 6; ++bit) {
+        const uint64_t bal = __ballot((key >> bit) & 1);
+        peers &= ((key >> bit) & 1) ? bal : ~bal;
+      }
+      const int rank = __popcll(peers & ((1ull << lane) - 1ull)), same = __popcll(peers);
+      if (on) {
+        const int place = hist[wave * SCAN_CLUSTERS + key];
+        order[p0 + place + rank] = i;
+        __builtin_amdgcn_wave_barrier();
+        if (rank == same - 1) hist[wave * SCAN_CLUSTERS + key] = place + same;
+      }
+      __threadfence_block();
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  if (all) return;
+  __syncthreads();
+  const T* X = xhat + p0 * D;
+  T* Cs = chat + ((size_t)sg * kk + c_lo) * D;
+  for (int c = tid / LPR; c < c_n; c += GROUPS)
+    if (changed[c] && cnt[c] <= UPD_BIG)
+      update_cluster<T, D, 8, false>(X, order + p0 + first[c], cnt[c], Cs + (size_t)c * D + sub * EPC, sub);
+  for (int c = 0; c < c_n; ++c)
+    if (changed[c] && cnt[c] > UPD_BIG)
+      update_cluster_by_workgroup<T, D, SCAN_NT>(X, order + p0 + first[c], cnt[c], Cs + (size_t)c * D, nullptr);
+}
+static_assert(SCAN_CLUSTERS == 64, "a cluster per lane, six key bits");
 
 // ============================================================================
 // Update from the points that moved (later rounds of the resident bf16 path): the fp64 member
@@ -2125,13 +2280,17 @@ static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t
       WAVE_LAUNCH("assign_mfma", (assign_mfma_kernel<D, 1, 8>), segs * wps, 64 * 8, 0, st, xhat, chat,
                   assign, flag, nflag, S, L, kk, N_idx, wps);
     }
+    WAVE_LAUNCH("refine", (refine_kernel<T, D>), refine_wgs, 256, 0, st, xhat, chat, assign, flag, nflag, S,
+                L, kk, N_idx);
   } else {
     const int frags = (Lmax + 31) / 32;
-    WAVE_LAUNCH("assign_f32", (assign_f32_kernel<D>), segs * frags, 64, 0, st, xhat, chat, assign, flag, nflag, S, L,
-                kk, N_idx, frags);
+    if (segs * frags < 1024)
+      WAVE_LAUNCH("assign_f32", (assign_f32_kernel<D, true>), segs * frags, 256, 0, st, xhat, chat, assign, S, L, kk,
+                  N_idx, frags);
+    else
+      WAVE_LAUNCH("assign_f32", (assign_f32_kernel<D, false>), segs * ((frags + 3) / 4), 256, 0, st, xhat, chat, assign,
+                  S, L, kk, N_idx, (frags + 3) / 4);
   }
-  WAVE_LAUNCH("refine", (refine_kernel<T, D>), refine_wgs, 256, 0, st, xhat, chat, assign, flag, nflag, S,
-              L, kk, N_idx);
 }
 
 template <typename T, int D>
@@ -2202,13 +2361,28 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   WAVE_LAUNCH("init", (init_kernel<T, D>), g.segs, 256, 2 * sizeof(int) * (size_t)kk, st, xhat, chat, S, L,
               kk, N_idx, ix.Hkv, seed, seg_id_base);
 
-  int W = SORT_HIST_INTS / kk;
-  if (W > 16) W = 16;
-  if (W < 1) W = 1;
-  const size_t sort_lds = ((size_t)W * kk + kk) * sizeof(int);
-  const int kb = key_bits_for(kk);
   const int cl_grid = (ncl + GROUPS - 1) / GROUPS;
-  if constexpr (sizeof(T) == 2) {
+  if constexpr (sizeof(T) == 4) {
+    // Two launches a round.  The assignments of even and of odd rounds have an array each.  At least as many
+    // clusters a workgroup as it has groups of lanes, more where that leaves a workgroup for every CU: each
+    // reads a segment's assignments (100 segments of 4096 points, 8 workgroups a segment 2.06 ms a build, 4 1.99).
+    int span = SCAN_NT / (D / Elem<T>::EPC);
+    while (2 * span <= SCAN_CLUSTERS && (long long)g.segs * ((kk + 2 * span - 1) / (2 * span)) >= 256) span *= 2;
+    const int pieces = (kk + span - 1) / span;
+    for (int t = 0; t < iters; ++t) {
+      int32_t* now = t & 1 ? prev : assign;
+      launch_assign<T, D>(xhat, chat, now, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr, t, flag, nflag, S, L, kk,
+                          N_idx, g.segs, 0, st);
+      WAVE_LAUNCH("update", (update_scan_kernel<T, D>), g.segs * pieces, SCAN_NT, 0, st, xhat, chat, now,
+                  t & 1 ? assign : prev, order, count, start, t == 0 ? 1 : 0, t + 1 == iters ? 1 : 0, S, L, kk, N_idx, span,
+                  pieces);
+    }
+  } else {
+    int W = SORT_HIST_INTS / kk;
+    if (W > 16) W = 16;
+    if (W < 1) W = 1;
+    const size_t sort_lds = ((size_t)W * kk + kk) * sizeof(int);
+    const int kb = key_bits_for(kk);
     if (small) {
       auto run = [&](auto kernel, int waves, bool keep_sums) {
         WAVE_LAUNCH("kmeans_small", kernel, g.segs, 64 * waves, small_kmeans_lds<D>(kk, keep_sums), st, xhat, chat,
@@ -2222,38 +2396,36 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
       else if (keep_sums) run(kmeans_small_kernel<D, 0, true>, SMALL_NW, true);
       else run(kmeans_small_kernel<D, 0, false>, SMALL_NW, false);
     }
-  }
-  auto sort = [&](int32_t* prev_or_null, int t) {
-    WAVE_LAUNCH("sort", sort_kernel, g.segs, 64 * W, sort_lds, st, assign, order, count, start, nflag,
-                prev_or_null, changed, t == 0 ? 1 : 0, S, L, kk, N_idx, kb);
-  };
-  // clusters whose marks a workgroup of the later updates reads: 256 in a large batch; few enough to
-  // give 1024 workgroups, down to one per group of lanes (2 segments of 128 clusters in one workgroup:
-  // 125 us a round, 12 us so)
-  int span = (ncl + 1023) / 1024;
-  span = span < GROUPS ? GROUPS : (span > 256 ? 256 : span);
-  auto update = [&](int t) {
-    // (first round: nothing to compare with, every cluster is updated and every mark cleared.
-    // Large clusters go onto a list, which the second kernel takes: nflag[1] counts them and
-    // the flagged-point list, consumed by refine, is free to hold them)
-    if (t == 0)
-      WAVE_LAUNCH("update", (update_kernel<T, D>), cl_grid, 256, 0, st, xhat, chat, order, count,
-                  start, changed, flag, nflag + 1, sums, sums_skip, S, L, kk, N_idx, ncl);
-    else
-      WAVE_LAUNCH("update", (update_touched_kernel<T, D>), (ncl + span - 1) / span, 256, 0, st, xhat, chat,
-                  order, count, start, changed, flag, nflag + 1, S, L, kk, N_idx, ncl, span);
-    const int big_grid = ncl / UPD_BIG + 1 < 2048 ? ncl / UPD_BIG + 1 : 2048;
-    WAVE_LAUNCH("update", (update_big_kernel<T, D>), big_grid, 256, 0, st, xhat, chat, order, count,
-                start, flag, nflag + 1, sums, sums_skip, S, L, kk, N_idx);
-  };
-  for (int t = 0; t < iters && !small; ++t) {
-    // Rounds 0 and 1 meet all new centroids; from round 2 on only the changed ones are compared.
-    launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, bounds_skip, delta && t >= 2 ? changed : nullptr,
-                        nchanged[(t + 1) & 1], nlisted[t & 1], nlisted[(t + 1) & 1], t, flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
-    const bool last = t + 1 == iters;
-    if (!delta || t == 0 || last) sort(delta ? nullptr : prev, t);
-    if (last) break;
-    if constexpr (sizeof(T) == 2) {
+    auto sort = [&](int32_t* prev_or_null, int t) {
+      WAVE_LAUNCH("sort", sort_kernel, g.segs, 64 * W, sort_lds, st, assign, order, count, start, nflag,
+                  prev_or_null, changed, t == 0 ? 1 : 0, S, L, kk, N_idx, kb);
+    };
+    // clusters whose marks a workgroup of the later updates reads: 256 in a large batch; few enough to
+    // give 1024 workgroups, down to one per group of lanes (2 segments of 128 clusters in one workgroup:
+    // 125 us a round, 12 us so)
+    int span = (ncl + 1023) / 1024;
+    span = span < GROUPS ? GROUPS : (span > 256 ? 256 : span);
+    auto update = [&](int t) {
+      // (first round: nothing to compare with, every cluster is updated and every mark cleared.
+      // Large clusters go onto a list, which the second kernel takes: nflag[1] counts them and
+      // the flagged-point list, consumed by refine, is free to hold them)
+      if (t == 0)
+        WAVE_LAUNCH("update", (update_kernel<T, D>), cl_grid, 256, 0, st, xhat, chat, order, count,
+                    start, changed, flag, nflag + 1, sums, sums_skip, S, L, kk, N_idx, ncl);
+      else
+        WAVE_LAUNCH("update", (update_touched_kernel<T, D>), (ncl + span - 1) / span, 256, 0, st, xhat, chat,
+                    order, count, start, changed, flag, nflag + 1, S, L, kk, N_idx, ncl, span);
+      const int big_grid = ncl / UPD_BIG + 1 < 2048 ? ncl / UPD_BIG + 1 : 2048;
+      WAVE_LAUNCH("update", (update_big_kernel<T, D>), big_grid, 256, 0, st, xhat, chat, order, count,
+                  start, flag, nflag + 1, sums, sums_skip, S, L, kk, N_idx);
+    };
+    for (int t = 0; t < iters && !small; ++t) {
+      // Rounds 0 and 1 meet all new centroids; from round 2 on only the changed ones are compared.
+      launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, bounds_skip, delta && t >= 2 ? changed : nullptr,
+                          nchanged[(t + 1) & 1], nlisted[t & 1], nlisted[(t + 1) & 1], t, flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
+      const bool last = t + 1 == iters;
+      if (!delta || t == 0 || last) sort(delta ? nullptr : prev, t);
+      if (last) break;
       if (delta && t >= 1) {
         // a few segments are shared by several workgroups each, of at least 64 clusters
         int pieces = 1;
@@ -2262,8 +2434,8 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
                     chat, sums, sums_skip, assign, prev, changed, nchanged[t & 1], nchanged[(t + 1) & 1], range, order, count, start, t, S, L, kk, N_idx, pieces, kb);
         continue;
       }
+      update(t);
     }
-    update(t);
   }
   WAVE_LAUNCH("finalize", (finalize_kernel<T, D>), cl_grid, 256, 0, st, K, V, order, count, start,
               static_cast<T*>(ix.centroids), static_cast<T*>(ix.vsum), ix.sizes, ix.offsets, ix.perm,

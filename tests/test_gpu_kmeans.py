@@ -189,3 +189,22 @@ def test_segments_of_one_workgroup_match_oracle(kind, d, L, k, iters):
     torch.cuda.synchronize()
     for name in wb.BUFFER_NAMES:
         assert torch.equal(ix.t[name].cpu().double(), ref[name].reshape(ix.t[name].shape).double()), name
+
+
+# f32 rounds: the tiles shared by the waves of a workgroup, or (1024 fragments of points or more: the last two)
+# a wave per fragment; workgroups of 16 .. 64 clusters with a remainder; clusters of more than 128 members
+# whose sums are exact in any order and ("wide") are not; clusters that stay empty.
+@pytest.mark.parametrize("kind,B,d,N,L,k,iters", [
+    ("mixture", 2, 64, 4101, 2048, 128, 6), ("plain", 2, 128, 1005, 1000, 33, 5), ("ties", 2, 64, 700, 333, 65, 5),
+    ("plain", 1, 128, 805, 800, 1, 3), ("wide", 2, 64, 2405, 1200, 7, 4), ("plain", 1, 64, 2405, 2400, 200, 4),
+    ("mixture", 2, 64, 17005, 8500, 17, 4), ("plain", 2, 128, 17005, 17000, 40, 3)])
+def test_f32_rounds_match_oracle(kind, B, d, N, L, k, iters):
+    wl = synth.scaled(synth.WORKLOADS["tiny_f32"], name="f32", dtype="f32", B=B, Hq=1, Hkv=1, N=N, d=d, n_sink=2,
+                      n_local=3, segment_len=L, clusters_per_segment=k, iters=iters)
+    K = _keys(kind, B, N, d, N + k)
+    V = torch.randn(B, 1, N, d, generator=torch.Generator().manual_seed(1))
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), wl.n_sink, wl.n_local, L, k, iters, 0)
+    torch.cuda.synchronize()
+    for name in wb.BUFFER_NAMES:
+        assert torch.equal(ix.t[name].cpu().double(), ref[name].reshape(ix.t[name].shape).double()), name
