@@ -60,7 +60,9 @@ __device__ __forceinline__ double div_shared(double a, double b, double r) {
 }
 
 // ============================================================================
-// Segment mean (fp64).  One workgroup per segment; fixed summation order.
+// Segment mean (fp64).  `pieces` workgroups per segment sum a run of its rows each, in a fixed order; with more than
+// one they leave their sums in `mean` for normalise_kernel to add up in order, [segment, piece, D].
+// (A few segments: 32 of 8192 points 70 us with one workgroup each, 14 us with eight.)
 // ============================================================================
 template <typename T, int D>
 __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, double* __restrict__ mean,
@@ -68,20 +70,21 @@ __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, 
                                                        int32_t* __restrict__ range,
                                                        int32_t* __restrict__ nchanged,
                                                        int32_t* __restrict__ nlisted, int S, int L,
-                                                       int kk, int N, int N_idx, int n_sink) {
+                                                       int kk, int N, int N_idx, int n_sink, int pieces) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
-  const int sg = blockIdx.x;
+  const int sg = blockIdx.x / pieces, piece = blockIdx.x - sg * pieces;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
-  if (sg == 0 && threadIdx.x == 0) *flag_count = 0;
-  if (range && threadIdx.x < 2) range[2 * sg + threadIdx.x] = threadIdx.x ? 0 : 255;  // for normalise_kernel
-  if (range && threadIdx.x == 0) nchanged[sg] = nlisted[sg] = 0;  // for update_moves_kernel, assign_listed_kernel
+  if (blockIdx.x == 0 && threadIdx.x == 0) *flag_count = 0;
+  if (range && piece == 0 && threadIdx.x < 2) range[2 * sg + threadIdx.x] = threadIdx.x ? 0 : 255;  // for normalise_kernel
+  if (range && piece == 0 && threadIdx.x == 0) nchanged[sg] = nlisted[sg] = 0;  // for update_moves_kernel, assign_listed_kernel
   const T* Ku = K + ((size_t)si.unit * N + n_sink + si.seg_start) * D + sub * EPC;
   double acc[EPC];
 #pragma unroll
   for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
-  int i = grp;
-  for (; i + 3 * GROUPS < si.L_s; i += 4 * GROUPS) {  // four rows in flight, added in row order
+  const int per = (si.L_s + pieces - 1) / pieces, hi = min(si.L_s, (piece + 1) * per);
+  int i = min(si.L_s, piece * per) + grp;
+  for (; i + 3 * GROUPS < hi; i += 4 * GROUPS) {  // four rows in flight, added in row order
     uint4 raw[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) raw[u] = load16(Ku + (size_t)(i + u * GROUPS) * D);
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, 
       for (int e = 0; e < EPC; ++e) acc[e] += (double)f[e];
     }
   }
-  for (; i < si.L_s; i += GROUPS) {
+  for (; i < hi; i += GROUPS) {
     float f[EPC];
     unpack<T>(load16(Ku + (size_t)i * D), f);
 #pragma unroll
@@ -106,7 +109,7 @@ __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, 
   if (threadIdx.x < D) {
     double s = 0.0;
     for (int g = 0; g < GROUPS; ++g) s += red[g][threadIdx.x];
-    mean[(size_t)sg * D + threadIdx.x] = s / (double)si.L_s;
+    mean[(size_t)blockIdx.x * D + threadIdx.x] = pieces == 1 ? s / (double)si.L_s : s;
   }
 }
 
@@ -153,25 +156,30 @@ struct MantissaBits<float> {
 };
 
 // ============================================================================
-// Centre, normalise, round to the storage type.  A workgroup takes NORM_ROWS rows of one
-// segment and keeps the mean in registers.  (HBM-bound.  With rows of any segment in a
-// workgroup every lane read its 64 bytes of the fp64 mean again for each 16 bytes of key:
-// 2.16 ms for 16 sequences x 120K tokens, 1.95 ms so, 4.1 TB/s.)  Four rows of a group in flight where
+// Centre, normalise, round to the storage type.  A workgroup takes `row_step` rows of one
+// segment and keeps the mean in registers; HBM-bound (16 sequences x 120K tokens 1.48 ms, 5.4 TB/s; with
+// every quotient and rounding in fp64 1.88 ms; with rows of any segment in a workgroup, every lane reading its 64
+// bytes of the fp64 mean again for each 16 bytes of key, 2.16 ms).  Four rows of a group in flight where
 // that many are left, else one by one: four with repeats of the last one took 485 us for 65536
 // segments of 16 rows, 172 us so.
+// row_step: 128, or 256 where these workgroups are all resident at once (6 per CU) and those of 128 are not: 32
+// segments of 8192 rows 42 and 33 us; 1920 of them 1.48 and 1.51 ms.
 // ============================================================================
-constexpr int NORM_ROWS = 128;
+constexpr int NORM_ROWS = 128, NORM_RESIDENT = 6 * 256;
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
                                                         const double* __restrict__ mean,
+                                                        double* __restrict__ mean_out,
                                                         T* __restrict__ xhat, int32_t* __restrict__ range, int S, int L, int kk, int N,
-                                                        int N_idx, int n_sink, int chunks) {
+                                                        int N_idx, int n_sink, int chunks, int row_step, int pieces) {
+  // mean: of every segment, or with pieces > 1 the sums of its pieces (a segment's first workgroup then leaves
+  // the mean in mean_out, where it is without pieces)
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR, U = 4;
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   const int sg = blockIdx.x / chunks, chunk = blockIdx.x - sg * chunks;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
-  const int lo = chunk * NORM_ROWS, hi = min(si.L_s, lo + NORM_ROWS);
+  const int lo = chunk * row_step, hi = min(si.L_s, lo + row_step);
   if (lo >= hi) return;
   // (range: the smallest and the largest exponent field of the segment's nonzero elements)
   __shared__ int seg_emin, seg_emax;
@@ -181,9 +189,21 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
   }
   typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
   u16x2 least = {0xffff, 0xffff}, most = {0, 0};  // magnitude bits - 1 (zero: the largest), magnitude bits
+  __shared__ double mean_s[D];
+  if (pieces > 1) {
+    if (threadIdx.x < D) {
+      double m = 0.0;
+#pragma unroll 8
+      for (int j = 0; j < pieces; ++j) m += mean[((size_t)sg * pieces + j) * D + threadIdx.x];
+      m /= (double)si.L_s;
+      mean_s[threadIdx.x] = m;
+      if (chunk == 0) mean_out[(size_t)sg * D + threadIdx.x] = m;
+    }
+    __syncthreads();
+  }
   double mu[EPC];
 #pragma unroll
-  for (int e = 0; e < EPC; ++e) mu[e] = mean[(size_t)sg * D + sub * EPC + e];
+  for (int e = 0; e < EPC; ++e) mu[e] = pieces == 1 ? mean[(size_t)sg * D + sub * EPC + e] : mean_s[sub * EPC + e];
   const T* Ku = K + ((size_t)si.unit * N + n_sink + si.seg_start) * D + sub * EPC;
   T* Xu = xhat + ((size_t)si.unit * N_idx + si.seg_start) * D + sub * EPC;
   auto rows = [&](auto batch, int r0) {  // rows r0, r0 + GROUPS, ... below hi, in flight together
@@ -206,8 +226,25 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
       const double dv = nrm > 0.0 ? nrm : 1.0;
       const double rdv = 1.0 / dv;
       T o[EPC];
+      bool exact = true;  // (the same for the wave)
+      if constexpr (sizeof(T) == 2) {
+        // In fp32 the quotient is off by three roundings at most (x, 1 / |x|, their product): where that
+        // cannot reach the middle between two bf16 values, it rounds as the fp64 quotient does.
+        const float rf = (float)rdv;
+        bool unsure = !(dv > 0x1p-20 && dv < 0x1p100);  // (so that no operand below is subnormal)
 #pragma unroll
-      for (int e = 0; e < EPC; ++e) o[e] = quant_store<T>(div_shared(x[e], dv, rdv));
+        for (int e = 0; e < EPC; ++e) {
+          const uint32_t u = __float_as_uint((float)x[e] * rf);
+          unsure |= (u & 0xffffu) - 0x7ffcu <= 8u ||                               // 4 steps around the middle
+                    (u & 0x7fffffffu) - 0x0d800000u >= 0x7f800000u - 0x0d800000u;  // below 2^-100, no number
+          o[e].bits = (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+        }
+        exact = __ballot(unsure) != 0;
+      }
+      if (exact) {
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) o[e] = quant_store<T>(div_shared(x[e], dv, rdv));
+      }
       store16(Xu + (size_t)(r0 + u * GROUPS) * D, *reinterpret_cast<uint4*>(o));
       if (range) {
         const u16x2* w = reinterpret_cast<const u16x2*>(o);
@@ -251,33 +288,43 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
 // position j_i and leaves position i's value there.  The value at position p
 // just before step b (p >= b) is p itself unless an earlier step targeted p; if
 // t < b is the latest such step, it is the value position t held before step t.
-// Every thread follows that chain for its own i (chains are short: k << L).
+// Every thread follows that chain for its own i (chains are short: k << L).  The steps are found through
+// buckets of their targets.  `pieces` workgroups a segment each know all targets and take a share of the draws;
+// eight rows of a group in flight.  (Every earlier step compared, rows one by one, one workgroup for 512 draws: 41 us
+// for 32 segments, 127 for 1920; 5.8 and 106 us so, the latter at the rate of its row reads.)
 // ============================================================================
 
 template <typename T, int D>
 __global__ __launch_bounds__(256) void init_kernel(const T* __restrict__ xhat, T* __restrict__ chat,
                                                    int S, int L, int kk, int N_idx, int Hkv,
-                                                   uint64_t seed, int seg_id_base) {
+                                                   uint64_t seed, int seg_id_base, int pieces, int buckets) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR;
-  const int sg = blockIdx.x;
+  const int sg = blockIdx.x / pieces, piece = blockIdx.x - sg * pieces;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
-  extern __shared__ int init_lds[];  // 2 * kk ints
+  extern __shared__ int init_lds[];  // 3 * kk + buckets ints
   int* target = init_lds;
-  int* chosen = init_lds + kk;
+  int* chosen = target + kk;
+  int* next = chosen + kk;           // the steps of a bucket of targets, in no order
+  int* head = next + kk;
+  for (int i = threadIdx.x; i < buckets; i += 256) head[i] = -1;
+  __syncthreads();
   // (seg_id_base: the segments of an index update continue the numbering of the build)
   const uint64_t st0 = init_stream_state(seed, si.unit / Hkv, si.unit % Hkv, si.s + seg_id_base);
   for (int i = threadIdx.x; i < si.k_s; i += 256) {
     uint64_t st = st0 + (uint64_t)i * 0x9E3779B97F4A7C15ull;  // state before draw i
     const uint64_t draw = splitmix64_next(st);
-    target[i] = i + (int)(draw % (uint64_t)(si.L_s - i));
+    const int t = i + (int)(draw % (uint64_t)(si.L_s - i));
+    target[i] = t;
+    next[i] = atomicExch(&head[t & (buckets - 1)], i);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < si.k_s; i += 256) {
+  const int per = (si.k_s + pieces - 1) / pieces, c_lo = min(si.k_s, piece * per), c_hi = min(si.k_s, c_lo + per);
+  for (int i = c_lo + threadIdx.x; i < c_hi; i += 256) {
     int cur = target[i], bound = i;
     while (true) {
-      int t = -1;
-#pragma unroll 8
-      for (int u = 0; u < bound; ++u) t = target[u] == cur ? u : t;  // latest earlier step onto cur
+      int t = -1;  // the latest step before `bound` onto cur
+      for (int u = head[cur & (buckets - 1)]; u >= 0; u = next[u])
+        if (u < bound && u > t && target[u] == cur) t = u;
       if (t < 0) break;
       cur = t;
       bound = t;
@@ -288,7 +335,15 @@ __global__ __launch_bounds__(256) void init_kernel(const T* __restrict__ xhat, T
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   const T* X = xhat + ((size_t)si.unit * N_idx + si.seg_start) * D + sub * EPC;
   T* Cs = chat + (size_t)sg * kk * D + sub * EPC;
-  for (int c = grp; c < si.k_s; c += GROUPS) store16(Cs + (size_t)c * D, load16(X + (size_t)chosen[c] * D));
+  constexpr int U = 8;
+  for (int c = c_lo + grp; c < c_hi; c += U * GROUPS) {
+    uint4 raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) raw[u] = load16(X + (size_t)chosen[min(c + u * GROUPS, c_hi - 1)] * D);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c + u * GROUPS < c_hi) store16(Cs + (size_t)(c + u * GROUPS) * D, raw[u]);
+  }
 }
 
 // ============================================================================
@@ -2351,15 +2406,33 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   double* mean = reinterpret_cast<double*>(w + g.off_init);
   constexpr int GROUPS = 256 / (D / Elem<T>::EPC);
 
-  WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs, 256, 0, st, K, mean, nflag, range, nchanged[1], nlisted[0], S, L, kk, ix.N,
-              N_idx, ns);
   {
-    const int chunks = ((L < N_idx ? L : N_idx) + NORM_ROWS - 1) / NORM_ROWS;
-    WAVE_LAUNCH("normalise", (normalise_kernel<T, D>), g.segs * chunks, 256, 0, st, K, mean, xhat, range, S, L, kk, ix.N,
-                N_idx, ns, chunks);
+    // A few segments: pieces of at least 256 rows until every CU has a workgroup.  Their sums go where the order of
+    // the points comes later (4 bytes a point).
+    int pieces = 1;
+    const int Lmax = L < N_idx ? L : N_idx;
+    while (g.segs * pieces < 256 && pieces < 16 && Lmax / (2 * pieces) >= 256 &&
+           (size_t)g.segs * 2 * pieces * D * sizeof(double) <= (size_t)units * N_idx * sizeof(int32_t))
+      pieces *= 2;
+    double* sums_of = pieces > 1 ? reinterpret_cast<double*>(order) : mean;
+    WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs * pieces, 256, 0, st, K, sums_of, nflag, range, nchanged[1],
+                nlisted[0], S, L, kk, ix.N, N_idx, ns, pieces);
+    int row_step = NORM_ROWS, chunks = (Lmax + NORM_ROWS - 1) / NORM_ROWS;
+    if (g.segs * chunks > NORM_RESIDENT && g.segs * ((chunks + 1) / 2) <= NORM_RESIDENT) {
+      row_step *= 2;
+      chunks = (chunks + 1) / 2;
+    }
+    WAVE_LAUNCH("normalise", (normalise_kernel<T, D>), g.segs * chunks, 256, 0, st, K, sums_of, mean, xhat, range, S, L, kk,
+                ix.N, N_idx, ns, chunks, row_step, pieces);
   }
-  WAVE_LAUNCH("init", (init_kernel<T, D>), g.segs, 256, 2 * sizeof(int) * (size_t)kk, st, xhat, chat, S, L,
-              kk, N_idx, ix.Hkv, seed, seg_id_base);
+  {
+    int pieces = 1;  // a workgroup for every CU, of at least 32 draws
+    while (g.segs * pieces < 256 && kk / pieces >= 64) pieces *= 2;
+    int buckets = 64;
+    while (buckets < kk) buckets *= 2;
+    WAVE_LAUNCH("init", (init_kernel<T, D>), g.segs * pieces, 256, sizeof(int) * (3 * (size_t)kk + buckets), st, xhat, chat,
+                S, L, kk, N_idx, ix.Hkv, seed, seg_id_base, pieces, buckets);
+  }
 
   const int cl_grid = (ncl + GROUPS - 1) / GROUPS;
   if constexpr (sizeof(T) == 4) {

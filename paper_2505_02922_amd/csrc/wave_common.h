@@ -126,9 +126,22 @@ __device__ __forceinline__ float group_sum(float x) {
   return x;
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+// (The lanes that a step joins hold equal sums, so the mirrored partner's is lane ^ 4's or lane ^ 8's.)
 template <int LPR>
 __device__ __forceinline__ double group_sum_f64(double x) {
-  for (int off = 1; off < LPR; off <<= 1) x += __shfl_xor(x, off);
+  static_assert(LPR == 8 || LPR == 16 || LPR == 32, "lanes per row");
+  x += dpp<DPP_XOR1>(x);
+  x += dpp<DPP_XOR2>(x);
+  x += dpp<DPP_HALF_MIRROR>(x);
+  if (LPR >= 16) x += dpp<DPP_MIRROR>(x);
+  if (LPR >= 32) x += __shfl_xor(x, 16);
   return x;
 }
 

@@ -208,3 +208,30 @@ def test_f32_rounds_match_oracle(kind, B, d, N, L, k, iters):
     torch.cuda.synchronize()
     for name in wb.BUFFER_NAMES:
         assert torch.equal(ix.t[name].cpu().double(), ref[name].reshape(ix.t[name].shape).double()), name
+
+
+# The front of a build: segment means from pieces of 256 rows or more (the last one short), key scales at which the
+# fp32 quotient of the normalise step has to give way to the fp64 one (subnormal and huge keys, a row equal to
+# the mean, quotients in the middle between two bf16 values), seeds of nearly all points of a segment.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("N,L,k,scale", [(2053, 2048, 64, 1.0), (1505, 1100, 20, 2.0 ** -118), (1505, 1500, 33, 2.0 ** 60),
+                                         (4105, 513, 8, 2.0 ** -30), (305, 300, 299, 1.0), (8197, 8192, 2000, 0.0)])
+def test_front_of_the_build_matches_oracle(dtype, N, L, k, scale):
+    d = 64
+    g = torch.Generator().manual_seed(N + k)
+    # halves, quarters, ...: sums and quotients land on and next to the middle between two bf16 values
+    x = torch.randint(-8, 9, (1, 1, N, d), generator=g).float() / 8
+    x[0, 0, 2:N - 3:2] *= 1 + torch.randint(0, 3, (1,), generator=g).float()
+    if scale == 0.0:
+        x = torch.randn(1, 1, N, d, generator=g)
+        scale = 1.0
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="front", dtype=dtype, B=1, Hq=1, Hkv=1, N=N, d=d, n_sink=2,
+                      n_local=3, segment_len=L, clusters_per_segment=k, iters=2)
+    K = (x * scale).to(tdt)
+    V = torch.randn(1, 1, N, d, generator=g).to(tdt)
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), wl.n_sink, wl.n_local, L, k, 2, 0)
+    torch.cuda.synchronize()
+    for name in ("sizes", "perm", "centroids"):
+        assert torch.equal(ix.t[name].cpu().double(), ref[name].reshape(ix.t[name].shape).double()), name
