@@ -521,16 +521,33 @@ struct ResidentTile {
   static constexpr int CPR = D / 8;        // 16-byte chunks per centroid row
 };
 
+// `rows` (a multiple of 32) of the centroids Cs into padded LDS rows, row i the centroid source(i), four requests
+// of a thread in flight (a request and its store one after the other are a round trip each).
+template <int D, int NT, typename Source>
+__device__ __forceinline__ void copy_centroids(const bf16_t* Cs, int rows, char* cent, Source&& source) {
+  using RT = ResidentTile<D>;
+  constexpr int U = 4;
+  const int chunks = rows * RT::CPR;
+  for (int id0 = threadIdx.x; id0 < chunks; id0 += U * NT) {
+    uint4 raw[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int id = min(id0 + u * NT, chunks - 1);
+      raw[u] = load16(Cs + (size_t)source(id / RT::CPR) * D + id % RT::CPR * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int id = min(id0 + u * NT, chunks - 1);
+      store16(cent + id / RT::CPR * RT::ROWB + id % RT::CPR * 16, raw[u]);
+    }
+  }
+}
+
 // The segment's k_s centroid rows into the padded LDS tiles (rows beyond k_s repeat the
 // last one; the epilogue ignores them).  All NT threads call this; the caller's barrier follows.
 template <int D, int NT>
 __device__ __forceinline__ void resident_load_centroids(const bf16_t* Cs, int k_s, char* cent) {
-  using RT = ResidentTile<D>;
-  const int ntiles = (k_s + 31) / 32;
-  for (int id = threadIdx.x; id < 32 * ntiles * RT::CPR; id += NT) {
-    const int row = id / RT::CPR, ch = id - row * RT::CPR;
-    store16(cent + row * RT::ROWB + ch * 16, load16(Cs + (size_t)min(row, k_s - 1) * D + ch * 8));
-  }
+  copy_centroids<D, NT>(Cs, 32 * ((k_s + 31) / 32), cent, [&](int row) { return min(row, k_s - 1); });
 }
 
 // Wave `wave` of NW takes the fragments f_lo + wave * NF, + NW * NF, ... below f_hi of the
@@ -625,9 +642,10 @@ __device__ __forceinline__ void resident_assign_fragments(const bf16_t* X, const
 // instruction interleaving, the next fragment's rows requested before the current one is
 // worked on.  Same similarities, same epilogue, same fetch and emit.  (fetch belongs to the
 // requests made ahead: a load issued behind them and used at once would wait for all of them.)
-template <int D, int NW, typename Fetch, typename Emit>
+// stage() fills `cent` once the first rows are requested; all threads of the workgroup call this.
+template <int D, int NW, typename Fetch, typename Emit, typename Stage>
 __device__ __forceinline__ void lean_assign_fragments(const bf16_t* X, const char* cent, int L_s, int k_s,
-                                                      int f_lo, int f_hi, Fetch&& fetch, Emit&& emit) {
+                                                      int f_lo, int f_hi, Fetch&& fetch, Emit&& emit, Stage&& stage) {
   using RT = ResidentTile<D>;
   constexpr int KS = RT::KS, ROWB = RT::ROWB;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -644,6 +662,7 @@ __device__ __forceinline__ void lean_assign_fragments(const bf16_t* X, const cha
   };
   uint4 cur[KS], nxt[KS];
   if (f_lo + wave < f_hi) load_frag(f_lo + wave, cur, state);
+  stage();
   for (int fb = f_lo + wave; fb < f_hi; fb += NW) {
     if (fb + NW < f_hi) load_frag(fb + NW, nxt, next_state);
     int best[1] = {0}, second[1] = {0}, btile[1] = {0};
@@ -766,19 +785,162 @@ __device__ __forceinline__ void publish_list(const uint16_t* left, int n, int fi
   for (int i = threadIdx.x; i < n; i += blockDim.x) list[at + i] = first + left[i];
 }
 
+// ============================================================================
+// Points that need every centroid (near-ties of a full pass; what a later round's bounds leave open): up to
+// LIST_POINTS of a segment at a time, by the NW waves of a workgroup.  point(i) is the i-th of n points.
+// The points' rows are staged in LDS, the waves share out the centroid tiles, read from the
+// cache, and the tiles' best two are merged per point.  A point whose two best are closer than the
+// guard gets fp64 similarities (exact for the stored operands up to fp64 rounding, ties to
+// the lowest centroid) of the centroids in every tile whose best is that close, one lane per
+// centroid; the bound on its other similarities is then `best` too.
+// ============================================================================
+constexpr int LIST_POINTS = 64;
+
+// (the rows, then per (tile, point): best, second, row)
 template <int D>
-inline size_t resident_lds(int kmax) {
-  return (size_t)32 * ((kmax + 31) / 32) * ResidentTile<D>::ROWB + sizeof(uint16_t) * ASSIGN_POINTS;
+constexpr size_t listed_lds(int kmax) {
+  return (size_t)LIST_POINTS * ResidentTile<D>::ROWB + sizeof(int) * 3 * LIST_POINTS * (size_t)((kmax + 31) / 32);
 }
 
-template <int D, int NF, int NW>
+template <int D, int NW, typename Point, typename Settle>
+__device__ __forceinline__ void assign_listed_batch(const bf16_t* X, const bf16_t* Cs, int k_s, int n, char* rows,
+                                                    Point&& point, Settle&& settle) {
+  using RT = ResidentTile<D>;
+  constexpr int KS = RT::KS, ROWB = RT::ROWB, CPR = RT::CPR, FRAGS = LIST_POINTS / 32;
+  int* part = reinterpret_cast<int*>(rows + LIST_POINTS * ROWB);
+  __shared__ int near_p[LIST_POINTS], near_best[LIST_POINTS], near_row[LIST_POINTS], nnear;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, col = lane & 31;
+  const int ntiles = (k_s + 31) / 32;
+  if (tid == 0) nnear = 0;
+  uint4 a[KS];
+  auto load_tile = [&](int t) {
+    const bf16_t* cr = Cs + (size_t)min(32 * t + col, k_s - 1) * D + half * 8;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) a[s] = load16(cr + 16 * s);
+  };
+  if (wave < ntiles) load_tile(wave);
+  for (int id = tid; id < LIST_POINTS * CPR; id += 64 * NW) {
+    const int p = id / CPR, ch = id - p * CPR;
+    store16(rows + p * ROWB + ch * 16, load16(X + (size_t)point(min(p, n - 1)) * D + ch * 8));
+  }
+  __syncthreads();
+  for (int t = wave; t < ntiles; t += NW) {
+    constexpr float B0 = kAssignBias;
+    floatx16 acc[FRAGS];
+#pragma unroll
+    for (int f = 0; f < FRAGS; ++f) acc[f] = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int f = 0; f < FRAGS; ++f)
+        acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            __builtin_bit_cast(bf16x8, a[s]),
+            __builtin_bit_cast(bf16x8, load16(rows + (32 * f + col) * ROWB + (2 * s + half) * 16)), acc[f], 0, 0, 0);
+    if (t + NW < ntiles) load_tile(t + NW);
+    int best[FRAGS] = {}, second[FRAGS] = {}, btile[FRAGS] = {};
+    assign_epilogue<FRAGS, true>(acc, best, second, btile, t, half, k_s);
+#pragma unroll
+    for (int f = 0; f < FRAGS; ++f) {
+      const int row = merge_halves(best[f], second[f], btile[f], half);
+      if (half == 0) {
+        int* o = part + (t * LIST_POINTS + 32 * f + col) * 3;
+        o[0] = best[f];
+        o[1] = second[f];
+        o[2] = row;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < LIST_POINTS && tid < n) {
+    const int* mine = part + tid * 3;
+    int best = mine[0], second = mine[1], row = mine[2];
+#pragma unroll 4
+    for (int t = 1; t < ntiles; ++t) {
+      const int* o = mine + t * LIST_POINTS * 3;
+      second = max(max(second, o[1]), min(best, o[0]));
+      row = o[0] > best ? o[2] : row;
+      best = max(best, o[0]);
+    }
+    if (key_gap(best, second) < kAssignGuard) {
+      const int q = atomicAdd(&nnear, 1);
+      near_p[q] = tid;
+      near_best[q] = best;
+      near_row[q] = row;
+    } else {
+      settle(point(tid), row, best, second);
+    }
+  }
+  __syncthreads();
+  for (int q = wave; q < nnear; q += NW) {
+    const int p = near_p[q], best = near_best[q];
+    uint64_t close = __ballot(lane < ntiles &&
+                              key_gap(best, part[(min(lane, ntiles - 1) * LIST_POINTS + p) * 3]) < kAssignGuard);
+    double bv = -1.0e300;
+    int bc = 0x7fffffff;
+    while (close) {  // two tiles at a time, one per half of the wave
+      const int t0 = __ffsll((unsigned long long)close) - 1;
+      close &= close - 1;
+      const int t1 = close ? __ffsll((unsigned long long)close) - 1 : t0;
+      close &= close - 1;
+      const int c = 32 * (half ? t1 : t0) + col;
+      const bf16_t* cr = Cs + (size_t)min(c, k_s - 1) * D;
+      double acc = 0.0;
+#pragma unroll D / 16
+      for (int e0 = 0; e0 < D; e0 += 8) {
+        float xf[8], cf[8];
+        unpack<bf16_t>(load16(rows + p * ROWB + e0 * 2), xf);
+        unpack<bf16_t>(load16(cr + e0), cf);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc = fma((double)xf[e], (double)cf[e], acc);
+      }
+      if (c < k_s && acc > bv) {  // (c ascends within a lane: strict > keeps the lowest)
+        bv = acc;
+        bc = c;
+      }
+    }
+    for (int off = 32; off >= 1; off >>= 1) {
+      const double ov = __shfl_xor(bv, off);
+      const int oc = __shfl_xor(bc, off);
+      if (ov > bv || (ov == bv && oc < bc)) {
+        bv = ov;
+        bc = oc;
+      }
+    }
+    // (nothing comparable: the fp32 decision stands)
+    if (lane == 0) settle(point(p), bc < k_s ? bc : near_row[q], best, best);
+  }
+  __syncthreads();
+}
+
+// The n points of a workgroup's own list (from point `first` of the segment on).
+template <int D, int NW, typename Settle>
+__device__ __forceinline__ void settle_left(const bf16_t* X, const bf16_t* Cs, int k_s, const uint16_t* left, int n,
+                                            int first, char* rows, Settle&& settle) {
+  for (int b0 = 0; b0 < n; b0 += LIST_POINTS)  // (the same for the whole workgroup)
+    assign_listed_batch<D, NW>(X, Cs, k_s, n - b0, rows, [&](int i) { return first + left[b0 + i]; }, settle);
+}
+
+// `rows` padded centroid rows, with room for a batch of listed points in their place (at_once).
+template <int D>
+constexpr size_t rows_lds(int rows, int kmax, bool at_once) {
+  const size_t held = (size_t)rows * ResidentTile<D>::ROWB, batch = at_once ? listed_lds<D>(kmax) : 0;
+  return held > batch ? held : batch;
+}
+
+template <int D>
+inline size_t resident_lds(int kmax, bool at_once) {
+  return rows_lds<D>(32 * ((kmax + 31) / 32), kmax, at_once) + sizeof(uint16_t) * ASSIGN_POINTS;
+}
+
+template <int D, int NF, int NW, bool AT_ONCE>
 __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
     int32_t* __restrict__ prev, PointBounds* bounds, long long bounds_skip, int32_t* __restrict__ listed,
     int32_t* __restrict__ nlisted, int32_t* __restrict__ nflag, int round, int S, int L, int kk, int N_idx,
     int pieces_per_seg) {
-  // Near-ties go to a list per segment in `listed`, for assign_listed_kernel, or (nlisted null) to one for
-  // all segments, counted by nflag, for refine_kernel (which may leave the fp32 decision).
+  // Near-ties are decided here (AT_ONCE), or go to a list per segment in `listed`, for assign_listed_kernel, or
+  // (nlisted null) to one for all segments, counted by nflag, for refine_kernel (which may leave the fp32 decision).
   // LDS: 32 * ceil(k_s / 32) padded rows, then the workgroup's near-ties
   extern __shared__ __attribute__((aligned(16))) char cent[];
   __shared__ int nleft;
@@ -794,7 +956,7 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
   if (bounds) bounds += si.unit * bounds_skip;
   const bf16_t* X = xhat + gp0 * D;
   const bf16_t* Cs = chat + (size_t)sg * kk * D;
-  uint16_t* left = reinterpret_cast<uint16_t*>(cent + (size_t)32 * ((si.k_s + 31) / 32) * ResidentTile<D>::ROWB);
+  uint16_t* left = reinterpret_cast<uint16_t*>(cent + rows_lds<D>(32 * ((si.k_s + 31) / 32), si.k_s, AT_ONCE));
   if (threadIdx.x == 0) nleft = 0;
   resident_load_centroids<D, 64 * NW>(Cs, si.k_s, cent);
   __syncthreads();
@@ -805,10 +967,12 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
                                        [&](int point, int cluster, int best, int second, NoState) {
                                          const bool near = key_gap(best, second) < kAssignGuard;
                                          if (near) left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
-                                         if (!near || !nlisted) settle(point, cluster, best, second);
+                                         if (!near || (!AT_ONCE && !nlisted)) settle(point, cluster, best, second);
                                        });
   __syncthreads();
-  if (nlisted)
+  if constexpr (AT_ONCE)
+    settle_left<D, NW>(X, Cs, si.k_s, left, nleft, 32 * f_lo, cent, settle);
+  else if (nlisted)
     publish_list(left, nleft, 32 * f_lo, listed + gp0, &nlisted[sg]);
   else
     publish_list(left, nleft, (int)gp0 + 32 * f_lo, listed, nflag);
@@ -833,7 +997,10 @@ __global__ __launch_bounds__(64 * NW) void assign_resident_kernel(
 // A workgroup lists the changed centroids of a segment, copies their rows into LDS and streams
 // a share of the segment's points past them as in the kernel above, two accumulator sets while
 // many tiles make the matrix pipe the bound, else the next fragment's rows requested ahead.
-// Points that need every centroid are listed for assign_listed_kernel.
+// Points that need every centroid are listed for assign_listed_kernel, or (AT_ONCE: a few segments,
+// where a launch costs more than the listed points) compared when the workgroup has streamed its points;
+// its first rows are then always requested before the list of changed centroids is made (a late round of
+// 32 segments of 8192 points: three launches of 4.5 + 16 + 12 us, 25 us so; 31 us without the rows requested ahead).
 // Two launches share the segments by their number of changed centroids: up to
 // delta_light_rows a workgroup of 8 waves needs half of a CU's LDS, so that one workgroup's start
 // and end (chains of short dependent steps, 10 .. 25 us) run under another's streaming;
@@ -847,26 +1014,25 @@ constexpr int delta_light_rows() {
 }
 
 template <int D>
-inline size_t delta_lds(int kmax, int rows, int points) {
+inline size_t delta_lds(int kmax, int rows, int points, bool at_once) {
   const size_t padded = 32 * (size_t)((kmax + 31) / 32);
   const size_t held = padded < (size_t)rows ? padded : rows;
-  return held * ResidentTile<D>::ROWB + padded / 8 + sizeof(uint16_t) * (held + points);
+  return rows_lds<D>((int)held, kmax, at_once) + padded / 8 + sizeof(uint16_t) * (held + points);
 }
 
 // The segments with lo < (changed centroids) <= hi; `hi` rows (or all, if fewer) fit in LDS.
-template <int D, int NW>
+template <int D, int NW, bool AT_ONCE>
 __global__ __launch_bounds__(64 * NW, 4) void assign_delta_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ assign,
     int32_t* __restrict__ prev, PointBounds* all_bounds, long long bounds_skip, const int32_t* __restrict__ changed,
     const int32_t* __restrict__ nchanged, int32_t* __restrict__ listed, int32_t* __restrict__ nlisted, int lo,
     int hi, int round, int S, int L, int kk, int N_idx,
     int pieces_per_seg, int total) {
-  using RT = ResidentTile<D>;
-  constexpr int ROWB = RT::ROWB, CPR = RT::CPR, NT = 64 * NW;
+  constexpr int NT = 64 * NW;
   extern __shared__ __attribute__((aligned(16))) char cent[];
   __shared__ int wave_n[NW], nleft;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int wg = xcd_logical_block(blockIdx.x, gridDim.x); wg < total; wg += gridDim.x) {
+  for (int wg = xcd_logical_block(blockIdx.x, gridDim.x); wg < total; wg += AT_ONCE ? total : gridDim.x) {
     const int sg = wg / pieces_per_seg, piece = wg - sg * pieces_per_seg;
     const int nch = nchanged[sg];
     if (nch <= lo || nch > hi) continue;  // (the same for the whole workgroup)
@@ -876,7 +1042,7 @@ __global__ __launch_bounds__(64 * NW, 4) void assign_delta_kernel(
     const int f_lo = piece * per, f_hi = min(nfrag, f_lo + per);
     if (f_lo >= f_hi) continue;
     const int ntiles_all = (si.k_s + 31) / 32, held = min(32 * ntiles_all, hi);
-    uint32_t* marks = reinterpret_cast<uint32_t*>(cent + (size_t)held * ROWB);  // one bit per centroid
+    uint32_t* marks = reinterpret_cast<uint32_t*>(cent + rows_lds<D>(held, si.k_s, AT_ONCE));  // one bit per centroid
     uint16_t* list = reinterpret_cast<uint16_t*>(marks + ntiles_all);           // changed centroids
     uint16_t* left = list + held;                                               // points for the full comparison
     const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
@@ -884,32 +1050,32 @@ __global__ __launch_bounds__(64 * NW, 4) void assign_delta_kernel(
     const bf16_t* X = xhat + gp0 * D;
     const bf16_t* Cs = chat + (size_t)sg * kk * D;
 
-    // the changed centroids, in ascending order
-    if (tid == 0) nleft = 0;
-    int n = 0;
-    for (int c0 = 0; c0 < si.k_s; c0 += NT) {
-      const int c = c0 + tid;
-      const bool on = c < si.k_s && changed[(size_t)sg * kk + c] != 0;
-      const uint64_t mk = __ballot(on);
-      if (lane == 0) {
-        wave_n[wave] = __popcll(mk);
-        if (c < 32 * ntiles_all) marks[c / 32] = (uint32_t)mk;
-        if (c + 32 < 32 * ntiles_all) marks[c / 32 + 1] = (uint32_t)(mk >> 32);
+    // the changed centroids, in ascending order, and their rows
+    const int first_mark = tid < si.k_s ? changed[(size_t)sg * kk + tid] : 0;  // (requested before the points' rows)
+    auto stage = [&]() {
+      if (tid == 0) nleft = 0;
+      int n = 0;
+      for (int c0 = 0; c0 < si.k_s; c0 += NT) {
+        const int c = c0 + tid;
+        const bool on = c < si.k_s && (c0 == 0 ? first_mark : changed[(size_t)sg * kk + c]) != 0;
+        const uint64_t mk = __ballot(on);
+        if (lane == 0) {
+          wave_n[wave] = __popcll(mk);
+          if (c < 32 * ntiles_all) marks[c / 32] = (uint32_t)mk;
+          if (c + 32 < 32 * ntiles_all) marks[c / 32 + 1] = (uint32_t)(mk >> 32);
+        }
+        __syncthreads();
+        int base = n;
+        for (int w = 0; w < NW; ++w) {
+          base += w < wave ? wave_n[w] : 0;
+          n += wave_n[w];
+        }
+        if (on) list[base + __popcll(mk & ((1ull << lane) - 1ull))] = (uint16_t)c;
+        __syncthreads();
       }
+      copy_centroids<D, NT>(Cs, (nch + 31) / 32 * 32, cent, [&](int row) { return list[min(row, nch - 1)]; });
       __syncthreads();
-      int base = n;
-      for (int w = 0; w < NW; ++w) {
-        base += w < wave ? wave_n[w] : 0;
-        n += wave_n[w];
-      }
-      if (on) list[base + __popcll(mk & ((1ull << lane) - 1ull))] = (uint16_t)c;
-      __syncthreads();
-    }
-    for (int id = tid; id < (nch + 31) / 32 * 32 * CPR; id += NT) {
-      const int row = id / CPR, ch = id - row * CPR;
-      store16(cent + row * ROWB + ch * 16, load16(Cs + (size_t)list[min(row, nch - 1)] * D + ch * 8));
-    }
-    __syncthreads();
+    };
 
     auto fetch = [&](int point) { return PointState{assign[gp0 + point], bounds[gp0 + point]}; };
     auto decide = [&](int point, int row, int c1, int c2, const PointState& ps) {
@@ -927,35 +1093,33 @@ __global__ __launch_bounds__(64 * NW, 4) void assign_delta_kernel(
       else
         left[atomicAdd(&nleft, 1)] = (uint16_t)(point - 32 * f_lo);
     };
-    if (nch > 64)
+    if (AT_ONCE || nch <= 64) {
+      lean_assign_fragments<D, NW>(X, cent, si.L_s, nch, f_lo, f_hi, fetch, decide, stage);
+    } else {
+      stage();
       resident_assign_fragments<D, 1, NW>(X, cent, si.L_s, nch, f_lo, f_hi, fetch, decide);
-    else
-      lean_assign_fragments<D, NW>(X, cent, si.L_s, nch, f_lo, f_hi, fetch, decide);
+    }
     __syncthreads();
-    publish_list(left, nleft, 32 * f_lo, listed + gp0, &nlisted[sg]);
-    __syncthreads();
+    if constexpr (AT_ONCE) {
+      settle_left<D, NW>(X, Cs, si.k_s, left, nleft, 32 * f_lo, cent, [&](int point, int cluster, int own, int others) {
+        settle_point(assign, prev, bounds, round, gp0 + point, assign[gp0 + point], cluster, own, others);
+      });
+    } else {
+      publish_list(left, nleft, 32 * f_lo, listed + gp0, &nlisted[sg]);
+      __syncthreads();
+    }
   }
 }
 
 // ============================================================================
-// Assign, the points that the kernels above list: each against every centroid of its segment.
+// Assign, the points that the kernels above list, where they are not decided at once.
 // A workgroup of four waves takes LIST_POINTS at a time; a segment's list is shared by LIST_SPLIT
 // workgroups (the lists are uneven: a large cluster whose centroid moved can put a thousand points on
 // one), the first shares of all segments before the second ones, most of which are empty.
-// The points' rows are staged in LDS, the waves share out the centroid tiles, read from the
-// cache, and the tiles' best two are merged per point.  A point whose two best are closer than the
-// guard gets fp64 similarities (exact for the stored operands up to fp64 rounding, ties to
-// the lowest centroid) of the centroids in every tile whose best is that close, one lane per
-// centroid; the bound on its other similarities is then `best` too.
 // (A chain of short dependent steps.  At the end of each listing workgroup, in the LDS that it
-// holds, the same steps added 270 .. 400 us to a round that streams its points in 700 us.)
+// holds, the same steps added 270 .. 400 us to a round of a large batch that streams its points in 700 us.)
 // ============================================================================
-constexpr int LIST_POINTS = 64, LIST_SPLIT = 16;
-
-template <int D>
-inline size_t listed_lds(int kmax) {
-  return (size_t)LIST_POINTS * ResidentTile<D>::ROWB + sizeof(int) * 3 * LIST_POINTS * (size_t)((kmax + 31) / 32);
-}
+constexpr int LIST_SPLIT = 16;
 
 template <int D>
 __global__ __launch_bounds__(256, 4) void assign_listed_kernel(
@@ -963,127 +1127,21 @@ __global__ __launch_bounds__(256, 4) void assign_listed_kernel(
     int32_t* __restrict__ prev, PointBounds* bounds, long long bounds_skip, const int32_t* __restrict__ listed,
     const int32_t* __restrict__ nlisted, int32_t* __restrict__ nlisted_next, int round, int segs, int S, int L,
     int kk, int N_idx) {
-  using RT = ResidentTile<D>;
-  constexpr int KS = RT::KS, ROWB = RT::ROWB, CPR = RT::CPR, NW = 4, FRAGS = LIST_POINTS / 32;
   extern __shared__ __attribute__((aligned(16))) char rows[];
-  int* part = reinterpret_cast<int*>(rows + LIST_POINTS * ROWB);  // per (tile, point): best, second, row
-  __shared__ int near_p[LIST_POINTS], near_best[LIST_POINTS], near_row[LIST_POINTS], nnear;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, col = lane & 31;
   const int share = blockIdx.x / segs, sg = blockIdx.x - share * segs;
-  if (share == 0 && tid == 0) nlisted_next[sg] = 0;
+  if (share == 0 && threadIdx.x == 0) nlisted_next[sg] = 0;
   const int n = nlisted[sg];
   if (share * LIST_POINTS >= n) return;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
-  const int ntiles = (si.k_s + 31) / 32;
   const size_t gp0 = (size_t)si.unit * N_idx + si.seg_start;
-  const bf16_t* X = xhat + gp0 * D;
-  const bf16_t* Cs = chat + (size_t)sg * kk * D;
   const int32_t* left = listed + gp0;
   if (bounds) bounds += si.unit * bounds_skip;
   auto settle = [&](int point, int cluster, int own, int others) {
     settle_point(assign, prev, bounds, round, gp0 + point, bounds ? assign[gp0 + point] : 0, cluster, own, others);
   };
-  for (int b0 = share * LIST_POINTS; b0 < n; b0 += LIST_SPLIT * LIST_POINTS) {
-    if (tid == 0) nnear = 0;
-    uint4 a[KS];
-    auto load_tile = [&](int t) {
-      const bf16_t* cr = Cs + (size_t)min(32 * t + col, si.k_s - 1) * D + half * 8;
-#pragma unroll
-      for (int s = 0; s < KS; ++s) a[s] = load16(cr + 16 * s);
-    };
-    if (wave < ntiles) load_tile(wave);
-    for (int id = tid; id < LIST_POINTS * CPR; id += 64 * NW) {
-      const int p = id / CPR, ch = id - p * CPR;
-      store16(rows + p * ROWB + ch * 16, load16(X + (size_t)left[min(b0 + p, n - 1)] * D + ch * 8));
-    }
-    __syncthreads();
-    for (int t = wave; t < ntiles; t += NW) {
-      constexpr float B0 = kAssignBias;
-      floatx16 acc[FRAGS];
-#pragma unroll
-      for (int f = 0; f < FRAGS; ++f) acc[f] = {B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0, B0};
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
-#pragma unroll
-        for (int f = 0; f < FRAGS; ++f)
-          acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8, a[s]),
-              __builtin_bit_cast(bf16x8, load16(rows + (32 * f + col) * ROWB + (2 * s + half) * 16)), acc[f], 0, 0, 0);
-      if (t + NW < ntiles) load_tile(t + NW);
-      int best[FRAGS] = {}, second[FRAGS] = {}, btile[FRAGS] = {};
-      assign_epilogue<FRAGS, true>(acc, best, second, btile, t, half, si.k_s);
-#pragma unroll
-      for (int f = 0; f < FRAGS; ++f) {
-        const int row = merge_halves(best[f], second[f], btile[f], half);
-        if (half == 0) {
-          int* o = part + (t * LIST_POINTS + 32 * f + col) * 3;
-          o[0] = best[f];
-          o[1] = second[f];
-          o[2] = row;
-        }
-      }
-    }
-    __syncthreads();
-    if (tid < LIST_POINTS && b0 + tid < n) {
-      const int* mine = part + tid * 3;
-      int best = mine[0], second = mine[1], row = mine[2];
-      for (int t = 1; t < ntiles; ++t) {
-        const int* o = mine + t * LIST_POINTS * 3;
-        second = max(max(second, o[1]), min(best, o[0]));
-        row = o[0] > best ? o[2] : row;
-        best = max(best, o[0]);
-      }
-      if (key_gap(best, second) < kAssignGuard) {
-        const int q = atomicAdd(&nnear, 1);
-        near_p[q] = tid;
-        near_best[q] = best;
-        near_row[q] = row;
-      } else {
-        settle(left[b0 + tid], row, best, second);
-      }
-    }
-    __syncthreads();
-    for (int q = wave; q < nnear; q += NW) {
-      const int p = near_p[q], best = near_best[q];
-      uint64_t close = __ballot(lane < ntiles &&
-                                key_gap(best, part[(min(lane, ntiles - 1) * LIST_POINTS + p) * 3]) < kAssignGuard);
-      double bv = -1.0e300;
-      int bc = 0x7fffffff;
-      while (close) {  // two tiles at a time, one per half of the wave
-        const int t0 = __ffsll((unsigned long long)close) - 1;
-        close &= close - 1;
-        const int t1 = close ? __ffsll((unsigned long long)close) - 1 : t0;
-        close &= close - 1;
-        const int c = 32 * (half ? t1 : t0) + col;
-        const bf16_t* cr = Cs + (size_t)min(c, si.k_s - 1) * D;
-        double acc = 0.0;
-#pragma unroll 4
-        for (int e0 = 0; e0 < D; e0 += 8) {
-          float xf[8], cf[8];
-          unpack<bf16_t>(load16(rows + p * ROWB + e0 * 2), xf);
-          unpack<bf16_t>(load16(cr + e0), cf);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc = fma((double)xf[e], (double)cf[e], acc);
-        }
-        if (c < si.k_s && acc > bv) {  // (c ascends within a lane: strict > keeps the lowest)
-          bv = acc;
-          bc = c;
-        }
-      }
-      for (int off = 32; off >= 1; off >>= 1) {
-        const double ov = __shfl_xor(bv, off);
-        const int oc = __shfl_xor(bc, off);
-        if (ov > bv || (ov == bv && oc < bc)) {
-          bv = ov;
-          bc = oc;
-        }
-      }
-      // (nothing comparable: the fp32 decision stands)
-      if (lane == 0) settle(left[b0 + p], bc < si.k_s ? bc : near_row[q], best, best);
-    }
-    __syncthreads();
-  }
+  for (int b0 = share * LIST_POINTS; b0 < n; b0 += LIST_SPLIT * LIST_POINTS)
+    assign_listed_batch<D, 4>(xhat + gp0 * D, chat + (size_t)sg * kk * D, si.k_s, n - b0, rows,
+                              [&](int i) { return left[b0 + i]; }, settle);
 }
 
 // ============================================================================
@@ -1607,7 +1665,8 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
 }
 
 // ============================================================================
-// The f32 builds' update, with the sort in it: a workgroup owns the clusters [c_lo, c_hi) of a segment, reads
+// The f32 builds' update, with the sort in it (and the first and last one of bf16 builds of a few segments; sums:
+// see update_moves_kernel): a workgroup owns the clusters [c_lo, c_hi) of a segment, reads
 // this round's and the last round's cluster of every point of the segment, and sorts the points of its
 // changed clusters (in the first round and where `all` is set: of all its clusters) into their place of order[],
 // positions ascending; their counts and first places go to count[] and start[].  Then a group of lanes
@@ -1623,7 +1682,7 @@ template <typename T, int D>
 __global__ __launch_bounds__(SCAN_NT) void update_scan_kernel(
     const T* __restrict__ xhat, T* __restrict__ chat, const int32_t* __restrict__ assign,
     const int32_t* __restrict__ before, int32_t* order, int32_t* __restrict__ count, int32_t* __restrict__ start,
-    int first_round, int all, int S, int L, int kk, int N_idx, int span, int pieces) {
+    double* sums, long long sums_skip, int first_round, int all, int S, int L, int kk, int N_idx, int span, int pieces) {
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = SCAN_NT / LPR, NW = SCAN_NT / 64, U = 4;
   __shared__ int hist[NW * SCAN_CLUSTERS];   // members per (wave's stripe of points, cluster); then places
   __shared__ int lower[NW];                  // points in clusters before c_lo, per stripe
@@ -1716,12 +1775,15 @@ __global__ __launch_bounds__(SCAN_NT) void update_scan_kernel(
   __syncthreads();
   const T* X = xhat + p0 * D;
   T* Cs = chat + ((size_t)sg * kk + c_lo) * D;
+  double* own = sums ? sums + si.unit * sums_skip + ((size_t)sg * kk + c_lo) * D : nullptr;
   for (int c = tid / LPR; c < c_n; c += GROUPS)
     if (changed[c] && cnt[c] <= UPD_BIG)
-      update_cluster<T, D, 8, false>(X, order + p0 + first[c], cnt[c], Cs + (size_t)c * D + sub * EPC, sub);
+      update_cluster<T, D, 8, false>(X, order + p0 + first[c], cnt[c], Cs + (size_t)c * D + sub * EPC, sub,
+                                     own ? own + (size_t)c * D + sub * EPC : nullptr);
   for (int c = 0; c < c_n; ++c)
     if (changed[c] && cnt[c] > UPD_BIG)
-      update_cluster_by_workgroup<T, D, SCAN_NT>(X, order + p0 + first[c], cnt[c], Cs + (size_t)c * D, nullptr);
+      update_cluster_by_workgroup<T, D, SCAN_NT>(X, order + p0 + first[c], cnt[c], Cs + (size_t)c * D,
+                                                 own ? own + (size_t)c * D : nullptr);
 }
 static_assert(SCAN_CLUSTERS == 64, "a cluster per lane, six key bits");
 
@@ -1990,7 +2052,7 @@ __global__ __launch_bounds__(64 * small_waves<KEEP>()) void kmeans_small_kernel(
     if constexpr (KEEP > 0)
       assign_kept_fragments<D, KEEP, NW>(kept, cent, si.L_s, si.k_s, emit);
     else
-      lean_assign_fragments<D, NW>(X, cent, si.L_s, si.k_s, 0, nfrag, [](int) { return NoState{}; }, emit);
+      lean_assign_fragments<D, NW>(X, cent, si.L_s, si.k_s, 0, nfrag, [](int) { return NoState{}; }, emit, [] {});
     __syncthreads();
     WAVE_PHASE(1);
     for (int c = tid; c < kk; c += NT) changed_s[c] = 0;  // (every wave is done with the last round's)
@@ -2309,21 +2371,36 @@ static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t
       };
       int pieces = cut(ASSIGN_POINTS, 256, 512);
       if (pieces < 2 && Lmax > 2048) pieces = 2;
-      if (changed) {
+      // One workgroup per CU or fewer: each decides the points of its list itself, and a later round is one
+      // launch for segments of all numbers of changed centroids instead of three (builds of 32 segments of 8192
+      // points 704 and 621 us, of 80 1956 and 1818, of 128 1743 and 1646; 512 waiting workgroups hide the chain
+      // at a list's end better).  Not where a workgroup takes a whole segment and CUs stay idle: the three
+      // launches cut it finer (136 segments of 2048 points 457, at once 464 us).
+      const bool at_once = nlisted && segs * pieces <= 256 && (pieces > 1 || Lmax <= 512);
+      if (at_once && changed) {
+        WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16, true>), segs * pieces, 1024,
+                    delta_lds<D>(kmax, 1 << 20, ASSIGN_POINTS, true), st, xhat, chat, assign, prev, bounds, bounds_skip,
+                    changed, nchanged, flag, nlisted, 0, 1 << 20, round, S, L, kk, N_idx, pieces, segs * pieces);
+      } else if (at_once) {
+        WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16, true>), segs * pieces, 1024,
+                    resident_lds<D>(kmax, true), st, xhat, chat, assign, prev, bounds, bounds_skip, flag, nlisted, nflag,
+                    round, S, L, kk, N_idx, pieces);
+      } else if (changed) {
         constexpr int light = delta_light_rows<D>();
         const int light_pieces = cut(LIGHT_POINTS, 512, 256);
         if (kmax > light) {  // (usually none after a few rounds: no more workgroups than a CU each)
           const int total = segs * pieces;
-          WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16>), total < 256 ? total : 256, 1024,
-                      delta_lds<D>(kmax, 1 << 20, ASSIGN_POINTS), st, xhat, chat, assign, prev, bounds, bounds_skip, changed,
+          WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 16, false>), total < 256 ? total : 256, 1024,
+                      delta_lds<D>(kmax, 1 << 20, ASSIGN_POINTS, false), st, xhat, chat, assign, prev, bounds, bounds_skip, changed,
                       nchanged, flag, nlisted, light, 1 << 20, round, S, L, kk, N_idx, pieces, total);
         }
-        WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 8>), segs * light_pieces, 512,
-                    delta_lds<D>(kmax, light, LIGHT_POINTS), st, xhat, chat, assign, prev, bounds, bounds_skip, changed,
+        WAVE_LAUNCH("assign_delta", (assign_delta_kernel<D, 8, false>), segs * light_pieces, 512,
+                    delta_lds<D>(kmax, light, LIGHT_POINTS, false), st, xhat, chat, assign, prev, bounds, bounds_skip, changed,
                     nchanged, flag, nlisted, 0, light, round, S, L, kk, N_idx, light_pieces, segs * light_pieces);
       } else
-        WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16>), segs * pieces, 1024, resident_lds<D>(kmax),
+        WAVE_LAUNCH("assign_mfma", (assign_resident_kernel<D, 1, 16, false>), segs * pieces, 1024, resident_lds<D>(kmax, false),
                     st, xhat, chat, assign, prev, bounds, bounds_skip, flag, nlisted, nflag, round, S, L, kk, N_idx, pieces);
+      if (at_once) return;
       if (nlisted) {
         WAVE_LAUNCH("assign_listed", (assign_listed_kernel<D>), segs * LIST_SPLIT, 256, listed_lds<D>(kmax), st, xhat,
                     chat, assign, prev, bounds, bounds_skip, flag, nlisted, nlisted_next, round, segs, S, L, kk, N_idx);
@@ -2435,20 +2512,22 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   }
 
   const int cl_grid = (ncl + GROUPS - 1) / GROUPS;
+  // update_scan_kernel: at least as many clusters a workgroup as it has groups of lanes, more where that leaves
+  // a workgroup for every CU: each reads a segment's assignments (100 fp32 segments of 4096 points, 8 workgroups a
+  // segment 2.06 ms a build, 4 1.99).
+  int scan_span = SCAN_NT / (D / Elem<T>::EPC);
+  while (2 * scan_span <= SCAN_CLUSTERS && (long long)g.segs * ((kk + 2 * scan_span - 1) / (2 * scan_span)) >= 256)
+    scan_span *= 2;
+  const int scan_pieces = (kk + scan_span - 1) / scan_span;
   if constexpr (sizeof(T) == 4) {
-    // Two launches a round.  The assignments of even and of odd rounds have an array each.  At least as many
-    // clusters a workgroup as it has groups of lanes, more where that leaves a workgroup for every CU: each
-    // reads a segment's assignments (100 segments of 4096 points, 8 workgroups a segment 2.06 ms a build, 4 1.99).
-    int span = SCAN_NT / (D / Elem<T>::EPC);
-    while (2 * span <= SCAN_CLUSTERS && (long long)g.segs * ((kk + 2 * span - 1) / (2 * span)) >= 256) span *= 2;
-    const int pieces = (kk + span - 1) / span;
+    // Two launches a round.  The assignments of even and of odd rounds have an array each.
     for (int t = 0; t < iters; ++t) {
       int32_t* now = t & 1 ? prev : assign;
       launch_assign<T, D>(xhat, chat, now, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr, t, flag, nflag, S, L, kk,
                           N_idx, g.segs, 0, st);
-      WAVE_LAUNCH("update", (update_scan_kernel<T, D>), g.segs * pieces, SCAN_NT, 0, st, xhat, chat, now,
-                  t & 1 ? assign : prev, order, count, start, t == 0 ? 1 : 0, t + 1 == iters ? 1 : 0, S, L, kk, N_idx, span,
-                  pieces);
+      WAVE_LAUNCH("update", (update_scan_kernel<T, D>), g.segs * scan_pieces, SCAN_NT, 0, st, xhat, chat, now,
+                  t & 1 ? assign : prev, order, count, start, nullptr, 0, t == 0 ? 1 : 0, t + 1 == iters ? 1 : 0, S, L, kk,
+                  N_idx, scan_span, scan_pieces);
     }
   } else {
     int W = SORT_HIST_INTS / kk;
@@ -2492,11 +2571,21 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
       WAVE_LAUNCH("update", (update_big_kernel<T, D>), big_grid, 256, 0, st, xhat, chat, order, count,
                   start, flag, nflag + 1, sums, sums_skip, S, L, kk, N_idx);
     };
+    // The first and the last round of a few segments: several workgroups sort and sum a segment, not one (32
+    // segments of 8192 points x 512 clusters: sort, update and large clusters 42 us, 36 us so, a build of 6 segments
+    // of 4096 x 256 495 and 483 us); 224 segments pay for reading their assignments eight times (3.03 and 3.12 ms).
+    const bool scan = delta && g.segs < 128;
     for (int t = 0; t < iters && !small; ++t) {
       // Rounds 0 and 1 meet all new centroids; from round 2 on only the changed ones are compared.
       launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, bounds_skip, delta && t >= 2 ? changed : nullptr,
                           nchanged[(t + 1) & 1], nlisted[t & 1], nlisted[(t + 1) & 1], t, flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
       const bool last = t + 1 == iters;
+      if (scan && (t == 0 || last)) {
+        WAVE_LAUNCH("update", (update_scan_kernel<T, D>), g.segs * scan_pieces, SCAN_NT, 0, st, xhat, chat, assign, assign,
+                    order, count, start, sums, sums_skip, t == 0 ? 1 : 0, last ? 1 : 0, S, L, kk, N_idx, scan_span,
+                    scan_pieces);
+        continue;
+      }
       if (!delta || t == 0 || last) sort(delta ? nullptr : prev, t);
       if (last) break;
       if (delta && t >= 1) {

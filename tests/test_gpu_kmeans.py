@@ -235,3 +235,26 @@ def test_front_of_the_build_matches_oracle(dtype, N, L, k, scale):
     torch.cuda.synchronize()
     for name in ("sizes", "perm", "centroids"):
         assert torch.equal(ix.t[name].cpu().double(), ref[name].reshape(ix.t[name].shape).double()), name
+
+
+# Around the most segments whose workgroups decide their near-ties and listed points themselves (128 segments of
+# two workgroups) and whose first and last rounds sort and sum in one launch (127); more changed centroids than half of
+# a CU's LDS holds, the most that are resident, and more listed points than one batch; a ragged last segment.
+@pytest.mark.parametrize("kind,B,d,L,k,listed,sort", [
+    ("plain", 42, 128, 2100, 300, 0, 0), ("mixture", 43, 128, 2100, 512, 1, 1), ("plain", 43, 64, 2050, 500, 1, 1),
+    ("ties", 43, 128, 2049, 65, 1, 1), ("plain", 32, 64, 2080, 200, 0, 1), ("wide", 42, 128, 2100, 100, 0, 0)])
+def test_rounds_around_the_most_segments_decided_at_once(kind, B, d, L, k, listed, sort):
+    S = 4 if B == 32 else 3
+    iters, N = 5, S * L - 70
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="at_once", B=B, Hq=1, Hkv=1, N=N, d=d, n_sink=0, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=iters)
+    K = _keys(kind, B, N, d, N + k).to(torch.bfloat16)
+    V = torch.randn(B, 1, N, d, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16)
+    wb.wave_profile_enable(True)
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), 0, 0, L, k, iters, 0)
+    launches = {name: n for name, (_, n) in wb.wave_profile_read().items()}
+    wb.wave_profile_enable(False)
+    assert launches.get("assign_listed", 0) == listed * iters and launches.get("sort", 0) == 2 * sort, launches
+    for (b, h), ref in pu.oracle_build(wl, K, V, units=[(0, 0), (B - 1, 0)]).items():
+        for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
+            assert np.array_equal(ix.t[name][b, h].double().cpu().numpy(), getattr(ref, name)), (b, name)
