@@ -17,7 +17,7 @@
 // workgroup each (kmeans_small_kernel); bf16 with a segment's centroids in LDS and four
 // points per cluster or more: later rounds compare changed centroids and sum moved
 // points (assign_delta_kernel, update_moves_kernel); else assign, refine, sort and update
-// of the touched clusters, a launch each.
+// of the touched clusters, a launch each (f32: assign with its near-ties, and sort with update).
 //   finalize    sizes, offsets, mean of raw keys, value sums, permuted K/V rows
 #include <stdlib.h>
 
