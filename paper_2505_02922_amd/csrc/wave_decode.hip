@@ -618,10 +618,9 @@ __device__ __forceinline__ void select_streaming(
   float tau = 0.f, lo = 0.f, hi = 0.f;
   int need_eq = 0;  // mode 3: how many clusters with score == tau are taken (lowest ids)
   int n_cand = 0, need = 0;
-  if (r_eff == 0) {
-    mode = 0;
-  } else if (r_eff == nvalid) {
-    mode = 1;
+  if (r_eff == 0 || r_eff == nvalid) {
+    mode = r_eff == 0 ? 0 : 1;
+    __syncthreads();  // every wave has read the extrema from tbl_cnt, which the ids step writes next
   } else {
     // ---- radix select: key of the r_eff-th largest score --------------------
     uint32_t prefix = 0, pmask = 0;
