@@ -618,9 +618,10 @@ __device__ __forceinline__ void select_streaming(
   float tau = 0.f, lo = 0.f, hi = 0.f;
   int need_eq = 0;  // mode 3: how many clusters with score == tau are taken (lowest ids)
   int n_cand = 0, need = 0;
-  if (r_eff == 0 || r_eff == nvalid) {
-    mode = r_eff == 0 ? 0 : 1;
-    __syncthreads();  // every wave has read the extrema from tbl_cnt, which the ids step writes next
+  if (r_eff == 0) {
+    mode = 0;
+  } else if (r_eff == nvalid) {
+    mode = 1;
   } else {
     // ---- radix select: key of the r_eff-th largest score --------------------
     uint32_t prefix = 0, pmask = 0;
@@ -1056,10 +1057,9 @@ __device__ __forceinline__ int select_core(
   uint32_t ktau = 0, klo_band = 0, khi_band = 0;
   float hi = 0.f;
   int n_cand = 0, need = 0;
-  if (r_eff == 0) {
-    mode = 0;
-  } else if (r_eff == nvalid) {
-    mode = 1;
+  if (r_eff == 0 || r_eff == nvalid) {
+    mode = r_eff == 0 ? 0 : 1;
+    __syncthreads();  // every wave has read the extrema from tbl_cnt, which the ids step writes next
   } else {
     // ---- threshold: largest key t with count(key >= t) >= r_eff ----------------
     // Stage 1, whole workgroup: halve the VALUE interval [klo, khi) (midpoint of
