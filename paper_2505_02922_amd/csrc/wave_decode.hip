@@ -2328,7 +2328,7 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
   __shared__ LeanLds<NT, VPT> lean;
   __shared__ int scan_scratch[NWV];
   __shared__ float smem[NWV * STR];
-  __shared__ float s_weight[SOLO_SLOTS + 2];  // of the other zones' partials; their maximum and sum
+  __shared__ float s_weight[SOLO_SLOTS + 2];  // of the other zones' partials (without any term: -1); their maximum and sum
   __shared__ float s_a[NSG * D];
   const int bh = blockIdx.x;
   const int b = bh / Hq, hq = bh - b * Hq, G = Hq / Hkv;
@@ -2377,10 +2377,10 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
     for (int i = lane; i < slots; i += 64) mx = fmaxf(mx, pslots[(size_t)i * STR]);
     mx = wave_max(mx);
     for (int i = lane; i < slots; i += 64) {
-      const float m1 = pslots[(size_t)i * STR];  // (a partial without any term: kNegBig)
-      const float w = m1 > 0.5f * kNegBig ? exp2f(m1 - mx) : 0.f;
-      s_weight[i] = w;
-      l = fmaf(w, pslots[(size_t)i * STR + 1], l);
+      const float m1 = pslots[(size_t)i * STR];
+      const bool counts = m1 > 0.5f * kNegBig;  // (a partial without any term: kNegBig)
+      s_weight[i] = counts ? exp2f(m1 - mx) : -1.f;
+      l = counts ? fmaf(s_weight[i], pslots[(size_t)i * STR + 1], l) : l;
     }
     l = wave_add_f(l);
     if (lane == 0) {
@@ -2490,11 +2490,18 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
       dst[1] = st.l[0];
     }
   }
+  // (what does not count is left out, not weighted with zero: its sums, or those of the partial read in
+  // place of one past the end, may be infinite)
   float A = 0.f;
 #pragma unroll
-  for (int u = 0; u < UB; ++u) A = fmaf(sg + u * NSG < slots ? s_weight[min(sg + u * NSG, slots - 1)] : 0.f, pa[u], A);
-  for (int s0 = sg + UB * NSG; s0 < slots; s0 += NSG)
-    A = fmaf(s_weight[s0], pslots[(size_t)s0 * STR + 2 + e], A);
+  for (int u = 0; u < UB; ++u) {
+    const float w = sg + u * NSG < slots ? s_weight[min(sg + u * NSG, slots - 1)] : -1.f;
+    A = w >= 0.f ? fmaf(w, pa[u], A) : A;
+  }
+  for (int s0 = sg + UB * NSG; s0 < slots; s0 += NSG) {
+    const float w = s_weight[s0];
+    A = w >= 0.f ? fmaf(w, pslots[(size_t)s0 * STR + 2 + e], A) : A;
+  }
   __syncthreads();
   // lane w: wave w's partial; lane NWV: the other zones'
   const float m_l = lane < NWV ? smem[lane * STR] : (lane == NWV ? s_weight[SOLO_SLOTS] : kNegBig);

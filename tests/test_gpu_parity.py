@@ -778,3 +778,52 @@ def test_selection_of_one_workgroup_per_head(m, r, nb, dtype, d):
             tag = f"m={m} r={rr} nb={nb} hq={hq}"
             assert np.array_equal(s_g[s_g >= 0], np.asarray(s_ref)), tag
             pu.check_outputs(o_g, np.array([l_g]), o, np.array([l]), dtype, tag)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("m,r,empty", [(1024, 20, False), (1024, 20, True), (200, 3, False), (1024, 300, False)])
+def test_infinite_value_sums_of_estimated_clusters(m, r, empty, dtype, d):
+    """A cluster that is estimated and whose value sum is infinite in one channel makes that channel of the
+    output infinite, no number of any other kind, and leaves the other channels alone: the cluster is in the last
+    range of the estimation, whose partial result the merge of a head may read again in place of one past
+    the end.  `empty`: it is a whole range of clusters without members, which counts nowhere.  The oracle has the
+    same arrays with a zero there."""
+    arrs, n = _hand_index(m, d, dtype, 8, seed=m + r)
+    arrs = {k: np.array(v) for k, v in arrs.items()}
+    g = np.random.default_rng(m)
+    q = torch.from_numpy(wo.quant(0.3 * g.standard_normal((1, 2, d)), dtype).astype(np.float32)).to(
+        torch.bfloat16 if dtype == "bf16" else torch.float32)
+    sizes = arrs["sizes"]
+    if empty:                                             # (ranges of 64, 128 or 256 clusters)
+        sizes[m - 256:] = 0
+        bad = np.arange(m - 256, m)
+    else:
+        sizes[m - 5] = 2
+        bad = np.array([m - 5])
+    arrs["offsets"] = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(arrs["offsets"][-1])
+    gen = np.random.default_rng(3)
+    arrs["k_perm"] = wo.quant(gen.standard_normal((n, d)), dtype)
+    arrs["v_perm"] = wo.quant(gen.standard_normal((n, d)), dtype)
+    for c in range(m):                                    # centroids and value sums of these rows
+        rows = slice(arrs["offsets"][c], arrs["offsets"][c + 1])
+        arrs["centroids"][c] = wo.quant(arrs["k_perm"][rows].mean(0) if sizes[c] else np.zeros(d), dtype)
+        arrs["vsum"][c] = wo.quant(arrs["v_perm"][rows].sum(0), dtype)
+    if not empty:                                         # a centroid whose score no head ranks high
+        arrs["centroids"][bad] = wo.quant(-0.5 * q[0].double().numpy().sum(0), dtype)
+    arrs["vsum"][bad, 5] = 0.0
+    fin = _decode_hand(arrs, n, m, d, dtype, q, r)
+    arrs["vsum"][bad, 5] = np.inf
+    with np.errstate(all="ignore"):
+        got = _decode_hand(arrs, n, m, d, dtype, q, r)
+    keep = np.arange(d) != 5
+    for hq in range(2):
+        o_g, l_g, s_g = got[hq][:3]
+        o, l, s_ref = fin[hq][3:6]
+        tag = f"m={m} r={r} hq={hq} empty={empty}"
+        assert np.array_equal(s_g[s_g >= 0], np.asarray(s_ref)) and not np.isin(bad, s_ref).any(), tag
+        pu.check_outputs(o_g[keep], np.array([l_g]), o[keep], np.array([l]), dtype, tag)
+        if empty:
+            pu.check_outputs(o_g, np.array([l_g]), o, np.array([l]), dtype, tag)
+        else:
+            assert o_g[5] == np.inf, (tag, o_g[5])
