@@ -1222,6 +1222,94 @@ __global__ __launch_bounds__(256) void refine_kernel(const T* __restrict__ xhat,
   }
 }
 
+// fp64 similarities of P points with one row each lane, summed in index order.
+template <int D, int P>
+__device__ __forceinline__ void similarities_f64(const float* const (&x)[P], const float* row, double (&a)[P]) {
+#pragma unroll P == 1 ? 4 : 2
+  for (int e0 = 0; e0 < D; e0 += 8) {
+    float f[8];
+    unpack<float>(load16(row + e0), *reinterpret_cast<float(*)[4]>(f));
+    unpack<float>(load16(row + e0 + 4), *reinterpret_cast<float(*)[4]>(f + 4));
+#pragma unroll
+    for (int j = 0; j < P; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[j] = fma((double)x[j][e0 + e], (double)f[e], a[j]);
+  }
+}
+
+// Near-ties of f32 builds, decided by the workgroup that finds them: the n points near_p[] of a segment (rows X, centroids
+// Cs) get the argmax of their fp64 similarities, ties to the lowest centroid.  Of its four waves up to
+// four waves share out the centroids, the others take other points, and a wave compares up to four points with every row
+// that it reads.  (A row per lane is a cache line per lane: with one point at a time the reads are the bound.  Builds of
+// few segments whose points are all near-ties, six rounds, the points one after the other by the workgroup and so:
+// 2 segments of 2048 points x 128 clusters x 64 channels 633 -> 358 us, 1 of 1024 x 64 x 128 938 -> 216 us.)
+template <int D>
+__device__ __forceinline__ void settle_near_f32(const float* __restrict__ X, const float* __restrict__ Cs, int k_s,
+                                                const int* near_p, int n, int32_t* __restrict__ assign) {
+  constexpr int NW = 4, MOST = 4;
+  __shared__ double bval[NW][MOST];
+  __shared__ int bidx[NW][MOST];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int shares = k_s > 128 ? 4 : k_s > 64 ? 2 : 1;  // waves that share out the centroids
+  const int pgroups = NW / shares, share = wave % shares, pgroup = wave / shares;
+  auto pass = [&](auto points, int i0) {  // the points i0 + j * pgroups + pgroup, j < P, those past the end again
+    constexpr int P = decltype(points)::value;
+    const float* x[P];
+    double bv[P];
+    int bi[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      const int p = near_p[min(i0 + j * pgroups + pgroup, n - 1)];
+      x[j] = X + (size_t)__builtin_amdgcn_readfirstlane(p) * D;
+      bv[j] = -1.0e300;
+      bi[j] = 0x7fffffff;
+    }
+    for (int c0 = 64 * share; c0 < k_s; c0 += 64 * shares) {
+      const int c = c0 + lane;
+      const float* row = Cs + (size_t)min(c, k_s - 1) * D;
+      double a[P] = {};
+      similarities_f64<D, P>(x, row, a);
+#pragma unroll
+      for (int j = 0; j < P; ++j)
+        if (c < k_s && a[j] > bv[j]) {  // c ascends within a lane, so strict > keeps the lowest index
+          bv[j] = a[j];
+          bi[j] = c;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+      for (int off = 32; off >= 1; off >>= 1) {
+        const double ov = __shfl_xor(bv[j], off);
+        const int oi = __shfl_xor(bi[j], off);
+        if (ov > bv[j] || (ov == bv[j] && oi < bi[j])) {
+          bv[j] = ov;
+          bi[j] = oi;
+        }
+      }
+      if (lane == 0) {
+        bval[wave][j] = bv[j];
+        bidx[wave][j] = bi[j];
+      }
+    }
+    __syncthreads();
+    const int t = threadIdx.x, j = t / pgroups, first = t % pgroups * shares;  // point t, its shares' waves
+    if (t < P * pgroups && i0 + t < n) {
+      double v = bval[first][j];
+      int c = bidx[first][j];
+      for (int w = first + 1; w < first + shares; ++w)
+        if (bval[w][j] > v || (bval[w][j] == v && bidx[w][j] < c)) {
+          v = bval[w][j];
+          c = bidx[w][j];
+        }
+      if (c < k_s) assign[near_p[i0 + t]] = c;  // (no similarity is comparable: the point stays where it is)
+    }
+    __syncthreads();
+  };
+  int i0 = 0;
+  for (; n - i0 > pgroups; i0 += MOST * pgroups) pass(std::integral_constant<int, MOST>{}, i0);
+  if (i0 < n) pass(std::integral_constant<int, 1>{}, i0);
+}
+
 // ============================================================================
 // Assign, f32: workgroups of four waves on v_mfma_f32_32x32x2_f32 (fp32 products and sums).  A wave keeps 32
 // points in registers as B operands; the centroids are A operands
@@ -1234,10 +1322,13 @@ __global__ __launch_bounds__(256) void refine_kernel(const T* __restrict__ xhat,
 // Points whose two best are closer than the guard are decided here, from fp64 similarities.
 // (4096 tokens x 128 clusters x 64 channels, a round: one point per thread with a chain of fp32 FMAs 60 us; one
 // wave per 32 points with all tiles and the near-ties in a launch of their own 11.4 + 3; 4.9 us so.  Split
-// with 8192 fragments, 64 clusters x 128 channels: 92 us, not split 67.)
+// with 8192 fragments, 64 clusters x 128 channels: 92 us, not split 67.  Builds around the line, split and not: 768
+// fragments x 512 clusters 410 and 525 us, x 64 557 and 568; 896 x 128 209 and 205, 1024 x 128 211 and 203, 1024 x 512
+// 469 and 520.)  Four waves a SIMD at 128 channels, without accumulation registers: 128 segments of 4096 points x 256
+// clusters 2.57 -> 2.31 ms; at 64 channels (two segments, 4096 clusters) that loses 3 %.
 // ============================================================================
 template <int D, bool SPLIT>
-__global__ __launch_bounds__(256) void assign_f32_kernel(
+__global__ __launch_bounds__(256, D == 128 ? 4 : 1) void assign_f32_kernel(
     const float* __restrict__ xhat, const float* __restrict__ chat, int32_t* __restrict__ assign, int S, int L, int kk,
     int N_idx, int wgs_per_seg) {
   constexpr int KS = D / 8, NW = 4;  // pairs of 16-byte chunks, one per half of the wave
@@ -1306,11 +1397,7 @@ __global__ __launch_bounds__(256) void assign_f32_kernel(
     if (best - second < kAssignGuard) near_p[atomicAdd(&near_n, 1)] = point;
   }
   __syncthreads();
-  for (int i = 0; i < near_n; ++i) {
-    const int p = near_p[i];
-    const int bi = refine_point<float, D>(xhat + (gp0 + p) * D, Cs, si.k_s);
-    if (threadIdx.x == 0 && bi < si.k_s) assign[gp0 + p] = bi;
-  }
+  settle_near_f32<D>(xhat + gp0 * D, Cs, si.k_s, near_p, near_n, assign + gp0);
 }
 
 // ============================================================================

@@ -258,3 +258,35 @@ def test_rounds_around_the_most_segments_decided_at_once(kind, B, d, L, k, liste
     for (b, h), ref in pu.oracle_build(wl, K, V, units=[(0, 0), (B - 1, 0)]).items():
         for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
             assert np.array_equal(ix.t[name][b, h].double().cpu().numpy(), getattr(ref, name)), (b, name)
+
+
+# f32: the points of a workgroup whose two best are closer than fp32 tells apart, decided from fp64 similarities by
+# a wave each and, what is left of four, by the workgroup: 0 .. 32 of a fragment's points (a workgroup has one
+# fragment, from 1024 fragments on four), the centroids of a lane at their edges.
+@pytest.mark.parametrize("d,L,k", [(64, 229, 2), (128, 229, 64), (64, 1000, 65), (128, 500, 129), (64, 300, 300), (64, 32900, 40)])
+def test_f32_near_ties_of_a_workgroup(d, L, k):
+    g = np.random.default_rng(L + k)
+    chat = g.standard_normal((k, d))
+    chat /= np.linalg.norm(chat, axis=1, keepdims=True)
+    chat = chat.astype(np.float32)
+    pairs = min(4, k // 2)
+    first, second = np.arange(pairs), k - 1 - np.arange(pairs)
+    chat[second] = chat[first]
+    chat[second[1::2], 3] = np.nextafter(chat[first[1::2], 3], np.float32(2.0))   # (every other pair: one step apart)
+    counts = [0, 1, 3, 4, 5, 7, 31, 32]                                            # near-ties of a fragment of 32 points
+    others = np.arange(pairs, k - pairs) if k > 2 * pairs else np.zeros(0, dtype=int)
+    target = np.empty(L, dtype=int)
+    for f in range((L + 31) // 32):
+        n = min(32, L - 32 * f)
+        near = np.arange(n) < counts[f % len(counts)] if others.size else np.ones(n, dtype=bool)
+        near = g.permutation(near)
+        target[32 * f:32 * f + n] = np.where(near, g.choice(np.concatenate([first, second]), n),
+                                             g.choice(others, n) if others.size else 0)
+    x = (chat[target] + 0.02 * g.standard_normal((L, d))).astype(np.float32)
+    # (equal rows get equal sums: one order for every centroid, which a matrix product does not promise)
+    x64 = x.astype(np.float64)
+    sims = np.stack([(x64 * c).sum(1) for c in chat.astype(np.float64)], axis=1)
+    a = wb.wave_kmeans_assign_step(torch.from_numpy(x).cuda(), torch.from_numpy(chat).cuda())
+    torch.cuda.synchronize()
+    # (a pair one step apart: the two fp64 sums, in whatever order, differ by 1e-9 where their rounding is 1e-16)
+    assert np.array_equal(a.cpu().numpy(), np.argmax(sims, axis=1))
