@@ -230,16 +230,31 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
       if constexpr (sizeof(T) == 2) {
         // In fp32 the quotient is off by three roundings at most (x, 1 / |x|, their product): where that
         // cannot reach the middle between two bf16 values, it rounds as the fp64 quotient does.
+        // A zero, as of a channel that is constant in the segment, is one; looked at only where something is unsure
+        // (16 sequences x 120K tokens with one such channel: 2.27 ms with both quotients of every row, 1.64 so).
         const float rf = (float)rdv;
-        bool unsure = !(dv > 0x1p-20 && dv < 0x1p100);  // (so that no operand below is subnormal)
+        const bool scale_unsure = !(dv > 0x1p-20 && dv < 0x1p100);  // (so that no operand below is subnormal)
+        bool unsure = scale_unsure;
+        auto quotient_unsure = [](uint32_t u) {
+          return (u & 0xffffu) - 0x7ffcu <= 8u ||                               // 4 steps around the middle
+                 (u & 0x7fffffffu) - 0x0d800000u >= 0x7f800000u - 0x0d800000u;  // below 2^-100, no number
+        };
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
           const uint32_t u = __float_as_uint((float)x[e] * rf);
-          unsure |= (u & 0xffffu) - 0x7ffcu <= 8u ||                               // 4 steps around the middle
-                    (u & 0x7fffffffu) - 0x0d800000u >= 0x7f800000u - 0x0d800000u;  // below 2^-100, no number
+          unsure |= quotient_unsure(u);
           o[e].bits = (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
         }
         exact = __ballot(unsure) != 0;
+        if (exact) {
+          unsure = scale_unsure;
+#pragma unroll
+          for (int e = 0; e < EPC; ++e) {
+            if (x[e] == 0.0) o[e].bits = 0;
+            else unsure |= quotient_unsure(__float_as_uint((float)x[e] * rf));
+          }
+          exact = __ballot(unsure) != 0;
+        }
       }
       if (exact) {
 #pragma unroll

@@ -290,3 +290,26 @@ def test_f32_near_ties_of_a_workgroup(d, L, k):
     torch.cuda.synchronize()
     # (a pair one step apart: the two fp64 sums, in whatever order, differ by 1e-9 where their rounding is 1e-16)
     assert np.array_equal(a.cpu().numpy(), np.argmax(sims, axis=1))
+
+
+# Channels that are constant in a segment (head dimensions padded with zeros, of either sign): their normalised keys are
+# zero beside quotients that fp32 decides and others that it does not, rows that are zero as a whole, tiny and huge keys.
+@pytest.mark.parametrize("d,scale", [(64, 1.0), (128, 1.0), (128, 2.0 ** -60), (64, 2.0 ** 110)])
+def test_constant_channels_match_oracle(d, scale):
+    N, L, k = 705, 350, 20
+    g = torch.Generator().manual_seed(d)
+    x = torch.randn(1, 1, N, d, generator=g)
+    x[..., d // 2:] = 0.0
+    x[:, :, ::3, d // 2:] = -0.0
+    x[..., 1] = 3.0
+    x[:, :, 9:12] = x[:, :, 9:10]
+    x[:, :, 2:352, 2] = torch.randint(0, 2, (350,), generator=g) * 2.0 ** -40    # (zero on average or next to it)
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="padded", B=1, Hq=1, Hkv=1, N=N, d=d, n_sink=2, n_local=3,
+                      segment_len=L, clusters_per_segment=k, iters=3)
+    K = (x * scale).to(torch.bfloat16)
+    V = torch.randn(1, 1, N, d, generator=g).to(torch.bfloat16)
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), wl.n_sink, wl.n_local, L, k, 3, 0)
+    torch.cuda.synchronize()
+    for name in ("sizes", "perm", "centroids"):
+        assert torch.equal(ix.t[name].cpu().double(), ref[name].reshape(ix.t[name].shape).double()), name
