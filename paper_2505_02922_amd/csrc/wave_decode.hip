@@ -2304,6 +2304,7 @@ __device__ __forceinline__ int select_lean(const uint32_t (&key)[VPT], const T* 
 // Eight rows of a lane group in flight instead of four: 26.1 -> 28.2 us.
 // ----------------------------------------------------------------------------
 constexpr int SOLO_NT = 1024;
+constexpr int SOLO_STAGE = SOLO_NT;  // most selected clusters of a head, a thread each
 constexpr int SOLO_SLOTS = 512;  // most partials of the other zones
 
 template <typename T, int D, int VPT>
@@ -2320,10 +2321,10 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
   constexpr int GROUPS = NWV * RPW, U = 4, TILE = 2 * NT, STR = D + 2;
   constexpr int NSG = NT / D, UB = 8;
   extern __shared__ uint32_t dyn_keys[];  // keys for the general selection, where the lean one gives up
-  __shared__ int s_pref[FUSED_STAGE + 1];
-  __shared__ int s_row[FUSED_STAGE];
-  __shared__ int s_ids[FUSED_STAGE];
-  __shared__ float s_score[FUSED_STAGE];
+  __shared__ int s_pref[SOLO_STAGE + 1];
+  __shared__ int s_row[SOLO_STAGE];
+  __shared__ int s_ids[SOLO_STAGE];
+  __shared__ float s_score[SOLO_STAGE];
   __shared__ int rowidx[TILE];
   __shared__ LeanLds<NT, VPT> lean;
   __shared__ int scan_scratch[NWV];
@@ -2389,17 +2390,16 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
     }
   }
   if (nsel >= 0) {
-    for (int base = 0; base < nsel; base += NT) {
-      const int t = base + tid;
-      const int id = s_ids[min(t, nsel - 1)];
-      const int r0 = off[id], size = t < nsel ? off[id + 1] - r0 : 0;
-      int tot;
-      const int ex = block_excl_scan<NT>(size, scan_scratch, tot);
-      if (t < nsel) {
-        s_row[t] = r0;
-        s_pref[t] = total + ex;
-      }
-      total += tot;
+    int r0 = 0, size = 0;
+    if (tid < nsel) {
+      const int id = s_ids[tid];
+      r0 = off[id];
+      size = off[id + 1] - r0;
+    }
+    const int ex = block_excl_scan<NT>(size, scan_scratch, total);
+    if (tid < nsel) {
+      s_row[tid] = r0;
+      s_pref[tid] = ex;
     }
     if (tid == 0) s_pref[nsel] = total;
     if (user_selected)
@@ -2409,7 +2409,7 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
     nsel = select_core<T, D, NT, 16, true>(
         q, C, offsets, z, cn2part, cn2_chunks, Hq, Hkv, m, r, rcap, mwords, mc, usel_stride, sel_ids,
         sel_pref, sel_row, bitmap, nsel_out, user_selected, vsum, scale_log2, part, slots,
-        neg_slot, bh, dyn_keys, s_pref, s_row, FUSED_STAGE, &total,
+        neg_slot, bh, dyn_keys, s_pref, s_row, SOLO_STAGE, &total,
         SelView{m, 0, nullptr, nullptr, 0, nullptr, nullptr, s_ids, 1});  // (ends with a barrier)
     for (int i = tid; i < nsel; i += NT) s_score[i] = key_to_float(dyn_keys[s_ids[i]]);
   }
@@ -3771,18 +3771,23 @@ __global__ void fill_i32_kernel(int32_t* p, size_t n, int32_t v) {
 // ============================================================================
 // Host: geometry and launches
 // ============================================================================
-// Retrieved tokens per head up to which one workgroup per head (attend_head_kernel) is faster than
-// selection, retrieval over several workgroups and merge as launches of their own.  A workgroup by
-// itself reads about 0.1 rows per ns: with few heads the crossing is near 1300 tokens, with a head for
-// nearly every CU the memory system is the bound either way.  Beyond a head per CU (the kernel takes a
-// CU's registers) a second round of them follows.  Us per step, launches of their own and one workgroup:
-// 4 heads 327 tokens 30.5 and 23.1, 1310 tokens 39.2 and 43.7; 32 heads 327 tokens 31.9 and 24.1, 655
-// tokens 33.1 and 27, 1310 tokens 44.8 and 49.4; 128 heads 1638 tokens 55.6 and 50.8, 2621 tokens 94.7 and 98.9;
-// 256 heads 655 tokens 63.8 and 56.8, 6553 tokens 241 and 232; 352 heads 655 tokens 84.6 and 85.0, 1310
-// tokens 166 and 182.
-static double solo_max_tokens(int heads) {
-  return heads > 256 ? 0.0 : heads >= 192 ? 1.0e9 : heads >= 128 ? 2048.0 : 1024.0;
-}
+// Retrieved tokens per head, expected from the mean cluster size, up to which one workgroup per head (attend_head_kernel)
+// is faster than selection, retrieval over several workgroups and merge as launches of their own.  A workgroup by itself
+// reads about 0.1 rows per ns, and the sizes of the clusters that a query selects are not known when the launches are
+// chosen: with uneven clusters (heavy-tailed channels) a head's tokens are often five times what is expected, and at more
+// than three tiles the launches of their own give it a fourth workgroup.  So the line lies where uneven clusters have it; even ones
+// would gain 10 .. 20 % up to some thousand tokens.  Us per step, launches of their own and one workgroup, mean of six
+// indexes (the last two rows: three) with four heavy-tailed channels, and with even clusters:
+//    expected       32 heads        64 heads        128 heads       192 heads       256 heads      even, 64 heads
+//       573      59.7    53.7    68.6    63.7    76.2    72.0    86.1    81.0   101.1    95.8
+//       697      62.8    57.0    71.0    67.5    80.6    76.9    90.7    86.2   107.5   102.1    43.1    33.4
+//       841      62.1    68.1    69.7    80.8    80.1    90.0    93.9   101.0   119.3   123.1    43.5    38.0
+//      1064      63.7    77.1    74.2    90.0    88.2   103.8   104.0   117.6   128.1   138.9    47.3    41.5
+//      2931                                                     155.7   212.3   201.1   258.5
+//      5821                                                     263.7   406.3   356.5   496.8
+// Beyond a head per CU (the kernel takes a CU's registers) a second round of them follows: 352 heads with 655 tokens
+// 84.6 and 85.0, with 1310 tokens 166 and 182.
+constexpr int SOLO_HEADS = 256, SOLO_TOKENS = 704;
 
 DecodeGeom decode_geometry(const wave_index& ix, int Hq, int topk) {
   DecodeGeom g{};
@@ -3877,8 +3882,9 @@ DecodeGeom decode_geometry(const wave_index& ix, int Hq, int topk) {
     g.est_chunks = g.score_chunks;
   }
   // Few heads over few clusters: the selection, the retrieval and the merge of a head in one workgroup.
-  g.solo = (m > 0 && r > 0 && !g.fused && !g.listed && m <= SOLO_NT * 16 && r < FUSED_STAGE &&
-            g.steady_chunks + g.est_chunks <= SOLO_SLOTS && expect <= solo_max_tokens(heads)) ? 1 : 0;
+  // (No cluster of a plan is without a token on average, so r <= SOLO_TOKENS.)
+  g.solo = (m > 0 && r > 0 && !g.fused && !g.listed && m <= SOLO_NT * 16 && r <= SOLO_STAGE &&
+            g.steady_chunks + g.est_chunks <= SOLO_SLOTS && heads <= SOLO_HEADS && expect <= SOLO_TOKENS) ? 1 : 0;
   if (g.solo) g.gather_chunks = 0;
   // partial results per head: retrieval, steady, estimation of all clusters per
   // range, and (see below) the selected clusters' estimation terms with a minus sign

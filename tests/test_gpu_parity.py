@@ -371,6 +371,17 @@ def test_decode_many_clusters_hand_index(m, dup, Hq, dtype, d):
             pu.check_selected(sel[0, hq].cpu().numpy(), s_ref, parts["z"], tag)
 
 
+def _launches(fn):
+    """fn's result and the names of the launches that it made."""
+    wb.wave_profile_read()
+    wb.wave_profile_enable(True)
+    out = fn()
+    torch.cuda.synchronize()
+    names = set(wb.wave_profile_read())
+    wb.wave_profile_enable(False)
+    return out, names
+
+
 def _decode_hand(arrs, n, m, d, dtype, q, r, Hq=2):
     """Decode on a hand-filled index of m clusters (one KV head) and the oracle on the same arrays."""
     p, Hkv = 8, 1
@@ -741,7 +752,7 @@ def test_index_append_matches_oracle_then_decode(case, n_news, U, ku, cap, scap,
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
-@pytest.mark.parametrize("m,r,nb", [(3, 2, 2), (64, 20, 30), (1024, 40, 33), (1025, 300, 64), (2048, 37, 3),
+@pytest.mark.parametrize("m,r,nb", [(3, 2, 2), (64, 20, 30), (1024, 40, 33), (1025, 170, 64), (2048, 37, 3),
                                     (2049, 60, 65), (4096, 5, 31), (4097, 80, 70), (16384, 50, 12)])
 def test_selection_of_one_workgroup_per_head(m, r, nb, dtype, d):
     """Few heads and few tokens: a workgroup selects with its keys in registers (1, 2, 4 or 16 a thread:
@@ -774,7 +785,9 @@ def test_selection_of_one_workgroup_per_head(m, r, nb, dtype, d):
     q = torch.from_numpy(np.stack([qv, wo.quant(g.standard_normal(d), dtype), np.zeros(d)])[None].astype(np.float32)
                          ).to(tdt)
     for rr in sorted({1, min(nb, m) // 2, r, min(nb, m)} - {0}):
-        for hq, (o_g, l_g, s_g, o, l, s_ref, z) in enumerate(_decode_hand(arrs, n, m, d, dtype, q, rr, Hq=3)):
+        heads, launches = _launches(lambda: _decode_hand(arrs, n, m, d, dtype, q, rr, Hq=3))
+        assert "attend" in launches and "gather" not in launches, launches
+        for hq, (o_g, l_g, s_g, o, l, s_ref, z) in enumerate(heads):
             tag = f"m={m} r={rr} nb={nb} hq={hq}"
             assert np.array_equal(s_g[s_g >= 0], np.asarray(s_ref)), tag
             pu.check_outputs(o_g, np.array([l_g]), o, np.array([l]), dtype, tag)
@@ -827,3 +840,64 @@ def test_infinite_value_sums_of_estimated_clusters(m, r, empty, dtype, d):
             pu.check_outputs(o_g, np.array([l_g]), o, np.array([l]), dtype, tag)
         else:
             assert o_g[5] == np.inf, (tag, o_g[5])
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("B,Hq,m,per,r,big,attend", [
+    (1, 4, 2049, 4, 20, 2040, True), (1, 4, 2048, 4, 16, 2048, True), (1, 2, 2048, 4, 3, 6000, True),
+    (1, 8, 4096, 4, 176, 9000, True), (1, 8, 4096, 4, 177, 0, False), (1, 3, 1000, 1, 704, 0, True),
+    (1, 3, 1000, 1, 705, 0, False), (128, 1, 300, 4, 60, 700, True), (24, 8, 500, 4, 100, 1200, True),
+    (32, 8, 260, 4, 176, 0, True), (256, 1, 700, 4, 90, 2049, True), (257, 1, 300, 4, 20, 500, False)])
+def test_one_workgroup_per_head_at_its_edges(B, Hq, m, per, r, big, attend, dtype, d):
+    """The launch that selects, retrieves and merges a head in one workgroup: up to 256 heads and 704 expected
+    tokens (r times the mean cluster size, `per`), with as many selected clusters as that allows, and with one
+    cluster of `big` rows among small ones that every query selects: a head's rows then go through one, two or several tiles
+    of 2048, which clusters cross.  Every sequence has the same index and its own queries."""
+    g = np.random.default_rng(m + r + B)
+    N_idx, p = per * m, 8
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    sizes = np.ones(m, dtype=np.int64)
+    where = m // 3
+    left = N_idx - m
+    if big:
+        sizes[where] += min(left, big - 1)
+        left -= min(left, big - 1)
+    other = np.arange(m) != where
+    while left > 0:                                        # the rest over the other clusters, 0 .. 3 rows at a time
+        c = g.choice(np.nonzero(other)[0], min(left, m - 1), replace=False)
+        sizes[c] += 1
+        left -= c.size
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    assert offsets[-1] == N_idx
+    Kp = wo.quant(0.3 * g.standard_normal((N_idx, d)), dtype)
+    Vp = wo.quant(g.standard_normal((N_idx, d)), dtype)
+    lean = np.zeros(d)
+    lean[:8] = 2.0                                         # the large cluster's side, which the queries look at
+    rows = slice(offsets[where], offsets[where + 1])
+    Kp[rows] = wo.quant(Kp[rows] + lean, dtype)
+    C, VS = np.zeros((m, d)), np.zeros((m, d))
+    for c in range(m):
+        C[c] = Kp[offsets[c]:offsets[c + 1]].mean(0)
+        VS[c] = Vp[offsets[c]:offsets[c + 1]].sum(0)
+    arrs = dict(centroids=wo.quant(C, dtype), vsum=wo.quant(VS, dtype), sizes=sizes, offsets=offsets,
+                perm=np.arange(N_idx), k_perm=Kp, v_perm=Vp, k_steady=wo.quant(g.standard_normal((p, d)), dtype),
+                v_steady=wo.quant(g.standard_normal((p, d)), dtype))
+    tens = {k: torch.from_numpy(np.asarray(v)[None, None].astype(
+        np.int32 if k in ("sizes", "offsets", "perm") else np.float32)).expand(B, 1, *np.asarray(v).shape).contiguous()
+        for k, v in arrs.items()}
+    ix = wb.index_from_arrays(tdt, B, 1, d, N_idx + p, 4, p - 4, per, 1, tens)
+    assert ix.m == m
+    ref = wo.UnitIndex(wo.make_plan(N_idx + p, 4, p - 4, per, 1), dtype, *[arrs[k] for k in (
+        "centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm", "k_steady", "v_steady")],
+        np.zeros(0, dtype=np.int64))
+    q = torch.from_numpy(wo.quant(0.5 * g.standard_normal((B, Hq, d)) + lean, dtype).astype(np.float32)).to(tdt)
+    (out, lse, sel), launches = _launches(lambda: wb.wave_attention_decode(q.cuda(), ix, r, want_selected=True))
+    assert ("attend" in launches) == attend and ("gather" in launches) != attend, launches
+    for bh in sorted({0, 1, B * Hq // 2, B * Hq - 2, B * Hq - 1}):
+        b, hq = divmod(bh, Hq)
+        parts = {}
+        o, l, s_ref = wo.decode_unit(q[b, hq].double().numpy(), ref, r, parts)
+        tag = f"b={b} hq={hq}"
+        assert not big or where in s_ref, tag
+        pu.check_outputs(out[b, hq].cpu().numpy(), lse[b, hq:hq + 1].cpu().numpy(), o, np.array([l]), dtype, tag)
+        pu.check_selected(sel[b, hq].cpu().numpy(), s_ref, parts["z"], tag)
