@@ -2319,7 +2319,8 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
     const T* __restrict__ v_perm, int N_idx, float* __restrict__ out, float* __restrict__ lse) {
   constexpr int NT = SOLO_NT, EPC = Elem<T>::EPC, LPR = D / EPC, RPW = 64 / LPR, NWV = NT / 64;
   constexpr int GROUPS = NWV * RPW, U = 4, TILE = 2 * NT, STR = D + 2;
-  constexpr int NSG = NT / D, UB = 8;
+  constexpr int NSG = NT / D, UB = 8, FOLD = UB * NSG;  // partials that are folded at a time
+  static_assert(SOLO_SLOTS % FOLD == 0 && FOLD >= 64, "a weight for each");
   extern __shared__ uint32_t dyn_keys[];  // keys for the general selection, where the lean one gives up
   __shared__ int s_pref[SOLO_STAGE + 1];
   __shared__ int s_row[SOLO_STAGE];
@@ -2329,7 +2330,7 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
   __shared__ LeanLds<NT, VPT> lean;
   __shared__ int scan_scratch[NWV];
   __shared__ float smem[NWV * STR];
-  __shared__ float s_weight[SOLO_SLOTS + 2];  // of the other zones' partials (without any term: -1); their maximum and sum
+  __shared__ float s_weight[SOLO_SLOTS + 2];  // of the other zones' partials (-1: does not count); their maximum and sum
   __shared__ float s_a[NSG * D];
   const int bh = blockIdx.x;
   const int b = bh / Hq, hq = bh - b * Hq, G = Hq / Hkv;
@@ -2374,15 +2375,19 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
   WAVE_STAMP(bitmap + (size_t)bh * mwords, 11);
   int total = 0;
   if (wave == NWV - 1) {  // (idle in the scan below) weights of the other zones' partials
-    float mx = kNegBig, l = 0.f;
-    for (int i = lane; i < slots; i += 64) mx = fmaxf(mx, pslots[(size_t)i * STR]);
+    const float* p0 = pslots + (size_t)min(lane, slots - 1) * STR;
+    const float m0 = lane < slots ? p0[0] : kNegBig, l0 = p0[1];
+    float mx = m0, l = 0.f;
+    for (int i = 64 + lane; i < slots; i += 64) mx = fmaxf(mx, pslots[(size_t)i * STR]);
     mx = wave_max(mx);
-    for (int i = lane; i < slots; i += 64) {
-      const float m1 = pslots[(size_t)i * STR];
-      const bool counts = m1 > 0.5f * kNegBig;  // (a partial without any term: kNegBig)
-      s_weight[i] = counts ? exp2f(m1 - mx) : -1.f;
-      l = counts ? fmaf(s_weight[i], pslots[(size_t)i * STR + 1], l) : l;
-    }
+    auto weigh = [&](int i, float m1, float l1) {  // (no term: kNegBig)
+      const float w = m1 > 0.5f * kNegBig ? exp2f(m1 - mx) : -1.f;
+      s_weight[i] = w;
+      l = w >= 0.f ? fmaf(w, l1, l) : l;
+    };
+    weigh(lane, m0, l0);
+    for (int i = 64 + lane; i < slots; i += 64) weigh(i, pslots[(size_t)i * STR], pslots[(size_t)i * STR + 1]);
+    for (int i = max(slots, 64) + lane; i < (slots + FOLD - 1) / FOLD * FOLD; i += 64) s_weight[i] = -1.f;
     l = wave_add_f(l);
     if (lane == 0) {
       s_weight[SOLO_SLOTS] = mx;
@@ -2493,14 +2498,19 @@ __global__ __launch_bounds__(SOLO_NT) void attend_head_kernel(
   // (what does not count is left out, not weighted with zero: its sums, or those of the partial read in
   // place of one past the end, may be infinite)
   float A = 0.f;
+  auto fold = [&](int s0, const float (&v)[UB]) {
 #pragma unroll
-  for (int u = 0; u < UB; ++u) {
-    const float w = sg + u * NSG < slots ? s_weight[min(sg + u * NSG, slots - 1)] : -1.f;
-    A = w >= 0.f ? fmaf(w, pa[u], A) : A;
-  }
-  for (int s0 = sg + UB * NSG; s0 < slots; s0 += NSG) {
-    const float w = s_weight[s0];
-    A = w >= 0.f ? fmaf(w, pslots[(size_t)s0 * STR + 2 + e], A) : A;
+    for (int u = 0; u < UB; ++u) {
+      const float w = s_weight[s0 + u * NSG];
+      A = fmaf(w, w >= 0.f ? v[u] : 0.f, A);
+    }
+  };
+  fold(sg, pa);
+  for (int s0 = sg + FOLD; s0 < slots; s0 += FOLD) {
+    float v[UB];
+#pragma unroll
+    for (int u = 0; u < UB; ++u) v[u] = pslots[(size_t)min(s0 + u * NSG, slots - 1) * STR + 2 + e];
+    fold(s0, v);
   }
   __syncthreads();
   // lane w: wave w's partial; lane NWV: the other zones'
