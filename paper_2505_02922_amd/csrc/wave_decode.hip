@@ -3799,6 +3799,17 @@ __global__ void fill_i32_kernel(int32_t* p, size_t n, int32_t v) {
 // 84.6 and 85.0, with 1310 tokens 166 and 182.
 constexpr int SOLO_HEADS = 256, SOLO_TOKENS = 704;
 
+// Whether the meta-index pass with the steady zone (dense_steady_kernel) may be cut into `workgroups`: with three query heads
+// per KV head or more as many as are resident at once, one wave of each on a SIMD with 512 registers, by what the kernel
+// takes (us per step before and after a cut from inside to beyond: 16 units with seven heads, 400 and 528 workgroups of 512, 30.5
+// and 36.5; 24 with four, 600 and 792 of 768, 28.2 and 30.7; 32 with four, 672 and 800, 32.1 and 31.5).  With one or two a cut
+// beyond still gains (48 units with two heads, 1008 and 1200 of 1024, 30.8 and 29.3), and in f32, which has no matrix
+// instructions here (48 units with four heads 48.6 and 43.1).
+static bool dense_steady_cut(int dtype, int G, long long workgroups) {
+  constexpr int registers[8] = {88, 124, 116, 140, 160, 176, 208, 232};  // bf16
+  return dtype == WAVE_F32 || G <= 2 || workgroups <= 256 * (512 / registers[G - 1]);
+}
+
 DecodeGeom decode_geometry(const wave_index& ix, int Hq, int topk) {
   DecodeGeom g{};
   const int m = ix.m, units = ix.B * ix.Hkv, heads = ix.B * Hq, D = ix.d;
@@ -3883,11 +3894,18 @@ DecodeGeom decode_geometry(const wave_index& ix, int Hq, int topk) {
     g.gather_wgs = (int)(grid < g.wtotal ? grid : g.wtotal);
     g.stage = (r < FUSED_STAGE ? r : FUSED_STAGE) + 1;  // (+ 1: the end of the last staged cluster)
   }
-  // The meta-index pass in smaller pieces when it does not give every CU a workgroup (8 units of 2048
-  // clusters with their steady zones: 13.6 us in 256-cluster pieces, 8.3 us in 64-cluster ones).
+  // The meta-index pass in smaller pieces when it does not give every CU a workgroup, as long as dense_steady_cut allows it
+  // and a head has no more than 128 estimation partials to merge.  Us per step in pieces of 256, 128 and 64 clusters: 8
+  // units of 1024 clusters 27.6, 24.5, 23.1, 16 of them 28.4, 25.7, 25.3, 24 of 2048 35.5, 35.2, 35.2; 1 unit of 16384 clusters in 64
+  // pieces 44.7, in 256 49.2.  Launches of their own: 4 heads with 2942 tokens 42.0, 39.0,
+  // 38.0, 32 heads with 9793 tokens 74.8, 74.7, 74.8.
   if (!g.fused && !g.listed && !g.sliced && g.steady_chunks > 0) {
-    while (g.score_rows > 64 && units * ((m + g.score_rows - 1) / g.score_rows) < 256) g.score_rows /= 2;
-    g.score_chunks = m > 0 ? (m + g.score_rows - 1) / g.score_rows : 0;
+    while (g.score_rows > 64 && units * g.score_chunks < 256) {
+      const int rows = g.score_rows / 2, finer = (m + rows - 1) / rows;
+      if (finer > 128 || !dense_steady_cut(ix.dtype, Hq / ix.Hkv, (long long)units * (finer + g.steady_chunks))) break;
+      g.score_rows = rows;
+      g.score_chunks = finer;
+    }
     g.est_rows = g.score_rows;
     g.est_chunks = g.score_chunks;
   }

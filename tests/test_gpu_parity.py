@@ -843,18 +843,21 @@ def test_infinite_value_sums_of_estimated_clusters(m, r, empty, dtype, d):
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
-@pytest.mark.parametrize("B,Hq,m,per,r,big,attend", [
-    (1, 4, 2049, 4, 20, 2040, True), (1, 4, 2048, 4, 16, 2048, True), (1, 2, 2048, 4, 3, 6000, True),
-    (1, 8, 4096, 4, 176, 9000, True), (1, 8, 4096, 4, 177, 0, False), (1, 3, 1000, 1, 704, 0, True),
-    (1, 3, 1000, 1, 705, 0, False), (128, 1, 300, 4, 60, 700, True), (24, 8, 500, 4, 100, 1200, True),
-    (32, 8, 260, 4, 176, 0, True), (256, 1, 700, 4, 90, 2049, True), (257, 1, 300, 4, 20, 500, False)])
-def test_one_workgroup_per_head_at_its_edges(B, Hq, m, per, r, big, attend, dtype, d):
+@pytest.mark.parametrize("B,Hq,m,per,r,big,p,attend", [
+    (1, 4, 2049, 4, 20, 2040, 8, True), (1, 4, 2048, 4, 16, 2048, 8, True), (1, 2, 2048, 4, 3, 6000, 8, True),
+    (1, 8, 4096, 4, 176, 9000, 8, True), (1, 8, 4096, 4, 177, 0, 8, False), (1, 3, 1000, 1, 704, 0, 8, True),
+    (1, 3, 1000, 1, 705, 0, 8, False), (128, 1, 300, 4, 60, 700, 8, True), (24, 8, 500, 4, 100, 1200, 8, True),
+    (32, 8, 260, 4, 176, 0, 8, True), (256, 1, 700, 4, 90, 2049, 8, True), (257, 1, 300, 4, 20, 500, 8, False),
+    (24, 8, 1400, 1, 50, 0, 8, True), (40, 6, 1001, 1, 50, 0, 640, True), (1, 2, 16384, 1, 100, 0, 70, True)])
+def test_one_workgroup_per_head_at_its_edges(B, Hq, m, per, r, big, p, attend, dtype, d):
     """The launch that selects, retrieves and merges a head in one workgroup: up to 256 heads and 704 expected
     tokens (r times the mean cluster size, `per`), with as many selected clusters as that allows, and with one
     cluster of `big` rows among small ones that every query selects: a head's rows then go through one, two or several tiles
-    of 2048, which clusters cross.  Every sequence has the same index and its own queries."""
+    of 2048, which clusters cross.  The meta-index pass before it works in pieces of 64 clusters, of 128 (24 units of
+    1400 clusters, 1 of 16384) and of 256 (40 units with ten steady pieces each; 128 units and more).  Every
+    sequence has the same index and its own queries."""
     g = np.random.default_rng(m + r + B)
-    N_idx, p = per * m, 8
+    N_idx = per * m
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
     sizes = np.ones(m, dtype=np.int64)
     where = m // 3
