@@ -170,9 +170,11 @@ constexpr int NORM_ROWS = 128, NORM_RESIDENT = 6 * 256;
 template <typename T, int D>
 __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
                                                         const double* __restrict__ mean,
+                                                        double* __restrict__ mean_out,
                                                         T* __restrict__ xhat, int32_t* __restrict__ range, int S, int L, int kk, int N,
                                                         int N_idx, int n_sink, int chunks, int row_step, int pieces) {
-  // mean: of every segment, or with pieces > 1 the sums of its pieces
+  // mean: of every segment, or with pieces > 1 the sums of its pieces (a segment's first workgroup then leaves
+  // the mean in mean_out, where it is without pieces)
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR, U = 4;
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   const int sg = blockIdx.x / chunks, chunk = blockIdx.x - sg * chunks;
@@ -195,6 +197,7 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
       for (int j = 0; j < pieces; ++j) m += mean[((size_t)sg * pieces + j) * D + threadIdx.x];
       m /= (double)si.L_s;
       mean_s[threadIdx.x] = m;
+      if (chunk == 0) mean_out[(size_t)sg * D + threadIdx.x] = m;
     }
     __syncthreads();
   }
@@ -2598,7 +2601,7 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
       row_step *= 2;
       chunks = (chunks + 1) / 2;
     }
-    WAVE_LAUNCH("normalise", (normalise_kernel<T, D>), g.segs * chunks, 256, 0, st, K, sums_of, xhat, range, S, L, kk,
+    WAVE_LAUNCH("normalise", (normalise_kernel<T, D>), g.segs * chunks, 256, 0, st, K, sums_of, mean, xhat, range, S, L, kk,
                 ix.N, N_idx, ns, chunks, row_step, pieces);
   }
   {
