@@ -1412,7 +1412,13 @@ __global__ __launch_bounds__(256, D == 128 ? 4 : 1) void assign_f32_kernel(
     if (best - second < kAssignGuard) near_p[atomicAdd(&near_n, 1)] = point;
   }
   __syncthreads();
-  settle_near_f32<D>(xhat + gp0 * D, Cs, si.k_s, near_p, near_n, assign + gp0);
+  if (near_n == 1) {  // (the usual number: the point's row in LDS; 2 segments of 2046 points x 128 clusters 208 -> 204 us)
+    const int p = near_p[0];
+    const int bi = refine_point<float, D>(xhat + (gp0 + p) * D, Cs, si.k_s);
+    if (threadIdx.x == 0 && bi < si.k_s) assign[gp0 + p] = bi;
+  } else {
+    settle_near_f32<D>(xhat + gp0 * D, Cs, si.k_s, near_p, near_n, assign + gp0);
+  }
 }
 
 // ============================================================================
