@@ -2077,7 +2077,8 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
 // 128 segments of 1024 points x 64 clusters, ten rounds: 200 us with every member summed again and the
 // points read again in each round, 165 with the changed clusters summed, 105 us so (about 3.5 us assign, where the
 // matrix instructions take 1.7, and 4 us update a round).  120K tokens x 16 in such segments: build
-// 17.4 -> 11.6 ms; in segments of 2048 points x 128 clusters (neither KEEP nor SUMS) 17.9 -> 15.1 ms.
+// 17.4 -> 11.6 ms; in segments of 2048 points x 128 clusters (neither KEEP nor SUMS) 17.9 -> 15.1 ms.  Whole builds of
+// 32 segments, ten rounds: 1024 points x 128 clusters (KEEP alone) 301 -> 215 us, 2048 x 64 (SUMS alone) 393 -> 318.
 // ============================================================================
 constexpr int SMALL_L_MAX = 2048;   // points per segment
 constexpr int SMALL_K_MAX = 128;    // clusters per segment
@@ -2681,12 +2682,15 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
     };
     // The first and the last round of a few segments: several workgroups sort and sum a segment, not one (32
     // segments of 8192 points x 512 clusters: sort, update and large clusters 42 us, 36 us so, a build of 6 segments
-    // of 4096 x 256 495 and 483 us); 224 segments pay for reading their assignments eight times (3.03 and 3.12 ms).
+    // of 4096 x 256 495 and 483 us); 224 segments pay for reading their assignments eight times (3.01 and 3.13 ms).  Of
+    // 8192 x 512, eight workgroups each, 64 segments are level (1106 and 1109), 96 and 127 lose 1.4 and 2.4 %; of 4096 x
+    // 256, four each, 96 are level (567) and 127 gain 1 %, 144 would lose 2 % (849 and 866 us).
     const bool scan = delta && g.segs < 128;
     for (int t = 0; t < iters && !small; ++t) {
       // Rounds 0 and 1 meet all new centroids; from round 2 on only the changed ones are compared.
-      launch_assign<T, D>(xhat, chat, assign, prev, t >= 1 ? bounds : nullptr, bounds_skip, delta && t >= 2 ? changed : nullptr,
-                          nchanged[(t + 1) & 1], nlisted[t & 1], nlisted[(t + 1) & 1], t, flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
+      const AssignRound ar{prev, t >= 1 ? bounds : nullptr, bounds_skip, delta && t >= 2 ? changed : nullptr,
+                           nchanged[(t + 1) & 1], nlisted[t & 1], nlisted[(t + 1) & 1]};
+      launch_assign<T, D>(xhat, chat, assign, ar, t, flag, nflag, S, L, kk, N_idx, g.segs, 1024, st);
       const bool last = t + 1 == iters;
       if (scan && (t == 0 || last)) {
         WAVE_LAUNCH("update", (update_scan_kernel<T, D>), g.segs * scan_pieces, SCAN_NT, 0, st, xhat, chat, assign, assign,
