@@ -2459,14 +2459,24 @@ static int key_bits_for(int kk) {
   return b;
 }
 
-// One assign step.  bounds, changed: null in a round that compares every point with every
-// centroid; with `bounds` alone such a round leaves what the next one needs to compare with the
-// changed centroids only, and in prev which points moved.  nlisted: points listed per segment (all
-// zero; nlisted_next is cleared), or null: near-ties of all segments go to one list, for refine_kernel.
+// What an incremental round of a bf16 build needs beside the points and centroids; all null elsewhere.
+// bounds, changed: null in a round that compares every point with every centroid; with `bounds` alone
+// such a round leaves what the next one needs to compare with the changed centroids only, and in prev
+// which points moved.  nlisted: points listed per segment (all zero; nlisted_next is cleared), or null:
+// near-ties of all segments go to one list, for refine_kernel.
+struct AssignRound {
+  int32_t* prev;
+  PointBounds* bounds;
+  long long bounds_skip;
+  const int32_t *changed, *nchanged;
+  int32_t *nlisted, *nlisted_next;
+};
+
+// One assign step of round `round`.
 template <typename T, int D>
-static void launch_assign(const T* xhat, const T* chat, int32_t* assign, int32_t* prev, PointBounds* bounds,
-                          long long bounds_skip, const int32_t* changed, const int32_t* nchanged, int32_t* nlisted, int32_t* nlisted_next, int round, int32_t* flag, int32_t* nflag, int S, int L, int kk, int N_idx,
-                          int segs, int refine_wgs, hipStream_t st) {
+static void launch_assign(const T* xhat, const T* chat, int32_t* assign, const AssignRound& ar, int round, int32_t* flag,
+                          int32_t* nflag, int S, int L, int kk, int N_idx, int segs, int refine_wgs, hipStream_t st) {
+  const auto [prev, bounds, bounds_skip, changed, nchanged, nlisted, nlisted_next] = ar;
   const int Lmax = L < N_idx ? L : N_idx, kmax = kk < Lmax ? kk : Lmax;
   if constexpr (sizeof(T) == 2) {
     if (nlisted || resident_full_passes(WAVE_BF16, D, kmax, Lmax, segs)) {
@@ -2632,8 +2642,7 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
     // Two launches a round.  The assignments of even and of odd rounds have an array each.
     for (int t = 0; t < iters; ++t) {
       int32_t* now = t & 1 ? prev : assign;
-      launch_assign<T, D>(xhat, chat, now, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr, t, flag, nflag, S, L, kk,
-                          N_idx, g.segs, 0, st);
+      launch_assign<T, D>(xhat, chat, now, AssignRound{}, t, flag, nflag, S, L, kk, N_idx, g.segs, 0, st);
       WAVE_LAUNCH("update", (update_scan_kernel<T, D>), g.segs * scan_pieces, SCAN_NT, 0, st, xhat, chat, now,
                   t & 1 ? assign : prev, order, count, start, nullptr, 0, t == 0 ? 1 : 0, t + 1 == iters ? 1 : 0, S, L, kk,
                   N_idx, scan_span, scan_pieces);
@@ -2737,8 +2746,13 @@ static wave_status assign_step_td(const void* xhat, const void* chat, int L_s, i
   int32_t* flag = nflag + 64;
   hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, nflag);
   // one unit, one segment: S = 1, L = N_idx = L_s, kk = k_s
-  launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, nullptr, nullptr, 0, nullptr, nullptr,
-                      centroids_resident(sizeof(T) == 2 ? WAVE_BF16 : WAVE_F32, D, k_s) ? nflag : nullptr, nflag + 1, 0, flag, nflag, 1, L_s, k_s, L_s, 1, 256, st);
+  AssignRound ar{};
+  if (centroids_resident(sizeof(T) == 2 ? WAVE_BF16 : WAVE_F32, D, k_s)) {
+    ar.nlisted = nflag;
+    ar.nlisted_next = nflag + 1;
+  }
+  launch_assign<T, D>(static_cast<const T*>(xhat), static_cast<const T*>(chat), assign, ar, 0, flag, nflag, 1, L_s, k_s, L_s,
+                      1, 256, st);
   return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;
 }
 
