@@ -286,19 +286,22 @@ def decode_phase(run: DecodeRun, steps: int, warmup: int, profile_steps: int):
         "meta_index+steady": meta + steady_b,
         "scores+steady": cbytes + units * ix.m * 4 + steady_b, "select+estimate+steady": cbytes + steady_b,
         "gather+estimate": gather_b + cbytes,
+        # selection, retrieval and merge of a head in one launch; the selected clusters' value sums come again
+        "attend": gather_b + wl.B * wl.Hq * run.r * row,
     }
     step_bytes = meta + steady_b + gather_b
     kern = {k: v[0] / max(v[1], 1) for k, v in dec_prof.items()}      # ms per launch
     roofline = None
     if kern:   # (no per-kernel profile was asked for: --profile-steps 0)
         dominant = max(kern, key=kern.get)
-        dom_gbs = bytes_k.get(dominant, 0) / (kern[dominant] * 1e-3) / 1e9
+        dom_bytes = bytes_k[dominant]  # (a launch without an entry is an error, not zero bytes)
+        dom_gbs = dom_bytes / (kern[dominant] * 1e-3) / 1e9
         roofline = {"bound": "hbm", "kernel": dominant, "achieved": round(dom_gbs, 1),
                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(dom_gbs / HBM_PEAK_GBS, 4),
                     "traffic": recorded_traffic(wl.name, dominant),
                     "traffic_source": "recorded rocprofv3 --pmc runs (profiles/traffic.json), quoted "
                                       "only when taken on the kernel sources present",
-                    "bytes_per_launch": int(bytes_k.get(dominant, 0)),
+                    "bytes_per_launch": int(dom_bytes),
                     "ms_per_launch": round(kern[dominant], 5)}
     info = {
         "ms_per_step": round(ms_per_step, 5),

@@ -1782,7 +1782,7 @@ __global__ __launch_bounds__(256) void update_touched_kernel(const T* __restrict
 // the whole workgroup one of more than UPD_BIG.  `all`: the last round; nothing is summed.
 // (One workgroup per segment sorting all points, update_touched_kernel and update_big_kernel: three launches
 // and 6.2 + 2 .. 12 + 1.3 us a round for 2 segments of 2048 points x 128 clusters, 4.2 .. 15 us so; a whole
-// build of them 285 -> 163 us, of 100 segments of 4096 points x 256 clusters 2.03 -> 1.99 ms.)
+// build of them 285 -> 155 us, of 100 segments of 4096 points x 256 clusters 2.03 -> 1.99 ms.)
 // ============================================================================
 constexpr int SCAN_NT = 512, SCAN_CLUSTERS = 64;  // threads; most clusters of a workgroup
 
