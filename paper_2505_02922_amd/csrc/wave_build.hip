@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
                                                         T* __restrict__ xhat, int32_t* __restrict__ range, int S, int L, int kk, int N,
                                                         int N_idx, int n_sink, int chunks, int row_step, int pieces) {
   // mean: of every segment, or with pieces > 1 the sums of its pieces (a segment's first workgroup then leaves
-  // the mean in mean_out, where it is without pieces)
+  // the mean in mean_out, where it is without pieces: the workspace holds the same in either form; no later step reads it)
   constexpr int EPC = Elem<T>::EPC, LPR = D / EPC, GROUPS = 256 / LPR, U = 4;
   const int sub = threadIdx.x % LPR, grp = threadIdx.x / LPR;
   const int sg = blockIdx.x / chunks, chunk = blockIdx.x - sg * chunks;
@@ -1253,8 +1253,8 @@ __device__ __forceinline__ void similarities_f64(const float* const (&x)[P], con
 }
 
 // Near-ties of f32 builds, decided by the workgroup that finds them: the n points near_p[] of a segment (rows X, centroids
-// Cs) get the argmax of their fp64 similarities, ties to the lowest centroid.  Of its four waves up to
-// four waves share out the centroids, the others take other points, and a wave compares up to four points with every row
+// Cs) get the argmax of their fp64 similarities, ties to the lowest centroid.  One, two or four of the four waves share out
+// the centroids, by their number; the others take other points.  A wave compares up to four points with every row
 // that it reads.  (A row per lane is a cache line per lane: with one point at a time the reads are the bound.  Builds of
 // few segments whose points are all near-ties, six rounds, the points one after the other by the workgroup and so:
 // 2 segments of 2048 points x 128 clusters x 64 channels 633 -> 358 us, 1 of 1024 x 64 x 128 938 -> 216 us.)

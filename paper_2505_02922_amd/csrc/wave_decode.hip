@@ -3785,8 +3785,8 @@ __global__ void fill_i32_kernel(int32_t* p, size_t n, int32_t v) {
 // is faster than selection, retrieval over several workgroups and merge as launches of their own.  A workgroup by itself
 // reads about 0.1 rows per ns, and the sizes of the clusters that a query selects are not known when the launches are
 // chosen: with uneven clusters (heavy-tailed channels) a head's tokens are often five times what is expected, and at more
-// than three tiles the launches of their own give it a fourth workgroup.  So the line lies where uneven clusters have it; even ones
-// would gain 10 .. 20 % up to some thousand tokens.  Us per step, launches of their own and one workgroup, mean of six
+// than three tiles (768 tokens) the launches of their own give it a fourth workgroup.  So the line lies where uneven clusters
+// have it; even ones would gain 10 .. 20 % up to some thousand tokens.  Us per step, launches of their own and one workgroup, mean of six
 // indexes (the last two rows: three) with four heavy-tailed channels, and with even clusters:
 //    expected       32 heads        64 heads        128 heads       192 heads       256 heads      even, 64 heads
 //       573      59.7    53.7    68.6    63.7    76.2    72.0    86.1    81.0   101.1    95.8
@@ -3800,8 +3800,8 @@ __global__ void fill_i32_kernel(int32_t* p, size_t n, int32_t v) {
 constexpr int SOLO_HEADS = 256, SOLO_TOKENS = 704;
 
 // Whether the meta-index pass with the steady zone (dense_steady_kernel) may be cut into `workgroups`: with three query heads
-// per KV head or more as many as are resident at once, one wave of each on a SIMD with 512 registers, by what the kernel
-// takes (us per step before and after a cut from inside to beyond: 16 units with seven heads, 400 and 528 workgroups of 512, 30.5
+// per KV head or more only as many as are resident at once, one wave of each on a SIMD with 512 registers, by what the kernel
+// takes (us per step before and after a cut from within that number to beyond: 16 units with seven heads, 400 and 528 workgroups of 512, 30.5
 // and 36.5; 24 with four, 600 and 792 of 768, 28.2 and 30.7; 32 with four, 672 and 800, 32.1 and 31.5).  With one or two a cut
 // beyond still gains (48 units with two heads, 1008 and 1200 of 1024, 30.8 and 29.3), and in f32, which has no matrix
 // instructions here (48 units with four heads 48.6 and 43.1).
