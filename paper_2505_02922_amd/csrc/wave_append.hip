@@ -35,46 +35,8 @@ __global__ __launch_bounds__(256) void set_first_kernel(int32_t* __restrict__ ds
   if (u < units) dst[(size_t)u * stride] = 0;
 }
 
-// Row j of a unit's sink + window (ns sink rows of the old steady buffer, lc_old
-// old local rows, n_new new tokens) goes to: the new steady buffer as it is
-// (sink), the scratch tensor (window rows before `flush`), or the new steady
-// buffer behind the sink rows.  One thread per 16-byte chunk of a row.
-template <int ROWB>
-__global__ __launch_bounds__(256) void route_window_kernel(
-    const char* __restrict__ ks_old, const char* __restrict__ vs_old, const char* __restrict__ k_new,
-    const char* __restrict__ v_new, char* __restrict__ k_flush, char* __restrict__ v_flush,
-    char* __restrict__ ks_out, char* __restrict__ vs_out, int ns, int lc_old, int n_new, int flush,
-    int p_old, int p_out, int units, int first) {
-  // p_old, p_out: rows per unit of the old and the new steady buffers; first: rows before it are
-  // already in place (the new buffers are the old ones and nothing is flushed)
-  constexpr int CPR = ROWB / 16;
-  const size_t rows_u = (size_t)ns + lc_old + n_new - first;
-  const size_t total = rows_u * units * CPR, step = (size_t)gridDim.x * 256;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += step) {
-    const size_t row = i / CPR, ch = i - row * CPR;
-    const size_t u = row / rows_u;
-    const int j = (int)(row - u * rows_u) + first;
-    const char *sk, *sv;
-    if (j < ns + lc_old) {
-      sk = ks_old + ((size_t)u * p_old + j) * ROWB;
-      sv = vs_old + ((size_t)u * p_old + j) * ROWB;
-    } else {
-      sk = k_new + ((size_t)u * n_new + (j - ns - lc_old)) * ROWB;
-      sv = v_new + ((size_t)u * n_new + (j - ns - lc_old)) * ROWB;
-    }
-    char *dk, *dv;
-    const int w = j - ns;  // position in the window; negative for sink rows
-    if (w >= 0 && w < flush) {
-      dk = k_flush + ((size_t)u * flush + w) * ROWB;
-      dv = v_flush + ((size_t)u * flush + w) * ROWB;
-    } else {
-      const int r = w < 0 ? j : ns + (w - flush);
-      dk = ks_out + ((size_t)u * p_out + r) * ROWB;
-      dv = vs_out + ((size_t)u * p_out + r) * ROWB;
-    }
-    *reinterpret_cast<uint4*>(dk + ch * 16) = *reinterpret_cast<const uint4*>(sk + ch * 16);
-    *reinterpret_cast<uint4*>(dv + ch * 16) = *reinterpret_cast<const uint4*>(sv + ch * 16);
-  }
+__global__ __launch_bounds__(256) void route_window_kernel(WindowRoute window) {
+  route_window<1>(window, (size_t)blockIdx.x * 256 + threadIdx.x, (size_t)gridDim.x * 256);
 }
 
 static int grid_for(size_t items) {
@@ -114,26 +76,17 @@ wave_status launch_append(const wave_index& o, const void* K_new, const void* V_
   copy_units<uint4>(nw.k_perm, o.k_perm, (size_t)o.N_idx * rowc, rs_new * rowc, rs_old * rowc, 0, units, st);
   copy_units<uint4>(nw.v_perm, o.v_perm, (size_t)o.N_idx * rowc, rs_new * rowc, rs_old * rowc, 0, units, st);
 
-  // (2) sink rows and the window
-  {
-    // with the old steady buffers as the new ones (no flush, room left) only the new tokens move
-    const int first = nw.k_steady == o.k_steady ? ns + g.lc_old : 0;
-    const size_t chunks = ((size_t)ns + g.lc_old + n_new - first) * units * rowc;
-    if (chunks > 0) {
-#define WAVE_ROUTE(ROWB)                                                                              \
-  WAVE_LAUNCH("append_window", (route_window_kernel<ROWB>), grid_for(chunks), 256, 0, st,             \
-              static_cast<const char*>(o.k_steady), static_cast<const char*>(o.v_steady),             \
-              static_cast<const char*>(K_new), static_cast<const char*>(V_new), w + g.off_k,          \
-              w + g.off_v, static_cast<char*>(nw.k_steady), static_cast<char*>(nw.v_steady), ns,      \
-              g.lc_old, n_new, flush, steady_stride(o), steady_stride(nw), units, first)
-      const size_t rowb = (size_t)D * es;
-      if (rowb == 128) WAVE_ROUTE(128);
-      else if (rowb == 256) WAVE_ROUTE(256);
-      else if (rowb == 512) WAVE_ROUTE(512);
-      else return WAVE_ERR_SHAPE;
-#undef WAVE_ROUTE
-    }
-  }
+  // (2) sink rows and the window.  Where the update flushes no more than the old window holds (as one after every U
+  // tokens does) and its segments leave CUs idle, the build routes the window beside its k-means.
+  // (with the old steady buffers as the new ones (no flush, room left) only the new tokens move)
+  const WindowRoute window{static_cast<const char*>(o.k_steady), static_cast<const char*>(o.v_steady),
+                           static_cast<const char*>(K_new), static_cast<const char*>(V_new),
+                           w + g.off_k, w + g.off_v, static_cast<char*>(nw.k_steady), static_cast<char*>(nw.v_steady),
+                           ns, g.lc_old, n_new, flush, steady_stride(o), steady_stride(nw), units,
+                           nw.k_steady == o.k_steady ? ns + g.lc_old : 0, (int)rowc};
+  const bool beside = g.F > 0 && flush <= g.lc_old && build_routes_window(g.mini);
+  if (!beside && window.total() > 0)
+    WAVE_LAUNCH("append_window", route_window_kernel, grid_for(window.total()), 256, 0, st, window);
   if (g.F == 0) return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;
 
   // (3) the flushed tokens are built as an index whose arrays are the new index's own, from
@@ -152,7 +105,7 @@ wave_status launch_append(const wave_index& o, const void* K_new, const void* V_
   mi.v_perm = static_cast<char*>(nw.v_perm) + (size_t)o.N_idx * rowb;
   mi.row_capacity = row_stride(nw);
   return launch_build(w + g.off_k, w + g.off_v, mi, iters, seed, w + g.off_build, st, o.S, o.N_idx,
-                      o.N - g.lc_old);
+                      o.N - g.lc_old, beside ? &window : nullptr);
 }
 
 }  // namespace wave

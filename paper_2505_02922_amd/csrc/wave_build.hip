@@ -2099,10 +2099,14 @@ inline size_t small_kmeans_lds(int kk, bool keep_sums) {
 template <int D, int KEEP, bool SUMS>
 __global__ __launch_bounds__(64 * small_waves<KEEP>()) void kmeans_small_kernel(
     const bf16_t* __restrict__ xhat, const bf16_t* __restrict__ chat, int32_t* __restrict__ order,
-    int32_t* __restrict__ count, int32_t* __restrict__ start, int S, int L, int kk, int N_idx, int iters,
-    int key_bits) {
+    int32_t* __restrict__ count, int32_t* __restrict__ start, WindowRoute window, int segs, int S, int L, int kk,
+    int N_idx, int iters, int key_bits) {
   using RT = ResidentTile<D>;
   constexpr int NW = small_waves<KEEP>(), NT = 64 * NW, LPR = D / 8, GROUPS = NT / LPR;
+  if ((int)blockIdx.x >= segs) {  // the workgroups behind the segments' route an update's window
+    route_window<8>(window, (size_t)(blockIdx.x - segs) * NT + threadIdx.x, (size_t)(gridDim.x - segs) * NT);
+    return;
+  }
   extern __shared__ __attribute__((aligned(16))) char small_lds[];
   char* cent = small_lds;
   int* hist = reinterpret_cast<int*>(small_lds + (size_t)32 * ((kk + 31) / 32) * RT::ROWB);  // sort_segment's
@@ -2453,6 +2457,13 @@ static bool no_small_kmeans() {
   return e && e[0] == '1';
 }
 
+// Whether launch_build takes an update's window: its segments go to kmeans_small_kernel and leave a quarter of the CUs
+// idle (16 x 8 segments of 1024 tokens: an update 220 us with the window routed first, 184 so; the k-means launch 105 and
+// 118 us.  64 CUs are enough to route as many rows as are clustered, 32 are not: 252 us).
+bool build_routes_window(const wave_index& ix) {
+  return ix.m > 0 && small_segments(ix) && !no_small_kmeans() && ix.B * ix.Hkv * ix.S <= 192;
+}
+
 static int key_bits_for(int kk) {
   int b = 1;
   while ((1 << b) < kk) ++b;
@@ -2547,7 +2558,7 @@ static void launch_assign(const T* xhat, const T* chat, int32_t* assign, const A
 template <typename T, int D>
 static wave_status build_td(const void* K_, const void* V_, const wave_index& ix, int iters,
                             uint64_t seed, void* ws, hipStream_t st, int seg_id_base, int row_base,
-                            int pos_base) {
+                            int pos_base, const WindowRoute* window) {
   const T* K = static_cast<const T*>(K_);
   const T* V = static_cast<const T*>(V_);
   const int units = ix.B * ix.Hkv;
@@ -2601,6 +2612,9 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   int32_t* nflag = reinterpret_cast<int32_t*>(w + g.off_nflag);
   double* mean = reinterpret_cast<double*>(w + g.off_init);
   constexpr int GROUPS = 256 / (D / Elem<T>::EPC);
+  // what the first steps read: K, or the window's rows where they lie
+  const T* K_in = window ? reinterpret_cast<const T*>(window->k_old) + (size_t)window->ns * D : K;
+  const int N_in = window ? window->p_old : ix.N;
 
   {
     // A few segments: pieces of at least 256 rows until every CU has a workgroup.  Their sums go where the order of
@@ -2611,15 +2625,15 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
            (size_t)g.segs * 2 * pieces * D * sizeof(double) <= (size_t)units * N_idx * sizeof(int32_t))
       pieces *= 2;
     double* sums_of = pieces > 1 ? reinterpret_cast<double*>(order) : mean;
-    WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs * pieces, 256, 0, st, K, sums_of, nflag, range, nchanged[1],
-                nlisted[0], S, L, kk, ix.N, N_idx, ns, pieces);
+    WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs * pieces, 256, 0, st, K_in, sums_of, nflag, range, nchanged[1],
+                nlisted[0], S, L, kk, N_in, N_idx, ns, pieces);
     int row_step = NORM_ROWS, chunks = (Lmax + NORM_ROWS - 1) / NORM_ROWS;
     if (g.segs * chunks > NORM_RESIDENT && g.segs * ((chunks + 1) / 2) <= NORM_RESIDENT) {
       row_step *= 2;
       chunks = (chunks + 1) / 2;
     }
-    WAVE_LAUNCH("normalise", (normalise_kernel<T, D>), g.segs * chunks, 256, 0, st, K, sums_of, mean, xhat, range, S, L, kk,
-                ix.N, N_idx, ns, chunks, row_step, pieces);
+    WAVE_LAUNCH("normalise", (normalise_kernel<T, D>), g.segs * chunks, 256, 0, st, K_in, sums_of, mean, xhat, range, S, L, kk,
+                N_in, N_idx, ns, chunks, row_step, pieces);
   }
   {
     int pieces = 1;  // a workgroup for every CU, of at least 32 draws
@@ -2654,9 +2668,11 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
     const size_t sort_lds = ((size_t)W * kk + kk) * sizeof(int);
     const int kb = key_bits_for(kk);
     if (small) {
+      // (a workgroup takes a CU at these sizes: the window goes to the others)
+      const int movers = window ? 256 - g.segs : 0;
       auto run = [&](auto kernel, int waves, bool keep_sums) {
-        WAVE_LAUNCH("kmeans_small", kernel, g.segs, 64 * waves, small_kmeans_lds<D>(kk, keep_sums), st, xhat, chat,
-                    order, count, start, S, L, kk, N_idx, iters, kb);
+        WAVE_LAUNCH("kmeans_small", kernel, g.segs + movers, 64 * waves, small_kmeans_lds<D>(kk, keep_sums), st, xhat, chat,
+                    order, count, start, window ? *window : WindowRoute{}, g.segs, S, L, kk, N_idx, iters, kb);
       };
       constexpr int KEEP = 512 / D, KW = small_waves<KEEP>();  // (128 registers a lane)
       const bool keep = (L < N_idx ? L : N_idx) <= 32 * KEEP * KW;
@@ -2728,13 +2744,14 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
 }
 
 wave_status launch_build(const void* K, const void* V, const wave_index& ix, int iters, uint64_t seed,
-                         void* ws, hipStream_t st, int seg_id_base, int row_base, int pos_base) {
+                         void* ws, hipStream_t st, int seg_id_base, int row_base, int pos_base,
+                         const WindowRoute* window) {
   if (ix.dtype == WAVE_BF16) {
-    if (ix.d == 128) return build_td<bf16_t, 128>(K, V, ix, iters, seed, ws, st, seg_id_base, row_base, pos_base);
-    if (ix.d == 64) return build_td<bf16_t, 64>(K, V, ix, iters, seed, ws, st, seg_id_base, row_base, pos_base);
+    if (ix.d == 128) return build_td<bf16_t, 128>(K, V, ix, iters, seed, ws, st, seg_id_base, row_base, pos_base, window);
+    if (ix.d == 64) return build_td<bf16_t, 64>(K, V, ix, iters, seed, ws, st, seg_id_base, row_base, pos_base, window);
   } else {
-    if (ix.d == 128) return build_td<float, 128>(K, V, ix, iters, seed, ws, st, seg_id_base, row_base, pos_base);
-    if (ix.d == 64) return build_td<float, 64>(K, V, ix, iters, seed, ws, st, seg_id_base, row_base, pos_base);
+    if (ix.d == 128) return build_td<float, 128>(K, V, ix, iters, seed, ws, st, seg_id_base, row_base, pos_base, window);
+    if (ix.d == 64) return build_td<float, 64>(K, V, ix, iters, seed, ws, st, seg_id_base, row_base, pos_base, window);
   }
   return WAVE_ERR_SHAPE;
 }

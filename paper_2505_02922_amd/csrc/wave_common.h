@@ -284,9 +284,57 @@ inline int full_attention_chunks(int N) { return (N + FULL_ATTN_ROWS - 1) / FULL
 wave_status launch_full_attention(const void* q, const void* K, const void* V, int dtype, int B, int Hq,
                                   int Hkv, int N, int d, float* out, float* lse, void* ws,
                                   hipStream_t st);
+// The rows of an index update's window: row j of a unit's sink + window (ns sink rows of the old steady buffer, lc_old
+// old local rows, n_new new tokens) goes to the new steady buffer as it is (sink), to a scratch tensor (window rows
+// before `flush`), or to the new steady buffer behind the sink rows.
+struct WindowRoute {
+  const char *k_old, *v_old, *k_new, *v_new;
+  char *k_flush, *v_flush, *k_out, *v_out;
+  int ns, lc_old, n_new, flush;
+  int p_old, p_out, units;  // rows per unit of the old and the new steady buffers
+  int first;                // rows before it are already in place (the new buffers are the old ones, nothing is flushed)
+  int chunks;               // 16-byte chunks of a row: 8, 16 or 32
+  __host__ __device__ size_t total() const { return ((size_t)ns + lc_old + n_new - first) * units * chunks; }
+};
+// The share of thread `t` of `threads`, a chunk of a key and of a value row at a time, U of both in flight.
+template <int U>
+__device__ __forceinline__ void route_window(const WindowRoute& m, size_t t, size_t threads) {
+  const size_t rows_u = (size_t)m.ns + m.lc_old + m.n_new - m.first, total = rows_u * m.units * m.chunks;
+  const int shift = 31 - __clz(m.chunks);
+  for (size_t i0 = t; i0 < total; i0 += U * threads) {
+    uint4 k[U], v[U];
+    char *dk[U], *dv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t i = i0 + u * threads < total ? i0 + u * threads : total - 1;
+      const size_t row = i >> shift, unit = row / rows_u, ch = (i & (size_t)(m.chunks - 1)) * 16;
+      const int j = (int)(row - unit * rows_u) + m.first, w = j - m.ns;  // w: place in the window, negative for sink rows
+      auto at = [&](size_t r) { return ((r << shift) * 16) + ch; };
+      const bool fresh = w >= m.lc_old;
+      const size_t from = at(fresh ? unit * m.n_new + (w - m.lc_old) : unit * m.p_old + j);
+      k[u] = load16((fresh ? m.k_new : m.k_old) + from);
+      v[u] = load16((fresh ? m.v_new : m.v_old) + from);
+      const bool out = w >= 0 && w < m.flush;
+      const size_t to = at(out ? unit * m.flush + w : unit * m.p_out + (w < 0 ? j : j - m.flush));
+      dk[u] = (out ? m.k_flush : m.k_out) + to;
+      dv[u] = (out ? m.v_flush : m.v_out) + to;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (u == 0 || i0 + u * threads < total) {
+        store16(dk[u], k[u]);
+        store16(dv[u], v[u]);
+      }
+  }
+}
+
+// window: an update's window whose flushed rows all lie in the old steady buffer.  The build's first steps then read
+// them there, its k-means launch routes the window beside the clustering, and the last step reads K and V, which are
+// window->k_flush and window->v_flush.  Only where build_routes_window says so.
 wave_status launch_build(const void* K, const void* V, const wave_index& ix, int iters,
                          uint64_t seed, void* ws, hipStream_t st, int seg_id_base = 0, int row_base = 0,
-                         int pos_base = 0);
+                         int pos_base = 0, const WindowRoute* window = nullptr);
+bool build_routes_window(const wave_index& ix);
 // Incremental update: geometry of its workspace and the launches (wave_append.hip).
 struct AppendGeom {
   int F, ks, lc_old;              // flushed segments, clusters per update segment, old local count

@@ -751,6 +751,35 @@ def test_index_append_matches_oracle_then_decode(case, n_news, U, ku, cap, scap,
     _decode_and_check(wl_now, ix, ref, q, ix.m, f"append {wl.name} all")
 
 
+# An update's window routed beside the k-means (`beside`), or by a launch of its own: all of the old window flushed and a
+# part of it, two segments of it, one row more than it holds, short segments sent the way of the long ones, f32; the
+# most units and one more.
+@pytest.mark.parametrize("dtype,d,units,n_local,n_new,U,beside", [
+    ("bf16", 128, 2, 40, 40, 40, True), ("bf16", 64, 3, 100, 33, 33, True), ("bf16", 128, 2, 70, 1, 35, False),
+    ("bf16", 64, 2, 64, 64, 32, True), ("bf16", 128, 2, 31, 32, 32, False), ("f32", 64, 2, 40, 40, 40, False),
+    ("bf16", 64, 192, 32, 32, 32, True), ("bf16", 64, 193, 32, 32, 32, False)])
+def test_append_routes_its_window_beside_the_clustering(dtype, d, units, n_local, n_new, U, beside):
+    wl = synth.scaled(WL["llama8b_32k"], name="window", dtype=dtype, B=units, Hq=1, Hkv=1, N=300, d=d, n_sink=3,
+                      n_local=n_local, segment_len=256, clusters_per_segment=16, iters=3, n_components=16)
+    big = synth.scaled(wl, N=wl.N + n_new)
+    Kall, Vall, _ = _inputs(big, 1)
+    K0, V0 = Kall[:, :, :wl.N].contiguous(), Vall[:, :, :wl.N].contiguous()
+    Kn, Vn = Kall[:, :, wl.N:].contiguous(), Vall[:, :, wl.N:].contiguous()
+    least = n_local + n_new - n_new // U * U     # (what the window keeps: all that does not fill a segment)
+    ix = wb.wave_index_build(K0.cuda(), V0.cuda(), wl.n_sink, wl.n_local, 256, 16, 3, 0)
+    wb.wave_profile_enable(True)
+    grown = wb.wave_index_append(ix, Kn.cuda(), Vn.cuda(), least, U, 4, 3, 0)
+    launches = {name: n for name, (_, n) in wb.wave_profile_read().items()}
+    wb.wave_profile_enable(False)
+    assert ("append_window" in launches) == (not beside), launches
+    some = [(b, 0) for b in sorted({0, 1, units - 1})]
+    for (b, h), u in pu.oracle_build(wl, K0, V0, units=some).items():
+        ref = wo.append_unit(u, Kn[b, h].double().numpy(), Vn[b, h].double().numpy(), least, U, 4, 3, 0, b, h)
+        for name in wb.BUFFER_NAMES:
+            got = grown.t[name][b, h].double().cpu().numpy()
+            assert np.array_equal(got, np.asarray(getattr(ref, name), dtype=np.float64)), (b, name)
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("m,r,nb", [(3, 2, 2), (64, 20, 30), (1024, 40, 33), (1025, 170, 64), (2048, 37, 3),
                                     (2049, 60, 65), (4096, 5, 31), (4097, 80, 70), (16384, 50, 12)])
