@@ -144,6 +144,25 @@ __device__ __forceinline__ void exponent_range<float>(const uint4& raw, int& emi
       emax = max(emax, e);
     }
 }
+// The same of many chunks of bf16, two elements at a time: add() each chunk, then range().
+struct ExponentRange {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  u16x2 least = {0xffff, 0xffff}, most = {0, 0};  // magnitude bits - 1 (zero: the largest), magnitude bits
+  __device__ __forceinline__ void add(const uint4& raw) {
+    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u16x2 mag = __builtin_bit_cast(u16x2, w[i] & 0x7fff7fffu);
+      most = __builtin_elementwise_max(most, mag);
+      least = __builtin_elementwise_min(least, mag - (unsigned short)1);
+    }
+  }
+  __device__ __forceinline__ void range(int& emin, int& emax) const {
+    const int lo = min(least.x, least.y);
+    emin = lo == 0xffff ? 255 : max(1, (lo + 1) >> 7);
+    emax = max(most.x, most.y) >> 7;
+  }
+};
 template <typename T>
 struct MantissaBits;
 template <>
@@ -187,8 +206,7 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
     seg_emin = 255;
     seg_emax = 0;
   }
-  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-  u16x2 least = {0xffff, 0xffff}, most = {0, 0};  // magnitude bits - 1 (zero: the largest), magnitude bits
+  ExponentRange seen;
   __shared__ double mean_s[D];
   if (pieces > 1) {
     if (threadIdx.x < D) {
@@ -261,23 +279,15 @@ __global__ __launch_bounds__(256) void normalise_kernel(const T* __restrict__ K,
         for (int e = 0; e < EPC; ++e) o[e] = quant_store<T>(div_shared(x[e], dv, rdv));
       }
       store16(Xu + (size_t)(r0 + u * GROUPS) * D, *reinterpret_cast<uint4*>(o));
-      if (range) {
-        const u16x2* w = reinterpret_cast<const u16x2*>(o);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const u16x2 mag = w[i] & (unsigned short)0x7fff;
-          most = __builtin_elementwise_max(most, mag);
-          least = __builtin_elementwise_min(least, mag - (unsigned short)1);
-        }
-      }
+      if (range) seen.add(*reinterpret_cast<uint4*>(o));
     }
   };
   int r0 = lo;
   for (; r0 + U * GROUPS <= hi; r0 += U * GROUPS) rows(std::integral_constant<int, U>{}, r0 + grp);
   for (r0 += grp; r0 < hi; r0 += GROUPS) rows(std::integral_constant<int, 1>{}, r0);
   if (range) {
-    int emax = max(most.x, most.y) >> 7, emin = min(least.x, least.y);
-    emin = emin == 0xffff ? 255 : max(1, (emin + 1) >> 7);
+    int emin, emax;
+    seen.range(emin, emax);
     for (int off = 32; off >= 1; off >>= 1) {
       emin = min(emin, __shfl_xor(emin, off));
       emax = max(emax, __shfl_xor(emax, off));
@@ -2126,6 +2136,8 @@ __global__ __launch_bounds__(64 * small_waves<KEEP>()) void kmeans_small_kernel(
   const size_t p0 = (size_t)si.unit * N_idx + si.seg_start;
   const bf16_t* X = xhat + p0 * D;
   [[maybe_unused]] const int nfrag = (si.L_s + 31) / 32;
+  uint4 kept[KEEP > 0 ? KEEP : 1][RT::KS];
+  if constexpr (KEEP > 0) load_kept_fragments<D, KEEP, NW>(X, si.L_s, kept);
   resident_load_centroids<D, NT>(chat + (size_t)sg * kk * D, si.k_s, cent);
 #ifdef WAVE_TRACE  // phase times of workgroup 0 (100 MHz clock), printed at the end
   unsigned long long tp[5] = {0, 0, 0, 0, 0}, tl = wall_clock64();
@@ -2143,17 +2155,40 @@ __global__ __launch_bounds__(64 * small_waves<KEEP>()) void kmeans_small_kernel(
       seg_emax = 0;
     }
     __syncthreads();
-    int emin = 255, emax = 0;
-#pragma unroll 2
-    for (int i = tid; i < si.L_s * RT::CPR; i += NT) exponent_range<bf16_t>(load16(X + (size_t)i * 8), emin, emax);
-    atomicMin(&seg_emin, emin);
-    atomicMax(&seg_emax, emax);
+    // (from the registers, or eight chunks in flight.  Chunk by chunk from memory and element by element: 20 us of a
+    // workgroup's start at 1024 points; ten rounds of 128 segments beside an update's window 118 us, 105 so; whole builds of
+    // 128 x 1024 x 64 169 and 159 us, of 1024 such segments 790 and 732)
+    ExponentRange seen;
+    if constexpr (KEEP > 0) {
+#pragma unroll
+      for (int f = 0; f < KEEP; ++f)  // (rows beyond the segment repeat its last one)
+#pragma unroll
+        for (int s = 0; s < RT::KS; ++s) seen.add(kept[f][s]);
+    } else {
+      constexpr int U = 8;
+      const int chunks = si.L_s * RT::CPR;
+      for (int i0 = tid; i0 < chunks; i0 += U * NT) {
+        uint4 raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[u] = load16(X + (size_t)min(i0 + u * NT, chunks - 1) * 8);
+#pragma unroll
+        for (int u = 0; u < U; ++u) seen.add(raw[u]);
+      }
+    }
+    int emin, emax;
+    seen.range(emin, emax);
+    for (int off = 32; off >= 1; off >>= 1) {
+      emin = min(emin, __shfl_xor(emin, off));
+      emax = max(emax, __shfl_xor(emax, off));
+    }
+    if (lane == 0) {
+      atomicMin(&seg_emin, emin);
+      atomicMax(&seg_emax, emax);
+    }
     __syncthreads();
     const int lg = si.L_s > 1 ? 32 - __clz(si.L_s - 1) : 0;  // ceil(log2 L_s)
     moves = seg_emax < seg_emin || seg_emax - seg_emin + lg <= 52 - MantissaBits<bf16_t>::value;
   }
-  uint4 kept[KEEP > 0 ? KEEP : 1][RT::KS];
-  if constexpr (KEEP > 0) load_kept_fragments<D, KEEP, NW>(X, si.L_s, kept);
   for (int t = 0; t < iters; ++t) {
     if (tid == 0) nflag = nmoved = 0;
     __syncthreads();
@@ -2458,8 +2493,7 @@ static bool no_small_kmeans() {
 }
 
 // Whether launch_build takes an update's window: its segments go to kmeans_small_kernel and leave a quarter of the CUs
-// idle (16 x 8 segments of 1024 tokens: an update 220 us with the window routed first, 184 so; the k-means launch 105 and
-// 118 us.  64 CUs are enough to route as many rows as are clustered, 32 are not: 252 us).
+// idle (16 x 8 segments of 1024 tokens: an update 220 us with the window routed first, 184 so.  64 CUs are enough to route as many rows as are clustered, 32 are not: 252 us).
 bool build_routes_window(const wave_index& ix) {
   return ix.m > 0 && small_segments(ix) && !no_small_kmeans() && ix.B * ix.Hkv * ix.S <= 192;
 }
