@@ -1933,27 +1933,6 @@ __global__ __launch_bounds__(256) void est_gather_kernel(
                         rcap2, rcap1, chunks, slots, slot0, scale_log2, part);
 }
 
-// The retrieval zone and the budgeted estimation zone in one launch: both only need the two
-// id lists, neither needs the other.  The estimation workgroups come first: they have the
-// scattered value-sum rows, the retrieval workgroups the long contiguous ranges.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void gather_est_kernel(
-    const T* __restrict__ q, const T* __restrict__ k_perm, const T* __restrict__ v_perm,
-    const int32_t* __restrict__ ids1, const int32_t* __restrict__ nsel1,
-    const int32_t* __restrict__ ids2, const int32_t* __restrict__ nsel2,
-    const int32_t* __restrict__ offsets, const float* __restrict__ z, const T* __restrict__ vsum,
-    int Hq, int Hkv, int N_idx, int m, int mc, int rcap1, int rcap2, int gather_chunks, int est_chunks, int slots,
-    int gather_slot0, int est_slot0, int n_est_wgs, float scale_log2, float* __restrict__ part) {
-  if ((int)blockIdx.x < n_est_wgs) {
-    est_gather_role<T, D>(blockIdx.x, ids2, nsel2, ids1, nsel1, offsets, z, vsum, Hq, Hkv, m, mc, rcap2, rcap1,
-                          est_chunks, slots, est_slot0, scale_log2, part);
-    return;
-  }
-  gather_role<T, D>((int)blockIdx.x - n_est_wgs, (int)gridDim.x - n_est_wgs, q, k_perm, v_perm, ids1, nsel1,
-                    offsets, z, vsum, Hq, Hkv, N_idx, m, mc, rcap1, gather_chunks, slots, scale_log2, 0,
-                    part + (size_t)gather_slot0 * (D + 2));
-}
-
 constexpr int MERGE_THREADS = 1024;
 
 template <int D, int NT = MERGE_THREADS>
@@ -2591,6 +2570,58 @@ __global__ __launch_bounds__(NT) void select_two_kernel(
                                    second ? nullptr : user_selected, vsum, scale_log2, nullptr, 0, 0, bh,
                                    dyn_keys, nullptr, nullptr, 0, &ntok,
                                    SelView{m, 0, nullptr, nullptr, 2, nullptr, nullptr});
+}
+
+// The retrieval zone, the budgeted estimation zone and the steady zone in one launch: the first two only need the two
+// id lists, none needs another.  The steady pieces come first, then the estimation workgroups: they have the
+// scattered value-sum rows, the retrieval workgroups the long contiguous ranges.
+// (Beside the scores the steady pieces ran at half of this launch's rate.  Us a step, so and here: 6 sequences of 50021
+// tokens x 32 heads 67.7 and 64.9, 16 of 122880 257 and 241, 64 of 16384 212 and 197, 64 of 65536 x 28 heads 674 and 650;
+// one of 32768 33.7 and 34.0.  Beside the selections they cost those their occupancy: 62, 271, 212, 668, 31.8.)
+struct SteadyWork {
+  const void* k_steady;
+  const void* v_steady;
+  int p, p_stride, chunks, rows;  // chunks: pieces of a unit
+};
+
+template <typename T, int D, int G>
+__global__ __launch_bounds__(256, 4) void gather_est_kernel(
+    const T* __restrict__ q, const T* __restrict__ k_perm, const T* __restrict__ v_perm,
+    const int32_t* __restrict__ ids1, const int32_t* __restrict__ nsel1,
+    const int32_t* __restrict__ ids2, const int32_t* __restrict__ nsel2,
+    const int32_t* __restrict__ offsets, const float* __restrict__ z, const T* __restrict__ vsum,
+    int Hq, int Hkv, int N_idx, int m, int mc, int rcap1, int rcap2, int gather_chunks, int est_chunks, int slots,
+    int gather_slot0, int est_slot0, int n_est_wgs, float scale_log2, float* __restrict__ part, const SteadyWork sw,
+    int n_steady_wgs) {
+  int wg = blockIdx.x;
+  if (wg < n_steady_wgs) {
+    // (more than 4 heads at once would cost the launch its occupancy: the rows are read a second time, from cache, for
+    // the heads beyond the fourth)
+    constexpr int G1 = G <= 4 ? G : 4;
+    __shared__ float smem[4 * G1 * (D + 2)];
+    const int unit = wg / sw.chunks, chunk = wg - unit * sw.chunks;
+    const int b = unit / Hkv, h = unit - b * Hkv, bh0 = b * Hq + h * G;
+    const int r0 = chunk * sw.rows, r1 = min(sw.p, r0 + sw.rows);
+    const T *ks = static_cast<const T*>(sw.k_steady), *vs = static_cast<const T*>(sw.v_steady);
+    const size_t head_stride = (size_t)slots * (D + 2);
+    float* mine = part + bh0 * head_stride + (size_t)chunk * (D + 2);  // (the first slots)
+    steady_rows_partial<T, D, G1, 256>(q, ks, vs, unit, bh0, sw.p_stride, r0, r1, scale_log2, smem, mine, head_stride);
+    if constexpr (G > 4) {
+      __syncthreads();
+      steady_rows_partial<T, D, G - 4, 256>(q, ks, vs, unit, bh0 + 4, sw.p_stride, r0, r1, scale_log2, smem,
+                                            mine + 4 * head_stride, head_stride);
+    }
+    return;
+  }
+  wg -= n_steady_wgs;
+  if (wg < n_est_wgs) {
+    est_gather_role<T, D>(wg, ids2, nsel2, ids1, nsel1, offsets, z, vsum, Hq, Hkv, m, mc, rcap2, rcap1,
+                          est_chunks, slots, est_slot0, scale_log2, part);
+    return;
+  }
+  gather_role<T, D>(wg - n_est_wgs, (int)gridDim.x - n_steady_wgs - n_est_wgs, q, k_perm, v_perm, ids1, nsel1,
+                    offsets, z, vsum, Hq, Hkv, N_idx, m, mc, rcap1, gather_chunks, slots, scale_log2, 0,
+                    part + (size_t)gather_slot0 * (D + 2));
 }
 
 template <typename T, int D, int G>
@@ -4178,7 +4209,7 @@ BudgetGeom budget_geometry(const wave_index& ix, int Hq, int topk, int est_clust
   g.sliced1 = sliced(r);
   g.sliced2 = sliced(g.k2);
   g.score_chunks = (m + DENSE_ROWS - 1) / DENSE_ROWS;
-  g.steady_rows = units >= 64 ? 256 : 64;
+  g.steady_rows = units >= 32 ? 256 : 64;  // (48 units: 65.8 us a step in pieces of 64, 64.9 of 256)
   g.steady_chunks = ix.p > 0 ? (ix.p + g.steady_rows - 1) / g.steady_rows : 0;
   double expect = (double)r * (double)ix.N_idx / (double)m;
   int gc = (int)((expect + GATHER_TILE - 1) / GATHER_TILE);
@@ -4234,14 +4265,13 @@ static wave_status budget_tdg(const void* q_, const wave_index& ix, int Hq, int 
   const int slots = g.slots + 1, spare_slot = g.slots;
 
   // Keys of a head fit in LDS (whole, or their upper halves with a re-read hot range): four
-  // launches.  The scores with the steady zone as extra workgroups; both selections at once (two
-  // workgroups per head); retrieval and estimation in one launch (neither needs the other); the merge.
+  // launches.  The scores; both selections at once (two workgroups per head); retrieval, estimation and the steady
+  // zone in one launch (none needs another); the merge.
   if (m <= 1024 * 64 && est_clusters > 0) {
-    WAVE_LAUNCH("scores+steady", (score_steady_kernel<T, D, G>), units * (g.score_chunks + g.steady_chunks),
+    WAVE_LAUNCH("scores", (score_steady_kernel<T, D, G>), units * g.score_chunks,
                 256, 0, st, q, C, ix.sizes, z, cn2, ix.Hkv, m, mc, g.score_chunks, static_cast<float*>(nullptr),
-                units * g.score_chunks, static_cast<const T*>(ix.k_steady), static_cast<const T*>(ix.v_steady),
-                ix.p, steady_stride(ix), g.steady_chunks, g.steady_rows, slots, 0, scale_log2, part,
-                static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr), 0);
+                units * g.score_chunks, static_cast<const T*>(nullptr), static_cast<const T*>(nullptr), 0, 0, 0, 0, slots, 0,
+                scale_log2, part, static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr), 0);
 #define WAVE_TWO_ARGS                                                                                   \
   q, C, ix.offsets, z, cn2, g.score_chunks, Hq, ix.Hkv, m, g.mwords, mc, bitmap, g.r, g.rcap1, ids1, nsel1, \
       selected, g.k2, g.rcap2, ids2, nsel2, VS, scale_log2
@@ -4257,12 +4287,13 @@ static wave_status budget_tdg(const void* q_, const wave_index& ix, int Hq, int 
       WAVE_LAUNCH("select x2", (select_two_kernel<T, D, 1024, 64, false>), 2 * heads, 1024,
                   sizeof(uint16_t) * 1024 * (size_t)((m + 1023) / 1024), st, WAVE_TWO_ARGS);
 #undef WAVE_TWO_ARGS
-    const int n_est = heads * g.est_chunks;
-    WAVE_LAUNCH("gather+estimate", (gather_est_kernel<T, D>), n_est + heads * g.gather_chunks, 256, 0, st, q,
+    const int n_est = heads * g.est_chunks, n_steady = units * g.steady_chunks;
+    const SteadyWork sw{ix.k_steady, ix.v_steady, ix.p, steady_stride(ix), g.steady_chunks, g.steady_rows};
+    WAVE_LAUNCH("gather+estimate", (gather_est_kernel<T, D, G>), n_steady + n_est + heads * g.gather_chunks, 256, 0, st, q,
                 static_cast<const T*>(ix.k_perm), static_cast<const T*>(ix.v_perm), ids1, nsel1, ids2, nsel2,
                 ix.offsets, z, VS, Hq, ix.Hkv, row_stride(ix), m, mc, g.rcap1, g.rcap2, g.gather_chunks,
                 g.est_chunks, slots, g.steady_chunks, g.steady_chunks + g.gather_chunks, n_est, scale_log2,
-                part);
+                part, sw, n_steady);
     if (heads <= 256)
       WAVE_LAUNCH("merge", (merge_kernel<D, MERGE_THREADS>), heads, MERGE_THREADS, 0, st, part, g.slots, slots,
                   out, lse);

@@ -608,6 +608,26 @@ def test_full_attention_is_the_limit_of_the_wave_decode():
     assert float((l1 - l2).abs().max()) < 2e-5
 
 
+# The steady zone beside the budgeted zones: none, one row, a piece and one row more in pieces of 64 and (from 32 units on)
+# of 256 rows; heads beyond the fourth of a KV head.
+@pytest.mark.parametrize("dtype,B,Hkv,G,n_sink,n_local", [
+    ("bf16", 1, 1, 1, 0, 0), ("bf16", 1, 1, 5, 0, 1), ("f32", 1, 2, 8, 4, 61), ("bf16", 31, 1, 3, 0, 257),
+    ("bf16", 32, 1, 5, 4, 253), ("bf16", 16, 2, 4, 0, 256), ("f32", 2, 16, 1, 0, 256)])
+def test_budget_with_steady_pieces_of_all_sizes(dtype, B, Hkv, G, n_sink, n_local):
+    wl = _small("llama8b_32k", name="pieces", dtype=dtype, B=B, Hq=Hkv * G, Hkv=Hkv, N=700, n_sink=n_sink, n_local=n_local,
+                segment_len=512, clusters_per_segment=32, n_components=32, iters=2)
+    K, V, q = _inputs(wl, 1)
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), n_sink, n_local, 512, 32, 2, 0)
+    r, e = 3, ix.m // 3
+    out, lse, _ = wb.wave_attention_decode_budget(q.cuda(), ix, r, e)
+    torch.cuda.synchronize()
+    units = [(b, h) for b in sorted({0, B - 1}) for h in sorted({0, Hkv - 1})]
+    for (b, h), ref in pu.oracle_build(wl, K, V, units=units).items():
+        for hq in range(h * G, (h + 1) * G):
+            o, l, _ = wo.decode_unit(q[b, hq].double().numpy(), ref, r, {}, est_clusters=e)
+            pu.check_outputs(out[b, hq].cpu().numpy(), lse[b, hq:hq + 1].cpu().numpy(), o, np.array([l]), dtype, f"{b} {hq}")
+
+
 @pytest.mark.parametrize("case", ["tiny_f32", "bf16_g4", "bf16_g7", "bf16_d64", "f32_d128",
                                   "bf16_many_heads_g7", "bf16_listed_heads"])
 def test_decode_with_estimation_budget(case):
