@@ -1057,6 +1057,13 @@ __global__ __launch_bounds__(64 * NW, 4) void assign_delta_kernel(
   extern __shared__ __attribute__((aligned(16))) char cent[];
   __shared__ int wave_n[NW], nleft;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (!AT_ONCE && total <= 64 * (long long)gridDim.x) {
+    // whether any segment is this launch's is seen at once, not segment by segment (usually none after a few rounds: 8 us a
+    // launch of 256 workgroups with 15 segments each, 5 so)
+    const long long w = xcd_logical_block(blockIdx.x, gridDim.x) + lane * (long long)gridDim.x;
+    const int nch = nchanged[(w < total ? (int)w : total - 1) / pieces_per_seg];
+    if (!__ballot(w < total && nch > lo && nch <= hi)) return;
+  }
   for (int wg = xcd_logical_block(blockIdx.x, gridDim.x); wg < total; wg += AT_ONCE ? total : gridDim.x) {
     const int sg = wg / pieces_per_seg, piece = wg - sg * pieces_per_seg;
     const int nch = nchanged[sg];
@@ -1920,14 +1927,14 @@ static_assert(SCAN_CLUSTERS == 64, "a cluster per lane, six key bits");
 // Also leaves in changed[] and nchanged[] which centroids the next round's assign step compares.
 //
 // A workgroup owns the clusters [c_lo, c_hi) of a segment: it counts the arrivals and departures
-// of each (MOVE_CAP at once; more are taken in ranges of the points, the centroids after the last
+// of each (MOVE_CAP at once, of MOVED_CAP points; more are taken in ranges of the points, the centroids after the last
 // one), lists them by cluster in LDS, and one group of lanes per changed cluster works through its list.
 // ============================================================================
-constexpr int MOVE_NT = 512, MOVE_CAP = 4096;
+constexpr int MOVE_NT = 512, MOVE_CAP = 4096, MOVED_CAP = MOVE_CAP / 2;
 
 inline size_t update_moves_lds(int kk) {
   const size_t list = MOVE_CAP, hist = (size_t)(MOVE_NT / 64 + 1) * kk;
-  return sizeof(int) * (3 * (size_t)kk + (list > hist ? list : hist));
+  return sizeof(int) * (3 * (size_t)kk + (list > hist ? list : hist)) + sizeof(int2) * MOVED_CAP;
 }
 
 template <int D>
@@ -1937,12 +1944,14 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
     int32_t* __restrict__ nchanged, int32_t* __restrict__ nchanged_next, const int32_t* __restrict__ range, int32_t* order, int32_t* count, int32_t* start, int round, int S, int L,
     int kk, int N_idx, int pieces, int key_bits) {
   constexpr int EPC = 8, LPR = D / EPC, GROUPS = MOVE_NT / LPR, U = 4;
-  extern __shared__ int moves_lds[];
-  int* cnt = moves_lds;         // entries per cluster
+  extern __shared__ __attribute__((aligned(16))) int moves_lds[];
+  int2* moved = reinterpret_cast<int2*>(moves_lds);  // the points that moved: place, cluster before | now << 16
+  int* cnt = moves_lds + 2 * MOVED_CAP;              // entries per cluster
   int* end = cnt + kk;          // behind its last entry
   int* touched = end + kk;      // the clusters with entries
   int* entry = touched + kk;    // point * 2 + (1: leaves); the sort's counters
   __shared__ int totals[2];     // entries, touched clusters
+  __shared__ int nmoved;
   const int wg = xcd_logical_block(blockIdx.x, gridDim.x);
   const int sg = wg / pieces, piece = wg - sg * pieces;
   const SegInfo si = seg_info(sg, S, L, kk, N_idx);
@@ -1959,7 +1968,57 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
   if (piece == 0 && tid == 0) nchanged_next[sg] = 0;
   if (c_lo >= c_hi) return;
 
+  // The points that moved, listed once: their tags are requested together, then their new clusters.  (With both visits
+  // below reading tags and, one by one, clusters from memory: 105 us over the eight launches of a build of 32 segments of
+  // 8192 points, 86 so, of 1920 segments 2005 and 1775, of 2048 over eighteen 4260 and 3920.)
+  if (tid == 0) nmoved = 0;
+  __syncthreads();
+  constexpr int TAGS = 16;
+  for (int i0 = tid; i0 - tid < si.L_s; i0 += TAGS * MOVE_NT) {
+    int tag[TAGS], n = 0;
+#pragma unroll
+    for (int u = 0; u < TAGS; ++u) tag[u] = pv[min(i0 + u * MOVE_NT, si.L_s - 1)];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int u = 0; u < TAGS; ++u) {
+      const bool on = i0 + u * MOVE_NT < si.L_s && tag[u] >> PREV_CLUSTER_BITS == round;
+      mine |= on ? 1u << u : 0u;
+      n += on ? 1 : 0;
+    }
+    if (!__ballot(n > 0)) continue;
+    const int inc = wave_incl_scan(n), all = __builtin_amdgcn_readlane(inc, 63);
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&nmoved, all);
+    at = __builtin_amdgcn_readfirstlane(at) + inc - n;
+#pragma unroll
+    for (int u = 0; u < TAGS; ++u)
+      if (mine >> u & 1u) {
+        if (at < MOVED_CAP) moved[at] = make_int2(i0 + u * MOVE_NT, tag[u] & ((1 << PREV_CLUSTER_BITS) - 1));
+        ++at;
+      }
+  }
+  __syncthreads();
+  const bool in_lds = nmoved <= MOVED_CAP;
+  if (in_lds && nmoved > 0) {  // (the same for the whole workgroup)
+    constexpr int PER = MOVED_CAP / MOVE_NT;
+    const int last = nmoved - 1;
+    int to[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) to[u] = as[moved[min(tid + u * MOVE_NT, last)].x];
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (tid + u * MOVE_NT <= last) moved[tid + u * MOVE_NT].y |= to[u] << 16;
+    __syncthreads();
+  }
   auto visit = [&](int lo, int hi, auto&& f) {  // f(cluster, entry) for the round's entries of points [lo, hi)
+    auto point = [&](int i, int from, int to) {
+      if (from >= c_lo && from < c_hi) f(from, 2 * i + 1);
+      if (to >= c_lo && to < c_hi) f(to, 2 * i);
+    };
+    if (in_lds) {  // (all points)
+      for (int j = tid; j < nmoved; j += MOVE_NT) point(moved[j].x, moved[j].y & 0xffff, moved[j].y >> 16);
+      return;
+    }
     for (int i0 = lo + tid; i0 < hi; i0 += U * MOVE_NT) {
       int tag[U];
 #pragma unroll
@@ -1967,10 +2026,7 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = i0 + u * MOVE_NT;
-        if (i >= hi || tag[u] >> PREV_CLUSTER_BITS != round) continue;
-        const int from = tag[u] & ((1 << PREV_CLUSTER_BITS) - 1), to = as[i];
-        if (from >= c_lo && from < c_hi) f(from, 2 * i + 1);
-        if (to >= c_lo && to < c_hi) f(to, 2 * i);
+        if (i < hi && tag[u] >> PREV_CLUSTER_BITS == round) point(i, tag[u] & ((1 << PREV_CLUSTER_BITS) - 1), as[i]);
       }
     }
   };
@@ -2016,7 +2072,7 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
     }
     return;
   }
-  const int span = totals[0] <= MOVE_CAP ? si.L_s : MOVE_CAP / 2;
+  const int span = totals[0] <= MOVE_CAP ? si.L_s : MOVE_CAP / 2;  // (in_lds: never more)
   for (int lo = 0; lo < si.L_s; lo += span) {
     const int hi = min(si.L_s, lo + span);
     if (span < si.L_s) {
