@@ -62,7 +62,8 @@ __device__ __forceinline__ double div_shared(double a, double b, double r) {
 // ============================================================================
 // Segment mean (fp64).  `pieces` workgroups per segment sum a run of its rows each, in a fixed order; with more than
 // one they leave their sums in `mean` for normalise_kernel to add up in order, [segment, piece, D].
-// (A few segments: 32 of 8192 points 70 us with one workgroup each, 14 us with eight.)
+// (A few segments: 32 of 8192 points 70 us with one workgroup each, 14 us with eight and four rows in flight, 11 us with
+// sixteen and eight; 128 of 1024 points 10 and 7.7 us.)
 // ============================================================================
 template <typename T, int D>
 __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, double* __restrict__ mean,
@@ -84,24 +85,23 @@ __global__ __launch_bounds__(256) void seg_mean_kernel(const T* __restrict__ K, 
   for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
   const int per = (si.L_s + pieces - 1) / pieces, hi = min(si.L_s, (piece + 1) * per);
   int i = min(si.L_s, piece * per) + grp;
-  for (; i + 3 * GROUPS < hi; i += 4 * GROUPS) {  // four rows in flight, added in row order
-    uint4 raw[4];
+  auto add = [&](auto batch) {  // rows in flight, added in row order
+    constexpr int U = decltype(batch)::value;
+    for (; i + (U - 1) * GROUPS < hi; i += U * GROUPS) {
+      uint4 raw[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) raw[u] = load16(Ku + (size_t)(i + u * GROUPS) * D);
+      for (int u = 0; u < U; ++u) raw[u] = load16(Ku + (size_t)(i + u * GROUPS) * D);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      float f[EPC];
-      unpack<T>(raw[u], f);
+      for (int u = 0; u < U; ++u) {
+        float f[EPC];
+        unpack<T>(raw[u], f);
 #pragma unroll
-      for (int e = 0; e < EPC; ++e) acc[e] += (double)f[e];
+        for (int e = 0; e < EPC; ++e) acc[e] += (double)f[e];
+      }
     }
-  }
-  for (; i < hi; i += GROUPS) {
-    float f[EPC];
-    unpack<T>(load16(Ku + (size_t)i * D), f);
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) acc[e] += (double)f[e];
-  }
+  };
+  add(std::integral_constant<int, 8>{});
+  add(std::integral_constant<int, 1>{});
   __shared__ double red[GROUPS][D];
 #pragma unroll
   for (int e = 0; e < EPC; ++e) red[grp][sub * EPC + e] = acc[e];
@@ -181,8 +181,9 @@ struct MantissaBits<float> {
 // bytes of the fp64 mean again for each 16 bytes of key, 2.16 ms).  Four rows of a group in flight where
 // that many are left, else one by one: four with repeats of the last one took 485 us for 65536
 // segments of 16 rows, 172 us so.
-// row_step: 128, or 256 where these workgroups are all resident at once (6 per CU) and those of 128 are not: 32
-// segments of 8192 rows 42 and 33 us; 1920 of them 1.48 and 1.51 ms.
+// row_step: 128; 64 where that leaves CUs without a workgroup (2 fp32 segments of 2048 rows 4.8 and 4.0 us); 256 where
+// these workgroups are all resident at once (6 per CU) and those of 128 are not: 32 segments of 8192 rows 42 and 33 us; 1920
+// of them 1.48 and 1.51 ms.
 // ============================================================================
 constexpr int NORM_ROWS = 128, NORM_RESIDENT = 6 * 256;
 
@@ -2707,17 +2708,17 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   const int N_in = window ? window->p_old : ix.N;
 
   {
-    // A few segments: pieces of at least 256 rows until every CU has a workgroup.  Their sums go where the order of
+    // A few segments: pieces of at least 256 rows until every CU has two workgroups.  Their sums go where the order of
     // the points comes later (4 bytes a point).
     int pieces = 1;
     const int Lmax = L < N_idx ? L : N_idx;
-    while (g.segs * pieces < 256 && pieces < 16 && Lmax / (2 * pieces) >= 256 &&
+    while (g.segs * pieces < 512 && pieces < 16 && Lmax / (2 * pieces) >= 256 &&
            (size_t)g.segs * 2 * pieces * D * sizeof(double) <= (size_t)units * N_idx * sizeof(int32_t))
       pieces *= 2;
     double* sums_of = pieces > 1 ? reinterpret_cast<double*>(order) : mean;
     WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs * pieces, 256, 0, st, K_in, sums_of, nflag, range, nchanged[1],
                 nlisted[0], S, L, kk, N_in, N_idx, ns, pieces);
-    int row_step = NORM_ROWS, chunks = (Lmax + NORM_ROWS - 1) / NORM_ROWS;
+    int row_step = g.segs * (Lmax / NORM_ROWS) < 256 ? NORM_ROWS / 2 : NORM_ROWS, chunks = (Lmax + row_step - 1) / row_step;
     if (g.segs * chunks > NORM_RESIDENT && g.segs * ((chunks + 1) / 2) <= NORM_RESIDENT) {
       row_step *= 2;
       chunks = (chunks + 1) / 2;
