@@ -2383,8 +2383,8 @@ __global__ __launch_bounds__(64 * small_waves<KEEP>()) void kmeans_small_kernel(
 // Finalize: sizes, offsets, mean of raw keys, value sums, permuted rows.  A group of lanes per cluster, FIN_ROWS members
 // in flight: the rows lie anywhere in the segment, and where the clusters do not fill the CUs what the launch takes is
 // one cluster's chain of round trips.  In us, two, four, eight and sixteen in flight (6, 4, 3 and 2 waves a SIMD): 1024
-// flushed rows of 128 units 37.5, 33.2, 32.3, 33.8; 2 fp32 segments of 2048 points 13.3, 11.4, 10.6, 11.2; one unit set of
-// 32768 tokens 54, 51, 53, 55; 16 x 122880 3280, 3260, 3220, 3105; 64 x 65536 3725, 3715, 3670, 3860.
+// flushed rows of 128 units 37.5, 33.2, 32.3, 33.8; 2 fp32 segments of 2048 points 13.3, 11.4, 10.6, 11.2; 8 units
+// of 32768 tokens 54, 51, 53, 55; 16 x 122880 3280, 3260, 3220, 3105; 64 x 65536 3725, 3715, 3670, 3860.
 // ============================================================================
 constexpr int FIN_ROWS = 8;
 template <typename T, int D>
@@ -2554,7 +2554,8 @@ static bool no_small_kmeans() {
 }
 
 // Whether launch_build takes an update's window: its segments go to kmeans_small_kernel and leave a quarter of the CUs
-// idle (16 x 8 segments of 1024 tokens: an update 220 us with the window routed first, 184 so.  64 CUs are enough to route as many rows as are clustered, 32 are not: 252 us).
+// idle (16 x 8 segments of 1024 tokens: an update 220 us with the window routed first, 184 so.  64 CUs are enough to route
+// as many rows as are clustered, 32 are not: 252 us).
 bool build_routes_window(const wave_index& ix) {
   return ix.m > 0 && small_segments(ix) && !no_small_kmeans() && ix.B * ix.Hkv * ix.S <= 192;
 }

@@ -4183,9 +4183,9 @@ static wave_status decode_td(int G, const void* q, const wave_index& ix, int Hq,
 }
 
 // ---------------------------------------------------------------------------
-// Decode with an estimation budget.  Not a tuned path: the scores alone, two
-// selections (the r best and the r + e best), then the steady zone, the retrieved
-// tokens, the estimated clusters and the merge as launches of their own.
+// Decode with an estimation budget.  Four launches: the scores alone; two
+// selections (the r best and the r + e best); the steady zone, the retrieved
+// tokens and the estimated clusters; the merge.
 // ---------------------------------------------------------------------------
 BudgetGeom budget_geometry(const wave_index& ix, int Hq, int topk, int est_clusters) {
   BudgetGeom g{};
