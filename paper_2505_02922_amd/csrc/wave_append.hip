@@ -77,14 +77,14 @@ wave_status launch_append(const wave_index& o, const void* K_new, const void* V_
   copy_units<uint4>(nw.v_perm, o.v_perm, (size_t)o.N_idx * rowc, rs_new * rowc, rs_old * rowc, 0, units, st);
 
   // (2) sink rows and the window.  Where the update flushes no more than the old window holds (as one after every U
-  // tokens does) and its segments leave CUs idle, the build routes the window beside its k-means.
+  // tokens does) and its segments leave CUs enough idle, the build routes the window beside its k-means.
   // (with the old steady buffers as the new ones (no flush, room left) only the new tokens move)
   const WindowRoute window{static_cast<const char*>(o.k_steady), static_cast<const char*>(o.v_steady),
                            static_cast<const char*>(K_new), static_cast<const char*>(V_new),
                            w + g.off_k, w + g.off_v, static_cast<char*>(nw.k_steady), static_cast<char*>(nw.v_steady),
                            ns, g.lc_old, n_new, flush, steady_stride(o), steady_stride(nw), units,
                            nw.k_steady == o.k_steady ? ns + g.lc_old : 0, (int)rowc};
-  const bool beside = g.F > 0 && flush <= g.lc_old && build_routes_window(g.mini);
+  const bool beside = g.F > 0 && flush <= g.lc_old && build_routes_window(g.mini, window, iters);
   if (!beside && window.total() > 0)
     WAVE_LAUNCH("append_window", route_window_kernel, grid_for(window.total()), 256, 0, st, window);
   if (g.F == 0) return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;

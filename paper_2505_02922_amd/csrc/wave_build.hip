@@ -2553,11 +2553,20 @@ static bool no_small_kmeans() {
   return e && e[0] == '1';
 }
 
-// Whether launch_build takes an update's window: its segments go to kmeans_small_kernel and leave a quarter of the CUs
-// idle (16 x 8 segments of 1024 tokens: an update 220 us with the window routed first, 184 so.  64 CUs are enough to route
-// as many rows as are clustered, 32 are not: 252 us).
-bool build_routes_window(const wave_index& ix) {
-  return ix.m > 0 && small_segments(ix) && !no_small_kmeans() && ix.B * ix.Hkv * ix.S <= 192;
+// Whether launch_build takes an update's window: its segments go to kmeans_small_kernel, a workgroup and a CU each, and
+// what the idle CUs take longer for the window than a launch of the whole chip is no more than the clustering.  A CU
+// moves 36 GB/s (64 of them 2.33 TB/s, 104 3.3, 128 4.3), the whole chip 5.3 TB/s; the clustering takes about 10 us and
+// 9 a round of 1024 points (1, 3, 10 rounds: 30, 58, 105), under 340 points 3 a round; after ten few points move.  A
+// quarter of the CUs is the least that was measured.
+// An update of segments of 1024 tokens, ten rounds, d = 128, window routed first and beside, in us: 128 segments, window
+// 1024 212 and 163; 192, window 1024 267 and 256, window 8192 521 and 804; of 512 tokens, 176, window 1024 152 and 148,
+// window 4096 263 and 332; of 1024 tokens, three rounds, 152, window 1024 193 and 169, 176 211 and 214.
+bool build_routes_window(const wave_index& ix, const WindowRoute& window, int iters) {
+  const long long segs = (long long)ix.B * ix.Hkv * ix.S;
+  if (ix.m == 0 || !small_segments(ix) || no_small_kmeans() || segs > 192) return false;
+  const double bytes = 64.0 * (double)window.total();  // a chunk of a key and of a value, read and written
+  const double rounds = iters < 10 ? iters : 10, points = ix.segment_len < 340 ? 340 : ix.segment_len;
+  return bytes / (36e3 * (double)(256 - segs)) <= bytes / 5.3e6 + 10.0 + rounds * 9.0 / 1024 * points;  // us
 }
 
 static int key_bits_for(int kk) {
@@ -2686,7 +2695,7 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
   int32_t* count = reinterpret_cast<int32_t*>(w + g.off_count);
   int32_t* start = count + ncl;
   const int S = ix.S, L = ix.segment_len, N_idx = ix.N_idx;
-  const bool small = small_segments(ix) && !no_small_kmeans();
+  const bool small = window || (small_segments(ix) && !no_small_kmeans());
   const bool delta = !small && iters <= PREV_ROUNDS && delta_rounds(ix);
   int32_t* changed = start + ncl;  // per cluster: a point entered or left it in the current round
   int32_t* prev = reinterpret_cast<int32_t*>(w + g.off_prev);  // every point's cluster of the round before
@@ -2764,9 +2773,10 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
     const size_t sort_lds = ((size_t)W * kk + kk) * sizeof(int);
     const int kb = key_bits_for(kk);
     if (small) {
-      // (a workgroup takes a CU at these sizes: the window goes to the others)
-      const int movers = window ? 256 - g.segs : 0;
       auto run = [&](auto kernel, int waves, bool keep_sums) {
+        // (a workgroup takes a CU at these sizes: the window goes to the others, as far as it has a chunk for each thread)
+        const size_t wanted = window ? (window->total() + 64 * waves - 1) / (64 * waves) : 0;
+        const int movers = (int)(wanted < (size_t)(256 - g.segs) ? wanted : (size_t)(256 - g.segs));
         WAVE_LAUNCH("kmeans_small", kernel, g.segs + movers, 64 * waves, small_kmeans_lds<D>(kk, keep_sums), st, xhat, chat,
                     order, count, start, window ? *window : WindowRoute{}, g.segs, S, L, kk, N_idx, iters, kb);
       };

@@ -334,7 +334,7 @@ __device__ __forceinline__ void route_window(const WindowRoute& m, size_t t, siz
 wave_status launch_build(const void* K, const void* V, const wave_index& ix, int iters,
                          uint64_t seed, void* ws, hipStream_t st, int seg_id_base = 0, int row_base = 0,
                          int pos_base = 0, const WindowRoute* window = nullptr);
-bool build_routes_window(const wave_index& ix);
+bool build_routes_window(const wave_index& ix, const WindowRoute& window, int iters);
 // Incremental update: geometry of its workspace and the launches (wave_append.hip).
 struct AppendGeom {
   int F, ks, lc_old;              // flushed segments, clusters per update segment, old local count

@@ -773,13 +773,14 @@ def test_index_append_matches_oracle_then_decode(case, n_news, U, ku, cap, scap,
 
 # An update's window routed beside the k-means (`beside`), or by a launch of its own: all of the old window flushed and a
 # part of it, two segments of it, one row more than it holds, short segments sent the way of the long ones, f32; the
-# most units and one more.
+# most units and one more; rows for two laps and a half of the idle workgroups' threads; a window too long for them.
 @pytest.mark.parametrize("dtype,d,units,n_local,n_new,U,beside", [
     ("bf16", 128, 2, 40, 40, 40, True), ("bf16", 64, 3, 100, 33, 33, True), ("bf16", 128, 2, 70, 1, 35, False),
     ("bf16", 64, 2, 64, 64, 32, True), ("bf16", 128, 2, 31, 32, 32, False), ("f32", 64, 2, 40, 40, 40, False),
-    ("bf16", 64, 192, 32, 32, 32, True), ("bf16", 64, 193, 32, 32, 32, False)])
+    ("bf16", 64, 192, 32, 32, 32, True), ("bf16", 64, 193, 32, 32, 32, False),
+    ("bf16", 128, 192, 160, 32, 32, True), ("bf16", 64, 192, 1000, 32, 32, False)])
 def test_append_routes_its_window_beside_the_clustering(dtype, d, units, n_local, n_new, U, beside):
-    wl = synth.scaled(WL["llama8b_32k"], name="window", dtype=dtype, B=units, Hq=1, Hkv=1, N=300, d=d, n_sink=3,
+    wl = synth.scaled(WL["llama8b_32k"], name="window", dtype=dtype, B=units, Hq=1, Hkv=1, N=max(300, n_local + 140), d=d, n_sink=3,
                       n_local=n_local, segment_len=256, clusters_per_segment=16, iters=3, n_components=16)
     big = synth.scaled(wl, N=wl.N + n_new)
     Kall, Vall, _ = _inputs(big, 1)
