@@ -134,9 +134,10 @@ def test_keys_that_are_no_numbers(dtype, L, k, bad):
 
 
 # Segments around the rows that the normalise step takes at once (64 of bf16 at d = 128, 32 of f32) and that a
-# workgroup takes (128): whole batches, rows one by one behind them, none of either.
+# workgroup takes (128): whole batches, rows one by one behind them, none of either.  (The segment mean takes batches of
+# eight and four rows of a lane group: 96 and 200 rows have fours and single rows behind them.)
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
-@pytest.mark.parametrize("L", [1, 15, 16, 33, 64, 127, 129, 191, 257])
+@pytest.mark.parametrize("L", [1, 15, 16, 33, 64, 96, 127, 129, 191, 200, 257])
 def test_segments_around_the_normalise_batches(dtype, d, L):
     N, k = 5 * L + 3, 4
     wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="rows", dtype=dtype, B=1, Hq=2, Hkv=2, N=N, d=d, n_sink=1, n_local=0,
