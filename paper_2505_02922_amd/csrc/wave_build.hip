@@ -183,9 +183,12 @@ struct MantissaBits<float> {
 // bytes of the fp64 mean again for each 16 bytes of key, 2.16 ms).  Four rows of a group in flight where
 // that many are left, else one by one: four with repeats of the last one took 485 us for 65536
 // segments of 16 rows, 172 us so.
-// row_step: 128; 64 where that leaves CUs without a workgroup (2 fp32 segments of 2048 rows 4.8 and 4.0 us); 256 where
-// these workgroups are all resident at once (6 per CU) and those of 128 are not: 32 segments of 8192 rows 42 and 33 us; 1920
-// of them 1.48 and 1.51 ms.
+// row_step: 128; 64 where that leaves CUs without a workgroup (2 fp32 segments of 2048 rows 4.8 and 4.0 us, 31 bf16 ones
+// of 1000 11.9 and 10.6; 5200 of 100 rows 51.8, in two pieces each 60.9); 256 where these workgroups are all resident
+// at once (6 per CU) and those of 128 are not: 32 segments of 8192 rows 42 and 33 us; 1920 of them 1.48 and 1.51 ms.
+// With `range` 64 only up to a workgroup a CU, and where the four rows in flight fit: every workgroup adds to the few lines
+// of range (d = 128: one segment of 4096 rows 11.3 and 9.3 us, six 15.5 and 17.2; d = 64, 128 rows in flight: three of
+// 4096 9.9 and 11.2).
 // ============================================================================
 constexpr int NORM_ROWS = 128, NORM_RESIDENT = 6 * 256;
 
@@ -2734,7 +2737,10 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
     double* sums_of = pieces > 1 ? reinterpret_cast<double*>(order) : mean;
     WAVE_LAUNCH("seg_mean", (seg_mean_kernel<T, D>), g.segs * pieces, 256, 0, st, K_in, sums_of, nflag, range, nchanged[1],
                 nlisted[0], S, L, kk, N_in, N_idx, ns, pieces);
-    int row_step = g.segs * (Lmax / NORM_ROWS) < 256 ? NORM_ROWS / 2 : NORM_ROWS, chunks = (Lmax + row_step - 1) / row_step;
+    const int half = NORM_ROWS / 2;
+    const bool halves = range ? 4 * GROUPS <= half && g.segs * ((Lmax + half - 1) / half) <= 256
+                              : g.segs * ((Lmax + NORM_ROWS - 1) / NORM_ROWS) < 256;
+    int row_step = halves ? half : NORM_ROWS, chunks = (Lmax + row_step - 1) / row_step;
     if (g.segs * chunks > NORM_RESIDENT && g.segs * ((chunks + 1) / 2) <= NORM_RESIDENT) {
       row_step *= 2;
       chunks = (chunks + 1) / 2;

@@ -151,6 +151,21 @@ def test_segments_around_the_normalise_batches(dtype, d, L):
         assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
 
 
+# Around the most segments that the normalise step takes in pieces of 64 rows: a piece for each row of workgroups that
+# 128 rows leave without one, the second short; with the exponent range, a workgroup a CU (four segments of 4096).
+@pytest.mark.parametrize("dtype,d,B,S,L,k", [
+    ("bf16", 128, 51, 5, 100, 4), ("bf16", 64, 64, 4, 127, 4), ("f32", 64, 51, 5, 65, 4), ("f32", 128, 64, 4, 65, 4),
+    ("bf16", 128, 4, 1, 4096, 20), ("bf16", 128, 5, 1, 4096, 20), ("bf16", 64, 1, 1, 4097, 20)])
+def test_segments_around_the_normalise_pieces(dtype, d, B, S, L, k):
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="pieces", dtype=dtype, B=B, Hq=1, Hkv=1, N=S * L, d=d, n_sink=0, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=3, n_components=16)
+    K, V = synth.make_kv(wl)
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), 0, 0, L, k, wl.iters, 0)
+    for (b, h), ref in pu.oracle_build(wl, K, V, units=[(b, 0) for b in sorted({0, B - 1})]).items():
+        for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
+            assert np.array_equal(ix.t[name][b, h].double().cpu().numpy(), getattr(ref, name)), (b, name)
+
+
 # Full passes with the centroids in LDS and one list of near-ties for all segments: 2048 segments of 1537 points
 # (a fragment with one point) with 31 * 13 clusters; three units against the oracle.  (refine, not
 # assign_listed, takes the near-ties.)
