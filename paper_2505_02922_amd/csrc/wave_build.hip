@@ -2385,14 +2385,17 @@ __global__ __launch_bounds__(64 * small_waves<KEEP>()) void kmeans_small_kernel(
 }
 
 // ============================================================================
-// Finalize: sizes, offsets, mean of raw keys, value sums, permuted rows.  A group of lanes per cluster, FIN_ROWS members
+// Finalize: sizes, offsets, mean of raw keys, value sums, permuted rows.  A group of lanes per cluster, R of its members
 // in flight: the rows lie anywhere in the segment, and where the clusters do not fill the CUs what the launch takes is
 // one cluster's chain of round trips.  In us, two, four, eight and sixteen in flight (6, 4, 3 and 2 waves a SIMD): 1024
 // flushed rows of 128 units 37.5, 33.2, 32.3, 33.8; 2 fp32 segments of 2048 points 13.3, 11.4, 10.6, 11.2; 8 units
 // of 32768 tokens 54, 51, 53, 55; 16 x 122880 3280, 3260, 3220, 3105; 64 x 65536 3725, 3715, 3670, 3860.
+// Two where a cluster has fewer than four members on average and the workgroups are not all resident at once: most of
+// eight rows would be repeats of the last.  Two and eight: 1024 segments of 1024 points x 700 clusters 281 and 406 us, x 512
+// 246 and 308, x 360 221 and 230, x 300 213 and 214, x 256 216 and 211; 32 of them x 700 15.3 and 16.8, x 360 (resident)
+// 13.7 and 12.9.
 // ============================================================================
-constexpr int FIN_ROWS = 8;
-template <typename T, int D>
+template <typename T, int D, int R>
 __global__ __launch_bounds__(256) void finalize_kernel(
     const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ order,
     const int32_t* __restrict__ count, const int32_t* __restrict__ start, T* __restrict__ centroids,
@@ -2424,18 +2427,18 @@ __global__ __launch_bounds__(256) void finalize_kernel(
   double ka[EPC], va[EPC];
 #pragma unroll
   for (int e = 0; e < EPC; ++e) ka[e] = va[e] = 0.0;
-  for (int i = 0; i < n; i += FIN_ROWS) {
-    int p[FIN_ROWS];
-    uint4 k[FIN_ROWS], v[FIN_ROWS];
+  for (int i = 0; i < n; i += R) {
+    int p[R];
+    uint4 k[R], v[R];
 #pragma unroll
-    for (int u = 0; u < FIN_ROWS; ++u) p[u] = ord[min(i + u, n - 1)];
+    for (int u = 0; u < R; ++u) p[u] = ord[min(i + u, n - 1)];
 #pragma unroll
-    for (int u = 0; u < FIN_ROWS; ++u) {
+    for (int u = 0; u < R; ++u) {
       k[u] = load16(Ku + (size_t)p[u] * D);
       v[u] = load16(Vu + (size_t)p[u] * D);
     }
 #pragma unroll
-    for (int u = 0; u < FIN_ROWS; ++u) {
+    for (int u = 0; u < R; ++u) {
       if (u > 0 && i + u >= n) continue;
       const size_t row = orow + row0 + i + u;
       float f[EPC];
@@ -2850,10 +2853,15 @@ static wave_status build_td(const void* K_, const void* V_, const wave_index& ix
       update(t);
     }
   }
-  WAVE_LAUNCH("finalize", (finalize_kernel<T, D>), cl_grid, 256, 0, st, K, V, order, count, start,
-              static_cast<T*>(ix.centroids), static_cast<T*>(ix.vsum), ix.sizes, ix.offsets, ix.perm,
-              static_cast<T*>(ix.k_perm), static_cast<T*>(ix.v_perm), S, L, kk, ix.N, N_idx, ns, ix.m,
-              cluster_stride(ix), ncl, row_stride(ix), row_base, pos_base);
+  const bool many_rows = cl_grid <= 3 * 256 || (long long)S * kk * 4 <= N_idx;  // (eight in flight: 3 workgroups a CU)
+  auto finalize = [&](auto kernel) {
+    WAVE_LAUNCH("finalize", kernel, cl_grid, 256, 0, st, K, V, order, count, start,
+                static_cast<T*>(ix.centroids), static_cast<T*>(ix.vsum), ix.sizes, ix.offsets, ix.perm,
+                static_cast<T*>(ix.k_perm), static_cast<T*>(ix.v_perm), S, L, kk, ix.N, N_idx, ns, ix.m,
+                cluster_stride(ix), ncl, row_stride(ix), row_base, pos_base);
+  };
+  if (many_rows) finalize(finalize_kernel<T, D, 8>);
+  else finalize(finalize_kernel<T, D, 2>);
   return hipGetLastError() == hipSuccess ? WAVE_OK : WAVE_ERR_HIP;
 }
 

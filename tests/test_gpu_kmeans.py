@@ -166,6 +166,24 @@ def test_segments_around_the_normalise_pieces(dtype, d, B, S, L, k):
             assert np.array_equal(ix.t[name][b, h].double().cpu().numpy(), getattr(ref, name)), (b, name)
 
 
+# Clusters of few members: eight or two of them in flight (all workgroups resident, the first that are not, four members a
+# cluster and fewer), clusters of no member, of one and of more than eight; a ragged last segment.
+@pytest.mark.parametrize("kind,dtype,d,B,L,k,N", [
+    ("plain", "bf16", 128, 24, 1024, 512, 1024), ("plain", "bf16", 128, 25, 1024, 512, 1024), ("ties", "bf16", 64, 49, 600, 512, 600),
+    ("mixture", "f32", 128, 13, 1100, 500, 1100), ("plain", "bf16", 64, 30, 512, 500, 960), ("plain", "bf16", 128, 50, 1024, 256, 1024),
+    ("plain", "bf16", 128, 50, 1023, 256, 1023)])
+def test_clusters_of_few_members_match_oracle(kind, dtype, d, B, L, k, N):
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="few", dtype=dtype, B=B, Hq=1, Hkv=1, N=N, d=d, n_sink=0, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=2)
+    K = _keys(kind, B, N, d, N + k).to(tdt)
+    V = torch.randn(B, 1, N, d, generator=torch.Generator().manual_seed(1)).to(tdt)
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), 0, 0, L, k, wl.iters, 0)
+    for (b, h), ref in pu.oracle_build(wl, K, V, units=[(0, 0), (B - 1, 0)]).items():
+        for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
+            assert np.array_equal(ix.t[name][b, h].double().cpu().numpy(), getattr(ref, name)), (b, name)
+
+
 # Full passes with the centroids in LDS and one list of near-ties for all segments: 2048 segments of 1537 points
 # (a fragment with one point) with 31 * 13 clusters; three units against the oracle.  (refine, not
 # assign_listed, takes the near-ties.)
