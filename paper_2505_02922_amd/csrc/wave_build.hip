@@ -1976,33 +1976,38 @@ __global__ __launch_bounds__(MOVE_NT) void update_moves_kernel(
 
   // The points that moved, listed once: their tags are requested together, then their new clusters.  (With both visits
   // below reading tags and, one by one, clusters from memory: 105 us over the eight launches of a build of 32 segments of
-  // 8192 points, 86 so, of 1920 segments 2005 and 1775, of 2048 over eighteen 4260 and 3920.)
+  // 8192 points, 86 so, of 1920 segments 2005 and 1775, of 2048 over eighteen 4260 and 3920.  Up to 2048 points four tags a
+  // thread cover a segment: 4096 segments of 1024 points 961 us with sixteen, 928 so.)
   if (tid == 0) nmoved = 0;
   __syncthreads();
-  constexpr int TAGS = 16;
-  for (int i0 = tid; i0 - tid < si.L_s; i0 += TAGS * MOVE_NT) {
-    int tag[TAGS], n = 0;
+  auto list = [&](auto batch) {  // tags in flight
+    constexpr int TAGS = decltype(batch)::value;
+    for (int i0 = tid; i0 - tid < si.L_s; i0 += TAGS * MOVE_NT) {
+      int tag[TAGS], n = 0;
 #pragma unroll
-    for (int u = 0; u < TAGS; ++u) tag[u] = pv[min(i0 + u * MOVE_NT, si.L_s - 1)];
-    uint32_t mine = 0;
+      for (int u = 0; u < TAGS; ++u) tag[u] = pv[min(i0 + u * MOVE_NT, si.L_s - 1)];
+      uint32_t mine = 0;
 #pragma unroll
-    for (int u = 0; u < TAGS; ++u) {
-      const bool on = i0 + u * MOVE_NT < si.L_s && tag[u] >> PREV_CLUSTER_BITS == round;
-      mine |= on ? 1u << u : 0u;
-      n += on ? 1 : 0;
-    }
-    if (!__ballot(n > 0)) continue;
-    const int inc = wave_incl_scan(n), all = __builtin_amdgcn_readlane(inc, 63);
-    int at = 0;
-    if (lane == 0) at = atomicAdd(&nmoved, all);
-    at = __builtin_amdgcn_readfirstlane(at) + inc - n;
-#pragma unroll
-    for (int u = 0; u < TAGS; ++u)
-      if (mine >> u & 1u) {
-        if (at < MOVED_CAP) moved[at] = make_int2(i0 + u * MOVE_NT, tag[u] & ((1 << PREV_CLUSTER_BITS) - 1));
-        ++at;
+      for (int u = 0; u < TAGS; ++u) {
+        const bool on = i0 + u * MOVE_NT < si.L_s && tag[u] >> PREV_CLUSTER_BITS == round;
+        mine |= on ? 1u << u : 0u;
+        n += on ? 1 : 0;
       }
-  }
+      if (!__ballot(n > 0)) continue;
+      const int inc = wave_incl_scan(n), all = __builtin_amdgcn_readlane(inc, 63);
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&nmoved, all);
+      at = __builtin_amdgcn_readfirstlane(at) + inc - n;
+#pragma unroll
+      for (int u = 0; u < TAGS; ++u)
+        if (mine >> u & 1u) {
+          if (at < MOVED_CAP) moved[at] = make_int2(i0 + u * MOVE_NT, tag[u] & ((1 << PREV_CLUSTER_BITS) - 1));
+          ++at;
+        }
+    }
+  };
+  if (si.L_s > 4 * MOVE_NT) list(std::integral_constant<int, 16>{});
+  else list(std::integral_constant<int, 4>{});
   __syncthreads();
   const bool in_lds = nmoved <= MOVED_CAP;
   if (in_lds && nmoved > 0) {  // (the same for the whole workgroup)

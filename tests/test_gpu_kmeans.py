@@ -77,6 +77,26 @@ def test_cluster_emptied_across_ranges_keeps_its_centroid(d, scale, seed):
         assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
 
 
+# The points that moved in a round: as many as the update lists at once, and one more.
+@pytest.mark.parametrize("d,L,k,seed,moved", [(64, 10750, 130, 192, 2048), (64, 10750, 130, 88, 2049),
+                                              (128, 10650, 70, 67, 2048), (128, 10650, 70, 63, 2049)])
+def test_most_points_that_an_update_lists(d, L, k, seed, moved):
+    iters = 4
+    x = torch.randn(L, d, generator=torch.Generator().manual_seed(seed)).to(torch.bfloat16)
+    trace = []
+    wo.kmeans_segment(x.double().numpy(), wo.init_indices(0, 0, 0, 0, L, k), iters, "bf16", trace)
+    assert (trace[0][2] != trace[1][2]).sum() == moved
+    wl = synth.scaled(synth.WORKLOADS["llama8b_32k"], name="moved", B=1, Hq=1, Hkv=1, N=L, d=d, n_sink=0, n_local=0,
+                      segment_len=L, clusters_per_segment=k, iters=iters)
+    K, V = x.view(1, 1, L, d), torch.randn(1, 1, L, d, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16)
+    ref = pu.oracle_index_arrays(wl, pu.oracle_build(wl, K, V))
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), 0, 0, L, k, iters, 0)
+    torch.cuda.synchronize()
+    for name in ("centroids", "vsum", "sizes", "offsets", "perm", "k_perm", "v_perm"):
+        got = ix.t[name].cpu()
+        assert torch.equal(got.double(), ref[name].reshape(got.shape).double()), name
+
+
 # (33 points: a fragment with one; k = 33, 129, 289: a tile with one centroid; equal centroids: the lowest wins)
 @pytest.mark.parametrize("d,L,k", [(128, 33, 33), (64, 4097, 129), (128, 1000, 289), (64, 1, 1), (64, 70, 31)])
 def test_assign_step_f32_tile_edges(d, L, k):
