@@ -271,6 +271,7 @@ struct BudgetGeom {
   int rcap1, rcap2, mwords;
   int sliced1, sliced2, nslices, slice_len;
   int score_chunks, steady_rows, steady_chunks, gather_chunks, est_chunks, slots;
+  bool steady_first;                // the steady pieces ride with the scores, not with the retrieval and the estimation
   size_t off_z, off_cn2, off_ids1, off_ids2, off_nsel1, off_nsel2, off_pref, off_srow, off_bitmap,
       off_slice_ids, off_slice_z, off_part, total;
 };

@@ -2573,11 +2573,12 @@ __global__ __launch_bounds__(NT) void select_two_kernel(
 }
 
 // The retrieval zone, the budgeted estimation zone and the steady zone in one launch: the first two only need the two
-// id lists, none needs another.  The steady pieces come first, then the estimation workgroups: they have the
-// scattered value-sum rows, the retrieval workgroups the long contiguous ranges.
+// id lists, none needs another.  The steady pieces come first (none where they ride with the scores, see
+// budget_geometry), then the estimation workgroups: they have the scattered value-sum rows, the retrieval workgroups the
+// long contiguous ranges.
 // (Beside the scores the steady pieces ran at half of this launch's rate.  Us a step, so and here: 6 sequences of 50021
-// tokens x 32 heads 67.7 and 64.9, 16 of 122880 257 and 241, 64 of 16384 212 and 197, 64 of 65536 x 28 heads 674 and 650;
-// one of 32768 33.7 and 34.0.  Beside the selections they cost those their occupancy: 62, 271, 212, 668, 31.8.)
+// tokens x 32 heads 67.7 and 64.9, 16 of 122880 257 and 241, 64 of 16384 212 and 197, 64 of 65536 x 28 heads 674 and 650.
+// Beside the selections they cost those their occupancy: 62, 271, 212, 668.)
 struct SteadyWork {
   const void* k_steady;
   const void* v_steady;
@@ -3601,7 +3602,7 @@ __global__ __launch_bounds__(NT, (G <= 4 || !FILTERED) ? 4 : 2) void select_esti
 #endif
 }
 
-// The scores with the steady-zone pieces as extra workgroups.
+// The scores with the steady-zone pieces as extra workgroups: of a budgeted step, where budget_geometry puts them here.
 template <typename T, int D, int G>
 __global__ __launch_bounds__(256, 4) void score_steady_kernel(
     const T* __restrict__ q, const T* __restrict__ C, const int32_t* __restrict__ sizes,
@@ -4028,7 +4029,7 @@ static wave_status decode_tdg(const void* q_, const wave_index& ix, int Hq, int 
       lo = ListOut{reinterpret_cast<int32_t*>(w + g.off_chunk_first), reinterpret_cast<int4*>(w + g.off_head_info),
                    reinterpret_cast<int32_t*>(w + g.off_work), reinterpret_cast<int32_t*>(w + g.off_work_count),
                    g.wmain, g.chunk_tokens};
-      // (the steady zone rides with the selection launch; this kernel's steady role stays idle)
+      // (the steady zone rides with the selection launch)
       WAVE_LAUNCH("scores", (score_steady_kernel<T, D, G>), units * g.score_chunks, 256, 0, st, q,
                   static_cast<const T*>(ix.centroids), ix.sizes, z, cn2, ix.Hkv, m, mc, g.score_chunks,
                   g.list_filtered ? reinterpret_cast<float*>(w + g.off_tile_max) : nullptr,
@@ -4183,10 +4184,14 @@ static wave_status decode_td(int G, const void* q, const wave_index& ix, int Hq,
 }
 
 // ---------------------------------------------------------------------------
-// Decode with an estimation budget.  Four launches: the scores alone; two
-// selections (the r best and the r + e best); the steady zone, the retrieved
-// tokens and the estimated clusters; the merge.
+// Decode with an estimation budget.  Up to 65536 clusters four launches: the
+// scores; two selections (the r best and the r + e best); the retrieved tokens and
+// the estimated clusters; the merge; the steady zone with the first or the third.
+// With more clusters, or none estimated, each of these is a launch of its own or more.
 // ---------------------------------------------------------------------------
+// Keys of a head fit in LDS, whole or their upper halves with a re-read hot range.
+static bool budget_in_four(int m, int est_clusters) { return m <= 1024 * 64 && est_clusters > 0; }
+
 BudgetGeom budget_geometry(const wave_index& ix, int Hq, int topk, int est_clusters) {
   BudgetGeom g{};
   const int m = ix.m, units = ix.B * ix.Hkv, heads = ix.B * Hq, D = ix.d;
@@ -4209,8 +4214,6 @@ BudgetGeom budget_geometry(const wave_index& ix, int Hq, int topk, int est_clust
   g.sliced1 = sliced(r);
   g.sliced2 = sliced(g.k2);
   g.score_chunks = (m + DENSE_ROWS - 1) / DENSE_ROWS;
-  g.steady_rows = units >= 32 ? 256 : 64;  // (48 units: 65.8 us a step in pieces of 64, 64.9 of 256)
-  g.steady_chunks = ix.p > 0 ? (ix.p + g.steady_rows - 1) / g.steady_rows : 0;
   double expect = (double)r * (double)ix.N_idx / (double)m;
   int gc = (int)((expect + GATHER_TILE - 1) / GATHER_TILE);
   gc = gc < 1 ? 1 : (gc > 256 ? 256 : gc);
@@ -4218,6 +4221,31 @@ BudgetGeom budget_geometry(const wave_index& ix, int Hq, int topk, int est_clust
   int ec = (est_clusters + 255) / 256;
   ec = ec < 1 ? 1 : (ec > 256 ? 256 : ec);
   g.est_chunks = est_clusters > 0 ? ec : 0;
+  auto pieces = [&](int rows) { return ix.p > 0 ? (ix.p + rows - 1) / rows : 0; };
+  auto steady_wgs = [&](int rows) { return (long long)units * pieces(rows); };
+  // The steady zone's pieces and the launch they ride with.  A launch of its own (e = 0, or more clusters): 256 rows from 64
+  // units on (32 and 40 units of 32768 tokens, e = 0: pieces of 64 43.0 and 45.9 us a step, of 256 45.0 and 47.4).
+  g.steady_rows = units >= 64 ? 256 : 64;
+  if (budget_in_four(m, est_clusters)) {
+    // Else beside the retrieval and the estimation (6 x 8 units of 50021 tokens, four heads each: 67.2 us beside the
+    // scores, 63.8 so; 16 x 8 of 122880 257 and 241), with two heads or fewer on few units beside the scores, whose launch is
+    // the shorter one (24 units of 16384, two heads: 31.5 and 32.5).  Pieces of 64 rows while these are a workgroup a CU with what
+    // they ride with; else beside the scores where they are that there (8 units of 45000 .. 57000, four heads: 36.0 .. 38.3,
+    // in the other launch 36.8 .. 39.2), else pieces of 128 (24 units of 50021, four heads: 45.3 beside the scores, pieces
+    // of 64 47.3, of 128 44.1), of 256 where there are many of them (48 units of 50021: 64 65.1, 256 64.2; 24 units with
+    // 3004 rows each of 32768: 64 45.2, 128 43.1, 256 41.8).  More than four heads take two passes over a piece's rows: their
+    // lines lie higher (12 units of 16384, seven heads: 64 33.6, 128 36.2; 32 units 128 44.8, 256 47.9; 3004 rows each 66.0, 62.7).
+    const int G = Hq / ix.Hkv;
+    const bool wide = G > 4;
+    const long long others = (long long)heads * (g.gather_chunks + g.est_chunks);
+    if (G <= 2 && units < 32) g.steady_first = true;
+    else if (units >= (wide ? 64 : 32) || steady_wgs(128) > (wide ? 512 : 256)) g.steady_rows = 256;
+    else if (others + steady_wgs(64) > 256 && (!wide || units >= 32 || steady_wgs(64) > 256)) {
+      g.steady_first = !wide && others + steady_wgs(128) > 256 && (long long)units * g.score_chunks + steady_wgs(64) <= 256;
+      if (!g.steady_first) g.steady_rows = 128;
+    }
+  }
+  g.steady_chunks = pieces(g.steady_rows);
   g.slots = g.steady_chunks + g.gather_chunks + g.est_chunks;
   size_t o = 0;
   g.off_z = o;       o = align_up(o + sizeof(float) * (size_t)heads * m);
@@ -4233,8 +4261,10 @@ BudgetGeom budget_geometry(const wave_index& ix, int Hq, int topk, int est_clust
     g.off_slice_ids = o; o = align_up(o + sizeof(int32_t) * (size_t)heads * g.nslices * g.rcap2);
     g.off_slice_z = o;   o = align_up(o + sizeof(float) * (size_t)heads * g.nslices * g.rcap2);
   }
-  // one more slot than the merge reads: the streaming selection leaves a partial there
-  g.off_part = o;    o = align_up(o + sizeof(float) * (size_t)heads * (g.slots + 1) * (D + 2));
+  // one more slot than the merge reads: the streaming selection leaves a partial there.  Room for the most steady
+  // pieces that this many units are cut into: a workspace planned for a longer context or for more clusters is enough
+  g.off_part = o;
+  o = align_up(o + sizeof(float) * (size_t)heads * (g.slots + 1 + pieces(units >= 64 ? 256 : 64) - g.steady_chunks) * (D + 2));
   g.total = o;
   return g;
 }
@@ -4264,14 +4294,15 @@ static wave_status budget_tdg(const void* q_, const wave_index& ix, int Hq, int 
   const float scale_log2 = kLog2e / sqrtf((float)D);
   const int slots = g.slots + 1, spare_slot = g.slots;
 
-  // Keys of a head fit in LDS (whole, or their upper halves with a re-read hot range): four
-  // launches.  The scores; both selections at once (two workgroups per head); retrieval, estimation and the steady
-  // zone in one launch (none needs another); the merge.
-  if (m <= 1024 * 64 && est_clusters > 0) {
-    WAVE_LAUNCH("scores", (score_steady_kernel<T, D, G>), units * g.score_chunks,
+  // Four launches: the scores; both selections at once (two workgroups per head); retrieval and estimation in one
+  // launch (none needs the other), the steady zone with one of these two launches (steady_first); the merge.
+  if (budget_in_four(m, est_clusters)) {
+    const int n_first = g.steady_first ? units * g.steady_chunks : 0, n_score = units * g.score_chunks;
+    WAVE_LAUNCH(n_first ? "scores+steady" : "scores", (score_steady_kernel<T, D, G>), n_score + n_first,
                 256, 0, st, q, C, ix.sizes, z, cn2, ix.Hkv, m, mc, g.score_chunks, static_cast<float*>(nullptr),
-                units * g.score_chunks, static_cast<const T*>(nullptr), static_cast<const T*>(nullptr), 0, 0, 0, 0, slots, 0,
-                scale_log2, part, static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr), 0);
+                n_score, static_cast<const T*>(ix.k_steady), static_cast<const T*>(ix.v_steady), ix.p, steady_stride(ix),
+                g.steady_chunks, g.steady_rows, slots, 0, scale_log2, part, static_cast<int32_t*>(nullptr),
+                static_cast<int32_t*>(nullptr), 0);
 #define WAVE_TWO_ARGS                                                                                   \
   q, C, ix.offsets, z, cn2, g.score_chunks, Hq, ix.Hkv, m, g.mwords, mc, bitmap, g.r, g.rcap1, ids1, nsel1, \
       selected, g.k2, g.rcap2, ids2, nsel2, VS, scale_log2
@@ -4287,7 +4318,7 @@ static wave_status budget_tdg(const void* q_, const wave_index& ix, int Hq, int 
       WAVE_LAUNCH("select x2", (select_two_kernel<T, D, 1024, 64, false>), 2 * heads, 1024,
                   sizeof(uint16_t) * 1024 * (size_t)((m + 1023) / 1024), st, WAVE_TWO_ARGS);
 #undef WAVE_TWO_ARGS
-    const int n_est = heads * g.est_chunks, n_steady = units * g.steady_chunks;
+    const int n_est = heads * g.est_chunks, n_steady = units * g.steady_chunks - n_first;
     const SteadyWork sw{ix.k_steady, ix.v_steady, ix.p, steady_stride(ix), g.steady_chunks, g.steady_rows};
     WAVE_LAUNCH("gather+estimate", (gather_est_kernel<T, D, G>), n_steady + n_est + heads * g.gather_chunks, 256, 0, st, q,
                 static_cast<const T*>(ix.k_perm), static_cast<const T*>(ix.v_perm), ids1, nsel1, ids2, nsel2,

@@ -374,3 +374,18 @@ def test_append_refuses_bad_arguments_on_the_host():
     cn2 = wb.wave_index()
     ctypes.memmove(ctypes.byref(cn2), ctypes.byref(cn), ctypes.sizeof(wb.wave_index))
     assert L_.wave_index_build(fake, fake, ctypes.byref(cn2), 3, 0, fake, 1 << 30, None) == 2
+
+
+# A workspace planned for a context is enough for every shorter one, and one planned for an estimation budget for every
+# smaller one, wherever the steady zone of the step is and in whatever pieces.
+@pytest.mark.parametrize("B,Hkv,G", [(1, 8, 4), (3, 8, 4), (1, 1, 1), (31, 1, 4), (40, 1, 4), (12, 1, 7), (64, 1, 4)])
+def test_budget_workspace_of_a_larger_step_is_enough(B, Hkv, G):
+    def need(N, e):
+        c, _, _, _ = wb.wave_index_plan(torch.bfloat16, B, Hkv, 128, N, 4, 1024, 8192, 512)
+        return wb.lib().wave_attention_decode_budget_workspace(ctypes.byref(c), Hkv * G, 40, e)
+
+    # (whole segments, so that the clusters' mean size stays: the retrieval's share of the workspace depends on it)
+    by_length = [need(1028 + 8192 * s, 400) for s in range(1, 140)]
+    assert all(a <= b for a, b in zip(by_length, by_length[1:])) and by_length[0] > 0
+    by_budget = [need(1028 + 8192 * 6, e) for e in range(0, 3000, 7)]
+    assert all(a <= b for a, b in zip(by_budget, by_budget[1:]))

@@ -608,24 +608,49 @@ def test_full_attention_is_the_limit_of_the_wave_decode():
     assert float((l1 - l2).abs().max()) < 2e-5
 
 
+def _budget_with_steady(dtype, B, Hkv, G, n_sink, n_local, no_estimate=False):
+    """A budgeted step against the oracle; the launches it took."""
+    wl = _small("llama8b_32k", name="pieces", dtype=dtype, B=B, Hq=Hkv * G, Hkv=Hkv, N=700, n_sink=n_sink, n_local=n_local,
+                segment_len=512, clusters_per_segment=32, n_components=32, iters=2)
+    K, V, q = _inputs(wl, 1)
+    ix = wb.wave_index_build(K.cuda(), V.cuda(), n_sink, n_local, 512, 32, 2, 0)
+    r, e = 3, 0 if no_estimate else ix.m // 3
+    wb.wave_profile_enable(True)
+    out, lse, _ = wb.wave_attention_decode_budget(q.cuda(), ix, r, e)
+    launches = set(wb.wave_profile_read())
+    wb.wave_profile_enable(False)
+    units = [(b, h) for b in sorted({0, B - 1}) for h in sorted({0, Hkv - 1})]
+    for (b, h), ref in pu.oracle_build(wl, K, V, units=units).items():
+        for hq in range(h * G, (h + 1) * G):
+            o, l, _ = wo.decode_unit(q[b, hq].double().numpy(), ref, r, {}, est_clusters=e)
+            pu.check_outputs(out[b, hq].cpu().numpy(), lse[b, hq:hq + 1].cpu().numpy(), o, np.array([l]), dtype, f"{b} {hq}")
+    return launches
+
+
 # The steady zone beside the budgeted zones: none, one row, a piece and one row more in pieces of 64 and (from 32 units on)
 # of 256 rows; heads beyond the fourth of a KV head.
 @pytest.mark.parametrize("dtype,B,Hkv,G,n_sink,n_local", [
     ("bf16", 1, 1, 1, 0, 0), ("bf16", 1, 1, 5, 0, 1), ("f32", 1, 2, 8, 4, 61), ("bf16", 31, 1, 3, 0, 257),
     ("bf16", 32, 1, 5, 4, 253), ("bf16", 16, 2, 4, 0, 256), ("f32", 2, 16, 1, 0, 256)])
 def test_budget_with_steady_pieces_of_all_sizes(dtype, B, Hkv, G, n_sink, n_local):
-    wl = _small("llama8b_32k", name="pieces", dtype=dtype, B=B, Hq=Hkv * G, Hkv=Hkv, N=700, n_sink=n_sink, n_local=n_local,
-                segment_len=512, clusters_per_segment=32, n_components=32, iters=2)
-    K, V, q = _inputs(wl, 1)
-    ix = wb.wave_index_build(K.cuda(), V.cuda(), n_sink, n_local, 512, 32, 2, 0)
-    r, e = 3, ix.m // 3
-    out, lse, _ = wb.wave_attention_decode_budget(q.cuda(), ix, r, e)
-    torch.cuda.synchronize()
-    units = [(b, h) for b in sorted({0, B - 1}) for h in sorted({0, Hkv - 1})]
-    for (b, h), ref in pu.oracle_build(wl, K, V, units=units).items():
-        for hq in range(h * G, (h + 1) * G):
-            o, l, _ = wo.decode_unit(q[b, hq].double().numpy(), ref, r, {}, est_clusters=e)
-            pu.check_outputs(out[b, hq].cpu().numpy(), lse[b, hq:hq + 1].cpu().numpy(), o, np.array([l]), dtype, f"{b} {hq}")
+    _budget_with_steady(dtype, B, Hkv, G, n_sink, n_local)
+
+
+# Which launch has the steady zone.  One or two heads per KV head on fewer than 32 units: the scores (no row: none).  More
+# heads: the scores where only they have CUs left (pieces of 64: a piece and one row more), else the retrieval and the estimation, in
+# pieces of 64 while these are a workgroup a CU, of 128 (one piece, and one row more), of 256.  Without estimation: a launch of its own.
+@pytest.mark.parametrize("dtype,B,Hkv,G,n_sink,n_local,first", [
+    ("bf16", 31, 1, 2, 1, 64, True), ("bf16", 31, 1, 2, 0, 0, False), ("bf16", 32, 1, 1, 4, 60, False), ("bf16", 24, 1, 4, 0, 257, True),
+    ("f32", 24, 1, 4, 0, 128, False), ("bf16", 24, 1, 4, 0, 129, False), ("bf16", 40, 1, 5, 0, 385, False),
+    ("bf16", 63, 1, 6, 0, 129, False), ("bf16", 40, 1, 4, 0, 257, False), ("bf16", 15, 1, 7, 2, 300, False)])
+def test_budget_puts_the_steady_zone_where_cus_are_left(dtype, B, Hkv, G, n_sink, n_local, first):
+    launches = _budget_with_steady(dtype, B, Hkv, G, n_sink, n_local)
+    assert "gather+estimate" in launches and ("scores+steady" in launches) == first, launches
+
+
+@pytest.mark.parametrize("B,n_local", [(1, 65), (40, 64), (40, 65), (64, 257)])
+def test_budget_without_estimation_and_its_steady_pieces(B, n_local):
+    assert "steady" in _budget_with_steady("bf16", B, 1, 4, 0, n_local, no_estimate=True)
 
 
 @pytest.mark.parametrize("case", ["tiny_f32", "bf16_g4", "bf16_g7", "bf16_d64", "f32_d128",
