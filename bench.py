@@ -285,7 +285,7 @@ def decode_phase(run: DecodeRun, steps: int, warmup: int, profile_steps: int):
         "scores": cbytes + units * ix.m * 4, "select_slices+side": steady_b, "select+side": cbytes,
         "meta_index+steady": meta + steady_b,
         "scores+steady": cbytes + units * ix.m * 4 + steady_b, "select+estimate+steady": cbytes + steady_b,
-        "gather+estimate": gather_b + cbytes,
+        "gather+estimate": gather_b + cbytes + steady_b,   # (without the steady zone where the scores have it)
         # selection, retrieval and merge of a head in one launch; the selected clusters' value sums come again
         "attend": gather_b + wl.B * wl.Hq * run.r * row,
     }

@@ -77,7 +77,7 @@ wave_status launch_append(const wave_index& o, const void* K_new, const void* V_
   copy_units<uint4>(nw.v_perm, o.v_perm, (size_t)o.N_idx * rowc, rs_new * rowc, rs_old * rowc, 0, units, st);
 
   // (2) sink rows and the window.  Where the update flushes no more than the old window holds (as one after every U
-  // tokens does) and its segments leave CUs enough idle, the build routes the window beside its k-means.
+  // tokens does) and its segments leave enough CUs idle, the build routes the window beside its k-means.
   // (with the old steady buffers as the new ones (no flush, room left) only the new tokens move)
   const WindowRoute window{static_cast<const char*>(o.k_steady), static_cast<const char*>(o.v_steady),
                            static_cast<const char*>(K_new), static_cast<const char*>(V_new),
